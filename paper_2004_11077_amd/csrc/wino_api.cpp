@@ -461,10 +461,7 @@ int wino_conv2d_launches(const wino_conv_desc_t* d, char* buf, size_t buf_bytes)
       if (w) add("weight_transform");
       add("fused_layer");
     } else {
-      if (p.fp32) {
-        if (w) add("weight_transform");
-        if (x) add("input_transform");
-      } else if (w && x) {
+      if (w && x) {
         add("operand_transforms");
       } else if (w) {
         add("weight_transform");
@@ -715,8 +712,8 @@ int wino_weight_transform(const wino_conv_desc_t* d, const void* w, void* V,
   if (int rc = need(w, "w")) return rc;
   if (int rc = need(V, "V")) return rc;
   if (p.fp32) {
-    hipError_t e = launch_stage_f32(0, p.g, p.legendre, (const float*)w, (const float*)nullptr,
-                                    (float*)V, false, (hipStream_t)hip_stream);
+    hipError_t e = launch_operands_f32(p.g, p.legendre, nullptr, nullptr, (const float*)w, (float*)V,
+                                       (hipStream_t)hip_stream);
     return e == hipSuccess ? WINO_OK : fail_hip(e, "fp32 weight launch");
   }
   if (int rc = need(s, "scales")) return rc;
@@ -739,8 +736,8 @@ int wino_input_transform(const wino_conv_desc_t* d, const void* x, void* U,
   if (int rc = need(x, "x")) return rc;
   if (int rc = need(U, "U")) return rc;
   if (p.fp32) {
-    hipError_t e = launch_stage_f32(1, p.g, p.legendre, (const float*)x, (const float*)nullptr,
-                                    (float*)U, false, (hipStream_t)hip_stream);
+    hipError_t e = launch_operands_f32(p.g, p.legendre, (const float*)x, (float*)U, nullptr, nullptr,
+                                       (hipStream_t)hip_stream);
     return e == hipSuccess ? WINO_OK : fail_hip(e, "fp32 input launch");
   }
   if (int rc = need(s, "scales")) return rc;
@@ -759,9 +756,16 @@ int wino_transform_operands(const wino_conv_desc_t* d, const void* x, void* U, c
   Plan p;
   if (int rc = make_plan(d, &p)) return rc;
   if ((long)p.g.T * p.g.C == 0 && (long)p.g.K * p.g.C == 0) return WINO_OK;   // empty problem: nothing to launch, pointers may be null
-  if (p.fp32) {   // the unquantised path keeps its two separate launches
-    if (int rc = wino_weight_transform(d, w, V, s, hip_stream)) return rc;
-    return wino_input_transform(d, x, U, s, hip_stream);
+  if (p.fp32) {
+    const bool some_x = (long)p.g.T * p.g.C != 0, some_w = (long)p.g.K * p.g.C != 0;
+    if (some_w) if (int rc = need(w, "w")) return rc;
+    if (some_w) if (int rc = need(V, "V")) return rc;
+    if (some_x) if (int rc = need(x, "x")) return rc;
+    if (some_x) if (int rc = need(U, "U")) return rc;
+    hipError_t e = launch_operands_f32(p.g, p.legendre, some_x ? (const float*)x : nullptr, (float*)U,
+                                       some_w ? (const float*)w : nullptr, (float*)V,
+                                       (hipStream_t)hip_stream);
+    return e == hipSuccess ? WINO_OK : fail_hip(e, "fp32 operand transforms launch");
   }
   if (int rc = need(x, "x")) return rc;
   if (int rc = need(U, "U")) return rc;
@@ -794,8 +798,8 @@ int wino_contract(const wino_conv_desc_t* d, const void* U, const void* V, void*
   }
   if (int rc = need(M, "M")) return rc;
   if (p.fp32) {
-    hipError_t e = launch_stage_f32(2, p.g, p.legendre, (const float*)U, (const float*)V,
-                                    (float*)M, false, (hipStream_t)hip_stream);
+    hipError_t e = launch_contract_f32(p.g, (const float*)U, (const float*)V, (float*)M,
+                                       (hipStream_t)hip_stream);
     return e == hipSuccess ? WINO_OK : fail_hip(e, "fp32 contract launch");
   }
   if (int rc = need(s, "scales")) return rc;
@@ -820,8 +824,8 @@ int wino_output_transform(const wino_conv_desc_t* d, const void* M, void* y,
   if (int rc = need(M, "M")) return rc;
   if (int rc = need(y, "y")) return rc;
   if (p.fp32) {
-    hipError_t e = launch_stage_f32(3, p.g, p.legendre, (const float*)M, (const float*)nullptr,
-                                    (float*)y, d->relu != 0, (hipStream_t)hip_stream);
+    hipError_t e = launch_output_f32(p.g, p.legendre, (const float*)M, (float*)y, d->relu != 0,
+                                     (hipStream_t)hip_stream);
     return e == hipSuccess ? WINO_OK : fail_hip(e, "fp32 output launch");
   }
   if (int rc = need(s, "scales")) return rc;

@@ -196,6 +196,15 @@ inline void geometry_set_divisors(Geometry& g) {
   fast_div_setup((uint32_t)(g.K >= 256 && g.K % 256 == 0 ? g.K / 256 : 1), &g.mul_kg, &g.sh_kg);
   fast_div_setup((uint32_t)(g.C > 64 ? (g.C + 63) / 64 : 1), &g.mul_ch, &g.sh_ch);
 }
+// A prepared divider as a kernel argument of its own (kernels that need one the Geometry does not hold).
+struct Divider {
+  uint32_t mul, sh;
+};
+inline Divider divider_of(int d) {
+  Divider r;
+  fast_div_setup((uint32_t)(d > 0 ? d : 1), &r.mul, &r.sh);
+  return r;
+}
 #if defined(__HIPCC__)
 // n / d with the pair prepared by fast_div_setup for d (n < 2^30).
 __device__ __forceinline__ uint32_t fast_div(uint32_t n, uint32_t mul, uint32_t sh) {
@@ -210,6 +219,18 @@ __device__ __forceinline__ void tile_coords(const Geometry& g, int t, int& b, in
   const uint32_t r = (uint32_t)t - (uint32_t)b * im;
   ty = (int)((g.mul_tw ? __umulhi(r, g.mul_tw) : r) >> g.sh_tw);
   tx = (int)(r - (uint32_t)ty * (uint32_t)g.TW);
+}
+// Item 256 * block + lane of the (tile, channel) items, `channels` (C or K) per tile with its
+// divider: the division of the group's first item is block-uniform (scalar), the lane's, of an
+// offset below channels + 256, is a multiply-high.  Items past the last one get a tile index >= T.
+__device__ __forceinline__ void item_of_lane(unsigned block, int channels, Divider d, int& t, int& c) {
+  const unsigned long long first = (unsigned long long)block * 256;
+  const unsigned t0 = (first >> 30) == 0 ? fast_div((uint32_t)first, d.mul, d.sh)
+                                         : (unsigned)(first / (unsigned)channels);
+  const unsigned r = (unsigned)(first - (unsigned long long)t0 * (unsigned)channels) + threadIdx.x;
+  const unsigned q = fast_div(r, d.mul, d.sh);
+  t = (int)(t0 + q);
+  c = (int)(r - q * (unsigned)channels);
 }
 #endif
 
@@ -436,9 +457,13 @@ hipError_t launch_backward_gemms(const Geometry& g, const float* dM, const int8_
 // kind 2 = bf16 MFMA loop (blocks * 4 waves * iters * 4 MFMAs of 32x32x16).
 hipError_t launch_probe(int kind, int blocks, int iters, int* sink, hipStream_t st);
 
-// fp32 path: stage 0 weight (a = w), 1 input (a = x), 2 contraction (a = U, b = V),
-// 3 output (a = M); no casts, float tensors in the int8 path's layouts.
-hipError_t launch_stage_f32(int stage, const Geometry& g, bool legendre, const float* a,
-                            const float* b, float* out, bool relu, hipStream_t st);
+// fp32 path (wino_fp32.hip): no casts, float tensors in the int8 path's layouts.
+// Operand transforms in one launch; x or w null leaves that one out.
+hipError_t launch_operands_f32(const Geometry& g, bool legendre, const float* x, float* U,
+                               const float* w, float* V, hipStream_t st);
+hipError_t launch_contract_f32(const Geometry& g, const float* U, const float* V, float* M,
+                               hipStream_t st);
+hipError_t launch_output_f32(const Geometry& g, bool legendre, const float* M, float* y, bool relu,
+                             hipStream_t st);
 
 }  // namespace wino

@@ -1,0 +1,37 @@
+"""The fp32 contraction on the matrix cores (operands cut into three bf16 pieces) against fp64, at the
+edges of its tiles: one tile, one row past a tile block, channel counts that fill no chunk or block.
+
+Bound, element by element: every product is represented to 2^-26 of its size, and its sum of C terms
+(at most 6 C roundings in fp32, each 2^-24 of a partial sum that never exceeds sum |u v|) adds
+6 C 2^-24 sum |u v|."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,N,H,W,C,K", [
+    (4, 1, 4, 4, 16, 16),        # one tile
+    (4, 1, 32, 32, 32, 64),      # 64 tiles: the last size of the 64-row block
+    (4, 1, 20, 52, 48, 80),      # 65 tiles, a partial chunk, K past one 64-wide block
+    (4, 1, 32, 64, 144, 128),    # 128 tiles
+    (2, 1, 6, 86, 16, 144),      # 129 tiles: one row in the second block
+    (6, 3, 23, 37, 80, 48),
+])
+def test_contract_f32_against_fp64(m, N, H, W, C, K):
+    import torch
+    import paper_2004_11077_amd as wn
+    d = wn.ConvDesc(N, H, W, C, K, m=m, bits_in=32)
+    n2, T = d.n ** 2, d.tiles
+    rng = np.random.default_rng(7)
+    # magnitudes spread over 2^+-12, so that no piece is always the small one
+    draw = lambda *s: (rng.standard_normal(s) * 2.0 ** rng.integers(-12, 13, s)).astype(np.float32)
+    u, v = draw(n2, T, C), draw(n2, K, C)
+    U, V = torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda()
+    M = torch.full((n2, T, K), float("nan"), dtype=torch.float32, device="cuda")
+    wn.wino_contract(d, U, V, M, wn.Scales.from_dict({}))
+    torch.cuda.synchronize()
+    u64, v64 = u.astype(np.float64), v.astype(np.float64).transpose(0, 2, 1)
+    bound = (6 * C * 2.0 ** -24 + 2.0 ** -26) * np.matmul(np.abs(u64), np.abs(v64))
+    err = np.abs(M.cpu().numpy().astype(np.float64) - np.matmul(u64, v64))
+    assert (err <= bound).all(), float((err / bound).max())
