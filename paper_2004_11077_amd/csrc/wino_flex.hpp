@@ -7,8 +7,7 @@
 //     out[i][j]  = ((left[i][0] T[j][0] + left[i][1] T[j][1]) + ...)
 // every product and every sum rounded to fp32, never fused, so that a CPU
 // reference can follow it bit for bit; its cast uses one multiplier for the
-// whole tensor.  These kernels serve trained matrices, whose entries have no
-// structure to exploit: one lane per item, plain global accesses.
+// whole tensor.  Trained matrices have no zeros or powers of two to exploit: a bracket is dense.
 #pragma once
 #include "wino_calibrate.hpp"
 
@@ -19,16 +18,17 @@ constexpr int kFlexRun = 0;       // produce the stage's tensor
 constexpr int kFlexCalFloat = 1;  // amax[0] = max |value| of the fp32 bracket (float bits)
 constexpr int kFlexCalInt = 2;    // weights, Legendre: per-(i,j) max |numerator| of the P^{-1} bracket
 
+// x: integer codes held as floats.
 template <int ROWS, int COLS>
 __device__ __forceinline__ void fsandwich(const float* __restrict__ Tm,
-                                          const int (&x)[COLS][COLS], float (&out)[ROWS][ROWS]) {
+                                          const float (&x)[COLS][COLS], float (&out)[ROWS][ROWS]) {
 #pragma clang fp contract(off)
   float left[ROWS][COLS];
   static_for<0, ROWS>([&](auto i) {
     static_for<0, COLS>([&](auto b) {
-      float acc = Tm[decltype(i)::value * COLS] * (float)x[0][b];
+      float acc = Tm[decltype(i)::value * COLS] * x[0][b];
       static_for<1, COLS>([&](auto a) {
-        const float prod = Tm[decltype(i)::value * COLS + decltype(a)::value] * (float)x[a][b];
+        const float prod = Tm[decltype(i)::value * COLS + decltype(a)::value] * x[a][b];
         acc = acc + prod;
       });
       left[i][b] = acc;
@@ -44,6 +44,30 @@ __device__ __forceinline__ void fsandwich(const float* __restrict__ Tm,
       out[i][j] = acc;
     });
   });
+}
+
+template <int R>
+__device__ __forceinline__ void to_floats(const int (&x)[R][R], float (&f)[R][R]) {
+  static_for<0, R>([&](auto i) { static_for<0, R>([&](auto j) { f[i][j] = (float)x[i][j]; }); });
+}
+
+// The input of a run-time bracket as floats: the codes themselves (canonical base) or the codes of
+// the cast after the integer bracket T = P^{-T}, |x| <= IN_MAX (Legendre).  A cast's biased float
+// 1.5 * 2^23 + q becomes q by one exact subtraction.
+template <const IMat& T, int64_t IN_MAX, bool LEG>
+__device__ __forceinline__ void flex_input(const int (&x)[T.cols][T.cols], const MultTable& inner,
+                                           float (&f)[T.rows][T.rows]) {
+  if constexpr (LEG) {
+    acc_t<T, IN_MAX> num[T.rows][T.rows];
+    sandwich<T, IN_MAX>(x, num);
+    uint32_t bits[T.rows][T.rows];
+    cast_result_biased<T, IN_MAX, true>(num, inner, 127.f, bits);
+    static_for<0, T.rows>([&](auto i) {
+      static_for<0, T.rows>([&](auto j) { f[i][j] = __uint_as_float(bits[i][j]) - kMagic; });
+    });
+  } else {
+    to_floats<T.cols>(x, f);
+  }
 }
 
 // Block-wide maximum of non-negative floats (as bit patterns), merged into amax[0].
@@ -68,15 +92,12 @@ __device__ __forceinline__ float tile_absmax(const float (&v)[R][R]) {
 }
 
 template <int M, bool LEG, int MODE>
-__device__ __forceinline__ void flex_weight_body(const int8_t* __restrict__ w,
-                                                 int8_t* __restrict__ V,
-                                                 unsigned long long* __restrict__ amax,
-                                                 const Geometry& g, const FlexMats& fm,
-                                                 const StageMults& mu, float mult_first,
-                                                 unsigned block) {
+__global__ __launch_bounds__(256) void k_flex_cal_weight(const int8_t* __restrict__ w,
+                                                         unsigned long long* __restrict__ amax,
+                                                         Geometry g, FlexMats fm, float mult_first) {
   constexpr int n = M + 2;
   using TB = Tab<M>;
-  const long gid = (long)block * 256 + threadIdx.x;
+  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   const long KC = (long)g.K * g.C;
   const bool active = gid < KC;
   int wi[3][3];
@@ -85,52 +106,31 @@ __device__ __forceinline__ void flex_weight_body(const int8_t* __restrict__ w,
       wi[a][b] = active ? w[gid * 9 + decltype(a)::value * 3 + decltype(b)::value] : 0;
     });
   });
-  float val[n][n];
-  fsandwich<n, 3>(fm.GP, wi, val);
+  float wf[3][3], val[n][n];
+  to_floats<3>(wi, wf);
+  fsandwich<n, 3>(fm.GP, wf, val);
   if constexpr (MODE == kFlexCalFloat) {
     merge_amax_float(tile_absmax<n>(val), active, amax);
     return;
   }
-  int q[n][n];
-  static_for<0, n>([&](auto i) {
-    static_for<0, n>([&](auto j) { q[i][j] = cast_code(val[i][j], mult_first, 127.f); });
-  });
-  if constexpr (LEG) {
+  if constexpr (LEG && MODE == kFlexCalInt) {
+    int q[n][n];
+    static_for<0, n>([&](auto i) {
+      static_for<0, n>([&](auto j) { q[i][j] = cast_code(val[i][j], mult_first, 127.f); });
+    });
     acc_t<TB::Pinv, 127> num2[n][n];
     sandwich<TB::Pinv, 127>(q, num2);
-    if constexpr (MODE == kFlexCalInt) {
-      merge_amax<TB::Pinv, 127>(num2, active, false, amax);
-      return;
-    }
-    cast_result<TB::Pinv, 127>(num2, mu.outer, 127.f, q);
+    merge_amax<TB::Pinv, 127>(num2, active, false, amax);
   }
-  if (!active) return;
-  static_for<0, n>([&](auto i) {
-    static_for<0, n>([&](auto j) {
-      V[(long)(decltype(i)::value * n + decltype(j)::value) * KC + gid] = (int8_t)q[i][j];
-    });
-  });
 }
 
-template <int M, bool LEG, int MODE>
-__global__ __launch_bounds__(256) void k_flex_weight(const int8_t* __restrict__ w,
-                                                     int8_t* __restrict__ V,
-                                                     unsigned long long* __restrict__ amax,
-                                                     Geometry g, FlexMats fm, StageMults mu,
-                                                     float mult_first) {
-  flex_weight_body<M, LEG, MODE>(w, V, amax, g, fm, mu, mult_first, blockIdx.x);
-}
-
-template <int M, bool LEG, int MODE>
-__device__ __forceinline__ void flex_input_body(const int8_t* __restrict__ x,
-                                                int8_t* __restrict__ U,
-                                                unsigned long long* __restrict__ amax,
-                                                const Geometry& g, const FlexMats& fm,
-                                                const StageMults& mu, float mult_u,
-                                                unsigned block) {
+template <int M, bool LEG>
+__global__ __launch_bounds__(256) void k_flex_cal_input(const int8_t* __restrict__ x,
+                                                        unsigned long long* __restrict__ amax,
+                                                        Geometry g, FlexMats fm, StageMults mu) {
   constexpr int n = M + 2;
   using TB = Tab<M>;
-  const long gid = (long)block * 256 + threadIdx.x;
+  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   const long total = (long)g.T * g.C;
   const bool active = gid < total;
   const int t = active ? (int)(gid / g.C) : 0;
@@ -154,35 +154,78 @@ __device__ __forceinline__ void flex_input_body(const int8_t* __restrict__ x,
     sandwich<TB::PinvT, 127>(xi, num1);
     cast_result<TB::PinvT, 127>(num1, mu.inner, 127.f, xi);
   }
-  float val[n][n];
-  fsandwich<n, n>(fm.BPT, xi, val);
-  if constexpr (MODE == kFlexCalFloat) {
-    merge_amax_float(tile_absmax<n>(val), active, amax);
-    return;
-  }
-  if (!active) return;
-  static_for<0, n>([&](auto i) {
-    static_for<0, n>([&](auto j) {
-      U[(long)(decltype(i)::value * n + decltype(j)::value) * total + gid] =
-          (int8_t)cast_code(val[i][j], mult_u, 127.f);
+  float xf[n][n], val[n][n];
+  to_floats<n>(xi, xf);
+  fsandwich<n, n>(fm.BPT, xf, val);
+  merge_amax_float(tile_absmax<n>(val), active, amax);
+}
+
+// The stages proper: the fetches and stores of the fixed-matrix transforms (weight_items,
+// input_items, fetch_m: 16-byte accesses through LDS) around the run-time brackets.  Bound by the
+// vector ALU: a dense bracket is 2 n^3 separately rounded products and as many sums (F(4,3): 829
+// instructions of an input item's 1200, 8 us at full issue rate for 262144 items and their filters).
+// 1024 tiles, C = K = 256: operand transforms 21.0 us with a byte load per pixel and a byte store per
+// code, 14.8 us with 16-byte accesses through LDS; output transform 11.3 -> 9.8 us.  The dealing to
+// XCDs takes the contraction between them from 9.5 to 8.4 us.
+template <int M, bool LEG>
+__device__ __forceinline__ void flex_weight_body(const int8_t* __restrict__ w, int8_t* __restrict__ V,
+                                                 const Geometry& g, const FlexMats& fm,
+                                                 const StageMults& mu, float mult_first,
+                                                 unsigned block) {
+  constexpr int n = M + 2;
+  using TB = Tab<M>;
+  weight_items<M>(w, V, g, block, [&](const int (&wi)[3][3], int (&q)[n][n]) {
+    float wf[3][3], val[n][n];
+    to_floats<3>(wi, wf);
+    fsandwich<n, 3>(fm.GP, wf, val);
+    uint32_t w1[n][n];
+    static_for<0, n>([&](auto i) {
+      static_for<0, n>([&](auto j) { w1[i][j] = cast_biased(val[i][j], mult_first, 127.f); });
+    });
+    if constexpr (LEG) {
+      acc_t<TB::Pinv, 127> num2[n][n];
+      sandwich_codes<TB::Pinv, 127>(w1, num2);
+      cast_result<TB::Pinv, 127, true>(num2, mu.outer, 127.f, q);
+    } else {
+      static_for<0, n>([&](auto i) { static_for<0, n>([&](auto j) { q[i][j] = (int)w1[i][j]; }); });
+    }
+  });
+}
+
+template <int M, bool LEG, bool WHOLE>
+__device__ __forceinline__ void flex_input_body(const int8_t* __restrict__ x, int8_t* __restrict__ U,
+                                                const Geometry& g, const FlexMats& fm,
+                                                const StageMults& mu, float mult_u,
+                                                unsigned block) {
+  constexpr int n = M + 2;
+  using TB = Tab<M>;
+  input_items<M, WHOLE>(x, U, g, block, [&](const int (&xi)[n][n], int (&q)[n][n]) {
+    float xf[n][n], val[n][n];
+    flex_input<TB::PinvT, 127, LEG>(xi, mu.inner, xf);
+    fsandwich<n, n>(fm.BPT, xf, val);
+    static_for<0, n>([&](auto i) {
+      static_for<0, n>([&](auto j) { q[i][j] = (int)cast_biased(val[i][j], mult_u, 127.f); });
     });
   });
 }
 
-// OUT: 0 fp32 (mult_out = scale of the bracket's input), 2 int8 codes
-// (mult_out = that scale / s_y).
-template <int M, bool LEG, int MODE>
-__global__ __launch_bounds__(256) void k_flex_input(const int8_t* __restrict__ x,
-                                                    int8_t* __restrict__ U,
-                                                    unsigned long long* __restrict__ amax,
-                                                    Geometry g, FlexMats fm, StageMults mu,
-                                                    float mult_u) {
-  flex_input_body<M, LEG, MODE>(x, U, amax, g, fm, mu, mult_u, blockIdx.x);
+template <int M, bool LEG>
+__global__ __launch_bounds__(256) void k_flex_weight(const int8_t* __restrict__ w,
+                                                     int8_t* __restrict__ V, Geometry g, FlexMats fm,
+                                                     StageMults mu, float mult_first) {
+  flex_weight_body<M, LEG>(w, V, g, fm, mu, mult_first, blockIdx.x);
 }
 
-// Both operand transforms of a layer in one launch (they are independent): the
-// first nb_in work groups transform input tiles, the rest filters.
-template <int M, bool LEG>
+template <int M, bool LEG, bool WHOLE>
+__global__ __launch_bounds__(256) void k_flex_input(const int8_t* __restrict__ x,
+                                                    int8_t* __restrict__ U, Geometry g, FlexMats fm,
+                                                    StageMults mu, float mult_u) {
+  flex_input_body<M, LEG, WHOLE>(x, U, g, fm, mu, mult_u, image_on_one_xcd(g, blockIdx.x));
+}
+
+// Both operand transforms of a layer in one launch: the slots, the padding and the dealing to XCDs
+// are those of k_operand_transforms.
+template <int M, bool LEG, bool WHOLE>
 __global__ __launch_bounds__(256) void k_flex_operands(const int8_t* __restrict__ x,
                                                        int8_t* __restrict__ U,
                                                        const int8_t* __restrict__ w,
@@ -190,71 +233,93 @@ __global__ __launch_bounds__(256) void k_flex_operands(const int8_t* __restrict_
                                                        FlexMats fm, StageMults mu_in, float mult_u,
                                                        StageMults mu_w, float mult_first,
                                                        unsigned nb_in) {
-  if (blockIdx.x < nb_in)
-    flex_input_body<M, LEG, kFlexRun>(x, U, nullptr, g, fm, mu_in, mult_u, blockIdx.x);
-  else
-    flex_weight_body<M, LEG, kFlexRun>(w, V, nullptr, g, fm, mu_w, mult_first, blockIdx.x - nb_in);
+  const unsigned wslots = gridDim.x - nb_in;          // a multiple of 8
+  if (blockIdx.x >= wslots)
+    flex_input_body<M, LEG, WHOLE>(x, U, g, fm, mu_in, mult_u, image_on_one_xcd(g, blockIdx.x - wslots));
+  else if (blockIdx.x < weight_blocks(g))             // the padding slots have nothing to do
+    flex_weight_body<M, LEG>(w, V, g, fm, mu_w, mult_first, blockIdx.x);
 }
 
-template <int M, bool LEG, typename MT, int OUT, int MODE>
-__global__ __launch_bounds__(256) void k_flex_output(const MT* __restrict__ Mq,
-                                                     void* __restrict__ yv,
-                                                     unsigned long long* __restrict__ amax,
-                                                     Geometry g, FlexMats fm, StageMults mu,
-                                                     float mult_out, int relu) {
+// max |value| of the output bracket over the pixels of the image.
+template <int M, bool LEG, typename MT>
+__global__ __launch_bounds__(256) void k_flex_cal_output(const MT* __restrict__ Mq,
+                                                         unsigned long long* __restrict__ amax,
+                                                         Geometry g, FlexMats fm, StageMults mu,
+                                                         int relu) {
   constexpr int n = M + 2;
-  constexpr int64_t IN_MAX = MTraits<MT>::in_max;
-  using TB = Tab<M>;
   const long total = (long)g.T * g.K;
   const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   const bool active = gid < total;
   const int t = active ? (int)(gid / g.K) : 0;
-  const int k = active ? (int)(gid - (long)t * g.K) : 0;
   const int tx = t % g.TW;
   const int ty = (t / g.TW) % g.TH;
-  const int b = t / (g.TW * g.TH);
   int xi[n][n];
   static_for<0, n>([&](auto i) {
     static_for<0, n>([&](auto j) {
       xi[i][j] = active ? (int)Mq[(long)(decltype(i)::value * n + decltype(j)::value) * total + gid] : 0;
     });
   });
-  if constexpr (LEG) {
-    acc_t<TB::PinvT, IN_MAX> num1[n][n];
-    sandwich<TB::PinvT, IN_MAX>(xi, num1);
-    cast_result<TB::PinvT, IN_MAX>(num1, mu.inner, 127.f, xi);
-  }
-  float val[M][M];
-  fsandwich<M, n>(fm.APT, xi, val);
-  if constexpr (MODE == kFlexCalFloat) {
-    // positions cropped from partial tiles do not count; with relu only the
-    // positive part has to be covered
-    float best = 0.f;
-    static_for<0, M>([&](auto i) {
-      static_for<0, M>([&](auto j) {
-        const bool inside = ty * M + decltype(i)::value < g.H && tx * M + decltype(j)::value < g.W;
-        const float v = relu ? fmaxf(val[i][j], 0.f) : fabsf(val[i][j]);
-        best = fmaxf(best, inside ? v : 0.f);
-      });
+  float xf[n][n], val[M][M];
+  flex_input<Tab<M>::PinvT, MTraits<MT>::in_max, LEG>(xi, mu.inner, xf);
+  fsandwich<M, n>(fm.APT, xf, val);
+  // positions cropped from partial tiles do not count; with relu only the
+  // positive part has to be covered
+  float best = 0.f;
+  static_for<0, M>([&](auto i) {
+    static_for<0, M>([&](auto j) {
+      const bool inside = ty * M + decltype(i)::value < g.H && tx * M + decltype(j)::value < g.W;
+      const float v = relu ? fmaxf(val[i][j], 0.f) : fabsf(val[i][j]);
+      best = fmaxf(best, inside ? v : 0.f);
     });
-    merge_amax_float(best, active, amax);
-    return;
+  });
+  merge_amax_float(best, active, amax);
+}
+
+// OUT: 0 fp32 (mult_out = scale of the bracket's input), 2 int8 codes
+// (mult_out = that scale / s_y).  WHOLE, addresses and dealing as in k_output_transform.
+template <int M, bool LEG, typename MT, int OUT, bool WHOLE>
+__global__ __launch_bounds__(256) void k_flex_output(const MT* __restrict__ Mq, void* __restrict__ yv,
+                                                     Geometry g, Divider by_k, FlexMats fm,
+                                                     StageMults mu, float mult_out, int relu) {
+  constexpr int n = M + 2;
+  const int tid = threadIdx.x;
+  const unsigned block = WHOLE ? image_on_one_xcd(g, blockIdx.x) : blockIdx.x;
+  const long total = (long)g.T * g.K;
+  int t, k;
+  if constexpr (WHOLE) {
+    t = (int)fast_div(block, g.mul_kg, g.sh_kg);
+    k = (int)(block - (unsigned)t * (unsigned)(g.K >> 8)) * 256 + tid;
+  } else {
+    item_of_lane(block, g.K, by_k, t, k);
   }
+  const bool active = WHOLE || t < g.T;
+  int xi[n][n];
+  fetch_m<n, WHOLE>(Mq, total, (long)block * 256, active, t, k, g.K, xi);
   if (!active) return;
-  const long ybase = (((long)b * g.H + ty * M) * g.W + tx * M) * g.K + k;
+  int tx, ty, b;
+  tile_coords(g, t, b, ty, tx);
+  float xf[n][n], val[M][M];
+  flex_input<Tab<M>::PinvT, MTraits<MT>::in_max, LEG>(xi, mu.inner, xf);
+  fsandwich<M, n>(fm.APT, xf, val);
+  // ReLU as a lower bound on the bit pattern (none: below every value)
+  const int lo = relu ? 0 : (int)0x80000000;
+  constexpr int YB = OUT == 2 ? 1 : 4;               // bytes of one output
+  const long ytile = (((long)b * g.H + ty * M) * g.W + tx * M) * g.K;
+  char* ybase = static_cast<char*>(yv) + (ytile + (WHOLE ? k - tid : k)) * YB;
+  unsigned lane_off = WHOLE ? (unsigned)tid * YB : 0u;
   const int wk = g.W * g.K;
   static_for<0, M>([&](auto i) {
     static_for<0, M>([&](auto j) {
-      const int h = ty * M + decltype(i)::value;
-      const int ww = tx * M + decltype(j)::value;
-      if (h < g.H && ww < g.W) {
+      if (ty * M + decltype(i)::value < g.H && tx * M + decltype(j)::value < g.W) {
         const int rel = decltype(i)::value * wk + decltype(j)::value * g.K;
+        if constexpr (WHOLE) asm("" : "+v"(lane_off));
+        char* at = ybase + (long)rel * YB + lane_off;
         if constexpr (OUT == 0) {
           const float v = val[i][j] * mult_out;
-          (static_cast<float*>(yv) + ybase)[rel] = relu ? fmaxf(v, 0.f) : v;
+          __builtin_nontemporal_store(max(__float_as_int(v), lo), reinterpret_cast<int*>(at));
         } else {
           const int v = cast_code(val[i][j], mult_out, 127.f);
-          (static_cast<int8_t*>(yv) + ybase)[rel] = (int8_t)(relu ? max(v, 0) : v);
+          __builtin_nontemporal_store((int8_t)max(v, lo), reinterpret_cast<int8_t*>(at));
         }
       }
     });
@@ -266,49 +331,69 @@ hipError_t PerMFlex<M>::weight(const Geometry& g, bool leg, int mode, const int8
                                unsigned long long* amax, const FlexMats& fm,
                                const StageMults& mu, float mult_first, hipStream_t st) {
   const dim3 nb(blocks_for((long)g.K * g.C)), bs(256);
-#define WINO_FLEX_W(LEG_, MODE_) \
-  wino_launch((k_flex_weight<M, LEG_, MODE_>), nb, bs, st, w, V, amax, g, fm, mu, mult_first)
   if (mode == kFlexRun) {
-    if (leg) WINO_FLEX_W(true, kFlexRun); else WINO_FLEX_W(false, kFlexRun);
+    if (leg) wino_launch((k_flex_weight<M, true>), nb, bs, st, w, V, g, fm, mu, mult_first);
+    else wino_launch((k_flex_weight<M, false>), nb, bs, st, w, V, g, fm, mu, mult_first);
   } else if (mode == kFlexCalFloat) {
-    if (leg) WINO_FLEX_W(true, kFlexCalFloat); else WINO_FLEX_W(false, kFlexCalFloat);
+    if (leg) wino_launch((k_flex_cal_weight<M, true, kFlexCalFloat>), nb, bs, st, w, amax, g, fm, mult_first);
+    else wino_launch((k_flex_cal_weight<M, false, kFlexCalFloat>), nb, bs, st, w, amax, g, fm, mult_first);
   } else {
     if (!leg) return hipErrorInvalidValue;
-    WINO_FLEX_W(true, kFlexCalInt);
+    wino_launch((k_flex_cal_weight<M, true, kFlexCalInt>), nb, bs, st, w, amax, g, fm, mult_first);
   }
-#undef WINO_FLEX_W
   return hipGetLastError();
 }
 
 template <int M>
-hipError_t PerMFlex<M>::input(const Geometry& g, bool leg, int mode, const int8_t* x, int8_t* U,
+hipError_t PerMFlex<M>::input(const Geometry& g0, bool leg, int mode, const int8_t* x, int8_t* U,
                               unsigned long long* amax, const FlexMats& fm, const StageMults& mu,
                               float mult_u, hipStream_t st) {
-  const dim3 nb(blocks_for((long)g.T * g.C)), bs(256);
-#define WINO_FLEX_I(LEG_, MODE_) \
-  wino_launch((k_flex_input<M, LEG_, MODE_>), nb, bs, st, x, U, amax, g, fm, mu, mult_u)
+  const dim3 nb(blocks_for((long)g0.T * g0.C)), bs(256);
   if (mode == kFlexRun) {
-    if (leg) WINO_FLEX_I(true, kFlexRun); else WINO_FLEX_I(false, kFlexRun);
+    const bool whole = whole_tiles(g0.C, g0.H, g0.W);
+    const Geometry g = with_image_groups(g0, whole);
+    if (leg && whole) wino_launch((k_flex_input<M, true, true>), nb, bs, st, x, U, g, fm, mu, mult_u);
+    else if (leg) wino_launch((k_flex_input<M, true, false>), nb, bs, st, x, U, g, fm, mu, mult_u);
+    else if (whole) wino_launch((k_flex_input<M, false, true>), nb, bs, st, x, U, g, fm, mu, mult_u);
+    else wino_launch((k_flex_input<M, false, false>), nb, bs, st, x, U, g, fm, mu, mult_u);
   } else {
-    if (leg) WINO_FLEX_I(true, kFlexCalFloat); else WINO_FLEX_I(false, kFlexCalFloat);
+    if (leg) wino_launch((k_flex_cal_input<M, true>), nb, bs, st, x, amax, g0, fm, mu);
+    else wino_launch((k_flex_cal_input<M, false>), nb, bs, st, x, amax, g0, fm, mu);
   }
-#undef WINO_FLEX_I
   return hipGetLastError();
 }
 
 template <int M>
-hipError_t PerMFlex<M>::operands(const Geometry& g, bool leg, const int8_t* x, int8_t* U,
+hipError_t PerMFlex<M>::operands(const Geometry& g0, bool leg, const int8_t* x, int8_t* U,
                                  const int8_t* w, int8_t* V, const FlexMats& fm,
                                  const StageMults& mu_in, float mult_u, const StageMults& mu_w,
                                  float mult_first, hipStream_t st) {
-  const unsigned nb_in = blocks_for((long)g.T * g.C), nb_w = blocks_for((long)g.K * g.C);
-  const dim3 grid(nb_in + nb_w), bs(256);
-  if (leg)
-    wino_launch((k_flex_operands<M, true>), grid, bs, st, x, U, w, V, g, fm, mu_in, mult_u, mu_w,
-                mult_first, nb_in);
+  const unsigned nb_in = input_blocks(g0), nb_w = weight_blocks(g0);
+  const bool whole = whole_tiles(g0.C, g0.H, g0.W);
+  const Geometry g = with_image_groups(g0, whole);
+  const dim3 grid(nb_in + (nb_w + 7) / 8 * 8), bs(256);   // filter slots padded to whole sets of XCDs
+#define WINO_FLEX_OPS(LEG_, WHOLE_)                                                              \
+  wino_launch((k_flex_operands<M, LEG_, WHOLE_>), grid, bs, st, x, U, w, V, g, fm, mu_in, mult_u, \
+              mu_w, mult_first, nb_in)
+  if (leg && whole) WINO_FLEX_OPS(true, true);
+  else if (leg) WINO_FLEX_OPS(true, false);
+  else if (whole) WINO_FLEX_OPS(false, true);
+  else WINO_FLEX_OPS(false, false);
+#undef WINO_FLEX_OPS
+  return hipGetLastError();
+}
+
+template <int M, bool LEG, typename MT, bool WHOLE>
+static hipError_t flex_output_mtw(const Geometry& g, const MT* mp, void* y, int out_type, bool relu,
+                                  const FlexMats& fm, const StageMults& mu, float mult_out,
+                                  hipStream_t st) {
+  const dim3 nb(blocks_for((long)g.T * g.K)), bs(256);
+  const Divider by_k = divider_of(g.K);
+  const int r = relu ? 1 : 0;
+  if (out_type == 0)
+    wino_launch((k_flex_output<M, LEG, MT, 0, WHOLE>), nb, bs, st, mp, y, g, by_k, fm, mu, mult_out, r);
   else
-    wino_launch((k_flex_operands<M, false>), grid, bs, st, x, U, w, V, g, fm, mu_in, mult_u, mu_w,
-                mult_first, nb_in);
+    wino_launch((k_flex_output<M, LEG, MT, 2, WHOLE>), nb, bs, st, mp, y, g, by_k, fm, mu, mult_out, r);
   return hipGetLastError();
 }
 
@@ -317,19 +402,17 @@ static hipError_t flex_output_mt(const Geometry& g, int mode, const void* Mq, vo
                                  int out_type, bool relu, unsigned long long* amax,
                                  const FlexMats& fm, const StageMults& mu, float mult_out,
                                  hipStream_t st) {
-  const dim3 nb(blocks_for((long)g.T * g.K)), bs(256);
   const MT* mp = static_cast<const MT*>(Mq);
-  const int r = relu ? 1 : 0;
-  if (mode == kFlexCalFloat)
-    wino_launch((k_flex_output<M, LEG, MT, 0, kFlexCalFloat>), nb, bs, st, mp, y, amax, g, fm, mu,
-                mult_out, r);
-  else if (out_type == 0)
-    wino_launch((k_flex_output<M, LEG, MT, 0, kFlexRun>), nb, bs, st, mp, y, amax, g, fm, mu,
-                mult_out, r);
-  else
-    wino_launch((k_flex_output<M, LEG, MT, 2, kFlexRun>), nb, bs, st, mp, y, amax, g, fm, mu,
-                mult_out, r);
-  return hipGetLastError();
+  if (mode == kFlexCalFloat) {
+    wino_launch((k_flex_cal_output<M, LEG, MT>), dim3(blocks_for((long)g.T * g.K)), dim3(256), st, mp,
+                amax, g, fm, mu, relu ? 1 : 0);
+    return hipGetLastError();
+  }
+  // the block-uniform form for the int8 M, as in the fixed-matrix output transform
+  if constexpr (sizeof(MT) == 1)
+    if (whole_tiles(g.K, g.H, g.W))
+      return flex_output_mtw<M, LEG, MT, true>(with_output_groups(g), mp, y, out_type, relu, fm, mu, mult_out, st);
+  return flex_output_mtw<M, LEG, MT, false>(g, mp, y, out_type, relu, fm, mu, mult_out, st);
 }
 
 template <int M>

@@ -460,12 +460,13 @@ __device__ __forceinline__ void cast_result_biased(const AccT (&num)[T.rows][T.r
 // loads into LDS and every lane picks its nine taps; the n*n results go back
 // through LDS ([point][filter]) to 16-byte stores, as in the input transform.
 // ---------------------------------------------------------------------------
-template <int M, bool LEG, int BASE = 1>
-__device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t* __restrict__ V,
-                                            const Geometry& g, const StageMults& mu,
-                                            unsigned block) {
+// Fetches the work group's taps, lets `math(taps [3][3], q [n][n])` turn a lane's nine taps into n*n
+// values whose low byte is the code, and stores them: shared by the brackets with the fixed matrices
+// (below) and with run-time matrices (wino_flex.hpp).
+template <int M, class Math>
+__device__ __forceinline__ void weight_items(const int8_t* __restrict__ w, int8_t* __restrict__ V,
+                                             const Geometry& g, unsigned block, Math&& math) {
   constexpr int n = M + 2, n2 = n * n;
-  using TB = Tab<M, BASE>;
   __shared__ __attribute__((aligned(16))) int8_t s_w[256 * 9];
   __shared__ __attribute__((aligned(16))) int8_t s_v[n2 * 256];
   const int tid = threadIdx.x;
@@ -497,19 +498,7 @@ __device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t
     static_for<0, 3>([&](auto b) { wi[a][b] = s_w[tid * 9 + decltype(a)::value * 3 + decltype(b)::value]; });
   });
   int q[n][n];
-  if constexpr (LEG) {
-    acc_t<TB::GP, 127> num1[n][n];
-    sandwich<TB::GP, 127>(wi, num1);
-    uint32_t w1[n][n];
-    cast_result_biased<TB::GP, 127, true>(num1, mu.inner, 127.f, w1);
-    acc_t<TB::Pinv, 127> num2[n][n];
-    sandwich_codes<TB::Pinv, 127>(w1, num2);
-    cast_result<TB::Pinv, 127>(num2, mu.outer, 127.f, q);
-  } else {
-    acc_t<TB::G, 127> num[n][n];
-    sandwich<TB::G, 127>(wi, num);
-    cast_result<TB::G, 127>(num, mu.outer, 127.f, q);
-  }
+  math(wi, q);
   static_for<0, n>([&](auto i) {
     static_for<0, n>([&](auto j) {
       s_v[(decltype(i)::value * n + decltype(j)::value) * 256 + tid] = (int8_t)q[i][j];
@@ -539,6 +528,29 @@ __device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t
   }
 }
 
+template <int M, bool LEG, int BASE = 1>
+__device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t* __restrict__ V,
+                                            const Geometry& g, const StageMults& mu,
+                                            unsigned block) {
+  constexpr int n = M + 2;
+  using TB = Tab<M, BASE>;
+  weight_items<M>(w, V, g, block, [&](const int (&wi)[3][3], int (&q)[n][n]) {
+    if constexpr (LEG) {
+      acc_t<TB::GP, 127> num1[n][n];
+      sandwich<TB::GP, 127>(wi, num1);
+      uint32_t w1[n][n];
+      cast_result_biased<TB::GP, 127, true>(num1, mu.inner, 127.f, w1);
+      acc_t<TB::Pinv, 127> num2[n][n];
+      sandwich_codes<TB::Pinv, 127>(w1, num2);
+      cast_result<TB::Pinv, 127>(num2, mu.outer, 127.f, q);
+    } else {
+      acc_t<TB::G, 127> num[n][n];
+      sandwich<TB::G, 127>(wi, num);
+      cast_result<TB::G, 127>(num, mu.outer, 127.f, q);
+    }
+  });
+}
+
 // ---------------------------------------------------------------------------
 // Input transform: one lane per (tile, channel).  A work group owns 256
 // consecutive (tile, channel) items (channel fastest).  Because C is a
@@ -553,12 +565,11 @@ __device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t
 // channels of ONE tile: the tile index and everything derived from it is
 // block-uniform (scalar registers, scalar arithmetic) and no item is out of
 // range.
-template <int M, bool LEG, bool WHOLE, int BASE = 1>
-__device__ __forceinline__ void input_body(const int8_t* __restrict__ x, int8_t* __restrict__ U,
-                                           const Geometry& g, const StageMults& mu,
-                                           unsigned block) {
+// math(pixels [n][n], q [n][n]) turns a lane's n*n pixels into n*n values whose low byte is the code.
+template <int M, bool WHOLE, class Math>
+__device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t* __restrict__ U,
+                                            const Geometry& g, unsigned block, Math&& math) {
   constexpr int n = M + 2, n2 = n * n;
-  using TB = Tab<M, BASE>;
   __shared__ __attribute__((aligned(16))) int8_t s_in[n2 * 256];
   __shared__ __attribute__((aligned(16))) int8_t s_out[n2 * 256];
   const int tid = threadIdx.x;
@@ -621,19 +632,7 @@ __device__ __forceinline__ void input_body(const int8_t* __restrict__ x, int8_t*
     });
   });
   int q[n][n];
-  if constexpr (LEG) {
-    acc_t<TB::PinvT, 127> num1[n][n];
-    sandwich<TB::PinvT, 127>(xi, num1);
-    uint32_t x1[n][n];
-    cast_result_biased<TB::PinvT, 127, true>(num1, mu.inner, 127.f, x1);
-    acc_t<TB::BPT, 127> num2[n][n];
-    sandwich_codes<TB::BPT, 127>(x1, num2);
-    cast_result<TB::BPT, 127>(num2, mu.outer, 127.f, q);
-  } else {
-    acc_t<TB::BT, 127> num[n][n];
-    sandwich<TB::BT, 127>(xi, num);
-    cast_result<TB::BT, 127>(num, mu.outer, 127.f, q);
-  }
+  math(xi, q);
   static_for<0, n>([&](auto i) {
     static_for<0, n>([&](auto j) {
       s_out[(decltype(i)::value * n + decltype(j)::value) * 256 + tid] = (int8_t)q[i][j];
@@ -663,6 +662,29 @@ __device__ __forceinline__ void input_body(const int8_t* __restrict__ x, int8_t*
       __builtin_nontemporal_store(*reinterpret_cast<const v4i*>(s_out + p * 256 + su * 16),
                                   reinterpret_cast<v4i*>(ub + (long)p * pstride));
   }
+}
+
+template <int M, bool LEG, bool WHOLE, int BASE = 1>
+__device__ __forceinline__ void input_body(const int8_t* __restrict__ x, int8_t* __restrict__ U,
+                                           const Geometry& g, const StageMults& mu,
+                                           unsigned block) {
+  constexpr int n = M + 2;
+  using TB = Tab<M, BASE>;
+  input_items<M, WHOLE>(x, U, g, block, [&](const int (&xi)[n][n], int (&q)[n][n]) {
+    if constexpr (LEG) {
+      acc_t<TB::PinvT, 127> num1[n][n];
+      sandwich<TB::PinvT, 127>(xi, num1);
+      uint32_t x1[n][n];
+      cast_result_biased<TB::PinvT, 127, true>(num1, mu.inner, 127.f, x1);
+      acc_t<TB::BPT, 127> num2[n][n];
+      sandwich_codes<TB::BPT, 127>(x1, num2);
+      cast_result<TB::BPT, 127>(num2, mu.outer, 127.f, q);
+    } else {
+      acc_t<TB::BT, 127> num[n][n];
+      sandwich<TB::BT, 127>(xi, num);
+      cast_result<TB::BT, 127>(num, mu.outer, 127.f, q);
+    }
+  });
 }
 
 template <int M, bool LEG, int BASE = 1>
@@ -719,6 +741,45 @@ struct MTraits<int32_t> {
   static constexpr int64_t in_max = kMaxAccUnquantised;
 };
 
+// The n*n codes of M of a lane's item (tile t, channel k; item gid0 + lane of the work group).
+template <int N, bool WHOLE, typename MT>
+__device__ __forceinline__ void fetch_m(const MT* __restrict__ Mq, long total, long gid0, bool active,
+                                        int t, int k, int K, int (&xi)[N][N]) {
+  if constexpr (sizeof(MT) == 1) {
+    // int8 M: fetch the block's 256 consecutive (tile, k) items of every point
+    // with 16-byte loads into LDS, then each lane picks its own byte.
+    __shared__ __attribute__((aligned(16))) int8_t s_in[N * N * 256];
+    const int tid = threadIdx.x;
+    const int u = tid & 15, prow = tid >> 4;
+    const long ug = gid0 + u * 16;
+    const bool uok = WHOLE || ug < total;
+#pragma unroll
+    for (int it = 0; it < (N * N + 15) / 16; ++it) {
+      const int p = it * 16 + prow;
+      if (p < N * N) {
+        v4i v = {0, 0, 0, 0};
+        if (uok) v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(Mq + (long)p * total + ug));
+        *reinterpret_cast<v4i*>(s_in + p * 256 + u * 16) = v;
+      }
+    }
+    __syncthreads();
+    static_for<0, N>([&](auto i) {
+      static_for<0, N>([&](auto j) {
+        xi[i][j] = s_in[(decltype(i)::value * N + decltype(j)::value) * 256 + tid];
+      });
+    });
+  } else {
+    if (!active) return;
+    const MT* mb = Mq + (long)t * K + k;
+    static_for<0, N>([&](auto i) {
+      static_for<0, N>([&](auto j) {
+        xi[i][j] = (int)__builtin_nontemporal_load(
+            mb + (long)(decltype(i)::value * N + decltype(j)::value) * total);
+      });
+    });
+  }
+}
+
 // WHOLE: K is a multiple of 256, so a work group's items are 256 output
 // channels of ONE tile and the tile arithmetic is block-uniform.
 // PP: M carries per-point power-of-two scales; the codes of point p enter the
@@ -750,39 +811,8 @@ __global__ __launch_bounds__(256) void k_output_transform(const MT* __restrict__
   tile_coords(g, t, b, ty, tx);
 
   int xi[n][n];
-  if constexpr (sizeof(MT) == 1) {
-    // int8 M: fetch the block's 256 consecutive (tile, k) items of every point
-    // with 16-byte loads into LDS, then each lane picks its own byte.
-    __shared__ __attribute__((aligned(16))) int8_t s_in[n2 * 256];
-    const int u = tid & 15, prow = tid >> 4;
-    const long ug = gid0 + u * 16;
-    const bool uok = WHOLE || ug < total;
-#pragma unroll
-    for (int it = 0; it < (n2 + 15) / 16; ++it) {
-      const int p = it * 16 + prow;
-      if (p < n2) {
-        v4i v = {0, 0, 0, 0};
-        if (uok) v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(Mq + (long)p * total + ug));
-        *reinterpret_cast<v4i*>(s_in + p * 256 + u * 16) = v;
-      }
-    }
-    __syncthreads();
-    static_for<0, n>([&](auto i) {
-      static_for<0, n>([&](auto j) {
-        xi[i][j] = s_in[(decltype(i)::value * n + decltype(j)::value) * 256 + tid];
-      });
-    });
-    if (!active) return;
-  } else {
-    if (!active) return;
-    const MT* mb = Mq + (long)t * g.K + k;
-    static_for<0, n>([&](auto i) {
-      static_for<0, n>([&](auto j) {
-        xi[i][j] = (int)__builtin_nontemporal_load(
-            mb + (long)(decltype(i)::value * n + decltype(j)::value) * total);
-      });
-    });
-  }
+  fetch_m<n, WHOLE>(Mq, total, gid0, active, t, k, g.K, xi);
+  if (!active) return;
 
   if constexpr (PP) {
     static_for<0, n>([&](auto i) {
