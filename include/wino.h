@@ -257,7 +257,7 @@ int wino_contract_output(const wino_conv_desc_t* d, const void* U, const void* V
  * (qmax = 127, or 255 for a 9-bit Hadamard stage; 1.0 for an all-zero tensor;
  * s_y covers only positive values when relu is set).  As a side effect the
  * layer is run: V, U, M are left in the workspace and, if y is not null, the
- * output is written.  This is the one call that synchronises the stream (once
+ * output is written.  This call synchronises the stream (once
  * per cast) and it is meant to be used when a layer is set up, not per step.
  * Needs wino_calibrate_workspace_bytes() of device workspace; int8 path only;
  * C <= 1040 (the exact int32 contraction result must convert to fp32 exactly). */
@@ -292,7 +292,9 @@ typedef struct {
  * EUNSUPPORTED, AUTO runs one kernel per stage).  Workspace of
  * wino_flex_conv2d: wino_workspace_bytes() with d->fused = OFF.
  * wino_flex_calibrate is wino_calibrate for this variant (same workspace
- * size, same rule: scale = float(max |real| / qmax) stage after stage).
+ * size, same rule: scale = float(max |real| / qmax) stage after stage), cheap
+ * enough for a training step: the scales are chosen on the device and the
+ * stream is synchronised once, at the end.
  * Errors as for the static calls, plus EINVAL for a null, non-finite or
  * too large matrix entry. */
 int wino_flex_weight_transform(const wino_conv_desc_t* d, const wino_flex_matrices_t* f,

@@ -1252,15 +1252,6 @@ float flex_scale_from(unsigned long long amax_bits, double s_prev, double qmax) 
   return real > 0.0 ? (float)(real / qmax) : 1.0f;
 }
 
-int flex_cal_launch(CalCtx& c, int stage, const FlexPlan& fp, int mode, const void* in,
-                    const StageMults& mu, float mult, bool relu) {
-  if (int rc = cal_reset(c)) return rc;
-  hipError_t e = launch_flex_stage(stage, fp.p.g, fp.p.two_brackets, mode, in, fp.p.m_bits, nullptr,
-                                   0, relu, c.d_amax, fp.fm, mu, mult, c.st);
-  if (e != hipSuccess) return fail_hip(e, "flex calibration launch");
-  return cal_read(c);
-}
-
 }  // namespace
 
 int wino_flex_weight_transform(const wino_conv_desc_t* d, const wino_flex_matrices_t* f,
@@ -1274,8 +1265,7 @@ int wino_flex_weight_transform(const wino_conv_desc_t* d, const wino_flex_matric
   StageMults mu;
   float first;
   if (int rc = flex_weight_mults(fp.p, s, &mu, &first)) return rc;
-  hipError_t e = launch_flex_stage(0, fp.p.g, fp.p.two_brackets, 0, w, 8, V, 0, false, nullptr,
-                                   fp.fm, mu, first, (hipStream_t)hip_stream);
+  hipError_t e = launch_flex_stage(0, fp.p.g, fp.p.two_brackets, w, 8, V, 0, false, fp.fm, mu, first, (hipStream_t)hip_stream);
   return e == hipSuccess ? WINO_OK : fail_hip(e, "flex weight transform launch");
 }
 
@@ -1290,8 +1280,7 @@ int wino_flex_input_transform(const wino_conv_desc_t* d, const wino_flex_matrice
   StageMults mu;
   float mult_u;
   if (int rc = flex_input_mults(fp.p, s, &mu, &mult_u)) return rc;
-  hipError_t e = launch_flex_stage(1, fp.p.g, fp.p.two_brackets, 0, x, 8, U, 0, false, nullptr,
-                                   fp.fm, mu, mult_u, (hipStream_t)hip_stream);
+  hipError_t e = launch_flex_stage(1, fp.p.g, fp.p.two_brackets, x, 8, U, 0, false, fp.fm, mu, mult_u, (hipStream_t)hip_stream);
   return e == hipSuccess ? WINO_OK : fail_hip(e, "flex input transform launch");
 }
 
@@ -1306,8 +1295,8 @@ int wino_flex_output_transform(const wino_conv_desc_t* d, const wino_flex_matric
   StageMults mu;
   float mult_out;
   if (int rc = flex_output_mults(fp.p, d, s, &mu, &mult_out)) return rc;
-  hipError_t e = launch_flex_stage(2, fp.p.g, fp.p.two_brackets, 0, M, fp.p.m_bits, y, d->out_type,
-                                   d->relu != 0, nullptr, fp.fm, mu, mult_out,
+  hipError_t e = launch_flex_stage(2, fp.p.g, fp.p.two_brackets, M, fp.p.m_bits, y, d->out_type,
+                                   d->relu != 0, fp.fm, mu, mult_out,
                                    (hipStream_t)hip_stream);
   return e == hipSuccess ? WINO_OK : fail_hip(e, "flex output transform launch");
 }
@@ -1382,51 +1371,36 @@ int wino_flex_calibrate(const wino_conv_desc_t* d, const wino_flex_matrices_t* f
   if (int rc = need(w, "w")) return rc;
   char* ws = static_cast<char*>(workspace);
   void *V = ws + oV, *U = ws + oU, *M = ws + oM, *M32 = ws + oM32;
-  CalCtx c{(hipStream_t)hip_stream, reinterpret_cast<unsigned long long*>(ws + oA), {}};
+  // The maxima and scales live in the region of the exact contraction result, which is never stored
+  // here: n*n T K 4 bytes, at least 64 per point.
+  const int n2 = (d->m + 2) * (d->m + 2);
+  static_assert(CalScratch::bytes(16) <= 16 * 64 && CalScratch::bytes(36) <= 36 * 64 &&
+                CalScratch::bytes(64) <= 64 * 64);
+  CalScratch cal{static_cast<unsigned long long*>(M32), n2};
+  hipStream_t st = (hipStream_t)hip_stream;
+  hipError_t e = launch_flex_calibrate(p.g, p.two_brackets, (const int8_t*)x, (int8_t*)U,
+                                       (const int8_t*)w, (int8_t*)V, M, p.m_bits, d->relu != 0, s->s_x,
+                                       s->s_w, cal, fp.fm, st);
+  if (e != hipSuccess) return fail_hip(e, "flex calibration launch");
+  // one read-back: the last maximum and, behind the maxima, the scales
+  struct { unsigned long long y[kMaxPts]; float scales[kCalScales]; } got;
+  const size_t y_bytes = sizeof(unsigned long long) * n2;
+  char back[sizeof got];
+  e = hipMemcpyAsync(back, cal.array(kCalY), y_bytes + sizeof got.scales, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return fail_hip(e, "flex calibration read-back");
+  std::memcpy(&got.y[0], back, sizeof got.y[0]);
+  std::memcpy(got.scales, back + y_bytes, sizeof got.scales);
+  s->s_u = got.scales[kCalSU];
+  s->s_v = got.scales[kCalSV];
+  if (p.two_brackets) s->s_x1 = got.scales[kCalSX1], s->s_w1 = got.scales[kCalSW1], s->s_m1 = got.scales[kCalSM1];
+  double s_prev = (double)s->s_u * (double)s->s_v;
+  if (p.m_bits != 32) s->s_m = got.scales[kCalSM], s_prev = (double)s->s_m;
+  if (p.two_brackets) s_prev = (double)s->s_m1;
+  s->s_y = flex_scale_from(got.y[0], s_prev, 127.0);
   wino_conv_desc_t dd = *d;
   dd.weights_pretransformed = 0;
   dd.fused = 0;
-  StageMults mu;
-  std::memset(&mu, 0, sizeof mu);
-
-  // filters: the fp32 G bracket first, then (Legendre) the integer P^{-1} bracket
-  if (int rc = flex_cal_launch(c, 0, fp, 1, w, mu, 1.f, false)) return rc;
-  if (p.two_brackets) {
-    s->s_w1 = flex_scale_from(c.h_amax[0], s->s_w, 127.0);
-    const float first = (float)((double)s->s_w / (double)s->s_w1);
-    if (int rc = flex_cal_launch(c, 0, fp, 2, w, mu, first, false)) return rc;
-    s->s_v = scale_from(c.h_amax, *p.st.Pinv, s->s_w1, 127.0);
-  } else {
-    s->s_v = flex_scale_from(c.h_amax[0], s->s_w, 127.0);
-  }
-  if (int rc = wino_flex_weight_transform(&dd, f, w, V, s, hip_stream)) return rc;
-
-  // activations: (Legendre) the integer P^{-T} bracket, then the fp32 B bracket
-  double s_prev = s->s_x;
-  if (p.two_brackets) {
-    if (int rc = cal_bracket(c, 1, p, 1, x, 8, mu, false)) return rc;
-    s->s_x1 = scale_from(c.h_amax, *p.st.PinvT, s->s_x, 127.0);
-    fill_mults(&mu.inner, *p.st.PinvT, s->s_x, s->s_x1);
-    s_prev = s->s_x1;
-  }
-  if (int rc = flex_cal_launch(c, 1, fp, 1, x, mu, 1.f, false)) return rc;
-  s->s_u = flex_scale_from(c.h_amax[0], s_prev, 127.0);
-  if (int rc = wino_flex_input_transform(&dd, f, x, U, s, hip_stream)) return rc;
-
-  double s_m_eff;
-  ShiftTable sh_unused;
-  if (int rc = calibrate_contraction(c, d, dd, p, U, V, M, M32, s, &s_m_eff, &sh_unused)) return rc;
-
-  // output: (Legendre) the integer P^{-T} bracket, then the fp32 A bracket
-  s_prev = s_m_eff;
-  if (p.two_brackets) {
-    if (int rc = cal_bracket(c, 2, p, 1, M, p.m_bits, mu, false)) return rc;
-    s->s_m1 = scale_from(c.h_amax, *p.st.PinvT, s_m_eff, 127.0);
-    fill_mults(&mu.inner, *p.st.PinvT, s_m_eff, s->s_m1);
-    s_prev = s->s_m1;
-  }
-  if (int rc = flex_cal_launch(c, 2, fp, 1, M, mu, 1.f, d->relu != 0)) return rc;
-  s->s_y = flex_scale_from(c.h_amax[0], s_prev, 127.0);
   if (y)
     if (int rc = wino_flex_output_transform(&dd, f, M, y, s, hip_stream)) return rc;
   return WINO_OK;

@@ -9,14 +9,9 @@
 // reference can follow it bit for bit; its cast uses one multiplier for the
 // whole tensor.  Trained matrices have no zeros or powers of two to exploit: a bracket is dense.
 #pragma once
-#include "wino_calibrate.hpp"
+#include "wino_transforms.hpp"
 
 namespace wino {
-
-// MODE of the kernels below
-constexpr int kFlexRun = 0;       // produce the stage's tensor
-constexpr int kFlexCalFloat = 1;  // amax[0] = max |value| of the fp32 bracket (float bits)
-constexpr int kFlexCalInt = 2;    // weights, Legendre: per-(i,j) max |numerator| of the P^{-1} bracket
 
 // x: integer codes held as floats.
 template <int ROWS, int COLS>
@@ -68,96 +63,6 @@ __device__ __forceinline__ void flex_input(const int (&x)[T.cols][T.cols], const
   } else {
     to_floats<T.cols>(x, f);
   }
-}
-
-// Block-wide maximum of non-negative floats (as bit patterns), merged into amax[0].
-__device__ __forceinline__ void merge_amax_float(float v, bool active,
-                                                 unsigned long long* __restrict__ amax) {
-  unsigned int u = active ? __float_as_uint(v) : 0u;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const unsigned int o = __shfl_xor(u, off);
-    u = o > u ? o : u;
-  }
-  if ((threadIdx.x & 63) == 0 && u != 0) atomicMax(amax, (unsigned long long)u);
-}
-
-template <int R>
-__device__ __forceinline__ float tile_absmax(const float (&v)[R][R]) {
-  float best = 0.f;
-  static_for<0, R>([&](auto i) {
-    static_for<0, R>([&](auto j) { best = fmaxf(best, fabsf(v[i][j])); });
-  });
-  return best;
-}
-
-template <int M, bool LEG, int MODE>
-__global__ __launch_bounds__(256) void k_flex_cal_weight(const int8_t* __restrict__ w,
-                                                         unsigned long long* __restrict__ amax,
-                                                         Geometry g, FlexMats fm, float mult_first) {
-  constexpr int n = M + 2;
-  using TB = Tab<M>;
-  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-  const long KC = (long)g.K * g.C;
-  const bool active = gid < KC;
-  int wi[3][3];
-  static_for<0, 3>([&](auto a) {
-    static_for<0, 3>([&](auto b) {
-      wi[a][b] = active ? w[gid * 9 + decltype(a)::value * 3 + decltype(b)::value] : 0;
-    });
-  });
-  float wf[3][3], val[n][n];
-  to_floats<3>(wi, wf);
-  fsandwich<n, 3>(fm.GP, wf, val);
-  if constexpr (MODE == kFlexCalFloat) {
-    merge_amax_float(tile_absmax<n>(val), active, amax);
-    return;
-  }
-  if constexpr (LEG && MODE == kFlexCalInt) {
-    int q[n][n];
-    static_for<0, n>([&](auto i) {
-      static_for<0, n>([&](auto j) { q[i][j] = cast_code(val[i][j], mult_first, 127.f); });
-    });
-    acc_t<TB::Pinv, 127> num2[n][n];
-    sandwich<TB::Pinv, 127>(q, num2);
-    merge_amax<TB::Pinv, 127>(num2, active, false, amax);
-  }
-}
-
-template <int M, bool LEG>
-__global__ __launch_bounds__(256) void k_flex_cal_input(const int8_t* __restrict__ x,
-                                                        unsigned long long* __restrict__ amax,
-                                                        Geometry g, FlexMats fm, StageMults mu) {
-  constexpr int n = M + 2;
-  using TB = Tab<M>;
-  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-  const long total = (long)g.T * g.C;
-  const bool active = gid < total;
-  const int t = active ? (int)(gid / g.C) : 0;
-  const int c = active ? (int)(gid - (long)t * g.C) : 0;
-  const int tx = t % g.TW;
-  const int ty = (t / g.TW) % g.TH;
-  const int b = t / (g.TW * g.TH);
-  int xi[n][n];
-  static_for<0, n>([&](auto a) {
-    static_for<0, n>([&](auto bb) {
-      const int h = ty * M - 1 + decltype(a)::value;
-      const int ww = tx * M - 1 + decltype(bb)::value;
-      int v = 0;
-      if (active && h >= 0 && h < g.H && ww >= 0 && ww < g.W)
-        v = x[(((long)b * g.H + h) * g.W + ww) * g.C + c];
-      xi[a][bb] = v;
-    });
-  });
-  if constexpr (LEG) {
-    acc_t<TB::PinvT, 127> num1[n][n];
-    sandwich<TB::PinvT, 127>(xi, num1);
-    cast_result<TB::PinvT, 127>(num1, mu.inner, 127.f, xi);
-  }
-  float xf[n][n], val[n][n];
-  to_floats<n>(xi, xf);
-  fsandwich<n, n>(fm.BPT, xf, val);
-  merge_amax_float(tile_absmax<n>(val), active, amax);
 }
 
 // The stages proper: the fetches and stores of the fixed-matrix transforms (weight_items,
@@ -240,41 +145,6 @@ __global__ __launch_bounds__(256) void k_flex_operands(const int8_t* __restrict_
     flex_weight_body<M, LEG>(w, V, g, fm, mu_w, mult_first, blockIdx.x);
 }
 
-// max |value| of the output bracket over the pixels of the image.
-template <int M, bool LEG, typename MT>
-__global__ __launch_bounds__(256) void k_flex_cal_output(const MT* __restrict__ Mq,
-                                                         unsigned long long* __restrict__ amax,
-                                                         Geometry g, FlexMats fm, StageMults mu,
-                                                         int relu) {
-  constexpr int n = M + 2;
-  const long total = (long)g.T * g.K;
-  const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-  const bool active = gid < total;
-  const int t = active ? (int)(gid / g.K) : 0;
-  const int tx = t % g.TW;
-  const int ty = (t / g.TW) % g.TH;
-  int xi[n][n];
-  static_for<0, n>([&](auto i) {
-    static_for<0, n>([&](auto j) {
-      xi[i][j] = active ? (int)Mq[(long)(decltype(i)::value * n + decltype(j)::value) * total + gid] : 0;
-    });
-  });
-  float xf[n][n], val[M][M];
-  flex_input<Tab<M>::PinvT, MTraits<MT>::in_max, LEG>(xi, mu.inner, xf);
-  fsandwich<M, n>(fm.APT, xf, val);
-  // positions cropped from partial tiles do not count; with relu only the
-  // positive part has to be covered
-  float best = 0.f;
-  static_for<0, M>([&](auto i) {
-    static_for<0, M>([&](auto j) {
-      const bool inside = ty * M + decltype(i)::value < g.H && tx * M + decltype(j)::value < g.W;
-      const float v = relu ? fmaxf(val[i][j], 0.f) : fabsf(val[i][j]);
-      best = fmaxf(best, inside ? v : 0.f);
-    });
-  });
-  merge_amax_float(best, active, amax);
-}
-
 // OUT: 0 fp32 (mult_out = scale of the bracket's input), 2 int8 codes
 // (mult_out = that scale / s_y).  WHOLE, addresses and dealing as in k_output_transform.
 template <int M, bool LEG, typename MT, int OUT, bool WHOLE>
@@ -327,39 +197,25 @@ __global__ __launch_bounds__(256) void k_flex_output(const MT* __restrict__ Mq, 
 }
 
 template <int M>
-hipError_t PerMFlex<M>::weight(const Geometry& g, bool leg, int mode, const int8_t* w, int8_t* V,
-                               unsigned long long* amax, const FlexMats& fm,
-                               const StageMults& mu, float mult_first, hipStream_t st) {
+hipError_t PerMFlex<M>::weight(const Geometry& g, bool leg, const int8_t* w, int8_t* V,
+                               const FlexMats& fm, const StageMults& mu, float mult_first,
+                               hipStream_t st) {
   const dim3 nb(blocks_for((long)g.K * g.C)), bs(256);
-  if (mode == kFlexRun) {
-    if (leg) wino_launch((k_flex_weight<M, true>), nb, bs, st, w, V, g, fm, mu, mult_first);
-    else wino_launch((k_flex_weight<M, false>), nb, bs, st, w, V, g, fm, mu, mult_first);
-  } else if (mode == kFlexCalFloat) {
-    if (leg) wino_launch((k_flex_cal_weight<M, true, kFlexCalFloat>), nb, bs, st, w, amax, g, fm, mult_first);
-    else wino_launch((k_flex_cal_weight<M, false, kFlexCalFloat>), nb, bs, st, w, amax, g, fm, mult_first);
-  } else {
-    if (!leg) return hipErrorInvalidValue;
-    wino_launch((k_flex_cal_weight<M, true, kFlexCalInt>), nb, bs, st, w, amax, g, fm, mult_first);
-  }
+  if (leg) wino_launch((k_flex_weight<M, true>), nb, bs, st, w, V, g, fm, mu, mult_first);
+  else wino_launch((k_flex_weight<M, false>), nb, bs, st, w, V, g, fm, mu, mult_first);
   return hipGetLastError();
 }
 
 template <int M>
-hipError_t PerMFlex<M>::input(const Geometry& g0, bool leg, int mode, const int8_t* x, int8_t* U,
-                              unsigned long long* amax, const FlexMats& fm, const StageMults& mu,
-                              float mult_u, hipStream_t st) {
+hipError_t PerMFlex<M>::input(const Geometry& g0, bool leg, const int8_t* x, int8_t* U,
+                              const FlexMats& fm, const StageMults& mu, float mult_u, hipStream_t st) {
   const dim3 nb(blocks_for((long)g0.T * g0.C)), bs(256);
-  if (mode == kFlexRun) {
-    const bool whole = whole_tiles(g0.C, g0.H, g0.W);
-    const Geometry g = with_image_groups(g0, whole);
-    if (leg && whole) wino_launch((k_flex_input<M, true, true>), nb, bs, st, x, U, g, fm, mu, mult_u);
-    else if (leg) wino_launch((k_flex_input<M, true, false>), nb, bs, st, x, U, g, fm, mu, mult_u);
-    else if (whole) wino_launch((k_flex_input<M, false, true>), nb, bs, st, x, U, g, fm, mu, mult_u);
-    else wino_launch((k_flex_input<M, false, false>), nb, bs, st, x, U, g, fm, mu, mult_u);
-  } else {
-    if (leg) wino_launch((k_flex_cal_input<M, true>), nb, bs, st, x, amax, g0, fm, mu);
-    else wino_launch((k_flex_cal_input<M, false>), nb, bs, st, x, amax, g0, fm, mu);
-  }
+  const bool whole = whole_tiles(g0.C, g0.H, g0.W);
+  const Geometry g = with_image_groups(g0, whole);
+  if (leg && whole) wino_launch((k_flex_input<M, true, true>), nb, bs, st, x, U, g, fm, mu, mult_u);
+  else if (leg) wino_launch((k_flex_input<M, true, false>), nb, bs, st, x, U, g, fm, mu, mult_u);
+  else if (whole) wino_launch((k_flex_input<M, false, true>), nb, bs, st, x, U, g, fm, mu, mult_u);
+  else wino_launch((k_flex_input<M, false, false>), nb, bs, st, x, U, g, fm, mu, mult_u);
   return hipGetLastError();
 }
 
@@ -398,16 +254,10 @@ static hipError_t flex_output_mtw(const Geometry& g, const MT* mp, void* y, int 
 }
 
 template <int M, bool LEG, typename MT>
-static hipError_t flex_output_mt(const Geometry& g, int mode, const void* Mq, void* y,
-                                 int out_type, bool relu, unsigned long long* amax,
+static hipError_t flex_output_mt(const Geometry& g, const void* Mq, void* y, int out_type, bool relu,
                                  const FlexMats& fm, const StageMults& mu, float mult_out,
                                  hipStream_t st) {
   const MT* mp = static_cast<const MT*>(Mq);
-  if (mode == kFlexCalFloat) {
-    wino_launch((k_flex_cal_output<M, LEG, MT>), dim3(blocks_for((long)g.T * g.K)), dim3(256), st, mp,
-                amax, g, fm, mu, relu ? 1 : 0);
-    return hipGetLastError();
-  }
   // the block-uniform form for the int8 M, as in the fixed-matrix output transform
   if constexpr (sizeof(MT) == 1)
     if (whole_tiles(g.K, g.H, g.W))
@@ -416,17 +266,13 @@ static hipError_t flex_output_mt(const Geometry& g, int mode, const void* Mq, vo
 }
 
 template <int M>
-hipError_t PerMFlex<M>::output(const Geometry& g, bool leg, int mode, const void* Mq, int m_bits,
-                               void* y, int out_type, bool relu, unsigned long long* amax,
-                               const FlexMats& fm, const StageMults& mu, float mult_out,
-                               hipStream_t st) {
+hipError_t PerMFlex<M>::output(const Geometry& g, bool leg, const void* Mq, int m_bits, void* y,
+                               int out_type, bool relu, const FlexMats& fm, const StageMults& mu,
+                               float mult_out, hipStream_t st) {
 #define WINO_FLEX_O(LEG_)                                                                        \
-  (m_bits == 8   ? flex_output_mt<M, LEG_, int8_t>(g, mode, Mq, y, out_type, relu, amax, fm, mu, \
-                                                   mult_out, st)                                 \
-   : m_bits == 9 ? flex_output_mt<M, LEG_, int16_t>(g, mode, Mq, y, out_type, relu, amax, fm,    \
-                                                    mu, mult_out, st)                            \
-                 : flex_output_mt<M, LEG_, int32_t>(g, mode, Mq, y, out_type, relu, amax, fm,    \
-                                                    mu, mult_out, st))
+  (m_bits == 8   ? flex_output_mt<M, LEG_, int8_t>(g, Mq, y, out_type, relu, fm, mu, mult_out, st)  \
+   : m_bits == 9 ? flex_output_mt<M, LEG_, int16_t>(g, Mq, y, out_type, relu, fm, mu, mult_out, st) \
+                 : flex_output_mt<M, LEG_, int32_t>(g, Mq, y, out_type, relu, fm, mu, mult_out, st))
   return leg ? WINO_FLEX_O(true) : WINO_FLEX_O(false);
 #undef WINO_FLEX_O
 }

@@ -58,12 +58,12 @@ __device__ __forceinline__ uint32_t cast_biased(float v, float mult, float qmax)
 }
 
 // kTT: tile rows (t) per work group, 128 or 64 (small problems: twice the work groups).
-template <typename MT, int kCK, int kTT>
-__global__ __launch_bounds__(256) void k_contract(const int8_t* __restrict__ U,
-                                                  const int8_t* __restrict__ V,
-                                                  MT* __restrict__ Mo, int T, int C, int K,
-                                                  int tblocks, int kblocks, int tgroups, int tpg,
-                                                  int units, MultTable mults, float qmax) {
+// mult_of(p): cast multiplier of point p (uniform).
+template <typename MT, int kCK, int kTT, class MultOf>
+__device__ __forceinline__ void contract_body(const int8_t* __restrict__ U,
+                                              const int8_t* __restrict__ V, MT* __restrict__ Mo, int T,
+                                              int C, int K, int tblocks, int kblocks, int tgroups,
+                                              int tpg, int units, float qmax, MultOf&& mult_of) {
   constexpr int kRow = kCK + 16;               // padded LDS row
   constexpr int LPR = kCK / 16;                // lanes per staged row
   constexpr int RPP = 256 / LPR;               // rows staged per pass
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void k_contract(const int8_t* __restrict__ U,
   const int tb = (unit - p * tgroups) * tpg + inner / kblocks;
   if (tb >= tblocks) return;
   const int t0 = tb * kTT, k0 = kb * kKT;
-  const float mult = mults.v[p];               // cast multiplier of this point (uniform)
+  const float mult = mult_of(p);
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wt = wave & 1, wk = wave >> 1;
@@ -238,6 +238,23 @@ __global__ __launch_bounds__(256) void k_contract(const int8_t* __restrict__ U,
                                       reinterpret_cast<v4i*>(Mp + ((uint32_t)tl * (uint32_t)K + kseg * 8)));
       }
     }
+  } else if constexpr (sizeof(MT) == 8) {
+    // calibration: only max |result| of the point leaves (rows past the edge repeat existing ones)
+    unsigned top = 0;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < JT; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) top = max(top, (unsigned)abs(acc[i][j][e]));
+    top = wave_max_u32(top);
+    __syncthreads();                     // LDS is reused
+    if (lane == 63) reinterpret_cast<unsigned*>(smem)[wave] = top;
+    __syncthreads();
+    if (tid == 0) {
+      const unsigned* w4 = reinterpret_cast<const unsigned*>(smem);
+      raise_max(Mo + p, max(max(w4[0], w4[1]), max(w4[2], w4[3])));
+    }
   } else {
     // unquantised int32 result (calibration, bits_hadamard = 32): stored from registers
 #pragma unroll
@@ -255,6 +272,41 @@ __global__ __launch_bounds__(256) void k_contract(const int8_t* __restrict__ U,
                                                            acc[i][j][4 * gq + 2], acc[i][j][4 * gq + 3]);
         }
       }
+  }
+}
+
+template <typename MT, int kCK, int kTT>
+__global__ __launch_bounds__(256) void k_contract(const int8_t* __restrict__ U,
+                                                  const int8_t* __restrict__ V,
+                                                  MT* __restrict__ Mo, int T, int C, int K,
+                                                  int tblocks, int kblocks, int tgroups, int tpg,
+                                                  int units, MultTable mults, float qmax) {
+  contract_body<MT, kCK, kTT>(U, V, Mo, T, C, K, tblocks, kblocks, tgroups, tpg, units, qmax,
+                              [&](int p) { return mults.v[p]; });
+}
+
+// Calibration.  MT = uint64_t: Mo[p] = max |contraction result| of point p.  Otherwise the cast with
+// the scale that those maxima call for, s_u and s_v read from the scratch memory, s_m written there.
+template <typename MT, int kCK, int kTT>
+__global__ __launch_bounds__(256) void k_contract_cal(const int8_t* __restrict__ U,
+                                                      const int8_t* __restrict__ V,
+                                                      MT* __restrict__ Mo, int T, int C, int K,
+                                                      int tblocks, int kblocks, int tgroups, int tpg,
+                                                      int units, CalScratch cal, float qmax) {
+  if constexpr (sizeof(MT) == 8) {
+    contract_body<MT, kCK, kTT>(U, V, Mo, T, C, K, tblocks, kblocks, tgroups, tpg, units, qmax,
+                                [](int) { return 0.f; });
+  } else {
+    const unsigned lane = threadIdx.x & 63;
+    unsigned top = (int)lane < cal.n2 ? (unsigned)cal.array(kCalM)[lane] : 0u;
+    top = (unsigned)__builtin_amdgcn_readlane((int)wave_max_u32(top), 63);
+    const double s_uv = (double)cal.scales()[kCalSU] * (double)cal.scales()[kCalSV];
+    const double real = (double)top * s_uv;
+    const float s_m = real > 0.0 ? (float)(real / (double)qmax) : 1.0f;
+    const float mult = (float)(s_uv / (double)s_m);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cal.scales()[kCalSM] = s_m;
+    contract_body<MT, kCK, kTT>(U, V, Mo, T, C, K, tblocks, kblocks, tgroups, tpg, units, qmax,
+                                [=](int) { return mult; });
   }
 }
 
@@ -369,26 +421,34 @@ hipError_t launch_calibrate_stage(int stage, const Geometry& g, bool leg, int ph
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_flex_stage(int stage, const Geometry& g, bool leg, int mode, const void* in,
-                             int m_bits, void* out, int out_type, bool relu,
-                             unsigned long long* amax, const FlexMats& fm, const StageMults& mu,
-                             float mult, hipStream_t st) {
+hipError_t launch_flex_stage(int stage, const Geometry& g, bool leg, const void* in, int m_bits,
+                             void* out, int out_type, bool relu, const FlexMats& fm,
+                             const StageMults& mu, float mult, hipStream_t st) {
   const long items = stage == 0 ? (long)g.K * g.C : stage == 1 ? (long)g.T * g.C : (long)g.T * g.K;
   if (items == 0) return hipSuccess;
 #define WINO_FLEX_M(MM)                                                                          \
   case MM:                                                                                       \
-    return stage == 0   ? PerMFlex<MM>::weight(g, leg, mode, (const int8_t*)in, (int8_t*)out,    \
-                                               amax, fm, mu, mult, st)                           \
-           : stage == 1 ? PerMFlex<MM>::input(g, leg, mode, (const int8_t*)in, (int8_t*)out,     \
-                                              amax, fm, mu, mult, st)                            \
-                        : PerMFlex<MM>::output(g, leg, mode, in, m_bits, out, out_type, relu,    \
-                                               amax, fm, mu, mult, st);
+    return stage == 0   ? PerMFlex<MM>::weight(g, leg, (const int8_t*)in, (int8_t*)out, fm, mu, mult, st) \
+           : stage == 1 ? PerMFlex<MM>::input(g, leg, (const int8_t*)in, (int8_t*)out, fm, mu, mult, st) \
+                        : PerMFlex<MM>::output(g, leg, in, m_bits, out, out_type, relu, fm, mu, mult, st);
   switch (g.m) {
     WINO_FLEX_M(2)
     WINO_FLEX_M(4)
     WINO_FLEX_M(6)
   }
 #undef WINO_FLEX_M
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_flex_calibrate(const Geometry& g, bool leg, const int8_t* x, int8_t* U,
+                                 const int8_t* w, int8_t* V, void* Mq, int m_bits, bool relu,
+                                 float s_x, float s_w, CalScratch cal, const FlexMats& fm,
+                                 hipStream_t st) {
+  switch (g.m) {
+    case 2: return PerMFlex<2>::calibrate(g, leg, x, U, w, V, Mq, m_bits, relu, s_x, s_w, cal, fm, st);
+    case 4: return PerMFlex<4>::calibrate(g, leg, x, U, w, V, Mq, m_bits, relu, s_x, s_w, cal, fm, st);
+    case 6: return PerMFlex<6>::calibrate(g, leg, x, U, w, V, Mq, m_bits, relu, s_x, s_w, cal, fm, st);
+  }
   return hipErrorInvalidValue;
 }
 
@@ -439,9 +499,9 @@ hipError_t launch_operand_transforms(const Geometry& g, int leg, const int8_t* x
   return hipErrorInvalidValue;
 }
 
-template <int kTT>
-static hipError_t contract_tt(const Geometry& g, const int8_t* U, const int8_t* V, void* Mo,
-                              int m_bits, const MultTable& mult, hipStream_t st) {
+// Calls launch(grid, T, C, K, tblocks, kblocks, tgroups, tpg, units) with the block numbering of a layer.
+template <int kTT, class Launch>
+static hipError_t contract_grid(const Geometry& g, Launch&& launch) {
   const int n = g.m + 2;
   const int tblocks = (g.T + kTT - 1) / kTT, kblocks = (g.K + kKT - 1) / kKT;
   const int tgroups = contract_tile_groups(g, kTT);
@@ -449,17 +509,43 @@ static hipError_t contract_tt(const Geometry& g, const int8_t* U, const int8_t* 
   const int units = n * n * tgroups;
   const long nblocks = (long)((units + 7) / 8) * 8 * tpg * kblocks;
   if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
-  dim3 grid((unsigned)nblocks);
-  if (m_bits == 8)
-    wino_launch((k_contract<int8_t, 128, kTT>), grid, dim3(256), st, U, V, (int8_t*)Mo, g.T, g.C,
-                       g.K, tblocks, kblocks, tgroups, tpg, units, mult, 127.f);
-  else if (m_bits == 9)
-    wino_launch((k_contract<int16_t, 128, kTT>), grid, dim3(256), st, U, V, (int16_t*)Mo, g.T,
-                       g.C, g.K, tblocks, kblocks, tgroups, tpg, units, mult, 255.f);
-  else
-    wino_launch((k_contract<int32_t, 128, kTT>), grid, dim3(256), st, U, V, (int32_t*)Mo, g.T,
-                       g.C, g.K, tblocks, kblocks, tgroups, tpg, units, mult, 0.f);
+  launch(dim3((unsigned)nblocks), g.T, g.C, g.K, tblocks, kblocks, tgroups, tpg, units);
   return hipGetLastError();
+}
+
+template <int kTT>
+static hipError_t contract_tt(const Geometry& g, const int8_t* U, const int8_t* V, void* Mo,
+                              int m_bits, const MultTable& mult, hipStream_t st) {
+  return contract_grid<kTT>(g, [&](dim3 grid, auto... a) {
+    if (m_bits == 8)
+      wino_launch((k_contract<int8_t, 128, kTT>), grid, dim3(256), st, U, V, (int8_t*)Mo, a..., mult, 127.f);
+    else if (m_bits == 9)
+      wino_launch((k_contract<int16_t, 128, kTT>), grid, dim3(256), st, U, V, (int16_t*)Mo, a..., mult, 255.f);
+    else
+      wino_launch((k_contract<int32_t, 128, kTT>), grid, dim3(256), st, U, V, (int32_t*)Mo, a..., mult, 0.f);
+  });
+}
+
+template <int kTT>
+static hipError_t contract_cal_tt(const Geometry& g, const int8_t* U, const int8_t* V, void* Mo,
+                                  int m_bits, CalScratch cal, hipStream_t st) {
+  hipError_t e = contract_grid<kTT>(g, [&](dim3 grid, auto... a) {
+    wino_launch((k_contract_cal<unsigned long long, 128, kTT>), grid, dim3(256), st, U, V,
+                cal.array(kCalM), a..., cal, 0.f);
+  });
+  if (e != hipSuccess) return e;
+  return contract_grid<kTT>(g, [&](dim3 grid, auto... a) {
+    if (m_bits == 8)
+      wino_launch((k_contract_cal<int8_t, 128, kTT>), grid, dim3(256), st, U, V, (int8_t*)Mo, a..., cal, 127.f);
+    else
+      wino_launch((k_contract_cal<int16_t, 128, kTT>), grid, dim3(256), st, U, V, (int16_t*)Mo, a..., cal, 255.f);
+  });
+}
+
+hipError_t launch_contract_cal(const Geometry& g, const int8_t* U, const int8_t* V, void* Mo, int m_bits,
+                               CalScratch cal, hipStream_t st) {
+  return contract_tile_rows(g) == 64 ? contract_cal_tt<64>(g, U, V, Mo, m_bits, cal, st)
+                                     : contract_cal_tt<128>(g, U, V, Mo, m_bits, cal, st);
 }
 
 // Zero fill in 16-byte stores (a kernel, not hipMemsetAsync, so that a caller may

@@ -297,36 +297,78 @@ struct FlexMats {
   float APT[6 * 8];
 };
 
-// Launchers of the flex kernels (wino_flex.hpp).  mode 0 runs the stage, 1
-// reduces max |fp32 bracket value| into amax[0] (float bit pattern), 2 (weights,
-// Legendre) reduces the per-(i, j) numerator maxima of the P^{-1} bracket.
+// Scratch memory of a calibration that chooses its scales on the device: one array of n*n maxima per
+// cast (zero at the start), then the scales that later kernels need.  A maximum is an integer
+// numerator or the bit pattern of a non-negative float.
+enum { kCalW1, kCalW2, kCalX1, kCalX2, kCalM, kCalM1, kCalY, kCalArrays };   // maxima: first and second bracket of w and x, M, brackets of M
+enum { kCalSX1, kCalSU, kCalSW1, kCalSV, kCalSM, kCalSM1, kCalScales };      // scales
+struct CalScratch {
+  unsigned long long* base;
+  int n2;
+  WINO_HOST_DEVICE unsigned long long* array(int which) const { return base + which * n2; }
+  WINO_HOST_DEVICE float* scales() const { return reinterpret_cast<float*>(base + kCalArrays * n2); }
+  static constexpr size_t bytes(int n2) { return (size_t)kCalArrays * n2 * 8 + kCalScales * 4; }
+};
+#if defined(__HIPCC__)
+// Maximum over the wave, in lane 63.
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+#define WINO_DPP_MAX(CTRL) v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false))
+  WINO_DPP_MAX(0x111);   // row_shr:1, 2, 4, 8: lane 15 of a row of 16 has the row's maximum
+  WINO_DPP_MAX(0x112);
+  WINO_DPP_MAX(0x114);
+  WINO_DPP_MAX(0x118);
+  WINO_DPP_MAX(0x142);   // row_bcast:15, row_bcast:31
+  WINO_DPP_MAX(0x143);
+#undef WINO_DPP_MAX
+  return v;
+}
+// *at = max(*at, v).  The plain read first: once the maximum has been met most groups find nothing to
+// raise, and the memory location sees a few atomics instead of one per group.
+__device__ __forceinline__ void raise_max(unsigned long long* at, unsigned long long v) {
+  if (v > __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(at, v);
+}
+#endif
+
+// Launchers of the flex kernels (wino_flex.hpp, wino_flex_calibrate.hpp).
 template <int M>
 struct PerMFlex {
-  static hipError_t weight(const Geometry& g, bool legendre, int mode, const int8_t* w, int8_t* V,
-                           unsigned long long* amax, const FlexMats& fm, const StageMults& mu,
-                           float mult_first, hipStream_t st);
-  static hipError_t input(const Geometry& g, bool legendre, int mode, const int8_t* x, int8_t* U,
-                          unsigned long long* amax, const FlexMats& fm, const StageMults& mu,
-                          float mult_u, hipStream_t st);
-  static hipError_t output(const Geometry& g, bool legendre, int mode, const void* M_, int m_bits,
-                           void* y, int out_type, bool relu, unsigned long long* amax,
-                           const FlexMats& fm, const StageMults& mu, float mult_out,
-                           hipStream_t st);
-  // input and weight stage (mode 0) in one launch
+  static hipError_t weight(const Geometry& g, bool legendre, const int8_t* w, int8_t* V,
+                           const FlexMats& fm, const StageMults& mu, float mult_first, hipStream_t st);
+  static hipError_t input(const Geometry& g, bool legendre, const int8_t* x, int8_t* U,
+                          const FlexMats& fm, const StageMults& mu, float mult_u, hipStream_t st);
+  static hipError_t output(const Geometry& g, bool legendre, const void* M_, int m_bits, void* y,
+                           int out_type, bool relu, const FlexMats& fm, const StageMults& mu,
+                           float mult_out, hipStream_t st);
+  // input and weight stage in one launch
   static hipError_t operands(const Geometry& g, bool legendre, const int8_t* x, int8_t* U,
                              const int8_t* w, int8_t* V, const FlexMats& fm,
                              const StageMults& mu_in, float mult_u, const StageMults& mu_w,
                              float mult_first, hipStream_t st);
+  // every launch of a calibration
+  static hipError_t calibrate(const Geometry& g, bool legendre, const int8_t* x, int8_t* U,
+                              const int8_t* w, int8_t* V, void* M_, int m_bits, bool relu, float s_x,
+                              float s_w, CalScratch cal, const FlexMats& fm, hipStream_t st);
 };
 extern template struct PerMFlex<2>;
 extern template struct PerMFlex<4>;
 extern template struct PerMFlex<6>;
 
 // stage 0 weight, 1 input, 2 output, dispatched on g.m.
-hipError_t launch_flex_stage(int stage, const Geometry& g, bool legendre, int mode, const void* in,
-                             int m_bits, void* out, int out_type, bool relu,
-                             unsigned long long* amax, const FlexMats& fm, const StageMults& mu,
-                             float mult, hipStream_t st);
+hipError_t launch_flex_stage(int stage, const Geometry& g, bool legendre, const void* in, int m_bits,
+                             void* out, int out_type, bool relu, const FlexMats& fm,
+                             const StageMults& mu, float mult, hipStream_t st);
+
+// Runs a flex layer up to M and chooses its scales on the device: when the stream has got there,
+// U, V, M hold the layer's tensors, cal the scales of all casts but the last and the maximum
+// (kCalY) that s_y follows from.  cal may overlap nothing the layer writes.
+hipError_t launch_flex_calibrate(const Geometry& g, bool legendre, const int8_t* x, int8_t* U,
+                                 const int8_t* w, int8_t* V, void* M_, int m_bits, bool relu,
+                                 float s_x, float s_w, CalScratch cal, const FlexMats& fm,
+                                 hipStream_t st);
+// Contraction of a calibration (m_bits 8 or 9): maxima of the exact result into cal, then the
+// contraction again with the cast that they call for.
+hipError_t launch_contract_cal(const Geometry& g, const int8_t* U, const int8_t* V, void* M_, int m_bits,
+                               CalScratch cal, hipStream_t st);
 
 // Input and weight stage of a flex layer in one launch (both outputs non-empty).
 hipError_t launch_flex_operands(const Geometry& g, bool legendre, const int8_t* x, int8_t* U,

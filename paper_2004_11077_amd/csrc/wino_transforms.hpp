@@ -463,7 +463,8 @@ __device__ __forceinline__ void cast_result_biased(const AccT (&num)[T.rows][T.r
 // Fetches the work group's taps, lets `math(taps [3][3], q [n][n])` turn a lane's nine taps into n*n
 // values whose low byte is the code, and stores them: shared by the brackets with the fixed matrices
 // (below) and with run-time matrices (wino_flex.hpp).
-template <int M, class Math>
+// STORE = false: `math` keeps what it needs (calibration); nothing is stored.
+template <int M, bool STORE = true, class Math>
 __device__ __forceinline__ void weight_items(const int8_t* __restrict__ w, int8_t* __restrict__ V,
                                              const Geometry& g, unsigned block, Math&& math) {
   constexpr int n = M + 2, n2 = n * n;
@@ -499,6 +500,7 @@ __device__ __forceinline__ void weight_items(const int8_t* __restrict__ w, int8_
   });
   int q[n][n];
   math(wi, q);
+  if constexpr (!STORE) return;
   static_for<0, n>([&](auto i) {
     static_for<0, n>([&](auto j) {
       s_v[(decltype(i)::value * n + decltype(j)::value) * 256 + tid] = (int8_t)q[i][j];
@@ -566,7 +568,9 @@ __device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t
 // block-uniform (scalar registers, scalar arithmetic) and no item is out of
 // range.
 // math(pixels [n][n], q [n][n]) turns a lane's n*n pixels into n*n values whose low byte is the code.
-template <int M, bool WHOLE, class Math>
+// STORE = false: `math` keeps what it needs (calibration); nothing is stored.  Items past the last one
+// have zero pixels.
+template <int M, bool WHOLE, bool STORE = true, class Math>
 __device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t* __restrict__ U,
                                             const Geometry& g, unsigned block, Math&& math) {
   constexpr int n = M + 2, n2 = n * n;
@@ -633,6 +637,7 @@ __device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t
   });
   int q[n][n];
   math(xi, q);
+  if constexpr (!STORE) return;
   static_for<0, n>([&](auto i) {
     static_for<0, n>([&](auto j) {
       s_out[(decltype(i)::value * n + decltype(j)::value) * 256 + tid] = (int8_t)q[i][j];
@@ -769,7 +774,7 @@ __device__ __forceinline__ void fetch_m(const MT* __restrict__ Mq, long total, l
       });
     });
   } else {
-    if (!active) return;
+    if (!active) return;                             // xi is left as it was
     const MT* mb = Mq + (long)t * K + k;
     static_for<0, N>([&](auto i) {
       static_for<0, N>([&](auto j) {
@@ -788,7 +793,7 @@ template <int M, bool LEG, typename MT, int OUT, bool WHOLE, bool PP, int BASE =
 __global__ __launch_bounds__(256) void k_output_transform(const MT* __restrict__ Mq,
                                                           void* __restrict__ yv, Geometry g,
                                                           StageMults mu, int relu, ShiftTable sh) {
-  constexpr int n = M + 2, n2 = n * n;
+  constexpr int n = M + 2;
   constexpr int64_t IN_MAX = PP ? (MTraits<MT>::in_max << kMaxMShift) : MTraits<MT>::in_max;
   using TB = Tab<M, BASE>;
   const int tid = threadIdx.x;

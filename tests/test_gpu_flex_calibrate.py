@@ -1,0 +1,42 @@
+"""Scales of a flex layer chosen on the device, at the ends of the range: one tile and 16 channels (the
+smallest scratch region), several work groups with a partly empty last one, a 64-row contraction, all
+widths of M in both bases.  Every scale and the output must equal the oracle's bit for bit."""
+import numpy as np
+import pytest
+
+from helpers import small_layer
+from oracle import flex, quantised as q
+from test_gpu_flex import noisy_matrices
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,base,bh,out_type,relu,shape", [
+    (2, "legendre", 8, "f32", False, (1, 2, 2, 16, 16)),
+    (4, "legendre", 9, "i8", True, (1, 3, 4, 16, 16)),
+    (6, "canonical", 9, "i8", False, (1, 6, 6, 16, 16)),
+    (4, "legendre", 8, "f32", True, (3, 13, 10, 48, 80)),
+    (6, "legendre", 32, "f32", False, (2, 7, 13, 32, 48)),
+    (4, "canonical", 32, "i8", True, (2, 9, 9, 80, 144)),
+    (2, "canonical", 8, "i8", True, (9, 8, 8, 16, 256)),
+])
+def test_device_chosen_scales_equal_the_oracles(m, base, bh, out_type, relu, shape):
+    import torch
+    import paper_2004_11077_amd as wn
+    N, H, W, C, K = shape
+    xq, wq, s_x, s_w = small_layer(N, H, W, C, K, seed=400 + m)
+    fm = noisy_matrices(m, base, seed=m + 50)
+    cfg = q.LayerConfig(m=m, base=base, bits_hadamard=bh, out_type=out_type, relu=relu)
+    ora, sc = flex.run_layer_flex(xq, wq, s_x, s_w, cfg, fm)
+    desc = wn.ConvDesc(N, H, W, C, K, m=m, bits_hadamard=bh, relu=int(relu),
+                       base=wn.BASE_LEGENDRE if base == "legendre" else wn.BASE_CANONICAL,
+                       out_type=wn.OUT_I8 if out_type == "i8" else wn.OUT_F32)
+    x, w = torch.from_numpy(xq).cuda(), torch.from_numpy(wq).cuda()
+    y = torch.zeros((N, H, W, K), dtype=torch.int8 if out_type == "i8" else torch.float32, device="cuda")
+    ws = torch.randint(0, 255, (wn.wino_calibrate_workspace_bytes(desc),), dtype=torch.uint8, device="cuda")
+    got = wn.wino_flex_calibrate(desc, wn.FlexMatrices(fm.GP, fm.BPT, fm.APT), x, w, y, float(s_x),
+                                 float(s_w), ws)
+    torch.cuda.synchronize()
+    for name, val in sc.items():
+        assert np.float32(getattr(got, name)) == np.float32(val), name
+    assert np.array_equal(y.cpu().numpy(), ora["y"].astype(np.int8 if out_type == "i8" else np.float32))
