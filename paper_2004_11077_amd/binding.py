@@ -223,10 +223,26 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
 
 
+_raw_stream = None
+
+
+def _current_raw_stream():
+    """Handle of PyTorch's current stream.  Asked for directly where PyTorch offers it (0.1 us), else
+    through the Stream object that torch.cuda.current_stream() builds (2.5 us, as long as a launch)."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.init()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        _raw_stream = ((lambda: raw(device())) if raw and device
+                       else lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        return C.c_void_p(_current_raw_stream())
     return C.c_void_p(getattr(stream, "cuda_stream", stream))
 
 
