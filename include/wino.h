@@ -133,7 +133,7 @@ typedef struct {
                                  workspace); needs bits_hadamard 8 or 9 and fp32
                                  or int8 output.  AUTO = the fastest of the three
                                  for the shape, as measured: the single kernel for
-                                 C, K <= 64; the two-kernel form (m = 2 or 4) for
+                                 C, K <= 64 and for small layers with C <= 64; the two-kernel form (m = 2 or 4) for
                                  layers with C <= 128, for layers with C <= 256
                                  whose M is 9 bits wide or whose grid is about
                                  one work group per compute unit, and whenever V

@@ -391,11 +391,25 @@ bool auto_takes_conout(const wino_conv_desc_t* d, const Plan& p) {
   return blocks <= (p.m_bits == 9 ? kConOutMaxBlocks9 : kConOutMaxBlocks8);
 }
 
+// C <= 64, K > 64: the single kernel recomputes its input transform per block of output channels, which
+// costs nothing while the chip is not full: it wins up to two of its smallest groups per compute unit.
+// Measured, int8 output, filters transformed / raw (us), single kernel against what AUTO took before:
+//   C = 64,  K = 128:  256 tiles (128 groups)   8.1 / 12.5 against 13.6 / 15.1
+//                     1024 tiles (512 groups)  10.2 / 14.3 against 14.1 / 14.9
+//                     2048 tiles (1024 groups) 15.0 / 18.5 against 15.5 / 16.4
+//   C = 32,  K = 512:  256 tiles (512 groups)   9.8 / 14.6 against 14.1 / 18.0
+//                      512 tiles (1024 groups) 14.5 / 18.9 against 14.5 / 18.5
+constexpr long kFusedMaxGroups = 512;
+bool auto_takes_fused(const Plan& p) {
+  const int kb = fused_channels(p.m_bits);
+  return ((long)p.g.T + 3) / 4 * ((p.g.K + kb - 1) / kb) <= kFusedMaxGroups;
+}
+
 // ON: M never leaves the chip.  The single kernel where the layer has one 64-channel chunk
 // (its input transform is recomputed per 64 output channels and it keeps no accumulators
 // across chunks), the two-kernel form otherwise.  AUTO: whichever form is the fastest for the
-// shape: the single kernel for C, K <= 64, the two-kernel form for every other covered layer
-// that is large enough.
+// shape: the single kernel for C, K <= 64 and for small layers with C <= 64, the two-kernel form for
+// every other covered layer that is large enough.
 int select_path(const wino_conv_desc_t* d, const Plan& p, Path* path) {
   *path = kPathSplit;
   if (d->fused != WINO_FUSED_OFF && d->fused != WINO_FUSED_ON && d->fused != WINO_FUSED_AUTO)
@@ -410,7 +424,7 @@ int select_path(const wino_conv_desc_t* d, const Plan& p, Path* path) {
     return WINO_OK;
   }
   const bool v_rows_given = d->weights_pretransformed && !p.g.frag;   // slow in the two-kernel form
-  if (fused_all_covers(d, p) && d->C <= 64 && d->K <= 64 && !p.g.frag)
+  if (fused_all_covers(d, p) && d->C <= 64 && !p.g.frag && (d->K <= 64 || auto_takes_fused(p)))
     *path = kPathFusedAll;
   else if (conout_covers(d, p) && d->weights_pretransformed && p.g.frag)
     *path = kPathConOut;                       // the only form that reads a V in fragment order
@@ -458,7 +472,7 @@ int wino_conv2d_launches(const wino_conv_desc_t* d, char* buf, size_t buf_bytes)
     const bool w = !d->weights_pretransformed && (long)p.g.K * p.g.C != 0;
     const bool x = (long)p.g.T * p.g.C != 0;
     if (path == kPathFusedAll) {
-      if (w) add("weight_transform");
+      if (w && !fused_takes_raw_filters(p.g)) add("weight_transform");
       add("fused_layer");
     } else {
       if (w && x) {
@@ -1114,10 +1128,16 @@ int wino_conv2d(const wino_conv_desc_t* d, const void* x, const void* w_or_V, vo
     ws += round256(v_bytes_of(p, frag));
     // the fused variant transforms the filters on their own; the split path
     // does it together with the input transform, in one launch (below)
-    if (d->fused)
+    if (d->fused && !fused_takes_raw_filters(p.g))
       if (int rc = wino_weight_transform(d, w_or_V, Vws, s, hip_stream)) return rc;
   }
   if (d->fused) {
+    const bool raw = Vws && fused_takes_raw_filters(p.g);
+    StageMults w_mu;
+    if (raw) {
+      if (int rc = need(w_or_V, "w")) return rc;
+      V = w_or_V;
+    }
     if (int rc = need(x, "x")) return rc;
     if (int rc = need(y, "y")) return rc;
     if (int rc = need(s, "scales")) return rc;
@@ -1126,12 +1146,14 @@ int wino_conv2d(const wino_conv_desc_t* d, const void* x, const void* w_or_V, vo
     MultTable m_mult;
     ShiftTable sh;
     double s_m;
+    if (raw) if (int rc = weight_mults(p, s, &w_mu)) return rc;
     if (int rc = input_mults(p, s, &in_mu)) return rc;
     if (int rc = contract_mults(p, s, &m_mult, &sh, &s_m)) return rc;
     if (int rc = output_mults(p, d, s, &out_mu, nullptr)) return rc;
     hipError_t e = launch_fused(p.g, p.two_brackets, (const int8_t*)x, (const int8_t*)V, y,
                                 p.m_bits, d->out_type, d->relu != 0, in_mu, out_mu, m_mult,
-                                s->per_point ? &sh : nullptr, (hipStream_t)hip_stream);
+                                s->per_point ? &sh : nullptr, raw ? &w_mu : nullptr,
+                                static_cast<int8_t*>(Vws), (hipStream_t)hip_stream);
     return e == hipSuccess ? WINO_OK : fail_hip(e, "fused launch");
   }
   void* U = ws;

@@ -2,8 +2,8 @@
 // contraction -> output transform in ONE kernel; the Winograd-domain tensors U and M never
 // leave the compute unit.  Only x, V and y touch HBM.
 //
-// Work group = 8 waves, 16 tiles x KB output channels (KB = 64 for an int8 M, 32 for the
-// 9-bit int16 M), all n*n Winograd points:
+// Work group = 8 waves, kFT = 16 tiles (8 or 4 where the grid is small, fused_tiles) x KB output channels
+// (KB = 64 for an int8 M, 32 for the 9-bit int16 M), all n*n Winograd points:
 //   A  eight tiles at a time (one per wave): their n*n pixels x 64 channels are staged in
 //      LDS with 16-byte loads (in the part of U_s that is still free), every lane
 //      transforms one (tile, channel) item exactly as the input-transform kernel does and
@@ -15,16 +15,18 @@
 //      accumulator outlives a point;
 //   C  every lane runs the output transform of (tile, k) items and stores y.
 //
+// With few filters (fused_takes_raw_filters) every work group transforms its own: one launch for the
+// whole layer.  F(2,3), C = K = 16, one 8x8 image: 9.5 -> 6.2 us.
+//
 // The input transform is recomputed by each of the K / KB work groups that share a tile
-// block, so the variant pays off for K <= 64 (one k block).  Wider layers keep M on chip
+// block, so the variant pays off for K <= 64 (one k block) or while the chip is not full.  Wider layers keep M on chip
 // with the two-kernel form of wino_conout.hpp instead.
 #include "wino_transforms.hpp"
 
 namespace wino {
 
-constexpr int kFT = 16;          // tiles per work group
 constexpr int kFC = 64;          // input channels (the whole reduction)
-constexpr int kPt = kFT * kFC;   // bytes of one point's block in LDS: 16 tiles x 64 bytes
+constexpr int kPt = 16 * kFC;    // bytes of one point's block in LDS: 16 tiles x 64 bytes
 constexpr int kFW = 8;           // waves per work group
 
 // Byte offset of (tile, byte) inside a point's 1 KB block.  Rows are 64 bytes
@@ -36,21 +38,31 @@ __device__ __forceinline__ int sw(int tile, int byte) {
   return tile * kFC + ((((byte >> 4) ^ ((tile >> 1) & 3)) << 4) | (byte & 15));
 }
 
+constexpr int kRawFilters = 1024;   // filters a work group transforms itself, at most
+template <bool RAW>
+struct FilterMults {};
+template <>
+struct FilterMults<true> {
+  StageMults mu;
+  int8_t* V;        // the first tile block also leaves the transformed filters here
+};
+
 // PP: per-point scales -- the cast of point p uses mm.v[p], and its codes enter
 // the output bracket shifted left by entry p of sh (<= kMaxMShift, priced into the
 // bounds).  Without PP every entry of mm is the same and sh is not read.
-template <int M, bool LEG, typename MT, int OUT, bool PP>
-__global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict__ x,
+template <int M, bool LEG, typename MT, int OUT, bool PP, int kFT, bool RAW>
+__global__ __launch_bounds__(kFW * 64, RAW ? 4 : 6) void k_fused(const int8_t* __restrict__ x,
                                                const int8_t* __restrict__ V,
                                                void* __restrict__ yv, Geometry g, StageMults in_mu,
                                                StageMults out_mu, MultTable mm, ShiftTable sh,
-                                               int relu, int tblocks) {
+                                               int relu, int tblocks, FilterMults<RAW> w_mu) {
   constexpr int n = M + 2, n2 = n * n;
   constexpr int KB = sizeof(MT) == 1 ? 64 : 32;      // output channels per work group
   constexpr int NKB = KB / 16;                       // 16-wide MFMA column blocks
   constexpr int NT = kFW * 64;                       // lanes per work group
   constexpr int NPW = (n2 + kFW - 1) / kFW;          // points per wave (the last may be empty)
-  static_assert(n2 % 4 == 0 && kFT == 2 * kFW);
+  constexpr int kPass = kFT < kFW ? kFT : kFW;       // tiles per pass of phase A
+  static_assert(n2 % 4 == 0 && (kFT == 2 * kFW || kFT == kFW || kFT == kFW / 2));
   constexpr float QM = sizeof(MT) == 1 ? 127.f : 255.f;
   using TB = Tab<M>;
   // U_s, then M_s: one KiB per point, tile-major.  The pixels of a pass (8 tiles x n*n
@@ -63,6 +75,9 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
   // Image and pixel origin of the block's 16 tiles, worked out once and read back from LDS
   // by the staging loop and the output transform: ti = {b, ty*M, tx*M, tile exists}.
   __shared__ int4 s_tile[kFT];
+  // RAW: the work group transforms its own filters into V_s[point][k][c], c < C, at most
+  // kRawFilters of them
+  __shared__ __attribute__((aligned(16))) int8_t V_s[RAW ? n2 * kRawFilters : 16];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // in a scalar register
@@ -75,18 +90,36 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
     tile_coords(g, t, b, ty, tx);
     s_tile[tid] = make_int4(b, ty * M, tx * M, t0 + tid < g.T ? 1 : 0);
   }
+  if constexpr (RAW) {
+    const int filters = min(KB, g.K - k0) * g.C;
+    for (int f = tid; f < filters; f += NT) {
+      const int8_t* wf = V + ((long)k0 * g.C + f) * 9;
+      int wi[3][3], q[n][n];
+      static_for<0, 3>([&](auto a) {
+        static_for<0, 3>([&](auto b) { wi[a][b] = wf[decltype(a)::value * 3 + decltype(b)::value]; });
+      });
+      weight_math<M, LEG>(wi, w_mu.mu, q);
+      static_for<0, n>([&](auto i) {
+        static_for<0, n>([&](auto j) {
+          constexpr int P = decltype(i)::value * n + decltype(j)::value;
+          V_s[P * filters + f] = (int8_t)q[i][j];
+          if (tb == 0) w_mu.V[(long)P * g.K * g.C + k0 * g.C + f] = (int8_t)q[i][j];
+        });
+      });
+    }
+  }
   __syncthreads();
 
   // ---- A: input transform of 16 tiles x 64 channels, one tile per wave and pass ----
 #pragma unroll 1
-  for (int it = 0; it < kFT / kFW; ++it) {
+  for (int it = 0; it < (kFT + kFW - 1) / kFW; ++it) {
     // stage the n*n pixels x 64 channels of the pass's 8 tiles with 16-byte loads (zeros
     // outside the image, past the last tile or channel)
     if (it) __syncthreads();                         // the previous pass's pixels are consumed
 #pragma unroll
-    for (int j = 0; j < (kFW * n2 * 4 + NT - 1) / NT; ++j) {
+    for (int j = 0; j < (kPass * n2 * 4 + NT - 1) / NT; ++j) {
       const int idx = j * NT + tid;
-      if (idx < kFW * n2 * 4) {
+      if (idx < kPass * n2 * 4) {
         const int tq = idx / (n2 * 4), rem = idx - tq * (n2 * 4);
         const int pix = rem >> 2, sg = rem & 3;
         const int4 ti = s_tile[it * kFW + tq];
@@ -110,6 +143,7 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
       });
     });
     if (it) __syncthreads();                         // this pass's codes go where its pixels were
+    if (kFT < kFW && wave >= kFT) continue;          // wave-uniform; the single pass has no barrier below
     int q[n][n];
     if constexpr (LEG) {
       acc_t<TB::PinvT, 127> num1[n][n];
@@ -139,7 +173,8 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
   unsigned voff[NKB];                                // the lane's V row and channel segment
 #pragma unroll
   for (int kb = 0; kb < NKB; ++kb)
-    voff[kb] = (unsigned)(min(k0 + kb * 16 + jl, g.K - 1) * g.C + (cok ? seg * 16 : 0));   // clamp, masked at the store
+    voff[kb] = (unsigned)(min(RAW ? kb * 16 + jl : k0 + kb * 16 + jl, (RAW ? min(KB, g.K - k0) : g.K) - 1) * g.C +
+                          (cok ? seg * 16 : 0));     // clamp, masked at the store
 #pragma clang loop unroll_count(3)
   for (int pi = 0; pi < NPW; ++pi) {
     const int p = pi * kFW + wave;
@@ -149,7 +184,8 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
       // a segment past C re-reads segment 0: its U_s codes are zero, whatever V holds
-      const v4i av = *reinterpret_cast<const v4i*>(V + (long)p * g.K * g.C + voff[kb]);
+      const int8_t* Vp = RAW ? V_s + p * min(KB, g.K - k0) * g.C : V + (long)p * g.K * g.C;
+      const v4i av = *reinterpret_cast<const v4i*>(Vp + voff[kb]);
       a4[kb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bu, v4i{0, 0, 0, 0}, 0, 0, 0);
     }
     const float m_mult = PP ? mm.v[p] : mm.v[0];     // p is wave-uniform
@@ -178,19 +214,21 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
   const int lo_f = relu ? 0 : (int)0x80000000;
   const int lo_i = relu ? 0 : -128;
 #pragma unroll 1
-  for (int it = 0; it < kFT * KB / NT; ++it) {
+  for (int it = 0; it < (kFT * KB + NT - 1) / NT; ++it) {
     int tl, kl;
     int4 ti;
     if constexpr (KB == 64) {
       // a wave = the 64 output channels of one tile: the tile's coordinates, the edge tests
       // and the tile part of every address stay in scalar registers
       tl = it * (NT / KB) + wave, kl = lane;
+      if (kFT < kFW && wave >= kFT) continue;        // wave-uniform
       const int4 tv = s_tile[tl];
       ti = make_int4(__builtin_amdgcn_readfirstlane(tv.x), __builtin_amdgcn_readfirstlane(tv.y),
                      __builtin_amdgcn_readfirstlane(tv.z), __builtin_amdgcn_readfirstlane(tv.w));
     } else {
       const int item = it * NT + tid;
       tl = item / KB, kl = item - tl * KB;
+      if (tl >= kFT) continue;
       ti = s_tile[tl];
     }
     const int k = k0 + kl;
@@ -246,60 +284,99 @@ __global__ __launch_bounds__(kFW * 64, 6) void k_fused(const int8_t* __restrict_
   }
 }
 
+template <int M, bool LEG, typename MT, bool PP, int FT, bool RAW>
+static hipError_t fused_ft(const Geometry& g, const int8_t* x, const int8_t* V, void* y, int out_type,
+                           bool relu, const StageMults& in_mu, const StageMults& out_mu,
+                           const MultTable& mm, const ShiftTable& sh, const FilterMults<RAW>& w_mu,
+                           hipStream_t st) {
+  constexpr int KB = sizeof(MT) == 1 ? 64 : 32;
+  const int tblocks = (g.T + FT - 1) / FT, kblocks = (g.K + KB - 1) / KB;
+  dim3 grid((unsigned)(tblocks * kblocks));
+  const int r = relu ? 1 : 0;
+  if (out_type == 0)
+    wino_launch((k_fused<M, LEG, MT, 0, PP, FT, RAW>), grid, dim3(kFW * 64), st, x, V, y, g, in_mu,
+                       out_mu, mm, sh, r, tblocks, w_mu);
+  else
+    wino_launch((k_fused<M, LEG, MT, 2, PP, FT, RAW>), grid, dim3(kFW * 64), st, x, V, y, g, in_mu,
+                       out_mu, mm, sh, r, tblocks, w_mu);
+  return hipGetLastError();
+}
+
+// Tiles per work group.  A launch takes about (first + each * rounds) us, rounds = work groups over 256
+// compute units: smaller groups have the shorter chain of phases, larger ones waste less of the
+// matrix instruction's 16 columns and of phase B.  Measured, F(4,3), C = K = 64, us per layer with
+// transformed filters:
+//   tiles          64 .. 1024   2048   3072   4096   6144   8192
+//   16 per group      15.6      15.7   15.8   15.9   23.6   23.7
+//    8                10.1      10.2   14.9   15.0   19.7   24.9
+//    4                 8.2      10.7   13.7   16.7   23.3   30.1
+// F(2,3), C = K = 16: 7.0, 5.2, 4.6 at 1024 tiles, 14.8, 17.0, 22.0 at 16384.
+static int fused_tiles(const Geometry& g, int kb) {
+  constexpr struct { int tiles; long first, each; } kCost[3] = {{16, 80, 78}, {8, 53, 49}, {4, 54, 30}};
+  int best = 16;
+  long best_cost = 0;
+  for (const auto& c : kCost) {
+    const long groups = ((long)g.T + c.tiles - 1) / c.tiles * ((g.K + kb - 1) / kb);
+    const long cost = c.first + c.each * ((groups + 255) / 256);
+    if (best_cost == 0 || cost < best_cost) best = c.tiles, best_cost = cost;
+  }
+  return best;
+}
+
 template <int M, bool LEG, typename MT, bool PP>
 static hipError_t fused_mt(const Geometry& g, const int8_t* x, const int8_t* V, void* y, int out_type,
                            bool relu, const StageMults& in_mu, const StageMults& out_mu,
-                           const MultTable& mm, const ShiftTable& sh, hipStream_t st) {
+                           const MultTable& mm, const ShiftTable& sh, const StageMults* w_mu,
+                           int8_t* Vout, hipStream_t st) {
   constexpr int KB = sizeof(MT) == 1 ? 64 : 32;
-  const int tblocks = (g.T + kFT - 1) / kFT, kblocks = (g.K + KB - 1) / KB;
-  dim3 grid((unsigned)(tblocks * kblocks));
-  const int r = relu ? 1 : 0;
   // One channel chunk only: wider layers take the two-kernel form (input transform, then
   // contraction + output transform), which does not recompute the input transform per block
   // of output channels.
   if (g.C > kFC) return hipErrorInvalidValue;
-  if (out_type == 0)
-    wino_launch((k_fused<M, LEG, MT, 0, PP>), grid, dim3(kFW * 64), st, x, V, y, g, in_mu,
-                       out_mu, mm, sh, r, tblocks);
-  else
-    wino_launch((k_fused<M, LEG, MT, 2, PP>), grid, dim3(kFW * 64), st, x, V, y, g, in_mu,
-                       out_mu, mm, sh, r, tblocks);
-  return hipGetLastError();
+  const int ft = fused_tiles(g, KB);
+  if (w_mu)
+    return fused_ft<M, LEG, MT, PP, 4, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {*w_mu, Vout}, st);
+  if (ft == 4)
+    return fused_ft<M, LEG, MT, PP, 4, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {}, st);
+  if (ft == 8)
+    return fused_ft<M, LEG, MT, PP, 8, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {}, st);
+  return fused_ft<M, LEG, MT, PP, 16, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {}, st);
 }
 
 template <int M, bool LEG>
 static hipError_t fused_ml(const Geometry& g, const int8_t* x, const int8_t* V, void* y, int m_bits,
                            int out_type, bool relu, const StageMults& in_mu,
                            const StageMults& out_mu, const MultTable& mm, const ShiftTable* sh,
-                           hipStream_t st) {
+                           const StageMults* w_mu, int8_t* Vout, hipStream_t st) {
   const ShiftTable none{};
   if (sh)
     return m_bits == 8
-               ? fused_mt<M, LEG, int8_t, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, *sh, st)
-               : fused_mt<M, LEG, int16_t, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, *sh, st);
+               ? fused_mt<M, LEG, int8_t, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, *sh, w_mu, Vout, st)
+               : fused_mt<M, LEG, int16_t, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, *sh, w_mu, Vout, st);
   return m_bits == 8
-             ? fused_mt<M, LEG, int8_t, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, none, st)
-             : fused_mt<M, LEG, int16_t, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, none, st);
+             ? fused_mt<M, LEG, int8_t, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, none, w_mu, Vout, st)
+             : fused_mt<M, LEG, int16_t, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, none, w_mu, Vout, st);
 }
 
 template <int M>
 static hipError_t fused_m(const Geometry& g, bool leg, const int8_t* x, const int8_t* V, void* y,
                           int m_bits, int out_type, bool relu, const StageMults& in_mu,
                           const StageMults& out_mu, const MultTable& mm, const ShiftTable* sh,
-                          hipStream_t st) {
-  return leg ? fused_ml<M, true>(g, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, st)
-             : fused_ml<M, false>(g, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, st);
+                          const StageMults* w_mu, int8_t* Vout, hipStream_t st) {
+  return leg ? fused_ml<M, true>(g, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, w_mu, Vout, st)
+             : fused_ml<M, false>(g, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, w_mu, Vout, st);
 }
 
 hipError_t launch_fused(const Geometry& g, bool legendre_inner, const int8_t* x, const int8_t* V,
                         void* y, int m_bits, int out_type, bool relu, const StageMults& in_mu,
                         const StageMults& out_mu, const MultTable& mm, const ShiftTable* sh,
-                        hipStream_t st) {
+                        const StageMults* w_mu, int8_t* Vout, hipStream_t st) {
   if ((long)g.T * g.K == 0) return hipSuccess;
   if ((m_bits != 8 && m_bits != 9) || (out_type != 0 && out_type != 2)) return hipErrorInvalidValue;
+  if (w_mu && !fused_takes_raw_filters(g)) return hipErrorInvalidValue;
   switch (g.m) {
-    case 2: return fused_m<2>(g, legendre_inner, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, st);
-    case 4: return fused_m<4>(g, legendre_inner, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, st);
+    case 2: return fused_m<2>(g, legendre_inner, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, w_mu, Vout, st);
+    case 4: return fused_m<4>(g, legendre_inner, x, V, y, m_bits, out_type, relu, in_mu, out_mu, mm, sh, w_mu, Vout, st);
   }
   return hipErrorInvalidValue;
 }

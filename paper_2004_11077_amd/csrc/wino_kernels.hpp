@@ -430,11 +430,19 @@ hipError_t launch_fill_zero(void* dst, long bytes, hipStream_t st);
 
 // Fused variant (input transform + contraction + output transform in one kernel);
 // V is the transformed filter tensor.  m = 2 or 4, m_bits 8 or 9, out_type 0 or 2.
-// mm: cast multiplier of the contraction per point; sh: per-point shifts or null.
+// mm: cast multiplier of the contraction per point; sh: per-point shifts or null.  w_mu not null: V is
+// the filter tensor itself, transformed with these multipliers (fused_takes_raw_filters); the
+// transformed filters are also left in Vout.
 hipError_t launch_fused(const Geometry& g, bool legendre_inner, const int8_t* x, const int8_t* V,
                         void* y, int m_bits, int out_type, bool relu, const StageMults& in_mu,
                         const StageMults& out_mu, const MultTable& mm, const ShiftTable* sh,
-                        hipStream_t st);
+                        const StageMults* w_mu, int8_t* Vout, hipStream_t st);
+// Output channels per work group of the fused kernel.
+inline int fused_channels(int m_bits) { return m_bits == 8 ? 64 : 32; }
+// Few enough filters (and tiles) for every work group of the fused kernel to transform its own.
+inline bool fused_takes_raw_filters(const Geometry& g) {
+  return (long)g.K * g.C <= 1024 && g.T <= 1024;
+}
 
 // Backward pass (wino_backward.hip), fp32.  which: 0 dY -> dM, 1 dU -> dx.
 hipError_t launch_backward_transform(int which, const Geometry& g, const float* in, float* out,

@@ -530,26 +530,34 @@ __device__ __forceinline__ void weight_items(const int8_t* __restrict__ w, int8_
   }
 }
 
+// Filter bracket(s) of one filter: taps -> codes.
+template <int M, bool LEG, int BASE = 1>
+__device__ __forceinline__ void weight_math(const int (&wi)[3][3], const StageMults& mu,
+                                            int (&q)[M + 2][M + 2]) {
+  constexpr int n = M + 2;
+  using TB = Tab<M, BASE>;
+  if constexpr (LEG) {
+    acc_t<TB::GP, 127> num1[n][n];
+    sandwich<TB::GP, 127>(wi, num1);
+    uint32_t w1[n][n];
+    cast_result_biased<TB::GP, 127, true>(num1, mu.inner, 127.f, w1);
+    acc_t<TB::Pinv, 127> num2[n][n];
+    sandwich_codes<TB::Pinv, 127>(w1, num2);
+    cast_result<TB::Pinv, 127>(num2, mu.outer, 127.f, q);
+  } else {
+    acc_t<TB::G, 127> num[n][n];
+    sandwich<TB::G, 127>(wi, num);
+    cast_result<TB::G, 127>(num, mu.outer, 127.f, q);
+  }
+}
+
 template <int M, bool LEG, int BASE = 1>
 __device__ __forceinline__ void weight_body(const int8_t* __restrict__ w, int8_t* __restrict__ V,
                                             const Geometry& g, const StageMults& mu,
                                             unsigned block) {
   constexpr int n = M + 2;
-  using TB = Tab<M, BASE>;
   weight_items<M>(w, V, g, block, [&](const int (&wi)[3][3], int (&q)[n][n]) {
-    if constexpr (LEG) {
-      acc_t<TB::GP, 127> num1[n][n];
-      sandwich<TB::GP, 127>(wi, num1);
-      uint32_t w1[n][n];
-      cast_result_biased<TB::GP, 127, true>(num1, mu.inner, 127.f, w1);
-      acc_t<TB::Pinv, 127> num2[n][n];
-      sandwich_codes<TB::Pinv, 127>(w1, num2);
-      cast_result<TB::Pinv, 127>(num2, mu.outer, 127.f, q);
-    } else {
-      acc_t<TB::G, 127> num[n][n];
-      sandwich<TB::G, 127>(wi, num);
-      cast_result<TB::G, 127>(num, mu.outer, 127.f, q);
-    }
+    weight_math<M, LEG, BASE>(wi, mu, q);
   });
 }
 
