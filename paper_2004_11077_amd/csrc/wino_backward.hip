@@ -208,27 +208,32 @@ __global__ __launch_bounds__(256, (M <= 4 ? 4 : 2)) void k_bwd_dx_dw(const float
 // are bf16 values as they stand, so every piece * code product is exact in the
 // fp32 accumulator of v_mfma_f32_32x32x16_bf16 and what is lost is what lies
 // below the 24th bit of A.  Three such MFMAs do the work of eight fp32 ones in
-// 3/16 of their cycles, which leaves LDS traffic and the splitting arithmetic
-// as the costs to keep down: hence the large tiles.
-// Work group = 4 waves (2 x 2) = (64 MB) x (64 NB) outputs, (32 MB) x (32 NB)
-// per wave as MB x NB blocks of 32 x 32, MB and NB 1 or 2.  The reduction runs
-// in chunks of 32 staged through LDS with the reduction index contiguous
-// ([row][red] and [col][red], rows of 40 bf16 = 80 bytes: 16-byte aligned
-// fragments, and the 32 rows a fragment read touches fall on distinct banks),
-// the next chunk's global loads in flight during the MFMAs.  Where the
-// reduction index is the slow one in memory (B always, A for dV) a lane loads
-// the same columns of two consecutive reduction rows and stores the pairs as
-// dwords.  red and cols are multiples of 4 resp. 16 (K and C are multiples of
-// 16), rows and red are otherwise arbitrary: out-of-range elements are staged
-// as zeros, out-of-range outputs are not stored.  Non-finite dM gives NaN.
+// 3/16 of their cycles.
+// Work group = 4 waves, WR of them along the rows: (32 WR) x (32 NB 4 / WR) outputs, a wave
+// 32 x (32 NB).  A never enters LDS: a lane loads the 8 reduction indices of its
+// MFMA row straight from memory (two 16-byte loads where the reduction is the fast index, eight
+// dwords with 128 contiguous bytes per 32 lanes where the row is) and cuts them in registers,
+// a stage of 64 ahead of their use.  With WR = 4 no two waves share rows, so nothing is
+// loaded or cut twice.  B is staged in stages of 64 as bf16 in fragment order, two buffers, one
+// barrier per stage: a lane loads four columns of eight reduction rows and stores four
+// whole 16-byte fragments.  Column c of a 32-wide block is MFMA column 8 (c % 4) + c / 4, so that
+// these stores and the fragment reads both touch consecutive LDS addresses.
+// red and cols are multiples of 4 resp. 16 (K and C are multiples of 16), rows and red are
+// otherwise arbitrary: A is zero past the end of the reduction, rows and columns past the last one
+// are computed from the last one and not stored.  Non-finite dM gives NaN.
+// Both contractions of 1024 tiles, C = K = 256 (9.7 GFLOP, 89 MB past the L2s): 48 us with A staged in
+// LDS in chunks of 32 (a quarter of a chunk's time spent waiting for loads that branches
+// closed too early), 44 us here; dU alone 28, dV alone 29.  What bounds it: all 864 groups start
+// at once, so that the waits for dM, 11 us of matrix work and the stores mostly follow one another
+// (without stores 36 us, without MFMAs 33 us).
 // ---------------------------------------------------------------------------
 using v4f = __attribute__((ext_vector_type(4))) float;
-using v2u = __attribute__((ext_vector_type(2))) unsigned;
+using v4u = __attribute__((ext_vector_type(4))) unsigned;
 using v16f = __attribute__((ext_vector_type(16))) float;
 using bf16x8 = __attribute__((ext_vector_type(8))) __bf16;
 
-constexpr int kGR = 32;        // reduction chunk
-constexpr int kLdH = 40;       // bf16 per staged row: the chunk and 8 of padding
+constexpr int kGR = 32;        // ranges of a split reduction are multiples of this
+constexpr int kStage = 64;     // reduction indices of B staged at a time
 constexpr int kXcds = 8;
 
 struct GemmArgs {
@@ -239,16 +244,12 @@ struct GemmArgs {
   int row_blocks, col_blocks, units;
   int blocks;                  // splits * ceil(units / 8) * 8 * col_blocks
   int splits, red_split;       // the reduction is cut into `splits` ranges of red_split (a multiple
-                               // of the chunk); range s writes its partial sum to C + s * n*n*rows*cols
+                               // of kGR); range s writes its partial sum to C + s * n*n*rows*cols
   long out_stride;             // n*n * rows * cols
 };
 
-// LDS of one work group in floats: three pieces of A and B as bf16, or (afterwards) one
-// 32 x (32 NB) output block per wave in rows of 32 NB + 4 floats.
-constexpr int gemm_lds(int mb, int nb) {
-  const int staged = (3 * mb + nb) * 64 * kLdH / 2, out = 4 * 32 * (32 * nb + 4);
-  return staged > out ? staged : out;
-}
+// Bytes of LDS for tiles of TC columns: two stages of B.
+constexpr int gemm_lds(int tc) { return 2 * kStage * tc * 2; }
 
 // x = h + m + l up to the bits below the 24th; each piece sits in the upper half of its word
 // (for l the caller drops the lower half).
@@ -263,20 +264,17 @@ __device__ __forceinline__ unsigned pack2(unsigned a, unsigned b) {
   return __builtin_amdgcn_perm(b, a, 0x07060302u);
 }
 
-template <bool ARED, int MB, int NB>
+template <bool ARED, int WR, int NB>
 __device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& scale,
-                                          unsigned block, float* __restrict__ smem) {
-  constexpr int TR = 64 * MB, TC = 64 * NB;
+                                          unsigned block, char* __restrict__ smem) {
+  constexpr int WC = 4 / WR, TR = 32 * WR, TC = 32 * NB * WC;
   const float* __restrict__ A = ga.A;
   const int8_t* __restrict__ B = ga.B;
   float* __restrict__ Cout = ga.C;
   const int rows = ga.rows, red = ga.red, cols = ga.cols;
   const int row_blocks = ga.row_blocks, col_blocks = ga.col_blocks, units = ga.units;
-  unsigned short* Ah = reinterpret_cast<unsigned short*>(smem);
-  unsigned short* Am = Ah + TR * kLdH;
-  unsigned short* Al = Am + TR * kLdH;
-  unsigned short* Bt = Al + TR * kLdH;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int per_split = ga.blocks / ga.splits;
   const int split = (int)(block / (unsigned)per_split);
   block -= (unsigned)split * (unsigned)per_split;
@@ -296,160 +294,164 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& s
   const int row0 = rb * TR, col0 = cb * TC;
   const float* Ap = A + (long)p * rows * red;
   const int8_t* Bp = B + (long)p * red * cols;
-  // Pair mapping: reduction rows 2 * rp and 2 * rp + 1 of the chunk, columns 4 * (pq + 16 j) .. + 3.
-  const int rp = tid & 15, pq = tid >> 4;
+  const int l32 = lane & 31, lk = lane >> 5;
+  const int wr = (wave / WC) * 32, wc = (wave % WC) * 32 * NB;
 
-  v4f ra[2 * MB];
-  int rbw[2 * NB];
-  auto fetch = [&](int r0) {
+  // MFMA operands: lane -> row (A) or column (B) lane % 32, reduction indices 8 (lane / 32) .. + 7.
+  const int arow = min(row0 + wr + l32, rows - 1);
+  const float* Al = ARED ? Ap + (long)arow * red + 8 * lk : Ap + (long)(8 * lk) * rows + arow;
+  float ra[kStage / 16][8];
+  auto fetch_a = [&](int r0, auto kkc) {         // indices r0 + 16 kk + 8 lk + 0 .. 7
+    constexpr int kk = decltype(kkc)::value;
+    const int r = r0 + 16 * kk;
+    if constexpr (ARED) {
+      const v4f v0 = *reinterpret_cast<const v4f*>(Al + r), v1 = *reinterpret_cast<const v4f*>(Al + r + 4);
 #pragma unroll
-    for (int it = 0; it < 2 * MB; ++it) {
-      v4f v = {0.f, 0.f, 0.f, 0.f};
-      if constexpr (ARED) {
-        const int idx = tid + it * 256;
-        const int row = idx >> 3, q = idx & 7;
-        if (row0 + row < rows && r0 + 4 * q < r_end)
-          v = *reinterpret_cast<const v4f*>(Ap + (long)(row0 + row) * red + r0 + 4 * q);
-      } else {
-        const int rr = r0 + 2 * rp + (it & 1), quad = pq + 16 * (it >> 1);
-        if (rr < r_end && row0 + 4 * quad < rows)
-          v = *reinterpret_cast<const v4f*>(Ap + (long)rr * rows + row0 + 4 * quad);
-      }
-      ra[it] = v;
-    }
+      for (int e = 0; e < 4; ++e) ra[kk][e] = v0[e], ra[kk][4 + e] = v1[e];
+    } else {
+      const float* src = Al + (long)r * rows;
 #pragma unroll
-    for (int it = 0; it < 2 * NB; ++it) {
-      const int rr = r0 + 2 * rp + (it & 1), quad = pq + 16 * (it >> 1);
-      rbw[it] = 0;
-      if (rr < r_end && col0 + 4 * quad < cols)
-        rbw[it] = *reinterpret_cast<const int*>(Bp + (long)rr * cols + col0 + 4 * quad);
+      for (int e = 0; e < 8; ++e) ra[kk][e] = src[(long)e * rows];
     }
   };
-  auto stage = [&]() {
-    if constexpr (ARED) {
+  // B: columns 4 bq .. + 3, reduction rows 8 bo .. + 7 of the stage (with 64 columns two lanes each
+  // carry the same).
+  constexpr int kQuads = TC / 4;
+  const int bq = tid % kQuads, bo = tid / kQuads % (kStage / 8);
+  const int8_t* Bl = Bp + min(col0 + 4 * bq, cols - 4);
+  int rbw[8];
+  auto fetch_b = [&](int r0) {
+    const int8_t* src = Bl + (long)(r0 + 8 * bo) * cols;
 #pragma unroll
-      for (int it = 0; it < 2 * MB; ++it) {
-        const int idx = tid + it * 256;
-        const int row = idx >> 3, q = idx & 7;
-        unsigned h[4], m[4], l[4];
+    for (int e = 0; e < 8; ++e) rbw[e] = *reinterpret_cast<const int*>(src + (long)e * cols);
+  };
+  auto stage_b = [&](int buf) {
+    char* at = smem + buf * (kStage * TC * 2) +
+               (((bo >> 1) * (TC / 32) + (bq >> 3)) * 64 + (bo & 1) * 32 + (bq & 7)) * 16;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) split3(ra[it][e], h[e], m[e], l[e]);
-        const int at = row * kLdH + 4 * q;
-        *reinterpret_cast<v2u*>(Ah + at) = v2u{pack2(h[0], h[1]), pack2(h[2], h[3])};
-        *reinterpret_cast<v2u*>(Am + at) = v2u{pack2(m[0], m[1]), pack2(m[2], m[3])};
-        *reinterpret_cast<v2u*>(Al + at) = v2u{pack2(l[0], l[1]), pack2(l[2], l[3])};
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          unsigned h0, m0, l0, h1, m1, l1;
-          split3(ra[2 * j][e], h0, m0, l0);
-          split3(ra[2 * j + 1][e], h1, m1, l1);
-          const int at = (4 * (pq + 16 * j) + e) * kLdH + 2 * rp;
-          *reinterpret_cast<unsigned*>(Ah + at) = pack2(h0, h1);
-          *reinterpret_cast<unsigned*>(Am + at) = pack2(m0, m1);
-          *reinterpret_cast<unsigned*>(Al + at) = pack2(l0, l1);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
+    for (int c = 0; c < 4; ++c) {
+      v4u f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         // A code as fp32 has at most 7 significant bits: its upper half is the bf16 value.
-        const float f0 = (float)(int8_t)((rbw[2 * j] >> (8 * e)) & 0xff);
-        const float f1 = (float)(int8_t)((rbw[2 * j + 1] >> (8 * e)) & 0xff);
-        *reinterpret_cast<unsigned*>(Bt + (4 * (pq + 16 * j) + e) * kLdH + 2 * rp) =
-            pack2(__float_as_uint(f0), __float_as_uint(f1));
+        const float f0 = (float)(int8_t)((rbw[2 * e] >> (8 * c)) & 0xff);
+        const float f1 = (float)(int8_t)((rbw[2 * e + 1] >> (8 * c)) & 0xff);
+        f[e] = pack2(__float_as_uint(f0), __float_as_uint(f1));
       }
+      *reinterpret_cast<v4u*>(at + c * 128) = f;
+    }
   };
 
-  v16f acc[MB][NB];
+  v16f acc[NB];
 #pragma unroll
-  for (int a = 0; a < MB; ++a)
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[b][i] = 0.f;
+  // One step of 16: cuts ra[kk], calls `refill` (whose loads may reuse those registers), multiplies.
+  auto step = [&](int buf, auto kkc, auto&& refill) {
+    constexpr int kk = decltype(kkc)::value;
+    const char* Bs = smem + buf * (kStage * TC * 2) + ((wave % WC) * NB * 64 + lane) * 16;
+    v4u h, m, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      unsigned h0, m0, l0, h1, m1, l1;
+      split3(ra[kk][2 * e], h0, m0, l0);
+      split3(ra[kk][2 * e + 1], h1, m1, l1);
+      h[e] = pack2(h0, h1), m[e] = pack2(m0, m1), l[e] = pack2(l0, l1);
+    }
+    refill(kkc);
+    bf16x8 bfrag[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
+      bfrag[b] = *reinterpret_cast<const bf16x8*>(Bs + (kk * (TC / 32) + b) * 1024);
+    const bf16x8 ah = __builtin_bit_cast(bf16x8, h), am = __builtin_bit_cast(bf16x8, m),
+                 al = __builtin_bit_cast(bf16x8, l);
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
-  const int wr = (wave >> 1) * 32 * MB, wc = (wave & 1) * 32 * NB;
-  const int l32 = lane & 31, lk = lane >> 5;
-  // MFMA operands: lane -> row (A) or column (B) lane % 32, reduction indices 8 * (lane / 32) .. + 7.
-  const int fa = (wr + l32) * kLdH + 8 * lk, fb = (wc + l32) * kLdH + 8 * lk;
+    for (int b = 0; b < NB; ++b)
+      acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bfrag[b], acc[b], 0, 0, 0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bfrag[b], acc[b], 0, 0, 0);
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+      acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bfrag[b], acc[b], 0, 0, 0);
+  };
 
-  fetch(r_begin);
-  for (int r0 = r_begin; r0 < r_end; r0 += kGR) {
-    __syncthreads();                  // the previous chunk's fragment reads are done
-    stage();
-    __syncthreads();
-    if (r0 + kGR < r_end) fetch(r0 + kGR);
-#pragma unroll
-    for (int kk = 0; kk < kGR; kk += 16) {
-      bf16x8 bfrag[NB];
-#pragma unroll
-      for (int b = 0; b < NB; ++b)
-        bfrag[b] = *reinterpret_cast<const bf16x8*>(Bt + fb + b * 32 * kLdH + kk);
-#pragma unroll
-      for (int a = 0; a < MB; ++a) {
-        const int at = fa + a * 32 * kLdH + kk;
-        const bf16x8 al = *reinterpret_cast<const bf16x8*>(Al + at);
-        const bf16x8 am = *reinterpret_cast<const bf16x8*>(Am + at);
-        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(Ah + at);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bfrag[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bfrag[b], acc[a][b], 0, 0, 0);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bfrag[b], acc[a][b], 0, 0, 0);
-      }
+  // Whole stages.  Nothing in this loop is conditional (past the last stage the loads repeat it and
+  // are dropped): a load under a branch would be waited for at the branch's end.
+  const int whole = max(r_end - r_begin, 0) / kStage;
+  if (whole) {
+    rfor<0, kStage / 16>([&](auto kkc) { fetch_a(r_begin, kkc); });
+    fetch_b(r_begin);
+    stage_b(0);
+    fetch_b(r_begin + min(1, whole - 1) * kStage);
+    for (int st = 0; st < whole; ++st) {
+      __syncthreads();                // this stage is written, the previous one has been read
+      const int next = r_begin + min(st + 1, whole - 1) * kStage;
+      rfor<0, kStage / 16>([&](auto kkc) { step(st & 1, kkc, [&](auto q) { fetch_a(next, q); }); });
+      stage_b((st + 1) & 1);
+      fetch_b(r_begin + min(st + 2, whole - 1) * kStage);
     }
   }
-
-  // acc[a][b][i] holds output (row = 32 a + (i / 4) * 8 + (lane / 32) * 4 + i % 4,
-  // col = 32 b + lane % 32) of the wave's block.  32 rows at a time go through the
-  // wave's own part of LDS so that they leave in 16-byte stores, a wave writing
-  // full row segments of 128 NB bytes.
-  constexpr int kLdC = 32 * NB + 4;
-  const float s = scale.v[p];
-  float* Cs = smem + wave * 32 * kLdC;
-  float* Cp = Cout + (long)p * rows * cols;
-#pragma unroll
-  for (int a = 0; a < MB; ++a) {
-    __syncthreads();                  // the fragments (a = 0) resp. the previous rows have been read
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        Cs[((i >> 2) * 8 + lk * 4 + (i & 3)) * kLdC + 32 * b + l32] = acc[a][b][i] * s;
+  const int rt = r_begin + whole * kStage;
+  if (rt < r_end) {                   // the rest, less than a stage
     __syncthreads();
 #pragma unroll
-    for (int it = 0; it < 4 * NB; ++it) {
-      const int idx = lane + it * 64;
-      const int r = idx / (8 * NB), q = idx % (8 * NB);
-      const int row = row0 + wr + 32 * a + r, col = col0 + wc + 4 * q;
-      if (row < rows && col < cols)   // cols is a multiple of 16: a quad is inside or outside
-        *reinterpret_cast<v4f*>(Cp + (long)row * cols + col) =
-            *reinterpret_cast<const v4f*>(Cs + r * kLdC + 4 * q);
-    }
+    for (int e = 0; e < 8; ++e)       // past the end A is zero: any code will do
+      rbw[e] = *reinterpret_cast<const int*>(Bl + (long)min(rt + 8 * bo + e, red - 1) * cols);
+    stage_b(0);
+    __syncthreads();
+    rfor<0, kStage / 16>([&](auto kkc) {
+      constexpr int kk = decltype(kkc)::value;
+      const int r = rt + 16 * kk;
+      if (r < r_end) {                // uniform
+        if constexpr (ARED) {
+          fetch_a(rt, kkc);           // r_end = red is a multiple of 16
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            ra[kk][e] = r + 8 * lk + e < r_end ? Al[(long)(r + e) * rows] : 0.f;
+        }
+        step(0, kkc, [](auto) {});
+      }
+    });
+  }
+
+  // acc[b][i] holds output (row = (i / 4) * 8 + (lane / 32) * 4 + i % 4, MFMA column lane % 32 of
+  // block b): 32 lanes store the 128 bytes of a row segment.
+  const float s = scale.v[p];
+  const int ocol = col0 + wc + 4 * (l32 & 7) + (l32 >> 3);
+  float* Cp = Cout + (long)p * rows * cols;
+  float* out = Cp + (long)(row0 + wr + lk * 4) * cols + ocol;
+  if (row0 + TR <= rows && col0 + TC <= cols) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) out[(long)((i >> 2) * 8 + (i & 3)) * cols + 32 * b] = acc[b][i] * s;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (row0 + wr + lk * 4 + (i >> 2) * 8 + (i & 3) < rows && ocol + 32 * b < cols)
+          out[(long)((i >> 2) * 8 + (i & 3)) * cols + 32 * b] = acc[b][i] * s;
   }
 }
 
 // Both contractions in one launch (they only share their input dM): the blocks of
 // the dV contraction, whose reduction over the tiles is the longer one, come first,
 // the blocks of dU fill the compute units as those drain.  Either may have no
-// blocks.  MBV: row blocks per wave of dV's tiles (rows = K); dU's tiles are
-// always 128 rows (of tiles) high; NB: column blocks per wave of both (cols = C).
-template <int MBV, int NB>
-__global__ __launch_bounds__(256) void k_bwd_gemm_both(GemmArgs for_dv, MultTable s_u,
-                                                        GemmArgs for_du, MultTable s_v) {
-  __shared__ __attribute__((aligned(16))) float smem[gemm_lds(2, NB)];
+// blocks.  WRV, NBV: waves along the rows and column blocks per wave of dV's tiles (rows = K);
+// dU's tiles are always 128 rows (of tiles) high, NBU column blocks (cols = C) wide.
+template <int WRV, int NBV, int NBU>
+__global__ __launch_bounds__(256, 3) void k_bwd_gemm_both(GemmArgs for_dv, MultTable s_u,
+                                                           GemmArgs for_du, MultTable s_v) {
+  constexpr int tcv = 128 / WRV * NBV, tcu = 32 * NBU;
+  __shared__ __attribute__((aligned(16))) char smem[gemm_lds(tcv > tcu ? tcv : tcu)];
   if (blockIdx.x < (unsigned)for_dv.blocks)
-    gemm_body<false, MBV, NB>(for_dv, s_u, blockIdx.x, smem);
+    gemm_body<false, WRV, NBV>(for_dv, s_u, blockIdx.x, smem);
   else
-    gemm_body<true, 2, NB>(for_du, s_v, blockIdx.x - (unsigned)for_dv.blocks, smem);
+    gemm_body<true, 4, NBU>(for_du, s_v, blockIdx.x - (unsigned)for_dv.blocks, smem);
 }
 
 inline unsigned blocks256(long items) { return (unsigned)((items + 255) / 256); }
@@ -667,14 +669,14 @@ static hipError_t launch_gemm_pair(const Geometry& g, const GemmArgs& for_dv, co
   const dim3 grid(blocks), wg(256);
   if (col_blocks_per_wave(g) == 2) {
     if (dv_row_blocks(g) == 2)
-      wino_launch((k_bwd_gemm_both<2, 2>), grid, wg, st, for_dv, s_u, for_du, s_v);
+      wino_launch((k_bwd_gemm_both<4, 4, 4>), grid, wg, st, for_dv, s_u, for_du, s_v);
     else
-      wino_launch((k_bwd_gemm_both<1, 2>), grid, wg, st, for_dv, s_u, for_du, s_v);
+      wino_launch((k_bwd_gemm_both<2, 2, 4>), grid, wg, st, for_dv, s_u, for_du, s_v);
   } else {
     if (dv_row_blocks(g) == 2)
-      wino_launch((k_bwd_gemm_both<2, 1>), grid, wg, st, for_dv, s_u, for_du, s_v);
+      wino_launch((k_bwd_gemm_both<4, 2, 2>), grid, wg, st, for_dv, s_u, for_du, s_v);
     else
-      wino_launch((k_bwd_gemm_both<1, 1>), grid, wg, st, for_dv, s_u, for_du, s_v);
+      wino_launch((k_bwd_gemm_both<2, 1, 2>), grid, wg, st, for_dv, s_u, for_du, s_v);
   }
   return hipGetLastError();
 }
