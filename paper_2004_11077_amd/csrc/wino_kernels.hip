@@ -37,8 +37,11 @@ ProfileEvents take_profile_events() {
 // the MFMAs.  Each wave owns 64 x 64 outputs as 2 x 2 blocks of the 32x32x32
 // int8 MFMA.  The A operand is V (rows k), the B operand U (rows t), so a lane
 // ends up with four consecutive k of one tile per accumulator quad.
-// int8 results are transposed through LDS so that global stores are full
-// 128-byte rows; the wider int16 / int32 results are stored from registers.
+// int8 and int16 results are transposed through LDS so that global stores are full 128- and
+// 256-byte rows, 16 bytes per lane; int32 results are stored from registers.  With int8 rows leaving
+// 4 bytes per lane (sixteen LDS reads, each waited for) and the columns past C zeroed while they are
+// fetched (each load waited for): F(6,3), 792 tiles, C = 80, K = 144: whole layer 34.7 us, now 32.5;
+// F(4,3), 1024 tiles, C = K = 256 with run-time matrices: 32.5, now 30.5; 65536 tiles: 890, now 875.
 //
 // Blocks are numbered so that all blocks of a (point, group of t blocks) run
 // on the same XCD (consecutive work group ids go round-robin over the 8 XCDs,
@@ -113,29 +116,25 @@ __device__ __forceinline__ void contract_body(const int8_t* __restrict__ U,
   // one register set: the next chunk is in flight while this one feeds the MFMAs
   // (a second set costs a third of the occupancy and measured slower)
   v4i ra[NPA], rb[NPB];
+  // Last chunk when C is not a multiple of the chunk: columns past C are read from an in-bounds
+  // column.  V's are zeroed before they are staged, not here, where that would wait for the loads.
   auto fetch = [&](int c0) {
-    if (c0 + kCK <= C) {               // uniform: the whole chunk lies inside C
+    const int cc = min(c0, C - 16 - sseg);
 #pragma unroll
-      for (int i = 0; i < NPA; ++i) ra[i] = *reinterpret_cast<const v4i*>(Vp + c0 + oa[i]);
+    for (int i = 0; i < NPA; ++i) ra[i] = *reinterpret_cast<const v4i*>(Vp + cc + oa[i]);
 #pragma unroll
-      for (int i = 0; i < NPB; ++i) rb[i] = *reinterpret_cast<const v4i*>(Up + c0 + ob[i]);
-    } else {
-      // last chunk when C is not a multiple of the chunk: columns past C are
-      // read from a clamped in-bounds column and zeroed, without branching
-      const bool ok = c0 + sseg < C;
-      const int cc = ok ? c0 : C - 16 - sseg;
-      const int keep = ok ? -1 : 0;
-#pragma unroll
-      for (int i = 0; i < NPA; ++i) ra[i] = *reinterpret_cast<const v4i*>(Vp + cc + oa[i]) & keep;
-#pragma unroll
-      for (int i = 0; i < NPB; ++i) rb[i] = *reinterpret_cast<const v4i*>(Up + cc + ob[i]) & keep;
-    }
+    for (int i = 0; i < NPB; ++i) rb[i] = *reinterpret_cast<const v4i*>(Up + cc + ob[i]);
   };
 
   v16i acc[2][JT];
   // FIRST: the accumulators start from the constant zero operand of the first
   // MFMA instead of being cleared beforehand.
   auto chunk = [&]<bool FIRST>(int c0) {
+    if (c0 + kCK > C) {                      // uniform
+      const int keep = c0 + sseg < C ? -1 : 0;
+#pragma unroll
+      for (int i = 0; i < NPA; ++i) ra[i] &= keep;
+    }
     if constexpr (!FIRST) __syncthreads();   // previous chunk fully consumed
 #pragma unroll
     for (int i = 0; i < NPA; ++i) *reinterpret_cast<v4i*>(sA + (srow + i * RPP) * kRow + sseg) = ra[i];
@@ -171,8 +170,9 @@ __device__ __forceinline__ void contract_body(const int8_t* __restrict__ U,
   // acc[i][j][4*g+v] = D[k = 32 i + 8 g + 4 h + v][t = 32 j + r] within the wave's 64 (k) x kTT/2 (t)
   if constexpr (sizeof(MT) == 1) {
     __syncthreads();                     // LDS is reused as the [t][k] output block
+    // rows of 128 bytes whose 16-byte segment q sits at q ^ (row % 8): they leave 16 bytes per lane
     uint32_t* so = reinterpret_cast<uint32_t*>(smem);
-    constexpr int kORow = kKT / 4 + 1;   // dwords per row, +1 against bank conflicts
+    static_assert(kTT * kKT <= kSm);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -188,20 +188,24 @@ __device__ __forceinline__ void contract_body(const int8_t* __restrict__ U,
           const uint32_t hi = __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu);
           const int tl = wt * (kTT / 2) + j * 32 + r;
           const int kl = wk * 64 + i * 32 + 8 * gq + 4 * h;
-          so[tl * kORow + (kl >> 2)] = lo | hi;
+          so[tl * (kKT / 4) + (((kl >> 4) ^ (tl & 7)) << 2) + ((kl >> 2) & 3)] = lo | hi;
         }
     __syncthreads();
     // M is written once and read by the next kernel from other compute units: streaming
     // (nontemporal) stores leave no dirty lines for the end-of-kernel write-back (measured:
     // 1 us per kernel at N = 256, and faster at large batch as well)
-    const int kq = tid & 31;             // dword within the 128-byte row
-    if (kq * 4 < krows) {
+    const int kseg = tid & 7, trow = tid >> 3;
+    v4i out[kTT / 32];
 #pragma unroll
-      for (int it = 0; it < kTT / 8; ++it) {
-        const int tl = it * 8 + (tid >> 5);
+    for (int it = 0; it < kTT / 32; ++it)
+      out[it] = *reinterpret_cast<const v4i*>(smem + (it * 32 + trow) * kKT + ((kseg ^ (trow & 7)) << 4));
+    if (kseg * 16 < krows) {             // K is a multiple of 16: a segment is inside or outside
+#pragma unroll
+      for (int it = 0; it < kTT / 32; ++it) {
+        const int tl = it * 32 + trow;
         if (tl < trows)
-          __builtin_nontemporal_store(so[tl * kORow + kq],
-                                      reinterpret_cast<uint32_t*>(Mp + ((uint32_t)tl * (uint32_t)K + kq * 4)));
+          __builtin_nontemporal_store(out[it],
+                                      reinterpret_cast<v4i*>(Mp + ((uint32_t)tl * (uint32_t)K + kseg * 16)));
       }
     }
   } else if constexpr (sizeof(MT) == 2) {
