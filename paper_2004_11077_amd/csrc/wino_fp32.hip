@@ -3,6 +3,8 @@
 // U [n*n][T][C], V [n*n][K][C], M [n*n][T][K], y NHWC), checked against fp64.
 // One lane per item in the transforms, which are bound by the bytes of U, M and
 // y; the contraction runs on the matrix cores.
+#include <cfloat>
+
 #include "wino_kernels.hpp"
 #include "wino_real_brackets.hpp"
 
@@ -96,7 +98,8 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 // bf16 pieces, each rounded to nearest: x = h + m + l exactly, |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.
 // Six of the nine piece products are accumulated in fp32 (exact products, smallest first); the
 // three that are left out (ml, lm, ll) are below 2^-26 of |x y|, a quarter of what rounding one
-// fp32 product loses.  A non-finite element gives NaN in the results it enters.
+// fp32 product loses.  Infinities, NaNs and values that round past the largest bf16 have no such
+// pieces: a result that is not finite is summed again in plain fp32, channel by channel.
 //
 // Work group = 4 waves (2 x 2) = (64 MB) tiles x (64 NB) output channels, a wave MB x NB blocks of
 // 32 x 32.  The channels run in chunks of 32 staged through LDS ([row][channel] per piece), the next chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
@@ -248,9 +251,22 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
       const int idx = lane + it * 64;
       const int r = idx / (8 * NB), q = 4 * (idx % (8 * NB));
       const int row = wr + 32 * a + r, col = wc + q;
-      if (row < trows && col < krows)   // K is a multiple of 16: a quad is inside or outside
-        __builtin_nontemporal_store(*reinterpret_cast<const v4f*>(Cs + r * kLdC + q),
-                                    reinterpret_cast<v4f*>(Mp + (long)row * K + col));
+      if (row < trows && col < krows) { // K is a multiple of 16: a quad is inside or outside
+        v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q);
+        const float top = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+        const float sum = (v[0] + v[1]) + (v[2] + v[3]);             // NaN if one of them is
+        if (__builtin_expect(!(top <= FLT_MAX && sum == sum), 0)) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            if (fabsf(v[e]) <= FLT_MAX) continue;
+            float acc1 = 0.f;
+            for (int c = 0; c < C; ++c)
+              acc1 = __builtin_fmaf(Up[(long)row * C + c], Vp[(long)(col + e) * C + c], acc1);
+            v[e] = acc1;
+          }
+        }
+        __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(Mp + (long)row * K + col));
+      }
     }
   }
 }

@@ -35,3 +35,33 @@ def test_contract_f32_against_fp64(m, N, H, W, C, K):
     bound = (6 * C * 2.0 ** -24 + 2.0 ** -26) * np.matmul(np.abs(u64), np.abs(v64))
     err = np.abs(M.cpu().numpy().astype(np.float64) - np.matmul(u64, v64))
     assert (err <= bound).all(), float((err / bound).max())
+
+
+def test_contract_f32_beyond_the_range_of_its_pieces():
+    """Infinities, NaNs and values past the largest bf16 give what plain fp32 sums give."""
+    import torch
+    import paper_2004_11077_amd as wn
+    d = wn.ConvDesc(1, 4, 20, 48, 80, m=4, bits_in=32)
+    n2, T, C, K = d.n ** 2, d.tiles, 48, 80
+    rng = np.random.default_rng(11)
+    u = rng.standard_normal((n2, T, C)).astype(np.float32)
+    v = rng.uniform(0.5, 1.0, (n2, K, C)).astype(np.float32)
+    u[0, 0, 3], u[1, 1, 40], u[2, 2, 7] = np.inf, -np.inf, np.nan
+    u[3, 3, 0], u[3, 3, 1] = np.inf, -np.inf
+    u[4, 4, 5] = 3.4e38                       # finite, rounds to an infinite bf16
+    v[5, 6, 7] = np.inf
+    M = torch.full((n2, T, K), 7.0, dtype=torch.float32, device="cuda")
+    wn.wino_contract(d, torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda(), M,
+                     wn.Scales.from_dict({}))
+    torch.cuda.synchronize()
+    got = M.cpu().numpy()
+    with np.errstate(all="ignore"):
+        # channel by channel: a library product of non-finite matrices may take any order
+        want = sum(u[..., None, c].astype(np.float64) * v[:, None, :, c] for c in range(C))
+    assert np.isinf(want[0, 0]).all() and np.isnan(want[2, 2]).all() and np.isnan(want[3, 3]).all()
+    for cls in (np.isnan, np.isposinf, np.isneginf):
+        assert np.array_equal(cls(got), cls(want)), cls
+    ok = np.isfinite(want)
+    size = sum(np.abs(u[..., None, c].astype(np.float64) * v[:, None, :, c]) for c in range(C))
+    bound = (6 * C * 2.0 ** -24 + 2.0 ** -26) * size
+    assert (np.abs(got[ok] - want[ok]) <= bound[ok]).all()
