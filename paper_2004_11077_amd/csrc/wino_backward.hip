@@ -29,16 +29,15 @@ using ICb = std::integral_constant<int, I>;
 // carry no gradient.
 template <int M>
 __global__ __launch_bounds__(256) void k_bwd_dm(const float* __restrict__ dy,
-                                                float* __restrict__ dM, Geometry g) {
+                                                float* __restrict__ dM, Geometry g,
+                                                Divider by_k) {
   constexpr int n = M + 2;
   const long total = (long)g.T * g.K;
   const long gid = (long)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= total) return;
-  const int t = (int)(gid / g.K);
-  const int k = (int)(gid - (long)t * g.K);
-  const int tx = t % g.TW;
-  const int ty = (t / g.TW) % g.TH;
-  const int b = t / (g.TW * g.TH);
+  int t, k, b, ty, tx;
+  item_of_lane(blockIdx.x, g.K, by_k, t, k);
+  if (t >= g.T) return;
+  tile_coords(g, t, b, ty, tx);
   float v[M][M];
   rfor<0, M>([&](auto i) {
     rfor<0, M>([&](auto j) {
@@ -112,17 +111,14 @@ __device__ __forceinline__ void dx_entries(Load&& load, float (&acc)[ACC][ACC]) 
 // in a fixed order; no tile ever writes a pixel of another.
 template <int M>
 __device__ __forceinline__ void bwd_dx_body(const float* __restrict__ dU, float* __restrict__ dx,
-                                            const Geometry& g, unsigned block) {
+                                            const Geometry& g, Divider by_c, unsigned block) {
   constexpr int n = M + 2;
   static constexpr RMat BT = TabF<M>::BT;
   const long total = (long)g.T * g.C;
-  const long gid = (long)block * 256 + threadIdx.x;
-  if (gid >= total) return;
-  const int t = (int)(gid / g.C);
-  const int c = (int)(gid - (long)t * g.C);
-  const int tx = t % g.TW;
-  const int ty = (t / g.TW) % g.TH;
-  const int b = t / (g.TW * g.TH);
+  int t, c, b, ty, tx;
+  item_of_lane(block, g.C, by_c, t, c);
+  if (t >= g.T) return;
+  tile_coords(g, t, b, ty, tx);
   float acc[M][M];
   rfor<0, M>([&](auto i) { rfor<0, M>([&](auto j) { acc[i][j] = 0.f; }); });
   // neighbour (DY, DX): its local rows [A0, A1] land on my pixel rows AO ...
@@ -153,8 +149,9 @@ __device__ __forceinline__ void bwd_dx_body(const float* __restrict__ dU, float*
 
 template <int M>
 __global__ __launch_bounds__(256) void k_bwd_dx(const float* __restrict__ dU,
-                                                float* __restrict__ dx, Geometry g) {
-  bwd_dx_body<M>(dU, dx, g, blockIdx.x);
+                                                float* __restrict__ dx, Geometry g,
+                                                Divider by_c) {
+  bwd_dx_body<M>(dU, dx, g, by_c, blockIdx.x);
 }
 
 // dV -> dw[k][c][3][3].
@@ -190,11 +187,11 @@ __global__ __launch_bounds__(256, (M <= 4 ? 4 : 2)) void k_bwd_dx_dw(const float
                                                    float* __restrict__ dx,
                                                    float* __restrict__ dV,
                                                    float* __restrict__ dw, Geometry g,
-                                                   unsigned nb_dw, int parts) {
+                                                   Divider by_c, unsigned nb_dw, int parts) {
   if (blockIdx.x < nb_dw)
     bwd_dw_body<M>(dV, dw, g, blockIdx.x, parts);
   else
-    bwd_dx_body<M>(dU, dx, g, blockIdx.x - nb_dw);
+    bwd_dx_body<M>(dU, dx, g, by_c, blockIdx.x - nb_dw);
 }
 
 // ---------------------------------------------------------------------------
@@ -459,9 +456,11 @@ inline unsigned blocks256(long items) { return (unsigned)((items + 255) / 256); 
 template <int M>
 hipError_t bwd_transform(int which, const Geometry& g, const float* in, float* out, hipStream_t st) {
   if (which == 0)
-    wino_launch((k_bwd_dm<M>), dim3(blocks256((long)g.T * g.K)), dim3(256), st, in, out, g);
+    wino_launch((k_bwd_dm<M>), dim3(blocks256((long)g.T * g.K)), dim3(256), st, in, out, g,
+                divider_of(g.K));
   else
-    wino_launch((k_bwd_dx<M>), dim3(blocks256((long)g.T * g.C)), dim3(256), st, in, out, g);
+    wino_launch((k_bwd_dx<M>), dim3(blocks256((long)g.T * g.C)), dim3(256), st, in, out, g,
+                divider_of(g.C));
   return hipGetLastError();
 }
 
@@ -476,8 +475,8 @@ template <int M>
 hipError_t bwd_dx_dw(const Geometry& g, const float* dU, float* dx, float* dV, float* dw,
                      hipStream_t st) {
   const unsigned nb_dx = blocks256((long)g.T * g.C), nb_dw = blocks256((long)g.K * g.C);
-  wino_launch((k_bwd_dx_dw<M>), dim3(nb_dx + nb_dw), dim3(256), st, dU, dx, dV, dw, g, nb_dw,
-              backward_dv_reader_parts(g));
+  wino_launch((k_bwd_dx_dw<M>), dim3(nb_dx + nb_dw), dim3(256), st, dU, dx, dV, dw, g,
+              divider_of(g.C), nb_dw, backward_dv_reader_parts(g));
   return hipGetLastError();
 }
 
