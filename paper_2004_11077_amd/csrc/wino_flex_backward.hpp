@@ -1,7 +1,7 @@
 // Backward pass of the flex layer (Section 4.2: G_P, B_P, A_P are trained, P and
 // P^{-1} stay fixed), fp32, casts passing their gradient on unchanged.
 // For a bracket R = T S T^T with a trained matrix T:
-//     dT = sum over items of  dR (T S^T) + dR^T (T S),      dS = T^T dR T,
+//     dT = sum over items of  A S^T + B S  with  A = dR T, B = dR^T T,      dS = T^T A,
 // and through a fixed bracket S1 = L S L^T:  dS = L^T dS1 L.  The inputs S of the
 // trained brackets are recomputed from the forward pass's integer tensors with the
 // forward pass's exact arithmetic (X1 from x, M1 from M) and dequantised.
@@ -12,90 +12,117 @@
 //   k_bwd_tile_sum  per-tile dX -> dx (fixed order over the <= 4 covering tiles)
 //   k_sum_partials  partial sums -> the three matrix gradients (fixed order)
 // The two contraction gradients between them are those of the static layer.
+// Bound by vector arithmetic (about 2400 instructions per (tile, channel) item of the input bracket) and
+// by the bytes of dM, dU and dX.  2048 tiles, C = K = 128, F(4,3): input and filter brackets 38.1 us with
+// sums over lanes by LDS permutes, 64-bit divisions and T S, T S^T formed per item, now 31.6; output
+// bracket 23.7, now 18.5; training step 278, now 267.
 #pragma once
 #include "wino_flex.hpp"
 #include "wino_real_brackets.hpp"
 
 namespace wino {
 
-// T (ROWS x COLS, run-time, row-major) applied to a square S: ts = T S, tst = T S^T.
+// With a run-time T (ROWS x COLS, row-major): A = dR T and this lane's share of dT = A S^T + B S.  dS
+// = T^T A follows from A (flex_input_grad): a sixth fewer multiply-adds than T S, T S^T and T^T dR T
+// take.  In this order no more than S, one of dR and A, and dT live at a time.
 template <int ROWS, int COLS>
-__device__ __forceinline__ void flex_left(const float* __restrict__ Tm, const float (&S)[COLS][COLS],
-                                          float (&ts)[ROWS][COLS], float (&tst)[ROWS][COLS]) {
+__device__ __forceinline__ void flex_matrix_grad(const float* __restrict__ Tm,
+                                                 const float (&S)[COLS][COLS],
+                                                 const float (&dR)[ROWS][ROWS],
+                                                 float (&dT)[ROWS * COLS], float (&A)[ROWS][COLS]) {
   static_for<0, ROWS>([&](auto i) {
-    static_for<0, COLS>([&](auto b) {
-      float a0 = 0.f, a1 = 0.f;
-      static_for<0, COLS>([&](auto a) {
-        const float c = Tm[decltype(i)::value * COLS + decltype(a)::value];
-        a0 = __builtin_fmaf(c, S[a][b], a0);
-        a1 = __builtin_fmaf(c, S[b][a], a1);
-      });
-      ts[i][b] = a0;
-      tst[i][b] = a1;
-    });
-  });
-}
-
-// dT[i][b] = sum_j dR[i][j] tst[j][b] + dR[j][i] ts[j][b]   (this lane's share).
-template <int ROWS, int COLS>
-__device__ __forceinline__ void flex_matrix_grad(const float (&dR)[ROWS][ROWS],
-                                                 const float (&ts)[ROWS][COLS],
-                                                 const float (&tst)[ROWS][COLS],
-                                                 float (&dT)[ROWS * COLS]) {
-  static_for<0, ROWS>([&](auto i) {
-    static_for<0, COLS>([&](auto b) {
+    float B[COLS];                               // row i of B
+    static_for<0, COLS>([&](auto k) {
       float acc = 0.f;
       static_for<0, ROWS>([&](auto j) {
-        acc = __builtin_fmaf(dR[i][j], tst[j][b], acc);
-        acc = __builtin_fmaf(dR[j][i], ts[j][b], acc);
+        acc = __builtin_fmaf(dR[j][i], Tm[decltype(j)::value * COLS + decltype(k)::value], acc);
       });
+      B[k] = acc;
+    });
+    static_for<0, COLS>([&](auto b) {
+      float acc = 0.f;
+      static_for<0, COLS>([&](auto k) { acc = __builtin_fmaf(B[k], S[k][b], acc); });
+      dT[decltype(i)::value * COLS + decltype(b)::value] = acc;
+    });
+  });
+  static_for<0, ROWS>([&](auto i) {
+    static_for<0, COLS>([&](auto k) {
+      float acc = 0.f;
+      static_for<0, ROWS>([&](auto j) {
+        acc = __builtin_fmaf(dR[i][j], Tm[decltype(j)::value * COLS + decltype(k)::value], acc);
+      });
+      A[i][k] = acc;
+    });
+    static_for<0, COLS>([&](auto b) {
+      float acc = dT[decltype(i)::value * COLS + decltype(b)::value];
+      static_for<0, COLS>([&](auto k) { acc = __builtin_fmaf(A[i][k], S[b][k], acc); });
       dT[decltype(i)::value * COLS + decltype(b)::value] = acc;
     });
   });
 }
 
-// dS = T^T dR T.
+// dS = T^T A.
 template <int ROWS, int COLS>
 __device__ __forceinline__ void flex_input_grad(const float* __restrict__ Tm,
-                                                const float (&dR)[ROWS][ROWS],
-                                                float (&dS)[COLS][COLS]) {
-  float tmp[COLS][ROWS];
-  static_for<0, COLS>([&](auto a) {
-    static_for<0, ROWS>([&](auto j) {
+                                                const float (&A)[ROWS][COLS], float (&dS)[COLS][COLS]) {
+  static_for<0, COLS>([&](auto b) {
+    static_for<0, COLS>([&](auto a) {
       float acc = 0.f;
       static_for<0, ROWS>([&](auto i) {
-        acc = __builtin_fmaf(Tm[decltype(i)::value * COLS + decltype(a)::value], dR[i][j], acc);
-      });
-      tmp[a][j] = acc;
-    });
-  });
-  static_for<0, COLS>([&](auto a) {
-    static_for<0, COLS>([&](auto b) {
-      float acc = 0.f;
-      static_for<0, ROWS>([&](auto j) {
-        acc = __builtin_fmaf(tmp[a][j], Tm[decltype(j)::value * COLS + decltype(b)::value], acc);
+        acc = __builtin_fmaf(Tm[decltype(i)::value * COLS + decltype(a)::value], A[i][b], acc);
       });
       dS[a][b] = acc;
     });
   });
 }
 
-// Sum of v[i] over the 256 lanes of the work group, in a fixed order (xor tree
-// inside a wave, then wave 0 + 1 + 2 + 3), written to row[i] by lane i.
+// a's two halves added in lanes 0 .. 31, b's in lanes 32 .. 63.
+__device__ __forceinline__ float add_halves(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Rows 0 + 1 and 2 + 3 (of 16 lanes) of a in rows 0 and 2, those of b in rows 1 and 3.
+__device__ __forceinline__ float add_rows(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Sums of v[i] over the 256 lanes of the work group, in a fixed order: a tree inside a wave
+// (wave_sums), then wave 0 + 1 + 2 + 3, written to row[i] by lane i (store_sums).  Four values share a
+// register from the second step on, a row of 16 lanes each: 7 adds for four values instead of
+// 24, and no LDS before the last step.
 template <int CNT>
-__device__ __forceinline__ void block_sum_to_row(const float (&v)[CNT], float* __restrict__ row) {
-  __shared__ float s_red[4][CNT];
+struct WaveSums {
+  static constexpr int regs = (CNT + 3) / 4;
+  float of[4][4 * regs];
+};
+template <int CNT>
+__device__ __forceinline__ void wave_sums(const float (&v)[CNT], WaveSums<CNT>& sums) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  static_for<0, CNT>([&](auto i) {
-    float x = v[decltype(i)::value];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    if (lane == 0) s_red[wave][decltype(i)::value] = x;
+  // register q: value 4 q in row 0, 4 q + 2 in row 1, 4 q + 1 in row 2, 4 q + 3 in row 3
+  const int mine = ((lane >> 4) & 1) * 2 + (lane >> 5);
+  static_for<0, WaveSums<CNT>::regs>([&](auto q) {
+    constexpr int Q = 4 * decltype(q)::value;
+    const float z = 0.f;
+    float x = add_rows(add_halves(v[Q], Q + 1 < CNT ? v[Q + 1 < CNT ? Q + 1 : Q] : z),
+                       add_halves(Q + 2 < CNT ? v[Q + 2 < CNT ? Q + 2 : Q] : z,
+                                  Q + 3 < CNT ? v[Q + 3 < CNT ? Q + 3 : Q] : z));
+#define WINO_DPP_ADD(CTRL) \
+  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false))
+    WINO_DPP_ADD(0x128);   // row_ror:8, 4, 2, 1: every lane of a row has the row's sum
+    WINO_DPP_ADD(0x124);
+    WINO_DPP_ADD(0x122);
+    WINO_DPP_ADD(0x121);
+#undef WINO_DPP_ADD
+    if ((lane & 15) == 0) sums.of[wave][Q + mine] = x;
   });
+}
+template <int CNT>
+__device__ __forceinline__ void store_sums(const WaveSums<CNT>& sums, float* __restrict__ row) {
   __syncthreads();
   if (threadIdx.x < CNT) {
     const int i = threadIdx.x;
-    row[i] = ((s_red[0][i] + s_red[1][i]) + s_red[2][i]) + s_red[3][i];
+    row[i] = ((sums.of[0][i] + sums.of[1][i]) + sums.of[2][i]) + sums.of[3][i];
   }
 }
 
@@ -108,18 +135,18 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
                                                      const float* __restrict__ dy,
                                                      float* __restrict__ dM,
                                                      float* __restrict__ part, Geometry g,
-                                                     FlexMats fm, StageMults mu, float s_in) {
+                                                     FlexMats fm, StageMults mu, float s_in,
+                                                     Divider by_k) {
   constexpr int n = M + 2;
   constexpr int64_t IN_MAX = MTraits<MT>::in_max;
   using TB = Tab<M>;
   const long total = (long)g.T * g.K;
   const long gid = (long)blockIdx.x * 256 + threadIdx.x;
   const bool active = gid < total;
-  const int t = active ? (int)(gid / g.K) : 0;
-  const int k = active ? (int)(gid - (long)t * g.K) : 0;
-  const int tx = t % g.TW;
-  const int ty = (t / g.TW) % g.TH;
-  const int b = t / (g.TW * g.TH);
+  int t, k, b, ty, tx;
+  item_of_lane(blockIdx.x, g.K, by_k, t, k);
+  if (!active) t = 0, k = 0;
+  tile_coords(g, t, b, ty, tx);
   int xi[n][n];
   static_for<0, n>([&](auto i) {
     static_for<0, n>([&](auto j) {
@@ -140,11 +167,15 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
       dR[i][j] = (active && h < g.H && w < g.W) ? dy[(((long)b * g.H + h) * g.W + w) * g.K + k] : 0.f;
     });
   });
-  float ts[M][n], tst[M][n], dT[M * n];
-  flex_left<M, n>(fm.APT, S, ts, tst);
-  flex_matrix_grad<M, n>(dR, ts, tst, dT);
+  __shared__ WaveSums<M * n> s_sums;
+  float A[M][n];
+  {
+    float dT[M * n];
+    flex_matrix_grad<M, n>(fm.APT, S, dR, dT, A);
+    wave_sums(dT, s_sums);
+  }
   float dS[n][n];
-  flex_input_grad<M, n>(fm.APT, dR, dS);
+  flex_input_grad<M, n>(fm.APT, A, dS);
   if (active) {
     if constexpr (LEG) {
       float out[n][n];
@@ -162,7 +193,7 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
       });
     }
   }
-  block_sum_to_row<M * n>(dT, part + (long)blockIdx.x * kPartialStride);
+  store_sums(s_sums, part + (long)blockIdx.x * kPartialStride);
 }
 
 // dU, x -> per-tile dX [a*n+b][t][c] and the partial sums of dBPT (n x n).
@@ -172,17 +203,17 @@ __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
                                                 const float* __restrict__ dU,
                                                 float* __restrict__ dXt, float* __restrict__ part,
                                                 const Geometry& g, const FlexMats& fm,
-                                                const StageMults& mu, float s_in, unsigned block) {
+                                                const StageMults& mu, float s_in, Divider by_c,
+                                                unsigned block) {
   constexpr int n = M + 2;
   using TB = Tab<M>;
   const long total = (long)g.T * g.C;
   const long gid = (long)block * 256 + threadIdx.x;
   const bool active = gid < total;
-  const int t = active ? (int)(gid / g.C) : 0;
-  const int c = active ? (int)(gid - (long)t * g.C) : 0;
-  const int tx = t % g.TW;
-  const int ty = (t / g.TW) % g.TH;
-  const int b = t / (g.TW * g.TH);
+  int t, c, b, ty, tx;
+  item_of_lane(block, g.C, by_c, t, c);
+  if (!active) t = 0, c = 0;
+  tile_coords(g, t, b, ty, tx);
   int xi[n][n];
   static_for<0, n>([&](auto a) {
     static_for<0, n>([&](auto bb) {
@@ -206,14 +237,15 @@ __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
       dR[i][j] = active ? dU[(long)(decltype(i)::value * n + decltype(j)::value) * total + gid] : 0.f;
     });
   });
-  float dT[n * n];
+  __shared__ WaveSums<n * n> s_sums;
+  float A[n][n];
   {
-    float ts[n][n], tst[n][n];
-    flex_left<n, n>(fm.BPT, S, ts, tst);
-    flex_matrix_grad<n, n>(dR, ts, tst, dT);
+    float dT[n * n];
+    flex_matrix_grad<n, n>(fm.BPT, S, dR, dT, A);
+    wave_sums(dT, s_sums);
   }
   float dS[n][n];
-  flex_input_grad<n, n>(fm.BPT, dR, dS);
+  flex_input_grad<n, n>(fm.BPT, A, dS);
   if (active) {
     if constexpr (LEG) {
       float out[n][n];
@@ -231,7 +263,7 @@ __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
       });
     }
   }
-  block_sum_to_row<n * n>(dT, part + (long)block * kPartialStride);
+  store_sums(s_sums, part + (long)block * kPartialStride);
 }
 
 // dV, w -> dw [k][c][3][3] and the partial sums of dGP (n x 3).
@@ -261,11 +293,15 @@ __device__ __forceinline__ void fbwd_weight_body(const int8_t* __restrict__ w,
       static_for<0, n>([&](auto i) { static_for<0, n>([&](auto j) { dR[i][j] = v[i][j]; }); });
     }
   }
-  float ts[n][3], tst[n][3], dT[n * 3];
-  flex_left<n, 3>(fm.GP, S, ts, tst);
-  flex_matrix_grad<n, 3>(dR, ts, tst, dT);
+  __shared__ WaveSums<n * 3> s_sums;
+  float A[n][3];
+  {
+    float dT[n * 3];
+    flex_matrix_grad<n, 3>(fm.GP, S, dR, dT, A);
+    wave_sums(dT, s_sums);
+  }
   float dS[3][3];
-  flex_input_grad<n, 3>(fm.GP, dR, dS);
+  flex_input_grad<n, 3>(fm.GP, A, dS);
   if (active) {
     static_for<0, 3>([&](auto a) {
       static_for<0, 3>([&](auto bb) {
@@ -273,7 +309,7 @@ __device__ __forceinline__ void fbwd_weight_body(const int8_t* __restrict__ w,
       });
     });
   }
-  block_sum_to_row<n * 3>(dT, part + (long)block * kPartialStride);
+  store_sums(s_sums, part + (long)block * kPartialStride);
 }
 
 // The input and the filter bracket are independent of each other: one launch, the first
@@ -284,11 +320,11 @@ __global__ __launch_bounds__(256, (M <= 4 ? 4 : 1)) void k_fbwd_input_weight(
     const int8_t* __restrict__ x, const float* __restrict__ dU, float* __restrict__ dXt,
     float* __restrict__ part_in, const int8_t* __restrict__ w, float* __restrict__ dV,
     float* __restrict__ dw, float* __restrict__ part_w, Geometry g, FlexMats fm, StageMults mu,
-    float s_in, float s_w, unsigned nb_w, int parts) {
+    float s_in, float s_w, Divider by_c, unsigned nb_w, int parts) {
   if (blockIdx.x < nb_w)
     fbwd_weight_body<M, LEG>(w, dV, dw, part_w, g, fm, s_w, blockIdx.x, parts);
   else
-    fbwd_input_body<M, LEG>(x, dU, dXt, part_in, g, fm, mu, s_in, blockIdx.x - nb_w);
+    fbwd_input_body<M, LEG>(x, dU, dXt, part_in, g, fm, mu, s_in, by_c, blockIdx.x - nb_w);
 }
 
 // dx[b][h][w][c] from per-tile gradients: tile ty reads input rows ty*M - 1 ... ty*M + M,
@@ -334,7 +370,7 @@ hipError_t PerMFlexBwd<M>::output(const Geometry& g, bool leg, const void* Mq, i
   const dim3 grid((unsigned)(((long)g.T * g.K + 255) / 256)), bs(256);
 #define WINO_FBWD_OUT(LEGV, MTV)                                                                 \
   wino_launch((k_fbwd_output<M, LEGV, MTV>), grid, bs, st, static_cast<const MTV*>(Mq), dy, dM, \
-              part, g, fm, mu, s_in)
+              part, g, fm, mu, s_in, divider_of(g.K))
   if (leg) {
     if (m_bits == 8) WINO_FBWD_OUT(true, int8_t);
     else if (m_bits == 9) WINO_FBWD_OUT(true, int16_t);
@@ -360,10 +396,10 @@ hipError_t PerMFlexBwd<M>::input_weight(const Geometry& g, bool leg, const int8_
   const int parts = backward_dv_reader_parts(g);
   if (leg)
     wino_launch((k_fbwd_input_weight<M, true>), grid, bs, st, x, dU, dXt, part_in, w, dV, dw, part_w,
-                g, fm, mu, s_in, s_w, nb_w, parts);
+                g, fm, mu, s_in, s_w, divider_of(g.C), nb_w, parts);
   else
     wino_launch((k_fbwd_input_weight<M, false>), grid, bs, st, x, dU, dXt, part_in, w, dV, dw,
-                part_w, g, fm, mu, s_in, s_w, nb_w, parts);
+                part_w, g, fm, mu, s_in, s_w, divider_of(g.C), nb_w, parts);
   return hipGetLastError();
 }
 
