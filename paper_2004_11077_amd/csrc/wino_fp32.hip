@@ -102,11 +102,9 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 // pieces: a result that is not finite is summed again in plain fp32, channel by channel.
 //
 // Work group = 4 waves (2 x 2) = (64 MB) tiles x (64 NB) output channels, a wave MB x NB blocks of
-// 32 x 32.  The channels run in chunks of 32 staged through LDS ([row][channel] per piece), the next
-// chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
+// 32 x 32.  The channels run in chunks of 32 staged through LDS ([row][channel] per piece), the next chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
 // What bounds it: at C = 128 the bytes of U and M.  2048 tiles, C = K = 128 (78 MB, 2.4 GFLOP): 159 us
-// with one lane per output and both panels in LDS as fp32, 22 us here (3.5 TB/s; 24.6 us with the
-// prefetch under a condition).  With 64-row or
+// with one lane per output and both panels in LDS as fp32, 24.6 us here (3.2 TB/s).  With 64-row or
 // 64-column blocks 25.4 us; with padded rows (61 KB of LDS, two groups per compute unit instead of
 // three, so that the 576 groups run in two rounds) 28.8 us.
 // ---------------------------------------------------------------------------
@@ -164,21 +162,21 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int srow = tid >> 3, sq = 4 * (tid & 7);                     // staging: 8 lanes per row
 
-  // Nothing here is conditional: a load under a branch would be waited for at the branch's end.  Rows
-  // past the last one are read from it (their results are not stored), channels past C from its last
-  // four; those are zeroed when they are staged.
-  int oa[2 * MB], ob[2 * NB];
-#pragma unroll
-  for (int it = 0; it < 2 * MB; ++it) oa[it] = min(srow + 32 * it, trows - 1) * C + sq;
-#pragma unroll
-  for (int it = 0; it < 2 * NB; ++it) ob[it] = min(srow + 32 * it, krows - 1) * C + sq;
   v4f ra[2 * MB], rb[2 * NB];
   auto fetch = [&](int c0) {
-    const int cc = min(c0, C - 4 - sq);
+    const bool cok = c0 + sq < C;                                    // C is a multiple of 16
 #pragma unroll
-    for (int it = 0; it < 2 * MB; ++it) ra[it] = *reinterpret_cast<const v4f*>(Up + (oa[it] + cc));
+    for (int it = 0; it < 2 * MB; ++it) {
+      ra[it] = v4f{0.f, 0.f, 0.f, 0.f};
+      if (cok && srow + 32 * it < trows)
+        ra[it] = *reinterpret_cast<const v4f*>(Up + (long)(srow + 32 * it) * C + c0 + sq);
+    }
 #pragma unroll
-    for (int it = 0; it < 2 * NB; ++it) rb[it] = *reinterpret_cast<const v4f*>(Vp + (ob[it] + cc));
+    for (int it = 0; it < 2 * NB; ++it) {
+      rb[it] = v4f{0.f, 0.f, 0.f, 0.f};
+      if (cok && srow + 32 * it < krows)
+        rb[it] = *reinterpret_cast<const v4f*>(Vp + (long)(srow + 32 * it) * C + c0 + sq);
+    }
   };
   auto put = [&](unsigned short* base, int rows, int row, const v4f& v) {
     unsigned h[2], m[2], l[2];
@@ -201,21 +199,15 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
   const int l32 = lane & 31, lk = lane >> 5;
   // MFMA operands: lane -> row lane % 32, channels 8 (lane / 32) .. + 7 of each 16
 
-  if (C > 0) fetch(0);
+  fetch(0);
   for (int c0 = 0; c0 < C; c0 += kF32Chunk) {
-    if (c0 + kF32Chunk > C && c0 + sq >= C) {
-#pragma unroll
-      for (int it = 0; it < 2 * MB; ++it) ra[it] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int it = 0; it < 2 * NB; ++it) rb[it] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
     __syncthreads();                  // the previous chunk's fragment reads are done
 #pragma unroll
     for (int it = 0; it < 2 * MB; ++it) put(As, TR, srow + 32 * it, ra[it]);
 #pragma unroll
     for (int it = 0; it < 2 * NB; ++it) put(Bs, TC, srow + 32 * it, rb[it]);
     __syncthreads();
-    fetch(c0 + kF32Chunk);            // past the last chunk: its last channels again, dropped
+    if (c0 + kF32Chunk < C) fetch(c0 + kF32Chunk);
 #pragma unroll
     for (int kk = 0; kk < kF32Chunk; kk += 16) {
       bf16x8 fA[3][MB], fB[3][NB];
