@@ -391,23 +391,30 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& s
     }
   }
   const int rt = r_begin + whole * kStage;
-  if (rt < r_end) {                   // the rest, less than a stage
-    __syncthreads();
+  if (rt < r_end) {                   // the rest, less than a stage: all loads first
+    rfor<0, kStage / 16>([&](auto kkc) {
+      constexpr int kk = decltype(kkc)::value;
+      if constexpr (ARED) {           // r_end = red is a multiple of 16; steps past it are skipped below
+        fetch_a(min(rt, red - 16 - 16 * kk), kkc);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          ra[kk][e] = Al[(long)(min(rt + 16 * kk + 8 * lk + e, red - 1) - 8 * lk) * rows];
+      }
+    });
 #pragma unroll
     for (int e = 0; e < 8; ++e)       // past the end A is zero: any code will do
       rbw[e] = *reinterpret_cast<const int*>(Bl + (long)min(rt + 8 * bo + e, red - 1) * cols);
+    __syncthreads();
     stage_b(0);
     __syncthreads();
     rfor<0, kStage / 16>([&](auto kkc) {
       constexpr int kk = decltype(kkc)::value;
       const int r = rt + 16 * kk;
       if (r < r_end) {                // uniform
-        if constexpr (ARED) {
-          fetch_a(rt, kkc);           // r_end = red is a multiple of 16
-        } else {
+        if constexpr (!ARED) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            ra[kk][e] = r + 8 * lk + e < r_end ? Al[(long)(r + e) * rows] : 0.f;
+          for (int e = 0; e < 8; ++e) ra[kk][e] = r + 8 * lk + e < r_end ? ra[kk][e] : 0.f;
         }
         step(0, kkc, [](auto) {});
       }
