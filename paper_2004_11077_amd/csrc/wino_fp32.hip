@@ -94,12 +94,15 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 
 // ---------------------------------------------------------------------------
 // Contraction: M[p][t][k] = sum_c U[p][t][c] V[p][k][c], n*n fp32 GEMMs on the bf16 matrix pipe
-// without giving up fp32 accuracy.  Both operands are cut, while they are staged, into three
-// bf16 pieces, each rounded to nearest: x = h + m + l exactly, |m| <= 2^-9 |x|, |l| <= 2^-18 |x|.
-// Six of the nine piece products are accumulated in fp32 (exact products, smallest first); the
-// three that are left out (ml, lm, ll) are below 2^-26 of |x y|, a quarter of what rounding one
-// fp32 product loses.  Infinities, NaNs and values that round past the largest bf16 have no such
-// pieces: a result that is not finite is summed again in plain fp32, channel by channel.
+// without giving up fp32 accuracy.  Both operands are scaled by 2^24 and cut, while they are staged,
+// into three bf16 pieces, each rounded to nearest: x = h + m + l exactly, |m| <= 2^-8 |x|,
+// |l| <= 2^-17 |x|.  The scale keeps every piece of every fp32 number, subnormals included, a normal
+// bf16 (a piece is a multiple of the last bit of x, at least 2^-149): unscaled, l is lost below 2^-110
+// and m below 2^-118, and results of such operands had a relative error of up to 3e-3.  Six of the nine
+// piece products are accumulated in fp32 (exact products, smallest first), and the sums are scaled by
+// 2^-48; the three that are left out (ml, lm, ll) are together at most 2^-24 of |x y|, what rounding
+// one fp32 product may lose.  Infinities, NaNs, operands from 2^103 and sums from 2^80 on leave that
+// range: a result that is not finite is summed again in plain fp32, channel by channel.
 //
 // Work group = 4 waves (2 x 2) = (64 MB) tiles x (64 NB) output channels, a wave MB x NB blocks of
 // 32 x 32.  The channels run in chunks of 32 staged through LDS ([row][channel] per piece), the next chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
@@ -122,6 +125,7 @@ constexpr int kF32Row = kF32Chunk;   // bf16 per staged row
 // phase fall on distinct banks.
 __device__ __forceinline__ int f32_seg(int row, int q) { return row * kF32Row + 8 * (q ^ ((row >> 2) & 3)); }
 
+constexpr float kF32Up = 0x1p24f, kF32Down = 0x1p-48f;   // scale of the operands, of the sums
 // Two values as bf16 pieces, the first at the lower address of each packed pair.
 __device__ __forceinline__ void split3_rne(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
   auto pack = [](float u, float v) {
@@ -180,8 +184,8 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
   };
   auto put = [&](unsigned short* base, int rows, int row, const v4f& v) {
     unsigned h[2], m[2], l[2];
-    split3_rne(v[0], v[1], h[0], m[0], l[0]);
-    split3_rne(v[2], v[3], h[1], m[1], l[1]);
+    split3_rne(v[0] * kF32Up, v[1] * kF32Up, h[0], m[0], l[0]);
+    split3_rne(v[2] * kF32Up, v[3] * kF32Up, h[1], m[1], l[1]);
     unsigned short* at = base + f32_seg(row, sq >> 3) + (sq & 4);
     *reinterpret_cast<v2u*>(at) = v2u{h[0], h[1]};
     *reinterpret_cast<v2u*>(at + rows * kF32Row) = v2u{m[0], m[1]};
@@ -252,7 +256,7 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
       const int r = idx / (8 * NB), q = 4 * (idx % (8 * NB));
       const int row = wr + 32 * a + r, col = wc + q;
       if (row < trows && col < krows) { // K is a multiple of 16: a quad is inside or outside
-        v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q);
+        v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q) * kF32Down;
         const float top = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
         const float sum = (v[0] + v[1]) + (v[2] + v[3]);             // NaN if one of them is
         if (__builtin_expect(!(top <= FLT_MAX && sum == sum), 0)) {

@@ -1,9 +1,9 @@
 """The fp32 contraction on the matrix cores (operands cut into three bf16 pieces) against fp64, at the
 edges of its tiles: one tile, one row past a tile block, channel counts that fill no chunk or block.
 
-Bound, element by element: every product is represented to 2^-26 of its size, and its sum of C terms
-(at most 6 C roundings in fp32, each 2^-24 of a partial sum that never exceeds sum |u v|) adds
-6 C 2^-24 sum |u v|."""
+Bound, element by element: the piece products that are left out are together at most 2^-24 of a
+product (|m| <= 2^-8 |x|, |l| <= 2^-17 |x|), and its sum of C terms (at most 6 C roundings in fp32, each
+2^-24 of a partial sum that never exceeds sum |u v|) adds 6 C 2^-24 sum |u v|."""
 import numpy as np
 import pytest
 
@@ -32,7 +32,7 @@ def test_contract_f32_against_fp64(m, N, H, W, C, K):
     wn.wino_contract(d, U, V, M, wn.Scales.from_dict({}))
     torch.cuda.synchronize()
     u64, v64 = u.astype(np.float64), v.astype(np.float64).transpose(0, 2, 1)
-    bound = (6 * C * 2.0 ** -24 + 2.0 ** -26) * np.matmul(np.abs(u64), np.abs(v64))
+    bound = (6 * C + 1) * 2.0 ** -24 * np.matmul(np.abs(u64), np.abs(v64))
     err = np.abs(M.cpu().numpy().astype(np.float64) - np.matmul(u64, v64))
     assert (err <= bound).all(), float((err / bound).max())
 
@@ -63,5 +63,34 @@ def test_contract_f32_beyond_the_range_of_its_pieces():
         assert np.array_equal(cls(got), cls(want)), cls
     ok = np.isfinite(want)
     size = sum(np.abs(u[..., None, c].astype(np.float64) * v[:, None, :, c]) for c in range(C))
-    bound = (6 * C * 2.0 ** -24 + 2.0 ** -26) * size
+    bound = (6 * C + 1) * 2.0 ** -24 * size
     assert (np.abs(got[ok] - want[ok]) <= bound[ok]).all()
+
+
+@pytest.mark.parametrize("eu,ev", [
+    (-124, 0),       # low pieces of u far below the smallest bf16
+    (-126, 20),      # the smallest normal numbers
+    (-140, 30),      # subnormal u
+    (0, -135),       # subnormal v
+    (-124, 110),     # tiny times large: an ordinary result
+    (-70, -70),      # subnormal result
+])
+def test_contract_f32_of_tiny_operands(eu, ev):
+    """Operands far below one keep all their 24 bits (what a subnormal has of them).  Bound as above,
+    plus half the smallest subnormal where the result is stored, and where a plain sum adds one (C of
+    them)."""
+    import torch
+    import paper_2004_11077_amd as wn
+    d = wn.ConvDesc(1, 12, 44, 48, 80, m=4, bits_in=32)
+    n2, T, C, K = d.n ** 2, d.tiles, 48, 80
+    rng = np.random.default_rng(5)
+    u = np.ldexp(rng.uniform(-1, 1, (n2, T, C)), eu).astype(np.float32)
+    v = np.ldexp(rng.uniform(-1, 1, (n2, K, C)), ev).astype(np.float32)
+    M = torch.full((n2, T, K), float("nan"), dtype=torch.float32, device="cuda")
+    wn.wino_contract(d, torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda(), M,
+                     wn.Scales.from_dict({}))
+    torch.cuda.synchronize()
+    u64, v64 = u.astype(np.float64), v.astype(np.float64).transpose(0, 2, 1)
+    bound = (6 * C + 1) * 2.0 ** -24 * np.matmul(np.abs(u64), np.abs(v64)) + (C + 1) * 2.0 ** -150
+    err = np.abs(M.cpu().numpy().astype(np.float64) - np.matmul(u64, v64))
+    assert (err <= bound).all(), float((err / bound).max())
