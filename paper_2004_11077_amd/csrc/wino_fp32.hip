@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 // piece products are accumulated in fp32 (exact products, smallest first), and the sums are scaled by
 // 2^-48; the three that are left out (ml, lm, ll) are together at most 2^-24 of |x y|, what rounding
 // one fp32 product may lose.  Infinities, NaNs, operands from 2^103 and sums from 2^80 on leave that
-// range: a result that is not finite is summed again in plain fp32, channel by channel.
+// range: work groups in which a result is not finite sum again in plain fp32.
 //
 // Work group = 4 waves (2 x 2) = (64 MB) tiles x (64 NB) output channels, a wave MB x NB blocks of
 // 32 x 32.  The channels run in chunks of 32 staged through LDS ([row][channel] per piece), the next chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
@@ -236,11 +236,63 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
     }
   }
 
+  float inf_or_nan = 0.f;             // turns NaN where a sum is not finite
+#pragma unroll
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        acc[a][b][i] *= kF32Down;
+        inf_or_nan = __builtin_fmaf(acc[a][b][i], 0.f, inf_or_nan);
+      }
+  float* Mp = Mo + ((long)p * T + row0) * K + col0;
   // acc[a][b][i] holds (tile = 32 a + (i / 4) * 8 + (lane / 32) * 4 + i % 4, k = 32 b + lane % 32) of
-  // the wave's block; 32 tiles at a time leave through the wave's own part of LDS in 16-byte stores.
+  // the wave's block.  A work group with a sum that is not finite forms all of its sums in plain fp32
+  // instead, channel by channel, one 32 x 32 block of each wave at a time from panels in LDS.  2048
+  // tiles, C = K = 128, all NaN: 120 us (2842 with every such sum on its own from memory).
+  if (__builtin_expect(__syncthreads_or(inf_or_nan != 0.f), 0)) {
+    constexpr int kRowF = kF32Chunk + 4;
+    float* Af = smem;
+    float* Bf = smem + TR * kRowF;
+    static_assert((TR + TC) * kRowF <= f32_lds_floats(MB, NB));
+#pragma unroll 1
+    for (int ab = 0; ab < MB * NB; ++ab) {
+      const int r32 = wr + 32 * (ab / NB) + lk * 4, k32 = wc + 32 * (ab % NB) + l32;
+      float sum[16] = {};
+#pragma unroll 1
+      for (int c0 = 0; c0 < C; c0 += kF32Chunk) {
+        fetch(c0);                    // zeros past C, the last tile and the last output channel
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < 2 * MB; ++it) *reinterpret_cast<v4f*>(Af + (srow + 32 * it) * kRowF + sq) = ra[it];
+#pragma unroll
+        for (int it = 0; it < 2 * NB; ++it) *reinterpret_cast<v4f*>(Bf + (srow + 32 * it) * kRowF + sq) = rb[it];
+        __syncthreads();
+        const int cend = min(kF32Chunk, C - c0);
+#pragma unroll 1
+        for (int c = 0; c < cend; c += 4) {
+          const v4f v = *reinterpret_cast<const v4f*>(Bf + k32 * kRowF + c);
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const v4f u = *reinterpret_cast<const v4f*>(Af + (r32 + (i >> 2) * 8 + (i & 3)) * kRowF + c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[i] = __builtin_fmaf(u[e], v[e], sum[i]);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int row = r32 + (i >> 2) * 8 + (i & 3);
+        if (row < trows && k32 < krows) Mp[(long)row * K + k32] = sum[i];
+      }
+    }
+    return;
+  }
+
+  // 32 tiles at a time leave through the wave's own part of LDS in 16-byte stores.
   constexpr int kLdC = 32 * NB + 4;
   float* Cs = smem + wave * 32 * kLdC;
-  float* Mp = Mo + ((long)p * T + row0) * K + col0;
 #pragma unroll
   for (int a = 0; a < MB; ++a) {
     __syncthreads();                  // the fragments (a = 0) resp. the previous rows have been read
@@ -256,19 +308,7 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
       const int r = idx / (8 * NB), q = 4 * (idx % (8 * NB));
       const int row = wr + 32 * a + r, col = wc + q;
       if (row < trows && col < krows) { // K is a multiple of 16: a quad is inside or outside
-        v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q) * kF32Down;
-        const float top = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
-        const float sum = (v[0] + v[1]) + (v[2] + v[3]);             // NaN if one of them is
-        if (__builtin_expect(!(top <= FLT_MAX && sum == sum), 0)) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (fabsf(v[e]) <= FLT_MAX) continue;
-            float acc1 = 0.f;
-            for (int c = 0; c < C; ++c)
-              acc1 = __builtin_fmaf(Up[(long)row * C + c], Vp[(long)(col + e) * C + c], acc1);
-            v[e] = acc1;
-          }
-        }
+        const v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q);
         __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(Mp + (long)row * K + col));
       }
     }

@@ -94,3 +94,35 @@ def test_contract_f32_of_tiny_operands(eu, ev):
     bound = (6 * C + 1) * 2.0 ** -24 * np.matmul(np.abs(u64), np.abs(v64)) + (C + 1) * 2.0 ** -150
     err = np.abs(M.cpu().numpy().astype(np.float64) - np.matmul(u64, v64))
     assert (err <= bound).all(), float((err / bound).max())
+
+
+@pytest.mark.parametrize("N,H,W,C,K", [
+    (1, 4, 4, 16, 16),           # one tile
+    (1, 20, 52, 48, 80),         # 65 tiles, a partial chunk, K past one 64-wide block
+    (1, 86, 24, 144, 144),       # 132 tiles: four rows and one 16-wide segment past a work group
+])
+def test_work_groups_with_sums_that_are_not_finite(N, H, W, C, K):
+    """Plain fp32 sums at the edges of a work group's tile: an infinity in the last channel of the last
+    tile, a NaN in the last filter, a point whose operands and sums are beyond the scaled range."""
+    import torch
+    import paper_2004_11077_amd as wn
+    d = wn.ConvDesc(N, H, W, C, K, m=4, bits_in=32)
+    n2, T = d.n ** 2, d.tiles
+    rng = np.random.default_rng(C)
+    u = rng.standard_normal((n2, T, C)).astype(np.float32)
+    v = rng.uniform(0.5, 1.0, (n2, K, C)).astype(np.float32)
+    u[0, -1, -1], v[1, -1, 0] = np.inf, np.nan
+    u[2] *= np.float32(2.0 ** 115)
+    M = torch.full((n2, T, K), 7.0, dtype=torch.float32, device="cuda")
+    wn.wino_contract(d, torch.from_numpy(u).cuda(), torch.from_numpy(v).cuda(), M,
+                     wn.Scales.from_dict({}))
+    torch.cuda.synchronize()
+    got = M.cpu().numpy().astype(np.float64)
+    u64, v64 = u.astype(np.float64), v.astype(np.float64).transpose(0, 2, 1)
+    assert np.isposinf(got[0, -1]).all() and np.isnan(got[1, :, -1]).all()
+    ok = np.ones(got.shape, bool)
+    ok[0, -1], ok[1, :, -1] = False, False
+    u64[0, -1, -1], v64[1, 0, -1] = 0.0, 0.0
+    bound = (6 * C + 1) * 2.0 ** -24 * np.matmul(np.abs(u64), np.abs(v64))
+    err = np.abs(got - np.matmul(u64, v64), where=ok, out=np.zeros_like(got))
+    assert (err <= bound).all()
