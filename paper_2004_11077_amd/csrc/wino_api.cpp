@@ -1413,12 +1413,21 @@ int wino_flex_calibrate(const wino_conv_desc_t* d, const wino_flex_matrices_t* f
   if (e != hipSuccess) return fail_hip(e, "flex calibration read-back");
   std::memcpy(&got.y[0], back, sizeof got.y[0]);
   std::memcpy(got.scales, back + y_bytes, sizeof got.scales);
-  s->s_u = got.scales[kCalSU];
+  // A scale that underflowed to zero or overflowed is refused as the stage call that would take it
+  // refuses it (U, V and M then hold nothing of use); s_m1 only where a stage call takes it, below.
+  StageMults mu_unused;
+  MultTable m_unused;
+  float f_unused;
+  double s_prev;
   s->s_v = got.scales[kCalSV];
-  if (p.two_brackets) s->s_x1 = got.scales[kCalSX1], s->s_w1 = got.scales[kCalSW1], s->s_m1 = got.scales[kCalSM1];
-  double s_prev = (double)s->s_u * (double)s->s_v;
-  if (p.m_bits != 32) s->s_m = got.scales[kCalSM], s_prev = (double)s->s_m;
-  if (p.two_brackets) s_prev = (double)s->s_m1;
+  if (p.two_brackets) s->s_w1 = got.scales[kCalSW1];
+  if (int rc = flex_weight_mults(p, s, &mu_unused, &f_unused)) return rc;
+  s->s_u = got.scales[kCalSU];
+  if (p.two_brackets) s->s_x1 = got.scales[kCalSX1];
+  if (int rc = flex_input_mults(p, s, &mu_unused, &f_unused)) return rc;
+  if (p.m_bits != 32) s->s_m = got.scales[kCalSM];
+  if (int rc = contract_mults(p, s, &m_unused, nullptr, &s_prev)) return rc;
+  if (p.two_brackets) s_prev = (double)(s->s_m1 = got.scales[kCalSM1]);
   s->s_y = flex_scale_from(got.y[0], s_prev, 127.0);
   wino_conv_desc_t dd = *d;
   dd.weights_pretransformed = 0;

@@ -40,3 +40,33 @@ def test_device_chosen_scales_equal_the_oracles(m, base, bh, out_type, relu, sha
     for name, val in sc.items():
         assert np.float32(getattr(got, name)) == np.float32(val), name
     assert np.array_equal(y.cpu().numpy(), ora["y"].astype(np.int8 if out_type == "i8" else np.float32))
+
+
+@pytest.mark.parametrize("m,base,bh,s_x,s_w,size,bad", [
+    (4, "legendre", 8, 0.1, 1e-45, 0.01, "s_w1"),      # the filters' scales underflow
+    (4, "canonical", 8, 0.1, 3e38, 1000.0, "s_v"),     # and overflow
+    (2, "legendre", 9, 3e38, 0.1, 1000.0, "s_x1"),     # those of the activations
+    (4, "canonical", 8, 1e-45, 0.1, 0.01, "s_u"),
+    (2, "canonical", 9, 1e-25, 1e-25, 1.0, "s_m"),     # the product of two good ones underflows
+])
+@pytest.mark.parametrize("with_y", [False, True])
+def test_scales_that_no_stage_call_takes_are_refused(m, base, bh, s_x, s_w, size, bad, with_y):
+    """A chosen scale that underflows to zero or overflows is an error of the calibration, whether or
+    not an output is asked for."""
+    import torch
+    import paper_2004_11077_amd as wn
+    N, H, W, C, K = 1, 9, 9, 16, 16
+    xq, wq, _, _ = small_layer(N, H, W, C, K, seed=3)
+    fm = noisy_matrices(m, base, seed=1)
+    desc = wn.ConvDesc(N, H, W, C, K, m=m, bits_hadamard=bh,
+                       base=wn.BASE_LEGENDRE if base == "legendre" else wn.BASE_CANONICAL)
+    x, w = torch.from_numpy(xq).cuda(), torch.from_numpy(wq).cuda()
+    y = torch.zeros((N, H, W, K), dtype=torch.float32, device="cuda") if with_y else None
+    ws = torch.empty(wn.wino_calibrate_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    gfm = wn.FlexMatrices(*(np.float32(size) * a for a in (fm.GP, fm.BPT, fm.APT)))
+    with pytest.raises(wn.WinoError, match="bad .*" + bad):
+        wn.wino_flex_calibrate(desc, gfm, x, w, y, s_x, s_w, ws)
+    torch.cuda.synchronize()
+    # the same call with ordinary scales goes through
+    sc = wn.wino_flex_calibrate(desc, wn.FlexMatrices(fm.GP, fm.BPT, fm.APT), x, w, y, 0.1, 0.1, ws)
+    assert 0 < sc.s_u < np.inf and 0 < sc.s_v < np.inf and 0 < sc.s_m < np.inf
