@@ -113,6 +113,8 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 // ---------------------------------------------------------------------------
 using v2f = __attribute__((ext_vector_type(2))) float;
 using v4f = __attribute__((ext_vector_type(4))) float;
+// The same in a tensor that may start at any float.
+typedef v4f v4f_any __attribute__((aligned(4)));
 using v2u = __attribute__((ext_vector_type(2))) unsigned;
 using v16f = __attribute__((ext_vector_type(16))) float;
 using bf16x2 = __attribute__((ext_vector_type(2))) __bf16;
@@ -173,13 +175,13 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
     for (int it = 0; it < 2 * MB; ++it) {
       ra[it] = v4f{0.f, 0.f, 0.f, 0.f};
       if (cok && srow + 32 * it < trows)
-        ra[it] = *reinterpret_cast<const v4f*>(Up + (long)(srow + 32 * it) * C + c0 + sq);
+        ra[it] = *reinterpret_cast<const v4f_any*>(Up + (long)(srow + 32 * it) * C + c0 + sq);
     }
 #pragma unroll
     for (int it = 0; it < 2 * NB; ++it) {
       rb[it] = v4f{0.f, 0.f, 0.f, 0.f};
       if (cok && srow + 32 * it < krows)
-        rb[it] = *reinterpret_cast<const v4f*>(Vp + (long)(srow + 32 * it) * C + c0 + sq);
+        rb[it] = *reinterpret_cast<const v4f_any*>(Vp + (long)(srow + 32 * it) * C + c0 + sq);
     }
   };
   auto put = [&](unsigned short* base, int rows, int row, const v4f& v) {
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
       const int row = wr + 32 * a + r, col = wc + q;
       if (row < trows && col < krows) { // K is a multiple of 16: a quad is inside or outside
         const v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q);
-        __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(Mp + (long)row * K + col));
+        __builtin_nontemporal_store(v, reinterpret_cast<v4f_any*>(Mp + (long)row * K + col));
       }
     }
   }

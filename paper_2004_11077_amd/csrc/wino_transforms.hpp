@@ -13,6 +13,10 @@
 namespace wino {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+// The same at any address: for the tensors a caller hands over.  The stage calls of a layer with
+// run-time matrices take them at any byte (those with fixed matrices at multiples of 16 only), and the
+// device's unaligned access mode serves both with one instruction.
+typedef v4i v4i_any __attribute__((aligned(1)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 template <int I>
@@ -490,7 +494,7 @@ __device__ __forceinline__ void weight_items(const int8_t* __restrict__ w, int8_
       src = w + ((long)(kq * 4 + run) * g.C + chunk * 64) * 9 + piece * 16;
     }
     v4i v = {0, 0, 0, 0};
-    if (ok) v = *reinterpret_cast<const v4i*>(src);
+    if (ok) v = *reinterpret_cast<const v4i_any*>(src);
     *reinterpret_cast<v4i*>(s_w + tid * 16) = v;
   }
   __syncthreads();
@@ -526,7 +530,7 @@ __device__ __forceinline__ void weight_items(const int8_t* __restrict__ w, int8_
     const int p = it * 16 + prow;
     if (p < n2 && sok)
       __builtin_nontemporal_store(*reinterpret_cast<const v4i*>(s_v + p * 256 + u * 16),
-                                  reinterpret_cast<v4i*>(vb + (long)p * pstride));
+                                  reinterpret_cast<v4i_any*>(vb + (long)p * pstride));
   }
 }
 
@@ -626,11 +630,11 @@ __device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t
       v4i v = {0, 0, 0, 0};
       if (uok && (unsigned)h < (unsigned)g.H && (unsigned)ww < (unsigned)g.W) {
         if constexpr (WHOLE)   // the launcher keeps H * W * C below 2^31 on this path
-          v = *reinterpret_cast<const v4i*>(xb + (uint32_t)((h * g.W + ww) * g.C));
+          v = *reinterpret_cast<const v4i_any*>(xb + (uint32_t)((h * g.W + ww) * g.C));
         else if (small_image)
-          v = *reinterpret_cast<const v4i*>(xb + __umul24(__umul24(h, g.W) + ww, g.C));
+          v = *reinterpret_cast<const v4i_any*>(xb + __umul24(__umul24(h, g.W) + ww, g.C));
         else
-          v = *reinterpret_cast<const v4i*>(xb + ((long)h * g.W + ww) * g.C);
+          v = *reinterpret_cast<const v4i_any*>(xb + ((long)h * g.W + ww) * g.C);
       }
       *reinterpret_cast<v4i*>(s_in + pix * 256 + u * 16) = v;
     }
@@ -673,7 +677,7 @@ __device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t
     const int p = it * 16 + prow;
     if (p < n2 && sok)
       __builtin_nontemporal_store(*reinterpret_cast<const v4i*>(s_out + p * 256 + su * 16),
-                                  reinterpret_cast<v4i*>(ub + (long)p * pstride));
+                                  reinterpret_cast<v4i_any*>(ub + (long)p * pstride));
   }
 }
 
@@ -771,7 +775,7 @@ __device__ __forceinline__ void fetch_m(const MT* __restrict__ Mq, long total, l
       const int p = it * 16 + prow;
       if (p < N * N) {
         v4i v = {0, 0, 0, 0};
-        if (uok) v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(Mq + (long)p * total + ug));
+        if (uok) v = __builtin_nontemporal_load(reinterpret_cast<const v4i_any*>(Mq + (long)p * total + ug));
         *reinterpret_cast<v4i*>(s_in + p * 256 + u * 16) = v;
       }
     }
