@@ -1141,7 +1141,7 @@ int wino_conv2d(const wino_conv_desc_t* d, const void* x, const void* w_or_V, vo
     if (int rc = need(x, "x")) return rc;
     if (int rc = need(y, "y")) return rc;
     if (int rc = need(s, "scales")) return rc;
-    if (int rc = aligned(V, 16, "V")) return rc;
+    if (int rc = aligned(V, 16, raw ? "w" : "V")) return rc;
     StageMults in_mu, out_mu;
     MultTable m_mult;
     ShiftTable sh;

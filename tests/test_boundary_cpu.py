@@ -134,6 +134,20 @@ def test_stage_calls_reject_bad_arguments_before_any_launch():
     assert lib.wino_contract_output(C.byref(d), fake, fake, None, C.byref(s), None) == -1
 
 
+@pytest.mark.parametrize("fused", [0, 1])
+def test_whole_layer_call_names_misaligned_filters(fused):
+    """Raw filters are called w whichever kernel transforms them, transformed ones V."""
+    lib = binding._load()
+    fake, off = C.c_void_p(4096), C.c_void_p(4104)
+    s = wn.Scales.from_dict({})
+    for pre, K, name in ((0, 16, b"w must"), (0, 80, b"w must"), (1, 16, b"V must")):
+        d = wn.ConvDesc(1, 8, 8, 16, K, m=4, fused=fused, weights_pretransformed=pre)
+        if pre and not fused:
+            continue                  # the input transform would be launched before V is looked at
+        assert lib.wino_conv2d(C.byref(d), fake, off, fake, C.byref(s), fake, 1 << 30, None) == -1
+        assert name in lib.wino_last_error()
+
+
 def test_no_alloc_call_rejects_oversized_layers_before_touching_the_device():
     lib = binding._load()
     fake = C.c_void_p(4096)
