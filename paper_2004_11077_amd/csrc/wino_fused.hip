@@ -302,27 +302,6 @@ static hipError_t fused_ft(const Geometry& g, const int8_t* x, const int8_t* V, 
   return hipGetLastError();
 }
 
-// Tiles per work group.  A launch takes about (first + each * rounds) us, rounds = work groups over 256
-// compute units: smaller groups have the shorter chain of phases, larger ones waste less of the
-// matrix instruction's 16 columns and of phase B.  Measured, F(4,3), C = K = 64, us per layer with
-// transformed filters:
-//   tiles          64 .. 1024   2048   3072   4096   6144   8192
-//   16 per group      15.6      15.7   15.8   15.9   23.6   23.7
-//    8                10.1      10.2   14.9   15.0   19.7   24.9
-//    4                 8.2      10.7   13.7   16.7   23.3   30.1
-// F(2,3), C = K = 16: 7.0, 5.2, 4.6 at 1024 tiles, 14.8, 17.0, 22.0 at 16384.
-static int fused_tiles(const Geometry& g, int kb) {
-  constexpr struct { int tiles; long first, each; } kCost[3] = {{16, 80, 78}, {8, 53, 49}, {4, 54, 30}};
-  int best = 16;
-  long best_cost = 0;
-  for (const auto& c : kCost) {
-    const long groups = ((long)g.T + c.tiles - 1) / c.tiles * ((g.K + kb - 1) / kb);
-    const long cost = c.first + c.each * ((groups + 255) / 256);
-    if (best_cost == 0 || cost < best_cost) best = c.tiles, best_cost = cost;
-  }
-  return best;
-}
-
 template <int M, bool LEG, typename MT, bool PP>
 static hipError_t fused_mt(const Geometry& g, const int8_t* x, const int8_t* V, void* y, int out_type,
                            bool relu, const StageMults& in_mu, const StageMults& out_mu,

@@ -439,6 +439,35 @@ hipError_t launch_fused(const Geometry& g, bool legendre_inner, const int8_t* x,
                         const StageMults* w_mu, int8_t* Vout, hipStream_t st);
 // Output channels per work group of the fused kernel.
 inline int fused_channels(int m_bits) { return m_bits == 8 ? 64 : 32; }
+// Tiles per work group of the fused kernel (kb = fused_channels).  A launch takes about (first + each *
+// rounds) / 10 us, rounds = work groups over 256 compute units: smaller groups have the shorter chain of
+// phases, larger ones waste less of the matrix instruction's 16 columns and of phase B.  Measured, C = K
+// = 64, us per layer with transformed filters, int8 M and output:
+//   tiles             1024   2048   3072   4096   6144   8192  10240  12288  16384  32768
+//   F(4,3)  16        15.7   15.8   15.9   16.0   23.7   23.8   31.8   31.8   40.7   77.9
+//            8        10.2   10.2   15.0   15.1   19.9   25.1   30.7   35.8   46.0   88.3
+//            4         8.4   10.8   13.8   16.8   23.4   30.2   36.5   43.0   55.9  106.8
+//   F(2,3)  16         7.4    7.4    7.5    7.5   10.2   10.2   11.8   11.9   15.2   27.0
+//            8         5.5    5.5    6.8    6.9    8.5   10.0   12.4   14.0   18.2   33.1
+//            4         5.5    5.9    6.8    8.3   10.8   13.5   16.2   18.9   24.3   45.9
+// The third round of 16-tile groups is cheap in F(2,3) with full blocks of 64 channels (at 10240 tiles and
+// K = 48 12.2 against 11.9 us with 8 tiles, K = 16 12.1 against 11.7): a dearer round of 8 there.  9-bit M (blocks of
+// 32), C = K = 64, F(4,3): 13.4, 8.9, 9.7 at 1024 tiles, 19.1, 19.9, 25.3 at 4096; F(2,3): 6.7, 5.6, 5.5 and
+// 8.9, 8.3, 10.9.  The choice is within 3 % of the best of the three over these shapes and C, K down
+// to 16, but for F(2,3) with a 9-bit M and C = K = 64 at 4096 tiles (8 %).
+inline int fused_tiles(const Geometry& g, int kb) {
+  struct Cost { int tiles; long first, each; };
+  constexpr Cost kCost[3] = {{16, 80, 78}, {8, 53, 49}, {4, 54, 30}};
+  constexpr Cost kCostFullBlocks2[3] = {{16, 80, 78}, {8, 50, 53}, {4, 54, 30}};
+  int best = 16;
+  long best_cost = 0;
+  for (const Cost& c : g.m == 2 && kb == 64 && g.K >= 64 ? kCostFullBlocks2 : kCost) {
+    const long groups = ((long)g.T + c.tiles - 1) / c.tiles * ((g.K + kb - 1) / kb);
+    const long cost = c.first + c.each * ((groups + 255) / 256);
+    if (best_cost == 0 || cost < best_cost) best = c.tiles, best_cost = cost;
+  }
+  return best;
+}
 // Few enough filters (and tiles) for every work group of the fused kernel to transform its own.
 inline bool fused_takes_raw_filters(const Geometry& g) {
   return (long)g.K * g.C <= 1024 && g.T <= 1024;

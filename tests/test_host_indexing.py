@@ -17,7 +17,7 @@ needs_hipcc = pytest.mark.skipif(
     reason="needs hipcc for the HIP runtime headers the library header includes")
 
 
-def run_host_program(tmp_path, name):
+def run_host_program(tmp_path, name, args=()):
     exe = str(tmp_path / name)
     hipcc = HIPCC if os.path.exists(HIPCC) else shutil.which("hipcc")
     # host compilation only: no device code is generated, nothing here touches a GPU
@@ -26,7 +26,7 @@ def run_host_program(tmp_path, name):
                     "-I", os.path.join(ROOT, "include"), "-I", "/opt/rocm/include",
                     os.path.join(ROOT, "tests", "host", name + ".cpp"), "-o", exe],
                    check=True, capture_output=True, text=True)
-    run = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    run = subprocess.run([exe, *args], capture_output=True, text=True, timeout=300)
     assert run.returncode == 0, run.stdout + run.stderr
     return run.stdout.split()
 
