@@ -7,15 +7,22 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+# shape, tile rows of a work group (64 unless 128-row blocks are many; test_launch_rules.py)
+CASES = [
+    ((1, 4, 4, 16, 16), 64),
+    ((33, 4, 4, 112, 144), 64),  # 33 tiles, 7 of 8 segments of a chunk, a block and one segment of filters
+    ((1, 32, 32, 128, 80), 64),  # 64 tiles, exactly a chunk
+    ((65, 4, 4, 144, 128), 64),  # 65 tiles, a chunk and a segment
+    ((1, 172, 48, 272, 48), 64),    # 516 tiles: eight blocks and four rows, two chunks and a segment
+    ((1, 172, 48, 144, 272), 128),  # 516 tiles: four blocks and four rows, two blocks of filters and a segment
+    ((15, 44, 44, 48, 16), 128),    # 1815 tiles: 14 blocks and 23 rows, less than a chunk, one segment of filters
+]
+
+
 @pytest.mark.parametrize("hadamard", [8, 9])
-@pytest.mark.parametrize("N,H,W,C,K", [
-    (1, 4, 4, 16, 16),
-    (33, 4, 4, 112, 144),        # 33 tiles, 7 of 8 segments of a chunk, a block and one segment of filters
-    (1, 32, 32, 128, 80),        # 64 tiles, exactly a chunk
-    (65, 4, 4, 144, 128),        # 65 tiles, a chunk and a segment
-    (1, 172, 48, 272, 48),       # 516 tiles: blocks of 128 rows and four left over
-])
-def test_contract_codes(N, H, W, C, K, hadamard):
+@pytest.mark.parametrize("shape,rows", CASES)
+def test_contract_codes(shape, rows, hadamard):
+    N, H, W, C, K = shape
     import torch
     import paper_2004_11077_amd as wn
     d = wn.ConvDesc(N, H, W, C, K, m=4, bits_hadamard=hadamard)

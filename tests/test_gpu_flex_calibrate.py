@@ -1,6 +1,6 @@
 """Scales of a flex layer chosen on the device, at the ends of the range: one tile and 16 channels (the
-smallest scratch region), several work groups with a partly empty last one, a 64-row contraction, all
-widths of M in both bases.  Every scale and the output must equal the oracle's bit for bit."""
+smallest scratch region), several work groups with a partly empty last one, contractions in blocks of 64 and
+of 128 rows, all widths of M in both bases.  Every scale and the output must equal the oracle's bit for bit."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,7 @@ from test_gpu_flex import noisy_matrices
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,base,bh,out_type,relu,shape", [
+CASES = [
     (2, "legendre", 8, "f32", False, (1, 2, 2, 16, 16)),
     (4, "legendre", 9, "i8", True, (1, 3, 4, 16, 16)),
     (6, "canonical", 9, "i8", False, (1, 6, 6, 16, 16)),
@@ -19,7 +19,18 @@ pytestmark = pytest.mark.gpu
     (6, "legendre", 32, "f32", False, (2, 7, 13, 32, 48)),
     (4, "canonical", 32, "i8", True, (2, 9, 9, 80, 144)),
     (2, "canonical", 8, "i8", True, (9, 8, 8, 16, 256)),
-])
+]
+# at least 512 blocks of 128 rows: the contraction's other block height (test_launch_rules.py), with
+# ragged tiles and filters
+WIDE_CASES = [
+    (4, "legendre", 8, "i8", True, (1, 172, 48, 16, 272)),      # 516 tiles: four rows in the last block
+    (4, "canonical", 9, "f32", False, (1, 172, 48, 16, 272)),
+    (6, "legendre", 9, "i8", False, (1, 78, 120, 16, 272)),     # 260 tiles
+    (2, "canonical", 8, "f32", True, (3, 39, 70, 32, 528)),     # 2100 tiles: 52 rows in the last block
+]
+
+
+@pytest.mark.parametrize("m,base,bh,out_type,relu,shape", CASES + WIDE_CASES)
 def test_device_chosen_scales_equal_the_oracles(m, base, bh, out_type, relu, shape):
     import torch
     import paper_2004_11077_amd as wn

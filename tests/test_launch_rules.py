@@ -1,6 +1,11 @@
-"""The rules of the library's header that choose launch shapes, at sizes where they were measured."""
+"""The GPU tests of kernels with several launch shapes name the shape each of their cases is to run: checked
+here against the rules of the library's header, so that a rule that moves cannot leave a shape
+untested.  And the rule of the single kernel's groups at sizes where it was measured."""
 import pytest
 
+import test_gpu_contract_edges as contract_edges
+import test_gpu_flex_calibrate as flex_calibrate
+import test_gpu_fused_small as fused_small
 from test_host_indexing import needs_hipcc, run_host_program
 
 pytestmark = needs_hipcc
@@ -12,6 +17,27 @@ def rules(tmp_path, layers):
     out = [int(v) for v in run_host_program(tmp_path, "launch_rules", args)]
     assert len(out) == 2 * len(layers)
     return list(zip(out[::2], out[1::2]))
+
+
+def test_contraction_cases_run_the_block_they_name(tmp_path):
+    got = rules(tmp_path, [(4, *shape, 8) for shape, _ in contract_edges.CASES])
+    assert [r for r, _ in got] == [rows for _, rows in contract_edges.CASES]
+    assert {r for r, _ in got} == {64, 128}
+
+
+def test_flex_calibration_cases_run_the_block_they_name(tmp_path):
+    cases = flex_calibrate.WIDE_CASES
+    got = rules(tmp_path, [(m, *shape, 8) for m, _, _, _, _, shape in cases])
+    assert [r for r, _ in got] == [128] * len(cases)
+
+
+def test_single_kernel_cases_run_the_group_they_name(tmp_path):
+    cases = fused_small.CASES
+    got = rules(tmp_path, [(c[0], *c[6], c[2]) for c in cases])
+    assert [t for _, t in got] == [c[7] for c in cases]
+    sixteen = [c for c in cases if c[7] == 16]
+    assert {c[0] for c in sixteen} == {2, 4} and {c[2] for c in sixteen} == {8, 9}
+    assert {c[5] for c in sixteen} == {True, False} and {c[1] for c in sixteen} == {"canonical", "legendre"}
 
 
 @pytest.mark.parametrize("m,T,K,bits,tiles", [
