@@ -362,12 +362,12 @@ static hipError_t contract_f32_shape(const Geometry& g, const float* U, const fl
   return hipGetLastError();
 }
 
-// A wave takes two 32-wide blocks along a dimension that is longer than one 64-wide block.
 static hipError_t contract_f32(const Geometry& g, const float* U, const float* V, float* Mo,
                                hipStream_t st) {
-  if (g.T > 64)
-    return g.K > 64 ? contract_f32_shape<2, 2>(g, U, V, Mo, st) : contract_f32_shape<2, 1>(g, U, V, Mo, st);
-  return g.K > 64 ? contract_f32_shape<1, 2>(g, U, V, Mo, st) : contract_f32_shape<1, 1>(g, U, V, Mo, st);
+  const F32Blocks w = f32_contract_blocks(g);
+  if (w.t == 2)
+    return w.k == 2 ? contract_f32_shape<2, 2>(g, U, V, Mo, st) : contract_f32_shape<2, 1>(g, U, V, Mo, st);
+  return w.k == 2 ? contract_f32_shape<1, 2>(g, U, V, Mo, st) : contract_f32_shape<1, 1>(g, U, V, Mo, st);
 }
 
 static inline unsigned nblk(long items) { return (unsigned)((items + 255) / 256); }

@@ -536,6 +536,22 @@ hipError_t launch_backward_gemms(const Geometry& g, const float* dM, const int8_
 // kind 2 = bf16 MFMA loop (blocks * 4 waves * iters * 4 MFMAs of 32x32x16).
 hipError_t launch_probe(int kind, int blocks, int iters, int* sink, hipStream_t st);
 
+// Blocks of 32 x 32 per wave of the fp32 contraction along the tiles and the output channels (a work
+// group: 64 t tiles x 64 k channels): two along a dimension longer than 64, but one along both where two
+// leave no more than one work group per compute unit.  Layer us, two / one: F(2,3), 4 tiles, C = K = 512
+// (64 / 128 groups) 38.1 / 33.5; 512 tiles, C = K = 128 (64 / 256) 21.0 / 17.5; 2048 tiles (256 / 1024) 30.7 /
+// 29.4; F(4,3), 1000 tiles, C = 112, K = 96 (288 / 1152) 32.6 / 33.1; 2048 tiles, C = K = 128 (576 / 2304)
+// 48.9 / 51.1.
+struct F32Blocks {
+  int t, k;
+};
+inline F32Blocks f32_contract_blocks(const Geometry& g) {
+  const F32Blocks w{g.T > 64 ? 2 : 1, g.K > 64 ? 2 : 1};
+  const long groups = (long)(g.m + 2) * (g.m + 2) * ((g.T + 64 * w.t - 1) / (64 * w.t)) *
+                      ((g.K + 64 * w.k - 1) / (64 * w.k));
+  return groups <= 256 ? F32Blocks{1, 1} : w;
+}
+
 // fp32 path (wino_fp32.hip): no casts, float tensors in the int8 path's layouts.
 // Operand transforms in one launch; x or w null leaves that one out.
 hipError_t launch_operands_f32(const Geometry& g, bool legendre, const float* x, float* U,

@@ -1,6 +1,6 @@
 // Prints, for each layer given as "m N H W C K bits", the launch shapes that the library's rules choose
 // for it: tile rows of a work group of the contraction (contract_tile_rows), tiles of a work group of
-// the single kernel (fused_tiles).
+// the single kernel (fused_tiles), blocks per wave of the fp32 contraction (f32_contract_blocks).
 #include <cstdio>
 #include <cstdlib>
 
@@ -13,7 +13,9 @@ int main(int argc, char** argv) {
     wino::Geometry g{};
     g.m = v[0], g.N = v[1], g.H = v[2], g.W = v[3], g.C = v[4], g.K = v[5];
     g.TH = (g.H + g.m - 1) / g.m, g.TW = (g.W + g.m - 1) / g.m, g.T = g.N * g.TH * g.TW;
-    std::printf("%d %d\n", wino::contract_tile_rows(g), wino::fused_tiles(g, wino::fused_channels(v[6])));
+    const wino::F32Blocks w = wino::f32_contract_blocks(g);
+    std::printf("%d %d %d%d\n", wino::contract_tile_rows(g),
+                wino::fused_tiles(g, wino::fused_channels(v[6])), w.t, w.k);
   }
   return 0;
 }

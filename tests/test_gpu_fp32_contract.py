@@ -10,15 +10,22 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("m,N,H,W,C,K", [
-    (4, 1, 4, 4, 16, 16),        # one tile
-    (4, 1, 32, 32, 32, 64),      # 64 tiles: the last size of the 64-row block
-    (4, 1, 20, 52, 48, 80),      # 65 tiles, a partial chunk, K past one 64-wide block
-    (4, 1, 32, 64, 144, 128),    # 128 tiles
-    (2, 1, 6, 86, 16, 144),      # 129 tiles: one row in the second block
-    (6, 3, 23, 37, 80, 48),
-])
-def test_contract_f32_against_fp64(m, N, H, W, C, K):
+# m, N, H, W, C, K, blocks per wave along tiles and output channels (test_launch_rules.py)
+CASES = [
+    (4, 1, 4, 4, 16, 16, 11),        # one tile
+    (4, 1, 32, 32, 32, 64, 11),      # 64 tiles
+    (4, 1, 20, 52, 48, 80, 11),      # 65 tiles, a partial chunk, K past one 64-wide block
+    (4, 1, 32, 64, 144, 128, 11),    # 128 tiles
+    (2, 1, 6, 86, 16, 144, 11),      # 129 tiles: one row in the third block
+    (6, 3, 23, 37, 80, 48, 11),
+    (4, 1, 172, 48, 48, 272, 22),    # 516 tiles: four rows in the last block, a segment of K in the last
+    (4, 1, 129, 125, 16, 48, 21),    # 1056 tiles: 32 rows in the last block, K short of one
+    (6, 1, 24, 18, 80, 528, 12),     # 12 tiles, a segment of K in the last block
+]
+
+
+@pytest.mark.parametrize("m,N,H,W,C,K,blocks", CASES)
+def test_contract_f32_against_fp64(m, N, H, W, C, K, blocks):
     import torch
     import paper_2004_11077_amd as wn
     d = wn.ConvDesc(N, H, W, C, K, m=m, bits_in=32)
@@ -100,6 +107,7 @@ def test_contract_f32_of_tiny_operands(eu, ev):
     (1, 4, 4, 16, 16),           # one tile
     (1, 20, 52, 48, 80),         # 65 tiles, a partial chunk, K past one 64-wide block
     (1, 86, 24, 144, 144),       # 132 tiles: four rows and one 16-wide segment past a work group
+    (1, 172, 48, 48, 272),       # the same past work groups of twice the rows and columns
 ])
 def test_work_groups_with_sums_that_are_not_finite(N, H, W, C, K):
     """Plain fp32 sums at the edges of a work group's tile: an infinity in the last channel of the last

@@ -5,6 +5,7 @@ import pytest
 
 import test_gpu_contract_edges as contract_edges
 import test_gpu_flex_calibrate as flex_calibrate
+import test_gpu_fp32_contract as fp32_contract
 import test_gpu_fused_small as fused_small
 from test_host_indexing import needs_hipcc, run_host_program
 
@@ -12,32 +13,39 @@ pytestmark = needs_hipcc
 
 
 def rules(tmp_path, layers):
-    """(contract_tile_rows, fused_tiles) of each (m, N, H, W, C, K, bits)."""
+    """(contract_tile_rows, fused_tiles, f32_contract_blocks as a number of two digits) of each (m, N, H,
+    W, C, K, bits)."""
     args = [str(v) for layer in layers for v in layer]
     out = [int(v) for v in run_host_program(tmp_path, "launch_rules", args)]
-    assert len(out) == 2 * len(layers)
-    return list(zip(out[::2], out[1::2]))
+    assert len(out) == 3 * len(layers)
+    return list(zip(out[::3], out[1::3], out[2::3]))
 
 
 def test_contraction_cases_run_the_block_they_name(tmp_path):
     got = rules(tmp_path, [(4, *shape, 8) for shape, _ in contract_edges.CASES])
-    assert [r for r, _ in got] == [rows for _, rows in contract_edges.CASES]
-    assert {r for r, _ in got} == {64, 128}
+    assert [r for r, _, _ in got] == [rows for _, rows in contract_edges.CASES]
+    assert {r for r, _, _ in got} == {64, 128}
 
 
 def test_flex_calibration_cases_run_the_block_they_name(tmp_path):
     cases = flex_calibrate.WIDE_CASES
     got = rules(tmp_path, [(m, *shape, 8) for m, _, _, _, _, shape in cases])
-    assert [r for r, _ in got] == [128] * len(cases)
+    assert [r for r, _, _ in got] == [128] * len(cases)
 
 
 def test_single_kernel_cases_run_the_group_they_name(tmp_path):
     cases = fused_small.CASES
     got = rules(tmp_path, [(c[0], *c[6], c[2]) for c in cases])
-    assert [t for _, t in got] == [c[7] for c in cases]
+    assert [t for _, t, _ in got] == [c[7] for c in cases]
     sixteen = [c for c in cases if c[7] == 16]
     assert {c[0] for c in sixteen} == {2, 4} and {c[2] for c in sixteen} == {8, 9}
     assert {c[5] for c in sixteen} == {True, False} and {c[1] for c in sixteen} == {"canonical", "legendre"}
+
+
+def test_fp32_contraction_cases_run_the_blocks_they_name(tmp_path):
+    got = rules(tmp_path, [(*c[:6], 8) for c in fp32_contract.CASES])
+    assert [b for _, _, b in got] == [c[6] for c in fp32_contract.CASES]
+    assert {b for _, _, b in got} == {11, 12, 21, 22}
 
 
 @pytest.mark.parametrize("m,T,K,bits,tiles", [
