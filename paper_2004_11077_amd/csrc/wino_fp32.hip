@@ -144,7 +144,8 @@ constexpr int f32_lds_floats(int mb, int nb) {
   return staged > out ? staged : out;
 }
 
-template <int MB, int NB>
+// STREAM: M leaves in nontemporal stores.
+template <int MB, int NB, bool STREAM>
 __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict__ U,
                                                          const float* __restrict__ V,
                                                          float* __restrict__ Mo, int T, int C, int K,
@@ -216,6 +217,7 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
     if (c0 + kF32Chunk < C) fetch(c0 + kF32Chunk);
 #pragma unroll
     for (int kk = 0; kk < kF32Chunk; kk += 16) {
+      if (kk && c0 + kk >= C) break;   // uniform: half a chunk
       bf16x8 fA[3][MB], fB[3][NB];
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
@@ -311,13 +313,18 @@ __global__ __launch_bounds__(256, 3) void k_contract_f32(const float* __restrict
       const int row = wr + 32 * a + r, col = wc + q;
       if (row < trows && col < krows) { // K is a multiple of 16: a quad is inside or outside
         const v4f v = *reinterpret_cast<const v4f*>(Cs + r * kLdC + q);
-        __builtin_nontemporal_store(v, reinterpret_cast<v4f_any*>(Mp + (long)row * K + col));
+        v4f_any* at = reinterpret_cast<v4f_any*>(Mp + (long)row * K + col);
+        if constexpr (STREAM)
+          __builtin_nontemporal_store(v, at);
+        else
+          *at = v;
       }
     }
   }
 }
 
-template <int M, bool LEG>
+// STREAM: M is read in nontemporal loads.
+template <int M, bool LEG, bool STREAM>
 __global__ __launch_bounds__(256) void k_output_f32(const float* __restrict__ Mq,
                                                     float* __restrict__ y, Geometry g,
                                                     Divider by_k, int relu) {
@@ -333,7 +340,8 @@ __global__ __launch_bounds__(256) void k_output_f32(const float* __restrict__ Mq
   float mi[n][n];
   rfor<0, n>([&](auto i) {
     rfor<0, n>([&](auto j) {
-      mi[i][j] = __builtin_nontemporal_load(mb + (long)(decltype(i)::value * n + decltype(j)::value) * total);
+      const float* at = mb + (long)(decltype(i)::value * n + decltype(j)::value) * total;
+      mi[i][j] = STREAM ? __builtin_nontemporal_load(at) : *at;
     });
   });
   float out[M][M];
@@ -350,6 +358,15 @@ __global__ __launch_bounds__(256) void k_output_f32(const float* __restrict__ Mq
   });
 }
 
+// M passes by the L2s (nontemporal) where it and U do not fit them (32 MB).  Layer us, nontemporal /
+// plain, the same tensors over and over: F(2,3), 16384 tiles, C = K = 16 (32 MB) 29.8 / 28.2, F(6,3), 512
+// tiles, C = K = 128 (32 MB) 37.7 / 30.6; four sets of tensors in turn: 23.5 / 23.1 and 29.1 / 29.1.  Past
+// that it depends on what else the caches hold: F(4,3), 2048 tiles, C = K = 128 (72 MB) 50.6 / 47.8 over and
+// over, 50.3 / 50.7 in turn.
+static bool f32_streams_m(const Geometry& g) {
+  return 4L * (g.m + 2) * (g.m + 2) * g.T * ((long)g.C + g.K) > (32L << 20);
+}
+
 template <int MB, int NB>
 static hipError_t contract_f32_shape(const Geometry& g, const float* U, const float* V, float* Mo,
                                      hipStream_t st) {
@@ -357,8 +374,11 @@ static hipError_t contract_f32_shape(const Geometry& g, const float* U, const fl
   const long units = (long)(g.m + 2) * (g.m + 2) * tblocks;
   const long blocks = (units + 7) / 8 * 8 * kblocks;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  wino_launch((k_contract_f32<MB, NB>), dim3((unsigned)blocks), dim3(256), st, U, V, Mo, g.T, g.C, g.K,
-              tblocks, kblocks, (int)units);
+  const dim3 grid((unsigned)blocks), bs(256);
+  if (f32_streams_m(g))
+    wino_launch((k_contract_f32<MB, NB, true>), grid, bs, st, U, V, Mo, g.T, g.C, g.K, tblocks, kblocks, (int)units);
+  else
+    wino_launch((k_contract_f32<MB, NB, false>), grid, bs, st, U, V, Mo, g.T, g.C, g.K, tblocks, kblocks, (int)units);
   return hipGetLastError();
 }
 
@@ -386,15 +406,20 @@ static hipError_t operands_f32(const Geometry& g, bool leg, const float* x, floa
   return hipGetLastError();
 }
 
+template <int M, bool LEG>
+static hipError_t output_f32_base(const Geometry& g, const float* Mq, float* y, bool relu, hipStream_t st) {
+  const dim3 grid(nblk((long)g.T * g.K)), bs(256);
+  if (f32_streams_m(g))
+    wino_launch((k_output_f32<M, LEG, true>), grid, bs, st, Mq, y, g, divider_of(g.K), relu ? 1 : 0);
+  else
+    wino_launch((k_output_f32<M, LEG, false>), grid, bs, st, Mq, y, g, divider_of(g.K), relu ? 1 : 0);
+  return hipGetLastError();
+}
+
 template <int M>
 static hipError_t output_f32(const Geometry& g, bool leg, const float* Mq, float* y, bool relu,
                              hipStream_t st) {
-  const dim3 grid(nblk((long)g.T * g.K)), bs(256);
-  if (leg)
-    wino_launch((k_output_f32<M, true>), grid, bs, st, Mq, y, g, divider_of(g.K), relu ? 1 : 0);
-  else
-    wino_launch((k_output_f32<M, false>), grid, bs, st, Mq, y, g, divider_of(g.K), relu ? 1 : 0);
-  return hipGetLastError();
+  return leg ? output_f32_base<M, true>(g, Mq, y, relu, st) : output_f32_base<M, false>(g, Mq, y, relu, st);
 }
 
 hipError_t launch_operands_f32(const Geometry& g, bool legendre, const float* x, float* U,

@@ -68,3 +68,18 @@ def test_fp32_path_cfg1_and_relu():
     y = run_fp32(x, w, 2, "legendre", True, relu=True)
     assert np.abs(y - np.maximum(yd, 0)).max() <= 1e-4 * np.abs(yd).max()
     assert (y == 0).any() and (y > 0).any()
+
+
+@pytest.mark.parametrize("m,base,shape", [
+    (4, "canonical", (1, 130, 130, 112, 128)),      # 1089 tiles, U and M 36 MB: past the L2s
+    (6, "legendre", (1, 130, 130, 144, 160)),       # 484 tiles, 36 MB
+])
+def test_fp32_layers_whose_tensors_pass_by_the_caches(m, base, shape):
+    import paper_2004_11077_amd as wn
+    N, H, W, C, K = shape
+    d = wn.ConvDesc(N, H, W, C, K, m=m, bits_in=32)
+    assert 4 * d.n ** 2 * d.tiles * (C + K) > 32 << 20
+    x, w = si.make_real(*shape, seed=m)
+    yd = direct.direct_conv(x, w)
+    y = run_fp32(x, w, m, base, True)
+    assert np.abs(y - yd).max() <= 1e-4 * np.abs(yd).max()

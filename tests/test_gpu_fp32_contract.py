@@ -19,6 +19,7 @@ CASES = [
     (2, 1, 6, 86, 16, 144, 11),      # 129 tiles: one row in the third block
     (6, 3, 23, 37, 80, 48, 11),
     (4, 1, 172, 48, 48, 272, 22),    # 516 tiles: four rows in the last block, a segment of K in the last
+    (4, 1, 172, 48, 192, 272, 22),   # the same with U and M past the L2s
     (4, 1, 129, 125, 16, 48, 21),    # 1056 tiles: 32 rows in the last block, K short of one
     (6, 1, 24, 18, 80, 528, 12),     # 12 tiles, a segment of K in the last block
 ]
