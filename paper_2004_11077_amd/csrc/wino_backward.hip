@@ -6,8 +6,8 @@
 // int8 codes U and V that it contracted, dequantised here by their scales.
 //
 //   dM[p][t][k]  = (A dY_t A^T)[p]                   k_bwd_dm
-//   dU[p][t][c]  = s_v[p] sum_k dM[p][t][k] V[p][k][c]   gemm_body<true>   \ one launch,
-//   dV[p][k][c]  = s_u[p] sum_t dM[p][t][k] U[p][t][c]   gemm_body<false>  / k_bwd_gemm_both
+//   dU[p][t][c]  = s_v[p] sum_k dM[p][t][k] V[p][k][c]   gemm_reg_body or   \ one launch,
+//   dV[p][k][c]  = s_u[p] sum_t dM[p][t][k] U[p][t][c]   gemm_lds_body      / k_bwd_gemm_both
 //   dx[b][h][w][c] = sum over the <= 4 tiles t covering the pixel of
 //                    (B dU_t B^T)[its local position in t]       bwd_dx_body  \ one launch,
 //   dw[k][c]     = G^T dV G                          bwd_dw_body  / k_bwd_dx_dw
@@ -206,30 +206,18 @@ __global__ __launch_bounds__(256, (M <= 4 ? 4 : 2)) void k_bwd_dx_dw(const float
 // fp32 accumulator of v_mfma_f32_32x32x16_bf16 and what is lost is what lies
 // below the 24th bit of A.  Three such MFMAs do the work of eight fp32 ones in
 // 3/16 of their cycles.
-// Work group = 4 waves, WR of them along the rows: (32 WR) x (32 NB 4 / WR) outputs, a wave
-// 32 x (32 NB).  A never enters LDS: a lane loads the 8 reduction indices of its
-// MFMA row straight from memory (two 16-byte loads where the reduction is the fast index, eight
-// dwords with 128 contiguous bytes per 32 lanes where the row is) and cuts them in registers,
-// a stage of 64 ahead of their use.  With WR = 4 no two waves share rows, so nothing is
-// loaded or cut twice.  B is staged in stages of 64 as bf16 in fragment order, two buffers, one
-// barrier per stage: a lane loads four columns of eight reduction rows and stores four
-// whole 16-byte fragments.  Column c of a 32-wide block is MFMA column 8 (c % 4) + c / 4, so that
-// these stores and the fragment reads both touch consecutive LDS addresses.
-// red and cols are multiples of 4 resp. 16 (K and C are multiples of 16), rows and red are
-// otherwise arbitrary: A is zero past the end of the reduction, rows and columns past the last one
-// are computed from the last one and not stored.  Non-finite dM gives NaN.
-// Both contractions of 1024 tiles, C = K = 256 (9.7 GFLOP, 89 MB past the L2s): 48 us with A staged in
-// LDS in chunks of 32 (a quarter of a chunk's time spent waiting for loads that branches
-// closed too early), 44 us here; dU alone 28, dV alone 29.  What bounds it: all 864 groups start
-// at once, so that the waits for dM, 11 us of matrix work and the stores mostly follow one another
-// (without stores 36 us, without MFMAs 33 us).
+// Tiles and numbering are the same in both bodies below: 128 (or 64) rows x 128 (or 64) columns of
+// outputs per work group of 4 waves.  red and cols are multiples of 4 resp. 16 (K and C are multiples of
+// 16), rows and red are otherwise arbitrary.  Non-finite dM gives NaN.  Which body takes which
+// contraction: backward_from_registers.
 // ---------------------------------------------------------------------------
 using v4f = __attribute__((ext_vector_type(4))) float;
+using v2u = __attribute__((ext_vector_type(2))) unsigned;
 using v4u = __attribute__((ext_vector_type(4))) unsigned;
 using v16f = __attribute__((ext_vector_type(16))) float;
 using bf16x8 = __attribute__((ext_vector_type(8))) __bf16;
 
-constexpr int kGR = 32;        // ranges of a split reduction are multiples of this
+constexpr int kGR = 32;        // reduction chunk of gemm_lds_body
 constexpr int kStage = 64;     // reduction indices of B staged at a time
 constexpr int kXcds = 8;
 
@@ -241,12 +229,19 @@ struct GemmArgs {
   int row_blocks, col_blocks, units;
   int blocks;                  // splits * ceil(units / 8) * 8 * col_blocks
   int splits, red_split;       // the reduction is cut into `splits` ranges of red_split (a multiple
-                               // of kGR); range s writes its partial sum to C + s * n*n*rows*cols
+                               // of 32); range s writes its partial sum to C + s * n*n*rows*cols
   long out_stride;             // n*n * rows * cols
 };
 
 // Bytes of LDS for tiles of TC columns: two stages of B.
-constexpr int gemm_lds(int tc) { return 2 * kStage * tc * 2; }
+constexpr int gemm_reg_lds(int tc) { return 2 * kStage * tc * 2; }
+constexpr int kLdH = 40;       // bf16 per staged row of gemm_lds_body: a chunk of 32 and 8 of padding
+// Bytes of LDS of gemm_lds_body: three pieces of A and B as bf16, or (afterwards) one 32 x (32 NB) output
+// block per wave in rows of 32 NB + 4 floats.
+constexpr int gemm_lds_bytes(int mb, int nb) {
+  const int staged = (3 * mb + nb) * 64 * kLdH * 2, out = 4 * 32 * (32 * nb + 4) * 4;
+  return staged > out ? staged : out;
+}
 
 // x = h + m + l up to the bits below the 24th; each piece sits in the upper half of its word
 // (for l the caller drops the lower half).
@@ -261,36 +256,58 @@ __device__ __forceinline__ unsigned pack2(unsigned a, unsigned b) {
   return __builtin_amdgcn_perm(b, a, 0x07060302u);
 }
 
-template <bool ARED, int WR, int NB>
-__device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& scale,
-                                          unsigned block, char* __restrict__ smem) {
-  constexpr int WC = 4 / WR, TR = 32 * WR, TC = 32 * NB * WC;
-  const float* __restrict__ A = ga.A;
-  const int8_t* __restrict__ B = ga.B;
-  float* __restrict__ Cout = ga.C;
-  const int rows = ga.rows, red = ga.red, cols = ga.cols;
-  const int row_blocks = ga.row_blocks, col_blocks = ga.col_blocks, units = ga.units;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+// Which outputs and which part of the reduction a work group takes, and where its results go; p < 0:
+// none (padding blocks).
+// Consecutive blocks are spread round-robin over the 8 XCDs, so block L runs on
+// XCD L % 8.  The column blocks that share one A panel (point p, row block rb: a
+// "unit") are given to consecutive blocks of ONE XCD, whose L2 then serves the
+// panel to all of them; and every XCD takes a contiguous eighth of the units, i.e.
+// all row blocks of four or five points, so that the codes of a point (the B
+// operand of all its row blocks) are fetched by one XCD, not by all eight.
+struct GemmTile {
+  int p, row0, col0, r_begin, r_end;
+  float* C;                    // of point p and, where the reduction is split, of its part
+};
+template <int TR, int TC>
+__device__ __forceinline__ GemmTile gemm_tile(const GemmArgs& ga, unsigned block) {
   const int per_split = ga.blocks / ga.splits;
   const int split = (int)(block / (unsigned)per_split);
   block -= (unsigned)split * (unsigned)per_split;
-  const int r_begin = split * ga.red_split, r_end = min(red, r_begin + ga.red_split);
-  Cout += (long)split * ga.out_stride;
-  // Consecutive blocks are spread round-robin over the 8 XCDs, so block L runs on
-  // XCD L % 8.  The column blocks that share one A panel (point p, row block rb: a
-  // "unit") are given to consecutive blocks of ONE XCD, whose L2 then serves the
-  // panel to all of them; and every XCD takes a contiguous eighth of the units, i.e.
-  // all row blocks of four or five points, so that the codes of a point (the B
-  // operand of all its row blocks) are fetched by one XCD, not by all eight.
   const int xcd = block % kXcds, slot = block / kXcds;
-  const int unit = xcd * ((units + kXcds - 1) / kXcds) + slot / col_blocks;
-  if (unit >= units) return;                     // padding blocks (uniform exit, no barrier yet)
-  const int cb = slot % col_blocks;
-  const int p = unit / row_blocks, rb = unit - p * row_blocks;
-  const int row0 = rb * TR, col0 = cb * TC;
-  const float* Ap = A + (long)p * rows * red;
-  const int8_t* Bp = B + (long)p * red * cols;
+  const int unit = xcd * ((ga.units + kXcds - 1) / kXcds) + slot / ga.col_blocks;
+  if (unit >= ga.units) return {-1, 0, 0, 0, 0, nullptr};
+  const int p = unit / ga.row_blocks, r_begin = split * ga.red_split;
+  return {p, (unit - p * ga.row_blocks) * TR, slot % ga.col_blocks * TC, r_begin,
+          min(ga.red, r_begin + ga.red_split),
+          ga.C + (long)split * ga.out_stride + (long)p * ga.rows * ga.cols};
+}
+// A in registers.  WR waves along the rows: (32 WR) x (32 NB 4 / WR) outputs per work group, a wave
+// 32 x (32 NB).  A never enters LDS: a lane loads the 8 reduction indices of its
+// MFMA row straight from memory (two 16-byte loads where the reduction is the fast index, eight
+// dwords with 128 contiguous bytes per 32 lanes where the row is) and cuts them in registers,
+// a stage of 64 ahead of their use.  With WR = 4 no two waves share rows, so nothing is
+// loaded or cut twice.  B is staged in stages of 64 as bf16 in fragment order, two buffers, one
+// barrier per stage: a lane loads four columns of eight reduction rows and stores four
+// whole 16-byte fragments.  Column c of a 32-wide block is MFMA column 8 (c % 4) + c / 4, so that
+// these stores and the fragment reads both touch consecutive LDS addresses.
+// A is zero past the end of the reduction, rows and columns past the last one are computed from the
+// last one and not stored.
+// Both contractions of 1024 tiles, C = K = 256 (9.7 GFLOP, 89 MB past the L2s): 44 us, 48 with both in
+// gemm_lds_body; dU alone 28, dV alone 29.  What bounds it: 768 of the 864 groups are resident and
+// start at once, so that the waits for dM, 11 us of matrix work and the stores mostly follow one another
+// (without stores 36 us, without MFMAs 33 us).
+template <bool ARED, int WR, int NB>
+__device__ __forceinline__ void gemm_reg_body(const GemmArgs& ga, const MultTable& scale,
+                                              unsigned block, char* __restrict__ smem) {
+  constexpr int WC = 4 / WR, TR = 32 * WR, TC = 32 * NB * WC;
+  const int rows = ga.rows, red = ga.red, cols = ga.cols;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const GemmTile tile = gemm_tile<TR, TC>(ga, block);
+  if (tile.p < 0) return;                        // uniform exit, no barrier yet
+  const int p = tile.p, row0 = tile.row0, col0 = tile.col0, r_begin = tile.r_begin, r_end = tile.r_end;
+  const float* __restrict__ Ap = ga.A + (long)p * rows * red;
+  const int8_t* __restrict__ Bp = ga.B + (long)p * red * cols;
   const int l32 = lane & 31, lk = lane >> 5;
   const int wr = (wave / WC) * 32, wc = (wave % WC) * 32 * NB;
 
@@ -391,7 +408,9 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& s
     }
   }
   const int rt = r_begin + whole * kStage;
-  if (rt < r_end) {                   // the rest, less than a stage: all loads first
+  // The rest, less than a stage: all loads first (F(6,3), 1000 tiles, C = K = 64: 36.4 us for the whole
+  // pass, 37.6 where dM was loaded step by step after the codes were staged).
+  if (rt < r_end) {
     rfor<0, kStage / 16>([&](auto kkc) {
       constexpr int kk = decltype(kkc)::value;
       if constexpr (ARED) {           // r_end = red is a multiple of 16; steps past it are skipped below
@@ -425,7 +444,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& s
   // block b): 32 lanes store the 128 bytes of a row segment.
   const float s = scale.v[p];
   const int ocol = col0 + wc + 4 * (l32 & 7) + (l32 >> 3);
-  float* Cp = Cout + (long)p * rows * cols;
+  float* Cp = tile.C;
   float* out = Cp + (long)(row0 + wr + lk * 4) * cols + ocol;
   if (row0 + TR <= rows && col0 + TC <= cols) {
 #pragma unroll
@@ -442,20 +461,191 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& ga, const MultTable& s
   }
 }
 
+// Both operands staged through LDS.  4 waves (2 x 2) = (64 MB) x (64 NB) outputs, (32 MB) x (32 NB) per
+// wave as MB x NB blocks of 32 x 32, MB and NB 1 or 2.  The reduction runs in chunks of 32 with the
+// reduction index contiguous ([row][red] and [col][red], rows of 80 bytes: 16-byte aligned fragments,
+// and the 32 rows a fragment read touches fall on distinct banks), the next chunk's global loads in
+// flight during the MFMAs.  Where the reduction index is the slow one in memory (B always, A for dV) a
+// lane loads the same columns of two consecutive reduction rows and stores the pairs as dwords.
+// Out-of-range elements are staged as zeros, out-of-range outputs are not stored.
+template <bool ARED, int MB, int NB>
+__device__ __forceinline__ void gemm_lds_body(const GemmArgs& ga, const MultTable& scale,
+                                              unsigned block, char* __restrict__ smem) {
+  constexpr int TR = 64 * MB, TC = 64 * NB;
+  const int rows = ga.rows, red = ga.red, cols = ga.cols;
+  unsigned short* Ah = reinterpret_cast<unsigned short*>(smem);
+  unsigned short* Am = Ah + TR * kLdH;
+  unsigned short* Al = Am + TR * kLdH;
+  unsigned short* Bt = Al + TR * kLdH;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const GemmTile tile = gemm_tile<TR, TC>(ga, block);
+  if (tile.p < 0) return;                        // uniform exit, no barrier yet
+  const int p = tile.p, row0 = tile.row0, col0 = tile.col0, r_begin = tile.r_begin, r_end = tile.r_end;
+  const float* __restrict__ Ap = ga.A + (long)p * rows * red;
+  const int8_t* __restrict__ Bp = ga.B + (long)p * red * cols;
+  // Pair mapping: reduction rows 2 * rp and 2 * rp + 1 of the chunk, columns 4 * (pq + 16 j) .. + 3.
+  const int rp = tid & 15, pq = tid >> 4;
+
+  v4f ra[2 * MB];
+  int rbw[2 * NB];
+  auto fetch = [&](int r0) {
+#pragma unroll
+    for (int it = 0; it < 2 * MB; ++it) {
+      v4f v = {0.f, 0.f, 0.f, 0.f};
+      if constexpr (ARED) {
+        const int idx = tid + it * 256;
+        const int row = idx >> 3, q = idx & 7;
+        if (row0 + row < rows && r0 + 4 * q < r_end)
+          v = *reinterpret_cast<const v4f*>(Ap + (long)(row0 + row) * red + r0 + 4 * q);
+      } else {
+        const int rr = r0 + 2 * rp + (it & 1), quad = pq + 16 * (it >> 1);
+        if (rr < r_end && row0 + 4 * quad < rows)
+          v = *reinterpret_cast<const v4f*>(Ap + (long)rr * rows + row0 + 4 * quad);
+      }
+      ra[it] = v;
+    }
+#pragma unroll
+    for (int it = 0; it < 2 * NB; ++it) {
+      const int rr = r0 + 2 * rp + (it & 1), quad = pq + 16 * (it >> 1);
+      rbw[it] = 0;
+      if (rr < r_end && col0 + 4 * quad < cols)
+        rbw[it] = *reinterpret_cast<const int*>(Bp + (long)rr * cols + col0 + 4 * quad);
+    }
+  };
+  auto stage = [&]() {
+    if constexpr (ARED) {
+#pragma unroll
+      for (int it = 0; it < 2 * MB; ++it) {
+        const int idx = tid + it * 256;
+        const int row = idx >> 3, q = idx & 7;
+        unsigned h[4], m[4], l[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) split3(ra[it][e], h[e], m[e], l[e]);
+        const int at = row * kLdH + 4 * q;
+        *reinterpret_cast<v2u*>(Ah + at) = v2u{pack2(h[0], h[1]), pack2(h[2], h[3])};
+        *reinterpret_cast<v2u*>(Am + at) = v2u{pack2(m[0], m[1]), pack2(m[2], m[3])};
+        *reinterpret_cast<v2u*>(Al + at) = v2u{pack2(l[0], l[1]), pack2(l[2], l[3])};
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < MB; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          unsigned h0, m0, l0, h1, m1, l1;
+          split3(ra[2 * j][e], h0, m0, l0);
+          split3(ra[2 * j + 1][e], h1, m1, l1);
+          const int at = (4 * (pq + 16 * j) + e) * kLdH + 2 * rp;
+          *reinterpret_cast<unsigned*>(Ah + at) = pack2(h0, h1);
+          *reinterpret_cast<unsigned*>(Am + at) = pack2(m0, m1);
+          *reinterpret_cast<unsigned*>(Al + at) = pack2(l0, l1);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        // A code as fp32 has at most 7 significant bits: its upper half is the bf16 value.
+        const float f0 = (float)(int8_t)((rbw[2 * j] >> (8 * e)) & 0xff);
+        const float f1 = (float)(int8_t)((rbw[2 * j + 1] >> (8 * e)) & 0xff);
+        *reinterpret_cast<unsigned*>(Bt + (4 * (pq + 16 * j) + e) * kLdH + 2 * rp) =
+            pack2(__float_as_uint(f0), __float_as_uint(f1));
+      }
+  };
+
+  v16f acc[MB][NB];
+#pragma unroll
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.f;
+  const int wr = (wave >> 1) * 32 * MB, wc = (wave & 1) * 32 * NB;
+  const int l32 = lane & 31, lk = lane >> 5;
+  // MFMA operands: lane -> row (A) or column (B) lane % 32, reduction indices 8 * (lane / 32) .. + 7.
+  const int fa = (wr + l32) * kLdH + 8 * lk, fb = (wc + l32) * kLdH + 8 * lk;
+
+  fetch(r_begin);
+  for (int r0 = r_begin; r0 < r_end; r0 += kGR) {
+    __syncthreads();                  // the previous chunk's fragment reads are done
+    stage();
+    __syncthreads();
+    if (r0 + kGR < r_end) fetch(r0 + kGR);
+#pragma unroll
+    for (int kk = 0; kk < kGR; kk += 16) {
+      bf16x8 bfrag[NB];
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        bfrag[b] = *reinterpret_cast<const bf16x8*>(Bt + fb + b * 32 * kLdH + kk);
+#pragma unroll
+      for (int a = 0; a < MB; ++a) {
+        const int at = fa + a * 32 * kLdH + kk;
+        const bf16x8 al = *reinterpret_cast<const bf16x8*>(Al + at);
+        const bf16x8 am = *reinterpret_cast<const bf16x8*>(Am + at);
+        const bf16x8 ah = *reinterpret_cast<const bf16x8*>(Ah + at);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bfrag[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bfrag[b], acc[a][b], 0, 0, 0);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bfrag[b], acc[a][b], 0, 0, 0);
+      }
+    }
+  }
+
+  // acc[a][b][i] holds output (row = 32 a + (i / 4) * 8 + (lane / 32) * 4 + i % 4,
+  // col = 32 b + lane % 32) of the wave's block.  32 rows at a time go through the
+  // wave's own part of LDS so that they leave in 16-byte stores, a wave writing
+  // full row segments of 128 NB bytes.
+  constexpr int kLdC = 32 * NB + 4;
+  const float s = scale.v[p];
+  float* Cs = reinterpret_cast<float*>(smem) + wave * 32 * kLdC;
+  float* Cp = tile.C;
+#pragma unroll
+  for (int a = 0; a < MB; ++a) {
+    __syncthreads();                  // the fragments (a = 0) resp. the previous rows have been read
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        Cs[((i >> 2) * 8 + lk * 4 + (i & 3)) * kLdC + 32 * b + l32] = acc[a][b][i] * s;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < 4 * NB; ++it) {
+      const int idx = lane + it * 64;
+      const int r = idx / (8 * NB), q = idx % (8 * NB);
+      const int row = row0 + wr + 32 * a + r, col = col0 + wc + 4 * q;
+      if (row < rows && col < cols)   // cols is a multiple of 16: a quad is inside or outside
+        *reinterpret_cast<v4f*>(Cp + (long)row * cols + col) =
+            *reinterpret_cast<const v4f*>(Cs + r * kLdC + 4 * q);
+    }
+  }
+}
+
 // Both contractions in one launch (they only share their input dM): the blocks of
 // the dV contraction, whose reduction over the tiles is the longer one, come first,
 // the blocks of dU fill the compute units as those drain.  Either may have no
-// blocks.  WRV, NBV: waves along the rows and column blocks per wave of dV's tiles (rows = K);
-// dU's tiles are always 128 rows (of tiles) high, NBU column blocks (cols = C) wide.
-template <int WRV, int NBV, int NBU>
-__global__ __launch_bounds__(256, 3) void k_bwd_gemm_both(GemmArgs for_dv, MultTable s_u,
-                                                           GemmArgs for_du, MultTable s_v) {
-  constexpr int tcv = 128 / WRV * NBV, tcu = 32 * NBU;
-  __shared__ __attribute__((aligned(16))) char smem[gemm_lds(tcv > tcu ? tcv : tcu)];
-  if (blockIdx.x < (unsigned)for_dv.blocks)
-    gemm_body<false, WRV, NBV>(for_dv, s_u, blockIdx.x, smem);
-  else
-    gemm_body<true, 4, NBU>(for_du, s_v, blockIdx.x - (unsigned)for_dv.blocks, smem);
+// blocks.  dV's tiles are 64 RB rows (of output channels) high, dU's always 128 rows (of tiles); both
+// 64 CB columns (of input channels) wide.  VREG, UREG: dV, dU by gemm_reg_body.
+template <int RB, int CB, bool VREG, bool UREG>
+__global__ __launch_bounds__(256, CB == 2 ? 3 : 4) void k_bwd_gemm_both(GemmArgs for_dv, MultTable s_u,
+                                                                        GemmArgs for_du, MultTable s_v) {
+  constexpr int reg = gemm_reg_lds(64 * CB), lds = gemm_lds_bytes(2, CB);
+  __shared__ __attribute__((aligned(16))) char smem[(VREG && UREG) || reg > lds ? reg : lds];
+  if (blockIdx.x < (unsigned)for_dv.blocks) {
+    if constexpr (VREG)
+      gemm_reg_body<false, 2 * RB, RB * CB>(for_dv, s_u, blockIdx.x, smem);
+    else
+      gemm_lds_body<false, RB, CB>(for_dv, s_u, blockIdx.x, smem);
+  } else {
+    const unsigned block = blockIdx.x - (unsigned)for_dv.blocks;
+    if constexpr (UREG)
+      gemm_reg_body<true, 4, 2 * CB>(for_du, s_v, block, smem);
+    else
+      gemm_lds_body<true, 2, CB>(for_du, s_v, block, smem);
+  }
 }
 
 inline unsigned blocks256(long items) { return (unsigned)((items + 255) / 256); }
@@ -617,38 +807,16 @@ hipError_t launch_flex_backward_tile_sum(const Geometry& g, const float* dXt, fl
 }
 #undef WINO_BY_M
 
-// Tile shapes of the two contractions: a wave takes two 32-wide blocks along a dimension that is
-// longer than one 64-wide tile, else one.
-static int dv_row_blocks(const Geometry& g) { return g.K > 64 ? 2 : 1; }
-static int col_blocks_per_wave(const Geometry& g) { return g.C > 64 ? 2 : 1; }
-
 // Parts of dV that the kernel reading dV finds and adds up itself.
 int backward_dv_reader_parts(const Geometry& g) {
   const int s = backward_dv_splits(g);
   return s <= kReaderParts ? s : 1;
 }
 
-// The dV contraction has few outputs (n*n x K x C) and a long reduction (all tiles): while it
-// has fewer tiles than the chip has compute units, the reduction is cut into 2^j ranges that
-// run as separate work groups and leave partial sums, added up in ascending order: up to eight
-// by the filter bracket that reads dV, more by k_sum_splits before it.  Ranges hold at least
-// four chunks; at most 32, and at most 64 MB of partial sums.
-int backward_dv_splits(const Geometry& g) {
-  const long n2 = (long)(g.m + 2) * (g.m + 2);
-  const int tr = 64 * dv_row_blocks(g), tc = 64 * col_blocks_per_wave(g);
-  const long tiles = n2 * ((g.K + tr - 1) / tr) * ((g.C + tc - 1) / tc);
-  const long chunks = ((long)g.T + kGR - 1) / kGR;
-  const long bytes = n2 * g.K * g.C * 4;
-  int s = 1;
-  while (tiles * s < 256 && (long)s * 2 * 4 <= chunks && s < 32 && (long)s * 2 * bytes <= (64L << 20))
-    s *= 2;
-  return s;
-}
-
 static bool gemm_args(bool for_weights, const Geometry& g, const float* dM, const int8_t* codes,
                       float* out, GemmArgs* ga) {
   const int n2 = (g.m + 2) * (g.m + 2);
-  const int tr = for_weights ? 64 * dv_row_blocks(g) : 128, tc = 64 * col_blocks_per_wave(g);
+  const int tr = for_weights ? 64 * backward_row_blocks(g) : 128, tc = 64 * backward_col_blocks(g);
   ga->A = dM;
   ga->B = codes;
   ga->C = out;
@@ -668,22 +836,26 @@ static bool gemm_args(bool for_weights, const Geometry& g, const float* dM, cons
   return blocks <= (1L << 30);
 }
 
+template <int RB, int CB>
+static void gemm_pair(const Geometry& g, dim3 grid, const GemmArgs& for_dv, const MultTable& s_u,
+                      const GemmArgs& for_du, const MultTable& s_v, hipStream_t st) {
+  const dim3 wg(256);
+  const FromRegisters reg = backward_from_registers(g);
+  if (reg.du)
+    wino_launch((k_bwd_gemm_both<RB, CB, true, true>), grid, wg, st, for_dv, s_u, for_du, s_v);
+  else if (reg.dv)
+    wino_launch((k_bwd_gemm_both<RB, CB, true, false>), grid, wg, st, for_dv, s_u, for_du, s_v);
+  else
+    wino_launch((k_bwd_gemm_both<RB, CB, false, false>), grid, wg, st, for_dv, s_u, for_du, s_v);
+}
+
 static hipError_t launch_gemm_pair(const Geometry& g, const GemmArgs& for_dv, const MultTable& s_u,
                                    const GemmArgs& for_du, const MultTable& s_v, hipStream_t st) {
   const unsigned blocks = (unsigned)for_dv.blocks + (unsigned)for_du.blocks;
   if (blocks == 0) return hipSuccess;
-  const dim3 grid(blocks), wg(256);
-  if (col_blocks_per_wave(g) == 2) {
-    if (dv_row_blocks(g) == 2)
-      wino_launch((k_bwd_gemm_both<4, 4, 4>), grid, wg, st, for_dv, s_u, for_du, s_v);
-    else
-      wino_launch((k_bwd_gemm_both<2, 2, 4>), grid, wg, st, for_dv, s_u, for_du, s_v);
-  } else {
-    if (dv_row_blocks(g) == 2)
-      wino_launch((k_bwd_gemm_both<4, 2, 2>), grid, wg, st, for_dv, s_u, for_du, s_v);
-    else
-      wino_launch((k_bwd_gemm_both<2, 1, 2>), grid, wg, st, for_dv, s_u, for_du, s_v);
-  }
+  const int rb = backward_row_blocks(g), cb = backward_col_blocks(g);
+  (rb == 2 ? cb == 2 ? gemm_pair<2, 2> : gemm_pair<2, 1> : cb == 2 ? gemm_pair<1, 2> : gemm_pair<1, 1>)(
+      g, dim3(blocks), for_dv, s_u, for_du, s_v, st);
   return hipGetLastError();
 }
 

@@ -476,11 +476,57 @@ inline bool fused_takes_raw_filters(const Geometry& g) {
 // Backward pass (wino_backward.hip), fp32.  which: 0 dY -> dM, 1 dU -> dx.
 hipError_t launch_backward_transform(int which, const Geometry& g, const float* in, float* out,
                                      hipStream_t st);
+// Tiles of the two contractions: 64 wide along a dimension of up to 64 channels, else 128 (two 64-wide
+// blocks); along the tiles always 128.
+inline int backward_row_blocks(const Geometry& g) { return g.K > 64 ? 2 : 1; }
+inline int backward_col_blocks(const Geometry& g) { return g.C > 64 ? 2 : 1; }
 // Number of partial sums (a power of two, 1 ... 32) the dV contraction leaves for this
 // shape; the dV buffer holds that many [n*n][K][C] tensors.  Up to eight are added, into the
 // first one, by whichever kernel reads dV next (backward_dv_reader_parts says how many it
 // will find); more are added by launch_backward_sum_splits, which launches nothing otherwise.
-int backward_dv_splits(const Geometry& g);
+// The dV contraction has few outputs (n*n x K x C) and a long reduction (all tiles): while it
+// has fewer tiles than the chip has compute units, the reduction is cut into 2^j ranges that
+// run as separate work groups.  Ranges hold at least four chunks of 32; at most 32, and at most
+// 64 MB of partial sums.
+inline int backward_dv_splits(const Geometry& g) {
+  const long n2 = (long)(g.m + 2) * (g.m + 2);
+  const int tr = 64 * backward_row_blocks(g), tc = 64 * backward_col_blocks(g);
+  const long tiles = n2 * ((g.K + tr - 1) / tr) * ((g.C + tc - 1) / tc);
+  const long chunks = ((long)g.T + 31) / 32;
+  const long bytes = n2 * g.K * g.C * 4;
+  int s = 1;
+  while (tiles * s < 256 && (long)s * 2 * 4 <= chunks && s < 32 && (long)s * 2 * bytes <= (64L << 20))
+    s *= 2;
+  return s;
+}
+// Which of the two contractions read dM straight into registers (gemm_reg_body), the other way being
+// through LDS (gemm_lds_body).  Registers keep a whole stage of 64 in flight per wave, which wins while a
+// compute unit has one or two work groups to hide its waits with, and on long reductions; LDS
+// coalesces the loads and shares them among waves, which wins once the chip is full and the reduction is
+// short.  Whole backward pass in us, both from registers / only dV / neither:
+//   F(4,3)    100 tiles, C = K = 128 (80 work groups)     21.2 /  21.8 /  22.4
+//            1000 tiles, C = 112, K = 96 (608)            38.7 /  37.1 /  35.5
+//            1000 tiles, C = K = 256 (864)                68.5 /  72.2 /  69.6
+//             512 tiles, C = K = 512 (1152)               99.4 / 100.2 / 107.9
+//            2048 tiles, C = K = 256 (1728)              120.1 / 123.1 / 134.0
+//           16384 tiles, C = K = 64 (5248)               225.2 / 208.7 / 230.6
+// Over 574 shapes (F(2,3), F(4,3), F(6,3), 16 to 16384 tiles, 16 to 512 channels) the choice takes 95.2 % of the
+// time of neither, 98.4 % of that of both and 100.4 % of that of the best of the three.  The narrowest
+// layers, one sixteenth of a tile of outputs: F(2,3), 512 tiles, C = K = 16: 14.9 / 15.1 / 14.0; F(4,3), 16384
+// tiles: 80.2 / 79.9 / 75.5, but F(2,3), 16384 tiles: 45.0 / 44.9 / 47.2.
+struct FromRegisters {
+  bool dv, du;
+};
+inline FromRegisters backward_from_registers(const Geometry& g) {
+  const long n2 = (long)(g.m + 2) * (g.m + 2);
+  const int tr = 64 * backward_row_blocks(g), tc = 64 * backward_col_blocks(g), splits = backward_dv_splits(g);
+  const long cols = (g.C + tc - 1) / tc;
+  const long groups = cols * ((n2 * ((g.K + tr - 1) / tr) + 7) / 8 * 8 * splits + (n2 * ((g.T + 127) / 128) + 7) / 8 * 8);
+  const long range = ((g.T + 31) / 32 + splits - 1) / splits * 32;    // of dV's reduction per work group
+  if (g.C + g.K <= 32 && (g.m == 4 || range <= 512)) return {false, false};
+  const bool few = groups <= 384;
+  return {few || g.K >= 256 || range >= 256, few || (g.K >= 256 && groups <= 5L * g.K)};
+}
 int backward_dv_reader_parts(const Geometry& g);
 hipError_t launch_backward_sum_splits(const Geometry& g, float* dV, hipStream_t st);
 // dV -> dw alone, and dU -> dx with dV -> dw in one launch (both non-empty).
