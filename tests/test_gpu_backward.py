@@ -158,7 +158,8 @@ def test_backward_random_shapes(m, shape, per_point, seed):
     check(reference(dy, Uq, Vq, shape, m, scales), got, 1e-5)
 
 
-ONE_TERM_CASES = [(4, (3, 12, 12, 80, 48)), (4, (5, 9, 9, 144, 272)), (2, (40, 4, 4, 16, 144))]
+ONE_TERM_CASES = [(4, (3, 12, 12, 80, 48)), (4, (5, 9, 9, 144, 272)), (2, (40, 4, 4, 16, 144)),
+                  (4, (997, 4, 4, 112, 96)), (4, (2051, 4, 4, 64, 80))]   # dM through LDS: both, dU only
 
 
 @pytest.mark.parametrize("m,shape", ONE_TERM_CASES)
