@@ -399,6 +399,10 @@ bool auto_takes_conout(const wino_conv_desc_t* d, const Plan& p) {
 //                     2048 tiles (1024 groups) 15.0 / 18.5 against 15.5 / 16.4
 //   C = 32,  K = 512:  256 tiles (512 groups)   9.8 / 14.6 against 14.1 / 18.0
 //                      512 tiles (1024 groups) 14.5 / 18.9 against 14.5 / 18.5
+// With a 9-bit M (blocks of 32 channels): C = 64, K = 128, 512 tiles (512 groups) 8.7 / 13.4 against 13.8 /
+// 14.3; C = 16, K = 512, 128 tiles (512) 8.6 / 13.6 against 14.0 / 17.5.  F(2,3): C = 64, K = 256, 512
+// tiles (512) 5.7 / 9.6 against 9.7 / 10.0, 9-bit 5.7 / 9.5 at 256 tiles against 9.7 / 10.0.  Raw filters
+// gain little where their transform is long: C = 64, K = 512, 256 tiles 15.4 against 15.3.
 constexpr long kFusedMaxGroups = 512;
 bool auto_takes_fused(const Plan& p) {
   const int kb = fused_channels(p.m_bits);

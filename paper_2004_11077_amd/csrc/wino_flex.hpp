@@ -71,7 +71,9 @@ __device__ __forceinline__ void flex_input(const int (&x)[T.cols][T.cols], const
 // instructions of an input item's 1200, 8 us at full issue rate for 262144 items and their filters).
 // 1024 tiles, C = K = 256: operand transforms 21.0 us with a byte load per pixel and a byte store per
 // code, 14.8 us with 16-byte accesses through LDS; output transform 11.3 -> 9.8 us.  The dealing to
-// XCDs takes the contraction between them from 9.5 to 8.4 us.
+// XCDs takes the contraction between them from 9.5 to 8.4 us.  That is for the same tensors call after
+// call (layer 36.4 -> 30.5 us), where part of what the dealing saves are lines that the call before left in
+// the L2s; the first call on new tensors takes 55 to 58 us against 58 to 59.
 template <int M, bool LEG>
 __device__ __forceinline__ void flex_weight_body(const int8_t* __restrict__ w, int8_t* __restrict__ V,
                                                  const Geometry& g, const FlexMats& fm,

@@ -105,11 +105,13 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 // range: work groups in which a result is not finite sum again in plain fp32.
 //
 // Work group = 4 waves (2 x 2) = (64 MB) tiles x (64 NB) output channels, a wave MB x NB blocks of
-// 32 x 32.  The channels run in chunks of 32 staged through LDS ([row][channel] per piece), the next chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
-// What bounds it: at C = 128 the bytes of U and M.  2048 tiles, C = K = 128 (78 MB, 2.4 GFLOP): 159 us
-// with one lane per output and both panels in LDS as fp32, 24.6 us here (3.2 TB/s).  With 64-row or
-// 64-column blocks 25.4 us; with padded rows (61 KB of LDS, two groups per compute unit instead of
-// three, so that the 576 groups run in two rounds) 28.8 us.
+// 32 x 32 (f32_contract_blocks).  The channels run in chunks of 32 staged through LDS ([row][channel] per
+// piece), the next chunk's global loads in flight during the 12 MB NB MFMAs of a wave.
+// What bounds it: at C = 128 the bytes of U and M.  2048 tiles, C = K = 128 (78 MB, 2.4 GFLOP): 160 us
+// with one lane per output and both panels in LDS as fp32, 23.3 us here (3.3 TB/s), both repeated on
+// their own; 28.9 us between the other kernels of a layer.  Before the scale, 23.9 us; with 64-row or 64-column
+// blocks 25.4; with padded rows (61 KB of LDS, two groups per compute unit instead of three, so that
+// the 576 groups run in two rounds) 28.8 us.
 // ---------------------------------------------------------------------------
 using v2f = __attribute__((ext_vector_type(2))) float;
 using v4f = __attribute__((ext_vector_type(4))) float;

@@ -214,7 +214,6 @@ __device__ __forceinline__ void contract_body(const int8_t* __restrict__ U,
     __syncthreads();
     constexpr int kORowB = kKT * 2 + 16;
     static_assert(kTT * kORowB <= kSm);
-    static_assert(kTT * (kKT + 4) <= kSm);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
