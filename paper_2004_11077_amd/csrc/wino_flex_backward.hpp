@@ -1,7 +1,7 @@
 // Backward pass of the flex layer (Section 4.2: G_P, B_P, A_P are trained, P and
 // P^{-1} stay fixed), fp32, casts passing their gradient on unchanged.
 // For a bracket R = T S T^T with a trained matrix T:
-//     dT = sum over items of  A S^T + B S  with  A = dR T, B = dR^T T,      dS = T^T A,
+//     dT = sum over items of  dR (T S^T) + dR^T (T S),      dS = T^T (dR T),
 // and through a fixed bracket S1 = L S L^T:  dS = L^T dS1 L.  The inputs S of the
 // trained brackets are recomputed from the forward pass's integer tensors with the
 // forward pass's exact arithmetic (X1 from x, M1 from M) and dequantised.
@@ -14,37 +14,18 @@
 // The two contraction gradients between them are those of the static layer.
 // Bound by vector arithmetic (about 2400 instructions per (tile, channel) item of the input bracket) and
 // by the bytes of dM, dU and dX.  2048 tiles, C = K = 128, F(4,3): input and filter brackets 38.1 us with
-// sums over lanes by LDS permutes, 64-bit divisions and T S, T S^T formed per item, now 31.6; output
-// bracket 23.7, now 18.5; training step 278, now 267.
+// sums over lanes by LDS permutes, 64-bit divisions and all of T S, T S^T and dT held at once (128
+// registers, now 95), now 27.5; output bracket 23.7, now 19.8; training step 278, now 264.
 #pragma once
 #include "wino_flex.hpp"
 #include "wino_real_brackets.hpp"
 
 namespace wino {
 
-// With a run-time T (ROWS x COLS, row-major): A = dR T and this lane's share of dT = A S^T + B S.  dS
-// = T^T A follows from A (flex_input_grad): a sixth fewer multiply-adds than T S, T S^T and T^T dR T
-// take.  In this order no more than S, one of dR and A, and dT live at a time.
+// With a run-time T (ROWS x COLS, row-major): A = dR T, from which dS = T^T A follows (flex_input_grad).
 template <int ROWS, int COLS>
-__device__ __forceinline__ void flex_matrix_grad(const float* __restrict__ Tm,
-                                                 const float (&S)[COLS][COLS],
-                                                 const float (&dR)[ROWS][ROWS],
-                                                 float (&dT)[ROWS * COLS], float (&A)[ROWS][COLS]) {
-  static_for<0, ROWS>([&](auto i) {
-    float B[COLS];                               // row i of B
-    static_for<0, COLS>([&](auto k) {
-      float acc = 0.f;
-      static_for<0, ROWS>([&](auto j) {
-        acc = __builtin_fmaf(dR[j][i], Tm[decltype(j)::value * COLS + decltype(k)::value], acc);
-      });
-      B[k] = acc;
-    });
-    static_for<0, COLS>([&](auto b) {
-      float acc = 0.f;
-      static_for<0, COLS>([&](auto k) { acc = __builtin_fmaf(B[k], S[k][b], acc); });
-      dT[decltype(i)::value * COLS + decltype(b)::value] = acc;
-    });
-  });
+__device__ __forceinline__ void flex_right(const float* __restrict__ Tm, const float (&dR)[ROWS][ROWS],
+                                           float (&A)[ROWS][COLS]) {
   static_for<0, ROWS>([&](auto i) {
     static_for<0, COLS>([&](auto k) {
       float acc = 0.f;
@@ -53,10 +34,29 @@ __device__ __forceinline__ void flex_matrix_grad(const float* __restrict__ Tm,
       });
       A[i][k] = acc;
     });
-    static_for<0, COLS>([&](auto b) {
-      float acc = dT[decltype(i)::value * COLS + decltype(b)::value];
-      static_for<0, COLS>([&](auto k) { acc = __builtin_fmaf(A[i][k], S[b][k], acc); });
-      dT[decltype(i)::value * COLS + decltype(b)::value] = acc;
+  });
+}
+
+// The same for G_P (COLS = 3, S the taps of a filter) as A S^T + (dR^T T) S: its error per item is 0.9 times that
+// of the other order.
+template <int ROWS>
+__device__ __forceinline__ void flex_filter_grad(const float* __restrict__ Tm, const float (&S)[3][3],
+                                                 const float (&dR)[ROWS][ROWS],
+                                                 const float (&A)[ROWS][3], float (&dT)[ROWS * 3]) {
+  static_for<0, ROWS>([&](auto i) {
+    float B[3];                                  // row i of dR^T T
+    static_for<0, 3>([&](auto k) {
+      float acc = 0.f;
+      static_for<0, ROWS>([&](auto j) {
+        acc = __builtin_fmaf(dR[j][i], Tm[decltype(j)::value * 3 + decltype(k)::value], acc);
+      });
+      B[k] = acc;
+    });
+    static_for<0, 3>([&](auto b) {
+      float acc = 0.f;
+      static_for<0, 3>([&](auto k) { acc = __builtin_fmaf(B[k], S[k][b], acc); });
+      static_for<0, 3>([&](auto k) { acc = __builtin_fmaf(A[i][k], S[b][k], acc); });
+      dT[decltype(i)::value * 3 + decltype(b)::value] = acc;
     });
   });
 }
@@ -96,34 +96,70 @@ struct WaveSums {
   static constexpr int regs = (CNT + 3) / 4;
   float of[4][4 * regs];
 };
-template <int CNT>
-__device__ __forceinline__ void wave_sums(const float (&v)[CNT], WaveSums<CNT>& sums) {
+// Values 4 Q .. 4 Q + 3 (those that exist).
+template <int Q, int CNT>
+__device__ __forceinline__ void wave_sum_of_four(const float (&v)[CNT], WaveSums<CNT>& sums) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // register q: value 4 q in row 0, 4 q + 2 in row 1, 4 q + 1 in row 2, 4 q + 3 in row 3
+  // value 4 Q in row 0, 4 Q + 2 in row 1, 4 Q + 1 in row 2, 4 Q + 3 in row 3
   const int mine = ((lane >> 4) & 1) * 2 + (lane >> 5);
-  static_for<0, WaveSums<CNT>::regs>([&](auto q) {
-    constexpr int Q = 4 * decltype(q)::value;
-    const float z = 0.f;
-    float x = add_rows(add_halves(v[Q], Q + 1 < CNT ? v[Q + 1 < CNT ? Q + 1 : Q] : z),
-                       add_halves(Q + 2 < CNT ? v[Q + 2 < CNT ? Q + 2 : Q] : z,
-                                  Q + 3 < CNT ? v[Q + 3 < CNT ? Q + 3 : Q] : z));
+  auto value = [&](auto i) { return 4 * Q + decltype(i)::value < CNT ? v[min(4 * Q + decltype(i)::value, CNT - 1)] : 0.f; };
+  using std::integral_constant;
+  float x = add_rows(add_halves(value(integral_constant<int, 0>{}), value(integral_constant<int, 1>{})),
+                     add_halves(value(integral_constant<int, 2>{}), value(integral_constant<int, 3>{})));
 #define WINO_DPP_ADD(CTRL) \
   x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false))
-    WINO_DPP_ADD(0x128);   // row_ror:8, 4, 2, 1: every lane of a row has the row's sum
-    WINO_DPP_ADD(0x124);
-    WINO_DPP_ADD(0x122);
-    WINO_DPP_ADD(0x121);
+  WINO_DPP_ADD(0x128);   // row_ror:8, 4, 2, 1: every lane of a row has the row's sum
+  WINO_DPP_ADD(0x124);
+  WINO_DPP_ADD(0x122);
+  WINO_DPP_ADD(0x121);
 #undef WINO_DPP_ADD
-    if ((lane & 15) == 0) sums.of[wave][Q + mine] = x;
-  });
+  if ((lane & 15) == 0) sums.of[wave][4 * Q + mine] = x;
 }
 template <int CNT>
+__device__ __forceinline__ void wave_sums(const float (&v)[CNT], WaveSums<CNT>& sums) {
+  static_for<0, WaveSums<CNT>::regs>([&](auto q) { wave_sum_of_four<decltype(q)::value>(v, sums); });
+}
+// COLUMN > 0: the values are a matrix column by column, COLUMN values each, stored row by row.
+template <int COLUMN = 0, int CNT>
 __device__ __forceinline__ void store_sums(const WaveSums<CNT>& sums, float* __restrict__ row) {
   __syncthreads();
   if (threadIdx.x < CNT) {
     const int i = threadIdx.x;
-    row[i] = ((sums.of[0][i] + sums.of[1][i]) + sums.of[2][i]) + sums.of[3][i];
+    const float sum = ((sums.of[0][i] + sums.of[1][i]) + sums.of[2][i]) + sums.of[3][i];
+    row[COLUMN ? i % COLUMN * (CNT / COLUMN) + i / COLUMN : i] = sum;
   }
+}
+
+// This lane's share of dT = dR (T S^T) + dR^T (T S), a column at a time, summed over the wave as soon as four
+// values are there (values column by column: store_sums<CNT, ROWS>).  The products with S come first: T S is
+// where the bracket's large terms cancel, and S holds codes.  dT = A S^T + (dR^T T) S takes a sixth
+// fewer multiply-adds with dS = T^T A, but cancels after the rounding of A: its error per item was 1.1 to
+// 1.4 times as large for A_P and 1.1 to 1.7 times for B_P.
+template <int ROWS, int COLS>
+__device__ __forceinline__ void flex_matrix_grad(const float* __restrict__ Tm,
+                                                 const float (&S)[COLS][COLS],
+                                                 const float (&dR)[ROWS][ROWS],
+                                                 WaveSums<ROWS * COLS>& sums) {
+  static_assert(ROWS * COLS % 4 == 0);
+  float dT[ROWS * COLS];
+  static_for<0, COLS>([&](auto b) {
+    constexpr int V = decltype(b)::value * ROWS;
+    static_for<0, ROWS>([&](auto i) { dT[V + decltype(i)::value] = 0.f; });
+    static_for<0, ROWS>([&](auto j) {
+      float ts = 0.f, tst = 0.f;                 // entries (j, b) of T S and T S^T
+      static_for<0, COLS>([&](auto a) {
+        const float c = Tm[decltype(j)::value * COLS + decltype(a)::value];
+        ts = __builtin_fmaf(c, S[a][b], ts);
+        tst = __builtin_fmaf(c, S[b][a], tst);
+      });
+      static_for<0, ROWS>([&](auto i) {
+        float& acc = dT[V + decltype(i)::value];
+        acc = __builtin_fmaf(dR[i][j], tst, acc);
+        acc = __builtin_fmaf(dR[j][i], ts, acc);
+      });
+    });
+    static_for<V / 4, (V + ROWS) / 4>([&](auto q) { wave_sum_of_four<decltype(q)::value>(dT, sums); });
+  });
 }
 
 constexpr int kPartialStride = 64;   // floats per work group in the partial-sum arrays
@@ -168,12 +204,9 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
     });
   });
   __shared__ WaveSums<M * n> s_sums;
+  flex_matrix_grad<M, n>(fm.APT, S, dR, s_sums);
   float A[M][n];
-  {
-    float dT[M * n];
-    flex_matrix_grad<M, n>(fm.APT, S, dR, dT, A);
-    wave_sums(dT, s_sums);
-  }
+  flex_right<M, n>(fm.APT, dR, A);
   float dS[n][n];
   flex_input_grad<M, n>(fm.APT, A, dS);
   if (active) {
@@ -193,7 +226,7 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
       });
     }
   }
-  store_sums(s_sums, part + (long)blockIdx.x * kPartialStride);
+  store_sums<M>(s_sums, part + (long)blockIdx.x * kPartialStride);
 }
 
 // dU, x -> per-tile dX [a*n+b][t][c] and the partial sums of dBPT (n x n).
@@ -238,12 +271,9 @@ __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
     });
   });
   __shared__ WaveSums<n * n> s_sums;
+  flex_matrix_grad<n, n>(fm.BPT, S, dR, s_sums);
   float A[n][n];
-  {
-    float dT[n * n];
-    flex_matrix_grad<n, n>(fm.BPT, S, dR, dT, A);
-    wave_sums(dT, s_sums);
-  }
+  flex_right<n, n>(fm.BPT, dR, A);
   float dS[n][n];
   flex_input_grad<n, n>(fm.BPT, A, dS);
   if (active) {
@@ -263,7 +293,7 @@ __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
       });
     }
   }
-  store_sums(s_sums, part + (long)block * kPartialStride);
+  store_sums<n>(s_sums, part + (long)block * kPartialStride);
 }
 
 // dV, w -> dw [k][c][3][3] and the partial sums of dGP (n x 3).
@@ -295,9 +325,10 @@ __device__ __forceinline__ void fbwd_weight_body(const int8_t* __restrict__ w,
   }
   __shared__ WaveSums<n * 3> s_sums;
   float A[n][3];
+  flex_right<n, 3>(fm.GP, dR, A);
   {
     float dT[n * 3];
-    flex_matrix_grad<n, 3>(fm.GP, S, dR, dT, A);
+    flex_filter_grad<n>(fm.GP, S, dR, A, dT);
     wave_sums(dT, s_sums);
   }
   float dS[3][3];

@@ -171,3 +171,34 @@ def test_flex_backward_random_shapes(m, base, shape, bits_hadamard):
     dy = np.random.default_rng(11 + K + W).standard_normal((N, H, W, K)).astype(np.float32)
     got = run_gpu(dy, xq, wq, fwd, sc, fm, m, base, bits_hadamard)
     check(reference(dy, xq, wq, fwd, sc, fm, m, base), got)
+
+
+@pytest.mark.parametrize("m", [2, 4, 6])
+def test_matrix_gradients_keep_what_cancels_in_a_bracket(m):
+    """Where every row of T S and T S^T is zero, so is the gradient of T, exactly: the products with
+    the codes are formed before the gradients, whose products with T would be rounded, come in.
+    Constant codes and matrices of small integers whose rows sum to zero; gradients only where the
+    input tile is free of padding."""
+    from types import SimpleNamespace
+    n, N, C, K = m + 2, 2, 16, 32
+    H = W = 3 * m
+    rng = np.random.default_rng(m)
+
+    def rows_of_sum_zero(r, c):
+        a = rng.integers(-4, 5, (r, c))
+        a[:, -1] -= a.sum(axis=1)
+        return a.astype(np.float32)
+
+    fm = SimpleNamespace(GP=rng.standard_normal((n, 3)).astype(np.float32), BPT=rows_of_sum_zero(n, n),
+                         APT=rows_of_sum_zero(m, n))
+    T = N * 9
+    fwd = {"U": rng.integers(-127, 128, (n * n, T, C)), "V": rng.integers(-127, 128, (n * n, K, C)),
+           "M": np.full((n * n, T, K), 113)}
+    dy = np.zeros((N, H, W, K), np.float32)
+    dy[:, m:2 * m, m:2 * m] = rng.standard_normal((N, m, m, K))
+    sc = {"s_x": 0.25, "s_u": 0.5, "s_w": 0.125, "s_v": 0.0625, "s_m": 2.0}
+    xq = np.full((N, H, W, C), 77)
+    wq = rng.integers(-127, 128, (K, C, 3, 3))
+    got = run_gpu(dy, xq, wq, fwd, sc, fm, m, "canonical", 8)
+    assert np.abs(got["dM"]).max() > 1 and np.abs(got["dU"]).max() > 1
+    assert (got["dAPT"] == 0).all() and (got["dBPT"] == 0).all()
