@@ -101,7 +101,8 @@ __global__ __launch_bounds__(256) void k_operands_f32(const float* __restrict__ 
 // and m below 2^-118, and results of such operands had a relative error of up to 3e-3.  Six of the nine
 // piece products are accumulated in fp32 (exact products, smallest first), and the sums are scaled by
 // 2^-48; the three that are left out (ml, lm, ll) are together at most 2^-24 of |x y|, what rounding
-// one fp32 product may lose.  Infinities, NaNs, operands from 2^103 and sums from 2^80 on leave that
+// one fp32 product may lose.  Error against 64 bits (2-norm), C = 16, 128, 512: 3.3e-8, 1.6e-7, 3.4e-7; plain
+// fp32 sums 7.4e-8, 2.0e-7, 4.1e-7.  Infinities, NaNs, operands from 2^103 and sums from 2^80 on leave that
 // range: work groups in which a result is not finite sum again in plain fp32.
 //
 // Work group = 4 waves (2 x 2) = (64 MB) tiles x (64 NB) output channels, a wave MB x NB blocks of
