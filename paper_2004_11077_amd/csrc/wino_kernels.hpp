@@ -167,12 +167,15 @@ inline Geometry with_dealt_units(Geometry g, long per_unit, long units) {
 }
 // Geometry for the input transform's launch (whole: the block-uniform row-order kernel, one
 // work group per tile and 256 channels).
-inline Geometry with_image_groups(const Geometry& g, bool whole) {
+// per: 256-item blocks per work group (1 or 2; an image of an odd number of blocks is then dealt
+// together with the next one).
+inline Geometry with_image_groups(const Geometry& g, bool whole, int per = 1) {
   const long nch = (g.C + 63) >> 6;
-  if (g.frag) return with_dealt_units(g, 8 * nch, g.T / 32);
+  if (g.frag) return with_dealt_units(g, 8 * nch / per, g.T / 32);
   if (!whole) return with_dealt_units(g, 0, 0);
-  if (const long chunk = xcd_chunk_tiles(g)) return with_dealt_units(g, chunk * (g.C / 256), 8);
-  return with_dealt_units(g, (long)g.TH * g.TW * (g.C / 256), g.N);
+  if (const long chunk = xcd_chunk_tiles(g)) return with_dealt_units(g, chunk * (g.C / 256) / per, 8);
+  const long blocks = (long)g.TH * g.TW * (g.C / 256);
+  return blocks % per ? with_dealt_units(g, blocks, g.N / per) : with_dealt_units(g, blocks / per, g.N);
 }
 // Geometry for the launch of the block-uniform output transform (one work group per tile and
 // 256 output channels).

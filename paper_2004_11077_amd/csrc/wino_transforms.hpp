@@ -8,6 +8,7 @@
 // numerators num = N x N^T (N = integer form of the stage matrix).
 #pragma once
 #include "wino_kernels.hpp"
+#include "wino_matrix_brackets.hpp"
 #include "wino_tables.hpp"
 
 namespace wino {
@@ -681,13 +682,131 @@ __device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t
   }
 }
 
-template <int M, bool LEG, bool WHOLE, int BASE = 1>
+// F(4,3) in the Legendre base: on the matrix pipe (MX), where an image's rows and offsets fit the
+// sixteen and thirty bits that input_pairs gives them.
+template <bool MX>
+using InputMults = std::conditional_t<MX, mb::PairMults, StageMults>;
+inline bool input_on_matrix_pipe(const Geometry& g, int brackets) {
+  return g.m == 4 && brackets == 1 && g.H < 65535 && g.W < 65535 && (long)g.W * g.C < 65536 &&
+         (long)g.H * g.W * g.C < (1L << 30);
+}
+
+// F(4,3) in the Legendre base: a wave takes 128 (tile, channel) items, eight channels of a tile per lane,
+// a work group two of the 256-item blocks of input_items: pairs of blocks slot, slot + step, ... < pairs.
+// The matrix operands are read once.  Lanes past the last item repeat it (and store the same codes to
+// the same place): with a condition around the stores the wait for the next pixels would wait for them too.
+template <bool WHOLE>
+__device__ __forceinline__ void input_pairs(const int8_t* __restrict__ x, int8_t* __restrict__ U,
+                                            const Geometry& g, const mb::PairMults& mu, unsigned slot,
+                                            unsigned pairs, unsigned step) {
+  using TB = Tab<4>;
+  using P = mb::Pair<TB::PinvT, TB::BPT, 1>;
+  typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+  constexpr int m = 4;
+  const int lane = threadIdx.x & 63, col = lane & 15;
+  int grp = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long total = (long)g.T * g.C;
+  const int nch = (g.C + 63) >> 6;
+  const long pstride = !WHOLE && g.frag ? ((long)(g.T + 15) >> 4) * nch * 1024 : total;
+  const long image = (long)g.H * g.W * g.C;
+  typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+  // Row and column of the lane's nine pixels in the tile, and the bytes between rows and pixels.  Offsets
+  // inside an image: one dot product each, compared with the image's edges two coordinates at a time,
+  // and left to the buffer's bounds check where they are outside (which yields zero).
+  const v2us pitch = {(unsigned short)(g.W * g.C), (unsigned short)g.C};
+  const v2us last = {(unsigned short)(g.H - 1), (unsigned short)(g.W - 1)};
+  uint32_t rc[5] = {};                             // row, column of two pixels each, a byte apiece
+  static_for<0, 9>([&](auto s) {
+    constexpr int S = decltype(s)::value;
+    rc[S / 2] |= (uint32_t)(mb::pixel_row<S>(grp) | mb::pixel_col<S>(grp) << 8) << (16 * (S & 1));
+  });
+  struct Item {
+    v2u v[9];
+    long at;                                       // byte of U at point 0
+  };
+  auto fetch = [&](unsigned pair, Item& f) {
+    const unsigned block = 2 * pair + (wave >> 1);
+    int t, c;
+    if (!WHOLE && g.frag) {
+      const int quad = (int)fast_div(block, g.mul_ch, g.sh_ch);      // uniform
+      // lanes: eight bytes, four tiles, two 16-channel slices
+      t = quad * 4 + ((col >> 1) & 3);
+      c = ((int)block - quad * nch) * 64 + (wave & 1) * 32 + (col >> 3) * 16 + (col & 1) * 8;
+      t = min(t, g.T - 1), c = min(c, g.C - 8);
+      f.at = ((long)(t >> 4) * nch + (c >> 6)) * 1024 + ((c & 63) >> 4) * 256 + (t & 15) * 16 + (c & 15);
+    } else if constexpr (WHOLE) {
+      t = (int)fast_div(block, g.mul_cg, g.sh_cg);                   // uniform: C / 256 blocks per tile
+      c = (int)(block - (unsigned)t * (unsigned)(g.C >> 8)) * 256 + (wave & 1) * 128 + col * 8;
+      t = min(t, g.T - 1);                                           // an odd number of blocks
+      f.at = (long)t * g.C + c;
+    } else {
+      const long item = min((long)block * 256 + (wave & 1) * 128 + col * 8, total - 8);
+      t = (int)(item / g.C);
+      c = (int)(item - (long)t * g.C);
+      f.at = item;
+    }
+    int tx, ty, b;
+    tile_coords(g, t, b, ty, tx);
+    const int y0 = ty * m - 1, x0 = tx * m - 1;
+    const int b0 = __builtin_amdgcn_readfirstlane(b);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x) + b0 * image, 0,
+                                                        (int)min((g.N - b0) * image, 0xfffffff0L), 0x00020000);
+    const unsigned origin = (unsigned)((b - b0) * (int)image + (y0 * g.W + x0) * g.C + c);
+    const v2us corner = {(unsigned short)y0, (unsigned short)x0};
+#pragma unroll
+    for (int i = 0; i < 5; ++i) asm volatile("" : "+v"(rc[i]));      // unpacked here, not ahead of the loop
+    static_for<0, 9>([&](auto s) {
+      constexpr int S = decltype(s)::value;
+      const v2us rowcol = __builtin_bit_cast(v2us, __builtin_amdgcn_perm(0, rc[S / 2], S & 1 ? 0x0c030c02u : 0x0c010c00u));
+      const v2us hw = corner + rowcol;                               // -1 is 65535
+      const bool in_image = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(hw, last)) == __builtin_bit_cast(uint32_t, hw);
+      const unsigned off = __builtin_amdgcn_udot2(rowcol, pitch, origin, false);
+      f.v[s] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rsrc, in_image ? (int)off : -1, 0, 0));
+    });
+  };
+  Item f;
+  fetch(image_on_one_xcd(g, slot), f);
+  P ops;
+  ops.load(mu, lane);
+  // all of it is here before the loop: a wait for it inside would also wait for the next pixels
+  __builtin_amdgcn_s_waitcnt(0x0f70);
+  for (;;) {
+    const long at = f.at;
+    uint32_t out[2][9];
+    static_for<0, 2>([&](auto d) {
+      constexpr int D = decltype(d)::value;
+      typename P::In in;
+#pragma unroll
+      for (int s = 0; s < 9; ++s) P::put(in, s, f.v[s][D]);
+      mb::input_codes<4>(ops, in, out[d]);
+      // (kept here: sunk below the next fetch, all their operands would stay live across it)
+#pragma unroll
+      for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(out[d][i]));
+    });
+    slot += step;
+    const bool more = slot < pairs;
+    if (more) fetch(image_on_one_xcd(g, slot), f);
+    int8_t* base = U + at + (long)(4 * grp) * pstride;
+    static_for<0, 9>([&](auto i) {
+      constexpr int I = decltype(i)::value;
+      int8_t* to = I < 8 ? base + (long)(16 * (I >> 2) + (I & 3)) * pstride : U + at + (long)(32 + grp) * pstride;
+      __builtin_nontemporal_store(v2u{out[0][i], out[1][i]}, reinterpret_cast<v2u*>(to));
+    });
+    if (!more) break;
+  }
+}
+
+template <int M, bool LEG, bool WHOLE, int BASE = 1, bool MX = false>
 __device__ __forceinline__ void input_body(const int8_t* __restrict__ x, int8_t* __restrict__ U,
-                                           const Geometry& g, const StageMults& mu,
-                                           unsigned block) {
+                                           const Geometry& g, const InputMults<MX>& mu,
+                                           unsigned slot, unsigned slots, unsigned pairs) {
   constexpr int n = M + 2;
   using TB = Tab<M, BASE>;
-  input_items<M, WHOLE>(x, U, g, block, [&](const int (&xi)[n][n], int (&q)[n][n]) {
+  if constexpr (MX) {
+    input_pairs<WHOLE>(x, U, g, mu, slot, pairs, slots);
+  } else
+  input_items<M, WHOLE>(x, U, g, image_on_one_xcd(g, slot), [&](const int (&xi)[n][n], int (&q)[n][n]) {
     if constexpr (LEG) {
       acc_t<TB::PinvT, 127> num1[n][n];
       sandwich<TB::PinvT, 127>(xi, num1);
@@ -711,11 +830,11 @@ __global__ __launch_bounds__(256) void k_weight_transform(const int8_t* __restri
   weight_body<M, LEG, BASE>(w, V, g, mu, blockIdx.x);
 }
 
-template <int M, bool LEG, bool WHOLE, int BASE = 1>
-__global__ __launch_bounds__(256) void k_input_transform(const int8_t* __restrict__ x,
+template <int M, bool LEG, bool WHOLE, int BASE = 1, bool MX = false>
+__global__ __launch_bounds__(256, MX ? 3 : 1) void k_input_transform(const int8_t* __restrict__ x,
                                                          int8_t* __restrict__ U, Geometry g,
-                                                         StageMults mu) {
-  input_body<M, LEG, WHOLE, BASE>(x, U, g, mu, image_on_one_xcd(g, blockIdx.x));
+                                                         InputMults<MX> mu, unsigned pairs) {
+  input_body<M, LEG, WHOLE, BASE, MX>(x, U, g, mu, blockIdx.x, gridDim.x, pairs);
 }
 
 // Both operand transforms in one launch (they are independent): one launch less per layer, and
@@ -725,16 +844,17 @@ __global__ __launch_bounds__(256) void k_input_transform(const int8_t* __restric
 // has to be dropped there before it can be written (measured on the 256-channel layer at
 // N = 256: 24.1 -> 23.0 us per step against filters last).  The filter slots are padded to a
 // multiple of 8, so that an input slot's XCD (slot % 8) is what image_on_one_xcd assumes.
-template <int M, bool LEG, bool WHOLE, int BASE = 1>
-__global__ __launch_bounds__(256) void k_operand_transforms(const int8_t* __restrict__ x,
+template <int M, bool LEG, bool WHOLE, int BASE = 1, bool MX = false>
+__global__ __launch_bounds__(256, MX ? 3 : 1) void k_operand_transforms(const int8_t* __restrict__ x,
                                                             int8_t* __restrict__ U,
                                                             const int8_t* __restrict__ w,
                                                             int8_t* __restrict__ V, Geometry g,
-                                                            StageMults mu_in, StageMults mu_w,
-                                                            unsigned nb_in) {
+                                                            InputMults<MX> mu_in,
+                                                            StageMults mu_w, unsigned nb_in,
+                                                            unsigned pairs) {
   const unsigned wslots = gridDim.x - nb_in;          // a multiple of 8
   if (blockIdx.x >= wslots)
-    input_body<M, LEG, WHOLE, BASE>(x, U, g, mu_in, image_on_one_xcd(g, blockIdx.x - wslots));
+    input_body<M, LEG, WHOLE, BASE, MX>(x, U, g, mu_in, blockIdx.x - wslots, nb_in, pairs);
   else if (blockIdx.x < weight_blocks(g))             // the padding slots have nothing to do
     weight_body<M, LEG, BASE>(w, V, g, mu_w, blockIdx.x);
 }
@@ -911,25 +1031,43 @@ hipError_t PerM<M>::weight(const Geometry& g, int br, const int8_t* w, int8_t* V
   return hipGetLastError();
 }
 
+// Work groups of an input transform on the matrix pipe, at most (a multiple of 8, so that a group's slots stay
+// on one XCD): a group reads 40 KB of matrix operands before its first item, and 1536 are two per resident one, which
+// evens out their ends.  Layer us with 768, 1536, 3072, 6144 groups: 16384 images 8x8, C = K = 256: 805, 803,
+// 804, 812; 2048 images 14x14, C = K = 192: 345, 344, 344, 347; one block pair per group: 327 us for the kernel
+// alone against 270.
+constexpr unsigned kPairGroups = 1536;
 template <int M>
 hipError_t PerM<M>::input(const Geometry& g0, int br, const int8_t* x, int8_t* U,
                           const StageMults& mu, hipStream_t st) {
-  const unsigned nb = input_blocks(g0);
-  const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
-  const Geometry g = with_image_groups(g0, whole);
   const bool leg = br != 0;
+  const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
+  const bool mx = input_on_matrix_pipe(g0, br);
+  const int per = mx ? 2 : 1;                      // 256-item blocks per work group
+  const unsigned pairs = (input_blocks(g0) + per - 1) / per;
+  const unsigned nb = per == 2 ? min(pairs, kPairGroups) : pairs;
+  const Geometry g = with_image_groups(g0, whole, per);
+  if constexpr (M == 4)
+    if (mx) {
+      const mb::PairMults pm = mb::pair_mults<Tab<M>::BPT>(mu);
+      if (whole)
+        wino_launch((k_input_transform<M, true, true, 1, true>), dim3(nb), dim3(256), st, x, U, g, pm, pairs);
+      else
+        wino_launch((k_input_transform<M, true, false, 1, true>), dim3(nb), dim3(256), st, x, U, g, pm, pairs);
+      return hipGetLastError();
+    }
   if (br == 2)
-    wino_launch((k_input_transform<M, true, false, 2>), dim3(nb), dim3(256), st, x, U, g, mu);
+    wino_launch((k_input_transform<M, true, false, 2>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (br == 3)
-    wino_launch((k_input_transform<M, true, false, 3>), dim3(nb), dim3(256), st, x, U, g, mu);
+    wino_launch((k_input_transform<M, true, false, 3>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (leg && whole)
-    wino_launch((k_input_transform<M, true, true>), dim3(nb), dim3(256), st, x, U, g, mu);
+    wino_launch((k_input_transform<M, true, true>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (leg)
-    wino_launch((k_input_transform<M, true, false>), dim3(nb), dim3(256), st, x, U, g, mu);
+    wino_launch((k_input_transform<M, true, false>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (whole)
-    wino_launch((k_input_transform<M, false, true>), dim3(nb), dim3(256), st, x, U, g, mu);
+    wino_launch((k_input_transform<M, false, true>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else
-    wino_launch((k_input_transform<M, false, false>), dim3(nb), dim3(256), st, x, U, g, mu);
+    wino_launch((k_input_transform<M, false, false>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   return hipGetLastError();
 }
 
@@ -937,23 +1075,35 @@ template <int M>
 hipError_t PerM<M>::operands(const Geometry& g0, int br, const int8_t* x, int8_t* U,
                              const int8_t* w, int8_t* V, const StageMults& mu_in,
                              const StageMults& mu_w, hipStream_t st) {
-  const unsigned nb_in = input_blocks(g0), nb_w = weight_blocks(g0);
   const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
-  const Geometry g = with_image_groups(g0, whole);
+  const bool mx = input_on_matrix_pipe(g0, br);
+  const int per = mx ? 2 : 1;                      // 256-item input blocks per work group
+  const unsigned pairs = (input_blocks(g0) + per - 1) / per;
+  const unsigned nb_in = per == 2 ? min(pairs, kPairGroups) : pairs, nb_w = weight_blocks(g0);
+  const Geometry g = with_image_groups(g0, whole, per);
   const dim3 grid(nb_in + (nb_w + 7) / 8 * 8), bs(256);   // filter slots padded to whole sets of XCDs
   const bool leg = br != 0;
+  if constexpr (M == 4)
+    if (mx) {
+      const mb::PairMults pm = mb::pair_mults<Tab<M>::BPT>(mu_in);
+      if (whole)
+        wino_launch((k_operand_transforms<M, true, true, 1, true>), grid, bs, st, x, U, w, V, g, pm, mu_w, nb_in, pairs);
+      else
+        wino_launch((k_operand_transforms<M, true, false, 1, true>), grid, bs, st, x, U, w, V, g, pm, mu_w, nb_in, pairs);
+      return hipGetLastError();
+    }
   if (br == 2)
-    wino_launch((k_operand_transforms<M, true, false, 2>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in);
+    wino_launch((k_operand_transforms<M, true, false, 2>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (br == 3)
-    wino_launch((k_operand_transforms<M, true, false, 3>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in);
+    wino_launch((k_operand_transforms<M, true, false, 3>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (leg && whole)
-    wino_launch((k_operand_transforms<M, true, true>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in);
+    wino_launch((k_operand_transforms<M, true, true>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (leg)
-    wino_launch((k_operand_transforms<M, true, false>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in);
+    wino_launch((k_operand_transforms<M, true, false>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (whole)
-    wino_launch((k_operand_transforms<M, false, true>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in);
+    wino_launch((k_operand_transforms<M, false, true>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else
-    wino_launch((k_operand_transforms<M, false, false>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in);
+    wino_launch((k_operand_transforms<M, false, false>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   return hipGetLastError();
 }
 
