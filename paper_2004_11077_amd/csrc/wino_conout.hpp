@@ -56,14 +56,25 @@ struct CoShape {
 
 // NW waves per work group, WPE waves per SIMD that the register budget must allow, DEPTH
 // operand units in flight per wave.
+// MX: phase 2 on the matrix pipe (F(4,3) in the Legendre base, one scale per tensor).  The 1 KiB blocks of
+// M_s then have their tiles permuted by the lane group that reads the point (mb::group_of), which keeps the four
+// groups' reads on different banks.  Kernel us, vector ALU -> matrix pipe: 2048 tiles, C = K = 128, 9-bit
+// M: 11.6 -> 9.8; 1024 tiles, C = K = 256: 14.7 -> 13.0.
 // FRAG: U and V are in MFMA-fragment order (wino_kernels.hpp), else rows [n*n][T or K][C].
+template <int M, bool LEG, bool PP>
+constexpr bool kCoMatrix = M == 4 && LEG && !PP;
+template <int M, bool LEG, bool PP>
+using CoMults = std::conditional_t<kCoMatrix<M, LEG, PP>, mb::PairMults, StageMults>;
+
 template <int M, bool LEG, typename MT, int OUT, bool PP, bool FRAG, int TB, int KB, int NW, int WPE,
           int DEPTH>
 __global__ __launch_bounds__(NW * 64, WPE) void k_contract_out(const int8_t* __restrict__ U,
                                                          const int8_t* __restrict__ V,
                                                          void* __restrict__ yv, Geometry g,
-                                                         StageMults mu, MultTable mm, ShiftTable sh,
-                                                         int relu, int tblocks, int kblocks) {
+                                                         CoMults<M, LEG, PP> mu, MultTable mm,
+                                                         ShiftTable sh, int relu, int tblocks,
+                                                         int kblocks) {
+  constexpr bool MX = kCoMatrix<M, LEG, PP>;
   constexpr int n = M + 2, n2 = n * n;
   constexpr int NTB = TB / 16, NKB = KB / 16;       // 16-row fragments per operand
   // All NW waves contract; the NT2 lanes of the first waves (a power of two) transform.
@@ -88,6 +99,10 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_contract_out(const int8_t* __r
     tile_coords(g, min(t, g.T - 1), b, ty, tx);
     s_tile[tid] = make_int4(b, ty * M, tx * M, t < g.T ? 1 : 0);
   }
+
+  using MatrixPair = mb::Pair<TBL::PinvT, TBL::APT, (int)sizeof(MT) == 1 ? 1 : 2>;
+  std::conditional_t<MX, MatrixPair, int> pair;
+  if constexpr (MX && FRAG) pair.load(mu, lane);     // on its way during phase 1 (rows: no registers to spare)
 
   // ---- phase 1: contraction of the wave's points --------------------------------------
   // The channel sum runs in units of 128 channels = two MFMA steps; the loads of a unit stay
@@ -244,7 +259,8 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_contract_out(const int8_t* __r
           for (int v = 0; v < 4; ++v) q[v] = cast_biased((float)acc[i][j][v], mult, QM);
           // the four-code group index inside a tile's row is XOR-ed with the tile's low
           // bits: the 16 tiles a store covers then fall on distinct LDS banks
-          MT* dst = M_s + (p * TB + j * 16 + jl) * KB + (((i * 4 + seg) ^ (jl & (KB / 4 - 1))) << 2);
+          const int tile = j * 16 + (MX ? jl ^ (2 * mb::group_of(p / n, p % n)) : jl);
+          MT* dst = M_s + (p * TB + tile) * KB + (((i * 4 + seg) ^ (jl & (KB / 4 - 1))) << 2);
           if constexpr (sizeof(MT) == 1) {
             const uint32_t lo = __builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u);
             const uint32_t hi = __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu);
@@ -271,6 +287,37 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_contract_out(const int8_t* __r
   __syncthreads();
 
   // ---- phase 2: output transform of TB x KB items ---------------------------------------
+  if constexpr (MX) {
+    // a wave: 16 columns of four output channels, i.e. the 32 channels of two tiles, per pass
+    const int grp = lane >> 4;
+    if constexpr (!FRAG) pair.load(mu, lane);
+#pragma unroll 1
+    for (int tl2 = wave; tl2 < TB / 2; tl2 += NW) {
+      const int tl = 2 * tl2 + ((lane >> 3) & 1), kq = lane & 7;
+      const int k = k0 + 4 * kq;
+      const int at = (tl ^ (2 * grp)) * KB + ((kq ^ (tl & 7)) << 2);
+      typename MatrixPair::In in;
+      static_for<0, 9>([&](auto s) {
+        const MT* from = M_s + mb::pixel<decltype(s)::value>(grp) * (TB * KB) + at;
+        if constexpr (sizeof(MT) == 1) {
+          MatrixPair::put(in, s, *reinterpret_cast<const uint32_t*>(from));
+        } else {
+          const uint2 v = *reinterpret_cast<const uint2*>(from);
+          MatrixPair::put(in, s, v.x, v.y);
+        }
+      });
+      const int4 ti = s_tile[tl];
+      const int h = ti.y + grp;
+      constexpr int YB = OUT == 0 ? 4 : 1;
+      char* yrow = static_cast<char*>(yv) + ((((long)ti.x * g.H + h) * g.W + ti.z) * g.K + k) * YB;
+      const bool ok = ti.w && k < g.K && h < g.H;
+      mb::finish_outputs<4, OUT>(pair, in, relu, [&](int r, auto v) {
+        if (ok && ti.z + r < g.W)
+          __builtin_nontemporal_store(v, reinterpret_cast<decltype(v)*>(yrow + (long)r * g.K * YB));
+      });
+    }
+    return;
+  } else {
   constexpr int64_t IN_MAX = (sizeof(MT) == 1 ? 127 : 255) << (PP ? kMaxMShift : 0);
   // ReLU as a lower bound (none: below every value).  A float is bounded through its bit
   // pattern: negative values are negative integers, so one integer maximum with 0 clears
@@ -339,6 +386,7 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_contract_out(const int8_t* __r
         finish.template operator()<TBL::AT, IN_MAX, false>(num);
     }
   }
+  }
 }
 
 template <int M, bool LEG, typename MT, int OUT, bool PP, bool FRAG, int TB, int KB, int NW, int WPE,
@@ -349,9 +397,14 @@ static hipError_t conout_launch(const Geometry& g, const int8_t* U, const int8_t
   const int tblocks = (g.T + TB - 1) / TB, kblocks = (g.K + KB - 1) / KB;
   const long nblocks = (long)((tblocks + 7) / 8) * 8 * kblocks;
   if (nblocks > 0x7fffffffL) return hipErrorInvalidValue;
-  wino_launch((k_contract_out<M, LEG, MT, OUT, PP, FRAG, TB, KB, NW, WPE, DEPTH>),
-              dim3((unsigned)nblocks), dim3(NW * 64), st, U, V, y, g, mu, mm, sh, relu ? 1 : 0,
-              tblocks, kblocks);
+  if constexpr (kCoMatrix<M, LEG, PP>)
+    wino_launch((k_contract_out<M, LEG, MT, OUT, PP, FRAG, TB, KB, NW, WPE, DEPTH>),
+                dim3((unsigned)nblocks), dim3(NW * 64), st, U, V, y, g, mb::pair_mults<Tab<M>::APT>(mu), mm,
+                sh, relu ? 1 : 0, tblocks, kblocks);
+  else
+    wino_launch((k_contract_out<M, LEG, MT, OUT, PP, FRAG, TB, KB, NW, WPE, DEPTH>),
+                dim3((unsigned)nblocks), dim3(NW * 64), st, U, V, y, g, mu, mm, sh, relu ? 1 : 0,
+                tblocks, kblocks);
   return hipGetLastError();
 }
 
@@ -374,6 +427,8 @@ static hipError_t conout_mt(const Geometry& g, const int8_t* U, const int8_t* V,
   (g.frag ? conout_shape<M, LEG, MT, OUT_, PP_, true>(g, U, V, y, relu, mu, mm, SH_, st) \
           : conout_shape<M, LEG, MT, OUT_, PP_, false>(g, U, V, y, relu, mu, mm, SH_, st))
   if (sh) return out_type == 0 ? CO_SH(0, true, *sh) : CO_SH(2, true, *sh);
+  // multipliers out of the matrix form's range: the per-point form, all shifts zero
+  if (kCoMatrix<M, LEG, false> && out_type == 0 && !mb::output_mults_fit(mu)) return CO_SH(0, true, none);
   return out_type == 0 ? CO_SH(0, false, none) : CO_SH(2, false, none);
 #undef CO_SH
 }
