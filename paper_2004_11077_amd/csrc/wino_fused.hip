@@ -284,6 +284,189 @@ __global__ __launch_bounds__(kFW * 64, RAW ? 4 : 6) void k_fused(const int8_t* _
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// The same for F(4,3) in the Legendre base with one scale per tensor: the brackets of phases A and C on
+// the matrix pipe (wino_matrix_brackets.hpp).  A lane works on four channels (a column of 64 bytes is a
+// tile's channels), or on two where the work group has fewer tiles than waves.  All pixels of the work group are
+// staged at once, beside U_s / M_s (74 KB for 16 tiles; two work groups per compute unit, which the
+// registers allow anyway).  Rows of 64 bytes are permuted (XOR) by the lane group that reads or writes
+// the pixel or point, so that the four groups meet different banks.  8192 tiles, C = K = 64, filters
+// transformed, fp32 output: 23.0 -> 20.5 us; one 32x32 image: 8.1 -> 7.3 (int8 output).  Both phases' vector
+// instructions halve; what is left is a chain per work group (pixels, operands, three barriers), two of which
+// share a compute unit.  With the pixels of eight tiles at a time in U_s's free half, as above, the
+// second batch waited for memory again: 28.7 us.
+// ---------------------------------------------------------------------------------------
+template <typename MT, int OUT, int kFT>
+__global__ __launch_bounds__(kFW * 64, 4)
+    void k_fused_matrix(const int8_t* __restrict__ x, const int8_t* __restrict__ V, void* __restrict__ yv,
+                        Geometry g, mb::PairMults in_mu, mb::PairMults out_mu, float m_mult, int relu,
+                        int tblocks) {
+  constexpr int M = 4, n = 6, n2 = 36;
+  constexpr int KB = sizeof(MT) == 1 ? 64 : 32, NKB = KB / 16, NT = kFW * 64;
+  constexpr float QM = sizeof(MT) == 1 ? 127.f : 255.f;
+  using TB = Tab<M>;
+  using InPair = mb::Pair<TB::PinvT, TB::BPT, 1>;
+  using OutPair = mb::Pair<TB::PinvT, TB::APT, (int)sizeof(MT)>;
+  __shared__ __attribute__((aligned(256))) int8_t smem[n2 * kPt];        // U_s, then M_s
+  __shared__ __attribute__((aligned(256))) int8_t pixels[n2 * kFT * 64];
+  __shared__ int4 s_tile[kFT];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tb = blockIdx.x % tblocks, kblk = blockIdx.x / tblocks;
+  const int t0 = tb * kFT, k0 = kblk * KB;
+  const int jl = lane & 15, grp = lane >> 4;
+  if (tid < kFT) {
+    const int t = min(t0 + tid, g.T - 1);
+    int b, ty, tx;
+    tile_coords(g, t, b, ty, tx);
+    s_tile[tid] = make_int4(b, ty * M, tx * M, t0 + tid < g.T ? 1 : 0);
+  }
+  __syncthreads();
+
+  // ---- pixels of all tiles -----------------------------------------------------------
+#pragma unroll
+  for (int j = 0; j < (kFT * n2 * 4 + NT - 1) / NT; ++j) {
+    const int idx = j * NT + tid;
+    if (idx < kFT * n2 * 4) {
+      const int tq = idx / (n2 * 4), rem = idx - tq * (n2 * 4);
+      const int pix = rem >> 2, sg = rem & 3, a = pix / n, bb = pix - a * n;
+      const int4 ti = s_tile[tq];
+      const int h = ti.y - 1 + a, ww = ti.z - 1 + bb;
+      v4i v = {0, 0, 0, 0};
+      if (ti.w && sg * 16 < g.C && h >= 0 && h < g.H && ww >= 0 && ww < g.W)
+        v = *reinterpret_cast<const v4i*>(x + (((long)ti.x * g.H + h) * g.W + ww) * g.C + sg * 16);
+      *reinterpret_cast<v4i*>(pixels + (pix * kFT + (tq ^ mb::group_of(a, bb))) * 64 + sg * 16) = v;
+    }
+  }
+  InPair in_pair;
+  in_pair.load(in_mu, lane);
+  __syncthreads();
+
+  // ---- A: input transform -------------------------------------------------------------
+  {
+    constexpr int NJ = kFT >= kFW ? 4 : 2;           // channels of a lane: its dword, or half of it
+    const int half = NJ == 4 ? 0 : wave / kFT;
+#pragma unroll 1
+    for (int tl = NJ == 4 ? wave : wave % kFT; tl < kFT; tl += kFW) {
+      typename InPair::In in;
+      static_for<0, 9>([&](auto s) {
+        const int8_t* from = pixels + (mb::pixel<decltype(s)::value>(grp) * kFT + (tl ^ grp)) * 64 + 4 * jl + 2 * half;
+        if constexpr (NJ == 4)
+          InPair::put(in, s, *reinterpret_cast<const uint32_t*>(from));
+        else
+          InPair::put(in, s, *reinterpret_cast<const uint16_t*>(from));
+      });
+      uint32_t codes[9];
+      mb::input_codes<NJ>(in_pair, in, codes);
+      int8_t* to = smem + sw(tl ^ grp, 4 * jl) + 2 * half;
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        // a dead item (tile or channel out of range) has all-zero input, hence zero codes
+        int8_t* at = to + mb::input_result(i, grp) * kPt;
+        if constexpr (NJ == 4)
+          *reinterpret_cast<uint32_t*>(at) = codes[i];
+        else
+          *reinterpret_cast<uint16_t*>(at) = (uint16_t)codes[i];
+      }
+    }
+  }
+  // Phase B's first filters and phase C's operands are on their way over the barrier.
+  const bool cok = grp * 16 < g.C;
+  unsigned voff[NKB];                                // the lane's V row and channel segment
+#pragma unroll
+  for (int kb = 0; kb < NKB; ++kb)
+    voff[kb] = (unsigned)(min(k0 + kb * 16 + jl, g.K - 1) * g.C + (cok ? grp * 16 : 0));   // clamp, masked at the store
+  v4i av[NKB];
+  auto filters = [&](int p) {
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+      av[kb] = *reinterpret_cast<const v4i*>(V + (long)min(p, n2 - 1) * g.K * g.C + voff[kb]);
+  };
+  filters(wave);
+  OutPair out_pair;
+  out_pair.load(out_mu, lane);
+  __syncthreads();
+
+  // ---- B: contraction for the wave's points; cast and park as M_s[p][tile][k] ----
+  // D[k = 16 kb + 4 grp + v][tile = jl]; a segment past C re-reads segment 0: its U_s codes are zero
+#pragma unroll 1
+  for (int p = wave; p < n2; p += kFW) {
+    const v4i bu = *reinterpret_cast<const v4i*>(smem + p * kPt + sw(jl ^ mb::out_group(p), grp * 16));
+    v4i a4[NKB];
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+      a4[kb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[kb], bu, v4i{0, 0, 0, 0}, 0, 0, 0);
+    filters(p + kFW);                                // the next point's (past the last: the last one again)
+    const int row = jl ^ (mb::group_of(p / n, p % n) * (int)sizeof(MT));
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb) {
+      uint32_t q[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) q[v] = cast_biased((float)a4[kb][v], m_mult, QM);
+      int8_t* dst = smem + p * kPt + sw(row, (kb * 16 + 4 * grp) * (int)sizeof(MT));
+      if constexpr (sizeof(MT) == 1) {
+        *reinterpret_cast<uint32_t*>(dst) = mb::pack_codes(q);
+      } else {
+        reinterpret_cast<uint32_t*>(dst)[0] = mb::low_halves(q[1], q[0]);
+        reinterpret_cast<uint32_t*>(dst)[1] = mb::low_halves(q[3], q[2]);
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- C: output transform -----------------------------------------------------------
+  constexpr int TW = 64 / KB;                        // tiles of a wave's 16 columns
+  constexpr int NJ = kFT / TW >= kFW ? 4 : 2;
+  constexpr int UNITS = kFT / TW;
+  const int half = NJ == 4 ? 0 : wave / UNITS;
+  if (half > 1) return;
+#pragma unroll 1
+  for (int u = NJ == 4 ? wave : wave % UNITS; u < UNITS; u += kFW) {
+    const int tl = u * TW + (TW == 2 ? (lane >> 3) & 1 : 0), kq = TW == 2 ? lane & 7 : jl;
+    const int at = sw(tl ^ (grp * (int)sizeof(MT)), 4 * kq * (int)sizeof(MT)) + 2 * half * (int)sizeof(MT);
+    typename OutPair::In in;
+    static_for<0, 9>([&](auto s) {
+      const int8_t* from = smem + mb::pixel<decltype(s)::value>(grp) * kPt + at;
+      if constexpr (sizeof(MT) == 1 && NJ == 4) {
+        OutPair::put(in, s, *reinterpret_cast<const uint32_t*>(from));
+      } else if constexpr (sizeof(MT) == 1) {
+        OutPair::put(in, s, *reinterpret_cast<const uint16_t*>(from));
+      } else if constexpr (NJ == 4) {
+        const uint2 v = *reinterpret_cast<const uint2*>(from);
+        OutPair::put(in, s, v.x, v.y);
+      } else {
+        OutPair::put(in, s, *reinterpret_cast<const uint32_t*>(from), 0);
+      }
+    });
+    const int4 ti = s_tile[tl];
+    const int k = k0 + 4 * kq + 2 * half, h = ti.y + grp;
+    constexpr int YB = OUT == 0 ? 4 : 1;
+    char* yrow = static_cast<char*>(yv) + ((((long)ti.x * g.H + h) * g.W + ti.z) * g.K + k) * YB;
+    const bool ok = ti.w && k < g.K && h < g.H;
+    mb::finish_outputs<NJ, OUT>(out_pair, in, relu, [&](int r, auto v) {
+      if (ok && ti.z + r < g.W)
+        __builtin_nontemporal_store(v, reinterpret_cast<decltype(v)*>(yrow + (long)r * g.K * YB));
+    });
+  }
+}
+
+template <typename MT, int FT>
+static hipError_t fused_matrix(const Geometry& g, const int8_t* x, const int8_t* V, void* y, int out_type,
+                               bool relu, const StageMults& in_mu, const StageMults& out_mu,
+                               const MultTable& mm, hipStream_t st) {
+  constexpr int KB = sizeof(MT) == 1 ? 64 : 32;
+  const int tblocks = (g.T + FT - 1) / FT, kblocks = (g.K + KB - 1) / KB;
+  const dim3 grid((unsigned)(tblocks * kblocks)), bs(kFW * 64);
+  const mb::PairMults pi = mb::pair_mults<Tab<4>::BPT>(in_mu), po = mb::pair_mults<Tab<4>::APT>(out_mu);
+  const int r = relu ? 1 : 0;
+  if (out_type == 0)
+    wino_launch((k_fused_matrix<MT, 0, FT>), grid, bs, st, x, V, y, g, pi, po, mm.v[0], r, tblocks);
+  else
+    wino_launch((k_fused_matrix<MT, 2, FT>), grid, bs, st, x, V, y, g, pi, po, mm.v[0], r, tblocks);
+  return hipGetLastError();
+}
+
 template <int M, bool LEG, typename MT, bool PP, int FT, bool RAW>
 static hipError_t fused_ft(const Geometry& g, const int8_t* x, const int8_t* V, void* y, int out_type,
                            bool relu, const StageMults& in_mu, const StageMults& out_mu,
@@ -312,14 +495,20 @@ static hipError_t fused_mt(const Geometry& g, const int8_t* x, const int8_t* V, 
   // contraction + output transform), which does not recompute the input transform per block
   // of output channels.
   if (g.C > kFC) return hipErrorInvalidValue;
-  const int ft = fused_tiles(g, KB);
-  if (w_mu)
+  const int ft = M == 4 && LEG && !PP ? fused_matrix_tiles(g, KB) : fused_tiles(g, KB);
+  if (w_mu)                                          // 4 tiles
     return fused_ft<M, LEG, MT, PP, 4, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {*w_mu, Vout}, st);
+  if constexpr (M == 4 && LEG && !PP) {
+    return ft == 4   ? fused_matrix<MT, 4>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, st)
+           : ft == 8 ? fused_matrix<MT, 8>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, st)
+                     : fused_matrix<MT, 16>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, st);
+  } else {
   if (ft == 4)
     return fused_ft<M, LEG, MT, PP, 4, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {}, st);
   if (ft == 8)
     return fused_ft<M, LEG, MT, PP, 8, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {}, st);
   return fused_ft<M, LEG, MT, PP, 16, false>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, sh, {}, st);
+  }
 }
 
 template <int M, bool LEG>
@@ -328,6 +517,8 @@ static hipError_t fused_ml(const Geometry& g, const int8_t* x, const int8_t* V, 
                            const StageMults& out_mu, const MultTable& mm, const ShiftTable* sh,
                            const StageMults* w_mu, int8_t* Vout, hipStream_t st) {
   const ShiftTable none{};
+  // multipliers out of the matrix form's range: the per-point form, all shifts zero
+  if (M == 4 && LEG && !sh && !w_mu && out_type == 0 && !mb::output_mults_fit(out_mu)) sh = &none;
   if (sh)
     return m_bits == 8
                ? fused_mt<M, LEG, int8_t, true>(g, x, V, y, out_type, relu, in_mu, out_mu, mm, *sh, w_mu, Vout, st)

@@ -1,0 +1,90 @@
+"""The integer brackets on the matrix pipe (F(4,3), Legendre base, one scale per tensor): the input
+transform, the contraction + output kernel and the single kernel, bit-exact against the oracle at
+the edges of their blocks, and where their rules send a layer to the general form."""
+import numpy as np
+import pytest
+
+from helpers import assert_layer_parity, gpu_layer, oracle_layer, small_layer
+
+pytestmark = pytest.mark.gpu
+
+# bits of M, output, relu, shape, tiles per work group of the single kernel (test_matrix_rules.py)
+FUSED_CASES = [
+    (8, "f32", True, (1, 17, 6, 16, 96), 4),          # 10 tiles, a partial second block of channels
+    (9, "i8", False, (2, 13, 9, 48, 48), 4),          # 24 tiles, half a block of 32
+    (8, "i8", True, (1, 148, 148, 16, 16), 8),        # 1369 tiles: one in the last group
+    (9, "f32", True, (1, 132, 132, 16, 32), 8),       # 1089 tiles: one in the last group
+    (8, "f32", False, (13, 66, 146, 32, 48), 16),     # 8177 tiles: one in the last group
+    (9, "i8", True, (13, 65, 147, 16, 32), 16),
+]
+
+
+@pytest.mark.parametrize("bh,out_type,relu,shape,tiles", FUSED_CASES)
+def test_single_kernel(bh, out_type, relu, shape, tiles):
+    xq, wq, s_x, s_w = small_layer(*shape, seed=5 + bh + tiles, outliers=0.01)
+    kw = dict(m=4, base="legendre", bits_hadamard=bh, out_type=out_type, relu=relu)
+    ora, sc = oracle_layer(xq, wq, s_x, s_w, **kw)
+    assert_layer_parity(ora, gpu_layer(xq, wq, sc, fused=True, **kw), out_type)
+
+
+def operands(x, w, sc, frag):
+    import torch
+    import paper_2004_11077_amd as wn
+    N, H, W, C = x.shape
+    d = wn.ConvDesc(N, H, W, C, w.shape[0], m=4, base=wn.BASE_LEGENDRE,
+                    operand_layout=wn.LAYOUT_FRAGMENTS if frag else wn.LAYOUT_ROWS)
+    vb, ub = wn.wino_operand_bytes(d)
+    U = torch.full((ub,), 77, dtype=torch.int8, device="cuda:0")
+    V = torch.full((vb,), 77, dtype=torch.int8, device="cuda:0")
+    wn.wino_transform_operands(d, x, U, w, V, sc)
+    U2 = torch.full((ub,), 77, dtype=torch.int8, device="cuda:0")
+    wn.wino_input_transform(d, x, U2, sc)
+    assert torch.equal(U, U2)
+    u = U.cpu().numpy()
+    return wn.defragment(u, d.n ** 2, d.tiles, C) if frag else u.reshape(d.n ** 2, d.tiles, C)
+
+
+# the last one: rows of 65536 bytes, which the general form transforms
+@pytest.mark.parametrize("frag", [False, True])
+@pytest.mark.parametrize("shape", [(1, 4, 4, 16), (3, 5, 6, 48), (1, 9, 13, 80), (5, 4, 4, 256), (2, 7, 9, 272),
+                                   (1, 4, 4096, 16)])
+def test_input_transform(shape, frag):
+    import torch
+    import paper_2004_11077_amd as wn
+    xq, wq, s_x, s_w = small_layer(*shape, 16, seed=3)
+    xq.reshape(-1)[:shape[3]] = -127                      # the most negative code of a cast
+    ora, sc = oracle_layer(xq, wq, s_x, s_w, m=4, base="legendre")
+    dev = torch.device("cuda:0")
+    x, w = (torch.from_numpy(np.ascontiguousarray(v, dtype=np.int8)).to(dev) for v in (xq, wq))
+    assert np.array_equal(operands(x, w, wn.Scales.from_dict(sc), frag), ora["U"])
+
+
+@pytest.mark.parametrize("frag,shape", [(False, (1025, 8, 8, 256)), (True, (1100, 8, 8, 192)), (False, (2101, 8, 8, 144))])
+def test_input_transform_work_groups_take_several_blocks(frag, shape):
+    """More blocks than work groups; every image's tiles come out as in a batch of eight images."""
+    import torch
+    import paper_2004_11077_amd as wn
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    x = torch.randint(-128, 128, shape, generator=gen, dtype=torch.int8, device="cuda:0")
+    w = torch.randint(-127, 128, (16, shape[3], 3, 3), generator=gen, dtype=torch.int8, device="cuda:0")
+    sc = wn.Scales.from_dict(dict(s_x=0.02, s_w=0.01, s_x1=0.03, s_w1=0.02, s_u=0.1, s_v=0.05, s_m=1.0, s_m1=1.0))
+    u = operands(x, w, sc, frag)
+    step = 8
+    for n in list(range(0, shape[0], 97 * step // 8)) + [shape[0] - step]:
+        part = operands(x[n:n + step].contiguous(), w, sc, frag)
+        assert np.array_equal(part, u[:, 4 * n:4 * n + part.shape[1]]), n
+
+
+@pytest.mark.parametrize("bh", [8, 9])
+@pytest.mark.parametrize("C", [32, 144])
+def test_output_scale_beyond_the_scaled_multipliers(bh, C):
+    """A dequantisation factor that 2^24 would take out of fp32: the general form, same values as the stages."""
+    xq, wq, s_x, s_w = small_layer(2, 9, 10, C, 48, seed=9)
+    kw = dict(m=4, base="legendre", bits_hadamard=bh)
+    _, sc = oracle_layer(xq, wq, s_x, s_w, **kw)
+    for factor in (2.0 ** 90, 2.0 ** 118):
+        big = dict(sc, **{k: sc[k] * factor for k in ("s_x", "s_x1", "s_u", "s_m", "s_m1")})
+        with np.errstate(over="ignore"):
+            a = gpu_layer(xq, wq, big, **kw)["y"]
+            b = gpu_layer(xq, wq, big, fused=True, **kw)["y"]
+        assert np.abs(a).max() > 1e20 and np.array_equal(a, b, equal_nan=True)
