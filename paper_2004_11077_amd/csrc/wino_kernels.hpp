@@ -178,9 +178,9 @@ inline Geometry with_image_groups(const Geometry& g, bool whole, int per = 1) {
   return blocks % per ? with_dealt_units(g, blocks, g.N / per) : with_dealt_units(g, blocks / per, g.N);
 }
 // Geometry for the launch of the block-uniform output transform (one work group per tile and
-// 256 output channels).
-inline Geometry with_output_groups(const Geometry& g) {
-  return with_dealt_units(g, xcd_chunk_tiles(g) * (g.K / 256), 8);
+// 256 output channels; per as above).
+inline Geometry with_output_groups(const Geometry& g, int per = 1) {
+  return with_dealt_units(g, xcd_chunk_tiles(g) * (g.K / 256) / per, 8);
 }
 
 // q = n / d for n < 2^30.  d a power of two: a shift (mul = 0).  Otherwise, with f = floor(log2 d),

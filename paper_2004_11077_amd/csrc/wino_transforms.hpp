@@ -1013,6 +1013,90 @@ __global__ __launch_bounds__(256) void k_output_transform(const MT* __restrict__
 }
 
 // ---------------------------------------------------------------------------
+// Output transform of F(4,3) in the Legendre base on the matrix pipe, int8 M: a wave takes 128 (tile, output
+// channel) items in two halves, four channels per lane, so that a store covers 256 (codes: 64) contiguous
+// bytes of one pixel; a work group takes two 256-item blocks at a time: pairs blockIdx.x, blockIdx.x +
+// gridDim.x, ... < pairs.  The codes of a half are fetched while the other half is computed.  Loads and
+// stores are unconditional: what is outside the image or the tensor is left to the buffer's bounds check, so
+// that a wait for the next codes never waits for stores.
+// us, vector ALU -> matrix pipe, fp32 / int8 y: 256 tiles, K = 512: 5.4 / 5.2 -> 4.8 / 4.4; 2048 tiles, K = 256: 9.9 /
+// 10.5 -> 9.1 / 7.8; 16384: 74.7 / 65.0 -> 67.5 / 44.9 (8x8 images).  Not where M is beyond what the last-level
+// cache holds (kMatrixOutputBytes): its loads of 64 bytes then cost more than the arithmetic saves, 32768
+// tiles 143 / 121 -> 187 / 121.  Not for a 9-bit M: 3.9 -> 4.4 us at 64 tiles, 25.4 -> 35.0 at 4096.
+// ---------------------------------------------------------------------------
+constexpr long kMatrixOutputBytes = 192L << 20;
+template <int OUT>
+__global__ __launch_bounds__(256, 3) void k_output_pairs(const int8_t* __restrict__ Mq, void* __restrict__ yv,
+                                                         Geometry g, mb::PairMults mu, Divider by_k, int relu,
+                                                         unsigned pairs) {
+  using TB = Tab<4>;
+  constexpr int YB = OUT == 0 ? 4 : 1;
+  using P = mb::Pair<TB::PinvT, TB::APT, 1>;
+  const int lane = threadIdx.x & 63, grp = lane >> 4, col = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long total = (long)g.T * g.K, image = (long)g.H * g.W * g.K * YB;
+  const auto m_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(Mq), 0, (int)(36 * total), 0x00020000);
+  uint32_t row[9];                                 // the lane's nine rows of M
+  static_for<0, 9>([&](auto s) {
+    row[s] = (uint32_t)((long)mb::pixel<decltype(s)::value>(grp) * total + 4 * col);
+  });
+  uint32_t v[2][9];
+  auto fetch = [&](unsigned pair, auto d) {
+    constexpr int D = decltype(d)::value;
+    const uint32_t first = (2 * pair + (wave >> 1)) * 256 + (wave & 1) * 128;
+    static_for<0, 9>([&](auto s) {
+      v[D][s] = __builtin_amdgcn_raw_buffer_load_b32(m_rsrc, row[s] + D * 64, first, 0);
+    });
+  };
+  unsigned pair = image_on_one_xcd(g, blockIdx.x);
+  fetch(pair, IC<0>{});
+  fetch(pair, IC<1>{});
+  P ops;
+  ops.load(mu, lane);
+  __builtin_amdgcn_s_waitcnt(0x0f70);              // as in input_pairs
+  for (unsigned slot = blockIdx.x;;) {
+    const uint32_t item0 = (2 * pair + (wave >> 1)) * 256 + (wave & 1) * 128;
+    // image of the wave's first item: the base of its stores
+    const int t0 = (int)fast_div(item0, by_k.mul, by_k.sh);
+    int b0, ty0, tx0;
+    tile_coords(g, min(t0, g.T - 1), b0, ty0, tx0);
+    b0 = __builtin_amdgcn_readfirstlane(b0);
+    const auto y_rsrc = __builtin_amdgcn_make_buffer_rsrc(static_cast<char*>(yv) + b0 * image, 0,
+                                                          (int)min((g.N - b0) * image, 0xfffffff0L), 0x00020000);
+    slot += gridDim.x;
+    const bool more = slot < pairs;
+    pair = image_on_one_xcd(g, more ? slot : blockIdx.x);          // past the last: any that exists
+    static_for<0, 2>([&](auto d) {
+      constexpr int D = decltype(d)::value;
+      typename P::In in;
+      static_for<0, 9>([&](auto s) { P::put(in, s, v[D][s]); });
+      fetch(pair, d);
+      const uint32_t rest = item0 - (uint32_t)t0 * (uint32_t)g.K + 4 * col + 64 * D;
+      const uint32_t dt = fast_div(rest, by_k.mul, by_k.sh);
+      const int t = t0 + (int)dt, k = (int)(rest - dt * (uint32_t)g.K);
+      int b, ty, tx;
+      tile_coords(g, min(t, g.T - 1), b, ty, tx);
+      const int h = ty * 4 + grp;
+      const int off = (b - b0) * (int)image + ((h * g.W + tx * 4) * g.K + k) * YB;
+      const int inside = t < g.T && h < g.H ? g.W - tx * 4 : 0;      // columns of the image
+      mb::finish_outputs<4, OUT>(ops, in, relu, [&](int r, auto out) {
+        const int at = r < inside ? off + r * g.K * YB : -1;
+        if constexpr (OUT == 0)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(mb::v4u, out), y_rsrc, at, 0, 2);
+        else
+          __builtin_amdgcn_raw_buffer_store_b32((uint32_t)out, y_rsrc, at, 0, 2);
+      });
+    });
+    if (!more) break;
+  }
+}
+// (offsets into M and into a few images of y then fit 32 bits, an item index 30)
+inline bool output_on_matrix_pipe(const Geometry& g, int out_type, const StageMults& mu) {
+  return 36L * g.T * g.K <= kMatrixOutputBytes && (long)g.H * g.W * g.K * 4 < (1L << 30) &&
+         (out_type == 2 || (out_type == 0 && mb::output_mults_fit(mu)));
+}
+
+// ---------------------------------------------------------------------------
 // Launchers of one M
 // ---------------------------------------------------------------------------
 template <int M>
@@ -1060,8 +1144,8 @@ hipError_t PerM<M>::input(const Geometry& g0, int br, const int8_t* x, int8_t* U
     wino_launch((k_input_transform<M, true, false, 2>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (br == 3)
     wino_launch((k_input_transform<M, true, false, 3>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
-  else if (leg && whole)
-    wino_launch((k_input_transform<M, true, true>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
+  else if (M != 4 && leg && whole)
+    wino_launch((k_input_transform<M, true, M != 4>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (leg)
     wino_launch((k_input_transform<M, true, false>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (whole)
@@ -1096,8 +1180,8 @@ hipError_t PerM<M>::operands(const Geometry& g0, int br, const int8_t* x, int8_t
     wino_launch((k_operand_transforms<M, true, false, 2>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (br == 3)
     wino_launch((k_operand_transforms<M, true, false, 3>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
-  else if (leg && whole)
-    wino_launch((k_operand_transforms<M, true, true>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
+  else if (M != 4 && leg && whole)
+    wino_launch((k_operand_transforms<M, true, M != 4>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (leg)
     wino_launch((k_operand_transforms<M, true, false>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (whole)
@@ -1137,6 +1221,18 @@ static hipError_t output_mt(const Geometry& g, const void* Mq, void* y, int out_
       return output_mtw<M, LEG, MT, false, true>(g, Mq, y, out_type, relu, mu, *sh, st);
   }
   const ShiftTable none{};
+  if constexpr (M == 4 && LEG && sizeof(MT) == 1)
+    if (output_on_matrix_pipe(g, out_type, mu)) {
+      const unsigned pairs = (blocks_for((long)g.T * g.K) + 1) / 2;
+      const dim3 nb(min(pairs, kPairGroups)), bs(256);
+      const Geometry gp = whole_tiles(g.K, g.H, g.W) ? with_output_groups(g, 2) : with_dealt_units(g, 0, 0);
+      const mb::PairMults pm = mb::pair_mults<Tab<M>::APT>(mu);
+      if (out_type == 0)
+        wino_launch((k_output_pairs<0>), nb, bs, st, static_cast<const int8_t*>(Mq), y, gp, pm, divider_of(g.K), (int)relu, pairs);
+      else
+        wino_launch((k_output_pairs<2>), nb, bs, st, static_cast<const int8_t*>(Mq), y, gp, pm, divider_of(g.K), (int)relu, pairs);
+      return hipGetLastError();
+    }
   // the block-uniform fast path is built for the int8 M of the all-8-bit pipeline
   if constexpr (sizeof(MT) == 1)
     if (whole_tiles(g.K, g.H, g.W))

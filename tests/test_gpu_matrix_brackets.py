@@ -88,3 +88,33 @@ def test_output_scale_beyond_the_scaled_multipliers(bh, C):
             a = gpu_layer(xq, wq, big, **kw)["y"]
             b = gpu_layer(xq, wq, big, fused=True, **kw)["y"]
         assert np.abs(a).max() > 1e20 and np.array_equal(a, b, equal_nan=True)
+
+
+# (images of one tile, ragged edges, partial last blocks of 128 and 256 items; more pairs of blocks than work groups)
+@pytest.mark.parametrize("shape", [(1, 4, 4, 16, 16), (3, 5, 7, 16, 48), (9, 3, 2, 16, 80), (5, 4, 4, 16, 256), (2, 18, 5, 16, 272)])
+@pytest.mark.parametrize("out_type,relu", [("f32", False), ("i8", True)])
+def test_output_transform(shape, out_type, relu):
+    xq, wq, s_x, s_w = small_layer(*shape, seed=13)
+    kw = dict(m=4, base="legendre", out_type=out_type, relu=relu)
+    ora, sc = oracle_layer(xq, wq, s_x, s_w, **kw)
+    assert_layer_parity(ora, gpu_layer(xq, wq, sc, **kw), out_type)
+
+
+@pytest.mark.parametrize("N,H,W,K", [(513, 16, 16, 208), (1030, 8, 8, 256)])
+def test_output_transform_work_groups_take_several_blocks(N, H, W, K):
+    import torch
+    import paper_2004_11077_amd as wn
+    sc = wn.Scales.from_dict(dict(s_x=0.02, s_w=0.01, s_x1=0.03, s_w1=0.02, s_u=0.1, s_v=0.05, s_m=1.0, s_m1=1.5))
+    gen = torch.Generator(device="cuda:0").manual_seed(2)
+    per = (H // 4) * (W // 4)
+    M = torch.randint(-127, 128, (36, N * per, K), generator=gen, dtype=torch.int8, device="cuda:0")
+
+    def outputs(m, n):
+        d = wn.ConvDesc(n, H, W, 16, K, m=4, base=wn.BASE_LEGENDRE)
+        y = torch.full((n, H, W, K), 7.0, device="cuda:0")
+        return wn.wino_output_transform(d, m, y, sc)
+
+    y = outputs(M, N)
+    for n in list(range(0, N - 8, 61)) + [N - 8]:
+        part = outputs(M[:, n * per:(n + 8) * per].contiguous(), 8)
+        assert torch.equal(part, y[n:n + 8]), n
