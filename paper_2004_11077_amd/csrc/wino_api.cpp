@@ -1531,11 +1531,11 @@ int wino_flex_backward(const wino_conv_desc_t* d, const wino_flex_matrices_t* f,
   if (e != hipSuccess) return fail_hip(e, "flex backward contraction launch");
   e = launch_backward_sum_splits(g, dV, st);            // no launch unless dV came in several parts
   if (e != hipSuccess) return fail_hip(e, "flex backward partial-sum launch");
-  e = launch_flex_backward_input_weight(g, p.legendre, (const int8_t*)x, dU, dXt, part_in,
+  e = launch_flex_backward_input_weight(g, p.legendre, (const int8_t*)x, dU, dXt, (float*)dx, part_in,
                                         (const int8_t*)w, dV, (float*)dw, part_w, fp.fm, mu_in,
                                         s_in_x, s->s_w, st);
   if (e != hipSuccess) return fail_hip(e, "flex backward input / filter bracket launch");
-  e = launch_flex_backward_tile_sum(g, dXt, (float*)dx, st);
+  e = launch_flex_backward_tile_sum(g, dXt, (float*)dx, st);   // no launch where the brackets left dx
   if (e != hipSuccess) return fail_hip(e, "flex backward tile-sum launch");
   const float* const parts[3] = {part_out, part_in, part_w};
   const long part_rows[3] = {l.out_blocks, l.in_blocks, l.w_blocks};

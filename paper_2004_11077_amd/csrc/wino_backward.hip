@@ -793,12 +793,12 @@ hipError_t launch_flex_backward_output(const Geometry& g, bool legendre, const v
 }
 
 hipError_t launch_flex_backward_input_weight(const Geometry& g, bool legendre, const int8_t* x,
-                                             const float* dU, float* dXt, float* part_in,
+                                             const float* dU, float* dXt, float* dx, float* part_in,
                                              const int8_t* w, float* dV, float* dw,
                                              float* part_w, const FlexMats& fm,
                                              const StageMults& mu, float s_in, float s_w,
                                              hipStream_t st) {
-  WINO_BY_M(input_weight(g, legendre, x, dU, dXt, part_in, w, dV, dw, part_w, fm, mu, s_in, s_w, st))
+  WINO_BY_M(input_weight(g, legendre, x, dU, dXt, dx, part_in, w, dV, dw, part_w, fm, mu, s_in, s_w, st))
 }
 
 hipError_t launch_flex_backward_tile_sum(const Geometry& g, const float* dXt, float* dx,

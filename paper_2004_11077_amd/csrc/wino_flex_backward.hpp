@@ -9,13 +9,14 @@
 //   k_fbwd_output   dY, M  -> dM, per-block partial sums of dA_P^T
 //   fbwd_input_body   dU, x  -> per-tile dX, per-block partial sums of dB_P^T   \ one launch,
 //   fbwd_weight_body  dV, w  -> dw, per-block partial sums of dG_P              / k_fbwd_input_weight
-//   k_bwd_tile_sum  per-tile dX -> dx (fixed order over the <= 4 covering tiles)
+//                     (dx itself where a work group takes whole images, fbwd_takes_images)
+//   k_bwd_tile_sum  per-tile dX -> dx elsewhere (fixed order over the <= 4 covering tiles)
 //   k_sum_partials  partial sums -> the three matrix gradients (fixed order)
 // The two contraction gradients between them are those of the static layer.
 // Bound by vector arithmetic (about 2400 instructions per (tile, channel) item of the input bracket) and
 // by the bytes of dM, dU and dX.  2048 tiles, C = K = 128, F(4,3): input and filter brackets 38.1 us with
 // sums over lanes by LDS permutes, 64-bit divisions and all of T S, T S^T and dT held at once (128
-// registers, now 95), now 27.5; output bracket 23.7, now 19.8; training step 278, now 264.
+// registers, now 95), then 27.5; output bracket 23.7, now 19.8.
 #pragma once
 #include "wino_flex.hpp"
 #include "wino_real_brackets.hpp"
@@ -229,22 +230,40 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
   store_sums<M>(s_sums, part + (long)blockIdx.x * kPartialStride);
 }
 
-// dU, x -> per-tile dX [a*n+b][t][c] and the partial sums of dBPT (n x n).
+// A work group of the input bracket can take all tiles of an image, 1, 2, 4, 8 or 16, for 256 / tiles channels: the
+// sum over the tiles that cover a pixel then needs no tensor of per-tile gradients (written and read, 38 MB
+// each for 128 images of 16x16, C = 128) and no launch of its own: 27.5 + 9.6 -> 32.4 us there, the step 9 us less.
+inline bool fbwd_takes_images(const Geometry& g) {
+  const int tiles = g.TH * g.TW;
+  return tiles <= 16 && (tiles & (tiles - 1)) == 0 && g.C % (256 / tiles) == 0 && (long)g.H * g.W * g.C < (1L << 29);
+}
+
+// dU, x -> per-tile dX [a*n+b][t][c] (IMAGES: dx) and the partial sums of dBPT (n x n).
 // s_in: what one code of the B_P bracket's input stands for (s_x1, or s_x).
-template <int M, bool LEG>
+template <int M, bool LEG, bool IMAGES>
 __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
                                                 const float* __restrict__ dU,
                                                 float* __restrict__ dXt, float* __restrict__ part,
                                                 const Geometry& g, const FlexMats& fm,
                                                 const StageMults& mu, float s_in, Divider by_c,
-                                                unsigned block) {
+                                                Divider by_w, unsigned block) {
   constexpr int n = M + 2;
   using TB = Tab<M>;
   const long total = (long)g.T * g.C;
-  const long gid = (long)block * 256 + threadIdx.x;
-  const bool active = gid < total;
   int t, c, b, ty, tx;
-  item_of_lane(block, g.C, by_c, t, c);
+  const int tiles = g.TH * g.TW, cw = IMAGES ? 256 / tiles : 0;      // powers of two
+  const int cw_bits = IMAGES ? 31 - __clz(cw) : 0;
+  if constexpr (IMAGES) {
+    const int chunks = g.C >> cw_bits;
+    block = image_on_one_xcd(g, block);            // the channel chunks of an image share its lines
+    const int image = (int)(block / (unsigned)chunks);
+    t = image * tiles + ((int)threadIdx.x >> cw_bits);
+    c = ((int)block - image * chunks) * cw + ((int)threadIdx.x & (cw - 1));
+  } else {
+    item_of_lane(block, g.C, by_c, t, c);
+  }
+  const long gid = IMAGES ? (long)t * g.C + c : (long)block * 256 + threadIdx.x;
+  const bool active = IMAGES || gid < total;
   if (!active) t = 0, c = 0;
   tile_coords(g, t, b, ty, tx);
   int xi[n][n];
@@ -276,24 +295,46 @@ __device__ __forceinline__ void fbwd_input_body(const int8_t* __restrict__ x,
   flex_right<n, n>(fm.BPT, dR, A);
   float dS[n][n];
   flex_input_grad<n, n>(fm.BPT, A, dS);
+  __shared__ __attribute__((aligned(16))) float s_dx[IMAGES ? n * n * 256 : 4];
   if (active) {
+    auto put = [&](int p, float v) {
+      if constexpr (IMAGES)
+        s_dx[p * 256 + threadIdx.x] = v;
+      else
+        dXt[(long)p * total + gid] = v;
+    };
     if constexpr (LEG) {
       float out[n][n];
       adjoint_bracket_f<TabF<M>::PinvT>(dS, out);
-      static_for<0, n>([&](auto i) {
-        static_for<0, n>([&](auto j) {
-          dXt[(long)(decltype(i)::value * n + decltype(j)::value) * total + gid] = out[i][j];
-        });
-      });
+      static_for<0, n>([&](auto i) { static_for<0, n>([&](auto j) { put(decltype(i)::value * n + decltype(j)::value, out[i][j]); }); });
     } else {
-      static_for<0, n>([&](auto i) {
-        static_for<0, n>([&](auto j) {
-          dXt[(long)(decltype(i)::value * n + decltype(j)::value) * total + gid] = dS[i][j];
-        });
-      });
+      static_for<0, n>([&](auto i) { static_for<0, n>([&](auto j) { put(decltype(i)::value * n + decltype(j)::value, dS[i][j]); }); });
     }
   }
-  store_sums<n>(s_sums, part + (long)block * kPartialStride);
+  store_sums<n>(s_sums, part + (long)block * kPartialStride);      // (a barrier first)
+  if constexpr (IMAGES) {
+    // the pixels of the image, four channels per lane; contributions in the order of k_bwd_tile_sum
+    using v4f = __attribute__((ext_vector_type(4))) float;
+    const int c0 = c & ~(cw - 1);
+    float* dx = dXt + (long)b * g.H * g.W * g.C + c0;
+    for (int e = threadIdx.x; e < (g.H * g.W << cw_bits >> 2); e += 256) {
+      const int pix = e >> (cw_bits - 2), c4 = (4 * e) & (cw - 1);
+      const int h = (int)fast_div((uint32_t)pix, by_w.mul, by_w.sh), w = pix - h * g.W;
+      v4f acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int dyv = 0; dyv < 2; ++dyv) {
+        const int ty1 = (h + 1) / M - dyv, i = (h + 1) % M + dyv * M;
+        if (ty1 < 0 || ty1 >= g.TH || i >= n) continue;
+#pragma unroll
+        for (int dxv = 0; dxv < 2; ++dxv) {
+          const int tx1 = (w + 1) / M - dxv, j = (w + 1) % M + dxv * M;
+          if (tx1 < 0 || tx1 >= g.TW || j >= n) continue;
+          acc += *reinterpret_cast<const v4f*>(s_dx + (i * n + j) * 256 + (ty1 * g.TW + tx1) * cw + c4);
+        }
+      }
+      *reinterpret_cast<v4f*>(dx + (long)pix * g.C + c4) = acc;
+    }
+  }
 }
 
 // dV, w -> dw [k][c][3][3] and the partial sums of dGP (n x 3).
@@ -346,16 +387,17 @@ __device__ __forceinline__ void fbwd_weight_body(const int8_t* __restrict__ w,
 // The input and the filter bracket are independent of each other: one launch, the first
 // nb_w work groups take filters (few, and the longer chain of loads where dV comes in
 // parts: they start first), the rest (tile, channel) items.
-template <int M, bool LEG>
+// dXt: dx itself where IMAGES.
+template <int M, bool LEG, bool IMAGES>
 __global__ __launch_bounds__(256, (M <= 4 ? 4 : 1)) void k_fbwd_input_weight(
     const int8_t* __restrict__ x, const float* __restrict__ dU, float* __restrict__ dXt,
     float* __restrict__ part_in, const int8_t* __restrict__ w, float* __restrict__ dV,
     float* __restrict__ dw, float* __restrict__ part_w, Geometry g, FlexMats fm, StageMults mu,
-    float s_in, float s_w, Divider by_c, unsigned nb_w, int parts) {
+    float s_in, float s_w, Divider by_c, Divider by_w, unsigned nb_w, int parts) {
   if (blockIdx.x < nb_w)
     fbwd_weight_body<M, LEG>(w, dV, dw, part_w, g, fm, s_w, blockIdx.x, parts);
   else
-    fbwd_input_body<M, LEG>(x, dU, dXt, part_in, g, fm, mu, s_in, by_c, blockIdx.x - nb_w);
+    fbwd_input_body<M, LEG, IMAGES>(x, dU, dXt, part_in, g, fm, mu, s_in, by_c, by_w, blockIdx.x - nb_w);
 }
 
 // dx[b][h][w][c] from per-tile gradients: tile ty reads input rows ty*M - 1 ... ty*M + M,
@@ -417,7 +459,7 @@ hipError_t PerMFlexBwd<M>::output(const Geometry& g, bool leg, const void* Mq, i
 
 template <int M>
 hipError_t PerMFlexBwd<M>::input_weight(const Geometry& g, bool leg, const int8_t* x,
-                                        const float* dU, float* dXt, float* part_in,
+                                        const float* dU, float* dXt, float* dx, float* part_in,
                                         const int8_t* w, float* dV, float* dw,
                                         float* part_w, const FlexMats& fm, const StageMults& mu,
                                         float s_in, float s_w, hipStream_t st) {
@@ -425,20 +467,29 @@ hipError_t PerMFlexBwd<M>::input_weight(const Geometry& g, bool leg, const int8_
   const unsigned nb_w = (unsigned)(((long)g.K * g.C + 255) / 256);
   const dim3 grid(nb_in + nb_w), bs(256);
   const int parts = backward_dv_reader_parts(g);
-  if (leg)
-    wino_launch((k_fbwd_input_weight<M, true>), grid, bs, st, x, dU, dXt, part_in, w, dV, dw, part_w,
-                g, fm, mu, s_in, s_w, divider_of(g.C), nb_w, parts);
-  else
-    wino_launch((k_fbwd_input_weight<M, false>), grid, bs, st, x, dU, dXt, part_in, w, dV, dw,
-                part_w, g, fm, mu, s_in, s_w, divider_of(g.C), nb_w, parts);
+  const bool images = fbwd_takes_images(g);
+  const Geometry gi = images ? with_dealt_units(g, (long)g.C * g.TH * g.TW / 256, g.N) : g;
+  float* out = images ? dx : dXt;
+#define WINO_FBWD_IN(LEGV, IMGV)                                                                              \
+  wino_launch((k_fbwd_input_weight<M, LEGV, IMGV>), grid, bs, st, x, dU, out, part_in, w, dV, dw, part_w, gi, \
+              fm, mu, s_in, s_w, divider_of(g.C), divider_of(g.W), nb_w, parts)
+  if (leg) {
+    if (images) WINO_FBWD_IN(true, true);
+    else WINO_FBWD_IN(true, false);
+  } else {
+    if (images) WINO_FBWD_IN(false, true);
+    else WINO_FBWD_IN(false, false);
+  }
+#undef WINO_FBWD_IN
   return hipGetLastError();
 }
 
+// dXt -> dx where the brackets did not leave dx.
 template <int M>
 hipError_t PerMFlexBwd<M>::tile_sum(const Geometry& g, const float* dXt, float* dx,
                                     hipStream_t st) {
   const long rows = (long)g.N * g.H, per_row = (long)g.W * (g.C / 4);
-  if (rows == 0 || per_row == 0) return hipSuccess;
+  if (rows == 0 || per_row == 0 || fbwd_takes_images(g)) return hipSuccess;
   // grid: x over a row's (pixel, 4 channels) items, y and z over the image rows
   const long zs = (rows + 65534) / 65535;
   if (zs > 65535 || per_row >= (1L << 31)) return hipErrorInvalidValue;

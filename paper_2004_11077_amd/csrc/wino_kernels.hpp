@@ -573,7 +573,7 @@ struct PerMFlexBwd {
                            const float* dy, float* dM, float* part, const FlexMats& fm,
                            const StageMults& mu, float s_in, hipStream_t st);
   static hipError_t input_weight(const Geometry& g, bool legendre, const int8_t* x,
-                                 const float* dU, float* dXt, float* part_in, const int8_t* w,
+                                 const float* dU, float* dXt, float* dx, float* part_in, const int8_t* w,
                                  float* dV, float* dw, float* part_w, const FlexMats& fm,
                                  const StageMults& mu, float s_in, float s_w, hipStream_t st);
   static hipError_t tile_sum(const Geometry& g, const float* dXt, float* dx, hipStream_t st);
@@ -586,7 +586,7 @@ hipError_t launch_flex_backward_output(const Geometry& g, bool legendre, const v
                                        const float* dy, float* dM, float* part, const FlexMats& fm,
                                        const StageMults& mu, float s_in, hipStream_t st);
 hipError_t launch_flex_backward_input_weight(const Geometry& g, bool legendre, const int8_t* x,
-                                             const float* dU, float* dXt, float* part_in,
+                                             const float* dU, float* dXt, float* dx, float* part_in,
                                              const int8_t* w, float* dV, float* dw,
                                              float* part_w, const FlexMats& fm,
                                              const StageMults& mu, float s_in, float s_w,
