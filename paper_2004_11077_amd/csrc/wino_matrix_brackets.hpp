@@ -12,7 +12,7 @@
 // The offset that makes the codes unsigned is taken back by two constant entries of the reduction.
 //
 // Why: the brackets are bound by vector issue.  Of the F(4,3) Legendre input transform 608 vector instructions
-// per 64 items become 310 (casts: two operations per code of X1, three per code of U; byte pairs; addresses), and
+// per 64 items become 310 in its loop (casts: two operations per code of X1, three per code of U; pairs; addresses), and
 // 48 matrix instructions run beside them on their own pipe.  Operand transforms of 16384 images, 8x8, C = K =
 // 256: 352 -> 272 us; of 128 images, 16x16, C = K = 128: 10.0 -> 8.6 us.  Its stores (604 MB) take 50 of the
 // 272 us (measured without them), vector issue 180.
