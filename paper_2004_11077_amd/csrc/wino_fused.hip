@@ -318,8 +318,8 @@ __global__ __launch_bounds__(kFW * 64, RAW ? 4 : 6) void k_fused(const int8_t* _
 // tile's channels), or on two where the work group has fewer tiles than waves.  All pixels of the work group are
 // staged at once, beside U_s / M_s (74 KB for 16 tiles; two work groups per compute unit, which the
 // registers allow anyway).  Rows of 64 bytes are permuted (XOR) by the lane group that reads or writes
-// the pixel or point, so that the four groups meet different banks.  8192 tiles, C = K = 64, filters
-// transformed, fp32 output: 23.0 -> 20.5 us; one 32x32 image: 8.1 -> 7.3 (int8 output).  Both phases' vector
+// the pixel or point, so that the four groups meet different banks.  8192 tiles, C = K = 64, raw
+// filters, fp32 output: 27.6 -> 22.2 us a layer (25.1 with ten registers spilled in phase A, see there); one 32x32 image: 8.1 -> 7.3 (int8 output).  Both phases' vector
 // instructions halve; what is left is a chain per work group (pixels, operands, three barriers), two of which
 // share a compute unit.  With the pixels of eight tiles at a time in U_s's free half, as above, the
 // second batch waited for memory again: 28.7 us.
@@ -377,9 +377,11 @@ __global__ __launch_bounds__(kFW * 64, 4)
     const int half = NJ == 4 ? 0 : wave / kFT;
 #pragma unroll 1
     for (int tl = NJ == 4 ? wave : wave % kFT; tl < kFT; tl += kFW) {
+      int gr = grp;                                  // opaque: the nine addresses are formed again in each
+      if constexpr (kFT > kFW) asm volatile("" : "+v"(gr));          // pass, not held over it
       typename InPair::In in;
       static_for<0, 9>([&](auto s) {
-        const int8_t* from = pixels + (mb::pixel<decltype(s)::value>(grp) * kFT + (tl ^ grp)) * 64 + 4 * jl + 2 * half;
+        const int8_t* from = pixels + (mb::pixel<decltype(s)::value>(gr) * kFT + (tl ^ gr)) * 64 + 4 * jl + 2 * half;
         if constexpr (NJ == 4)
           InPair::put(in, s, *reinterpret_cast<const uint32_t*>(from));
         else
