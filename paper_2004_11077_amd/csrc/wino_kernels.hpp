@@ -495,6 +495,19 @@ inline int fused_matrix_tiles(const Geometry& g, int kb) {
   }
   return best;
 }
+// Row and column of a pixel as input_pairs holds them, sixteen bits each (-1 is 65535).
+typedef unsigned short PixelPair __attribute__((ext_vector_type(2)));
+WINO_HOST_DEVICE bool inside_image(PixelPair pixel, PixelPair last) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(pixel, last)) == __builtin_bit_cast(uint32_t, pixel);
+}
+// The input transform of F(4,3) in the Legendre base runs on the matrix pipe (input_pairs) where every pixel of
+// a tile has sixteen-bit coordinates and an image's offsets fit thirty bits.  Tiles reach row 4 TH and column
+// 4 TW, past the image's edge: those, not H and W, must stay below 2^16, or a row of padding would wrap round
+// to row 0.
+inline bool input_on_matrix_pipe(const Geometry& g, int brackets) {
+  return g.m == 4 && brackets == 1 && 4L * g.TH < 65536 && 4L * g.TW < 65536 && (long)g.W * g.C < 65536 &&
+         (long)g.H * g.W * g.C < (1L << 30);
+}
 // Few enough filters (and tiles) for every work group of the fused kernel to transform its own.
 inline bool fused_takes_raw_filters(const Geometry& g) {
   return (long)g.K * g.C <= 1024 && g.T <= 1024;

@@ -682,14 +682,9 @@ __device__ __forceinline__ void input_items(const int8_t* __restrict__ x, int8_t
   }
 }
 
-// F(4,3) in the Legendre base: on the matrix pipe (MX), where an image's rows and offsets fit the
-// sixteen and thirty bits that input_pairs gives them.
+// F(4,3) in the Legendre base: on the matrix pipe (MX) where input_on_matrix_pipe.
 template <bool MX>
 using InputMults = std::conditional_t<MX, mb::PairMults, StageMults>;
-inline bool input_on_matrix_pipe(const Geometry& g, int brackets) {
-  return g.m == 4 && brackets == 1 && g.H < 65535 && g.W < 65535 && (long)g.W * g.C < 65536 &&
-         (long)g.H * g.W * g.C < (1L << 30);
-}
 
 // F(4,3) in the Legendre base: a wave takes 128 (tile, channel) items, eight channels of a tile per lane,
 // a work group two of the 256-item blocks of input_items: pairs of blocks slot, slot + step, ... < pairs.
@@ -710,12 +705,11 @@ __device__ __forceinline__ void input_pairs(const int8_t* __restrict__ x, int8_t
   const int nch = (g.C + 63) >> 6;
   const long pstride = !WHOLE && g.frag ? ((long)(g.T + 15) >> 4) * nch * 1024 : total;
   const long image = (long)g.H * g.W * g.C;
-  typedef unsigned short v2us __attribute__((ext_vector_type(2)));
   // Row and column of the lane's nine pixels in the tile, and the bytes between rows and pixels.  Offsets
   // inside an image: one dot product each, compared with the image's edges two coordinates at a time,
   // and left to the buffer's bounds check where they are outside (which yields zero).
-  const v2us pitch = {(unsigned short)(g.W * g.C), (unsigned short)g.C};
-  const v2us last = {(unsigned short)(g.H - 1), (unsigned short)(g.W - 1)};
+  const PixelPair pitch = {(unsigned short)(g.W * g.C), (unsigned short)g.C};
+  const PixelPair last = {(unsigned short)(g.H - 1), (unsigned short)(g.W - 1)};
   uint32_t rc[5] = {};                             // row, column of two pixels each, a byte apiece
   static_for<0, 9>([&](auto s) {
     constexpr int S = decltype(s)::value;
@@ -753,14 +747,13 @@ __device__ __forceinline__ void input_pairs(const int8_t* __restrict__ x, int8_t
     const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(x) + b0 * image, 0,
                                                         (int)min((g.N - b0) * image, 0xfffffff0L), 0x00020000);
     const unsigned origin = (unsigned)((b - b0) * (int)image + (y0 * g.W + x0) * g.C + c);
-    const v2us corner = {(unsigned short)y0, (unsigned short)x0};
+    const PixelPair corner = {(unsigned short)y0, (unsigned short)x0};
 #pragma unroll
     for (int i = 0; i < 5; ++i) asm volatile("" : "+v"(rc[i]));      // unpacked here, not ahead of the loop
     static_for<0, 9>([&](auto s) {
       constexpr int S = decltype(s)::value;
-      const v2us rowcol = __builtin_bit_cast(v2us, __builtin_amdgcn_perm(0, rc[S / 2], S & 1 ? 0x0c030c02u : 0x0c010c00u));
-      const v2us hw = corner + rowcol;                               // -1 is 65535
-      const bool in_image = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(hw, last)) == __builtin_bit_cast(uint32_t, hw);
+      const PixelPair rowcol = __builtin_bit_cast(PixelPair, __builtin_amdgcn_perm(0, rc[S / 2], S & 1 ? 0x0c030c02u : 0x0c010c00u));
+      const bool in_image = inside_image(corner + rowcol, last);
       const unsigned off = __builtin_amdgcn_udot2(rowcol, pitch, origin, false);
       f.v[s] = __builtin_bit_cast(v2u, __builtin_amdgcn_raw_buffer_load_b64(rsrc, in_image ? (int)off : -1, 0, 0));
     });

@@ -59,6 +59,22 @@ def test_input_transform(shape, frag):
     assert np.array_equal(operands(x, w, wn.Scales.from_dict(sc), frag), ora["U"])
 
 
+# the tallest image of the matrix pipe, and two whose last tiles reach row 65536: beyond sixteen bits it would count
+# as row 0, and the next image's rows would be read for padding
+@pytest.mark.parametrize("H", [65532, 65533, 65534])
+def test_input_transform_tall_images(H):
+    import torch
+    import paper_2004_11077_amd as wn
+    from oracle import quantised as q
+    rng = np.random.default_rng(H)
+    xq = rng.integers(-127, 128, (2, H, 4, 16)).astype(np.int8)
+    wq = rng.integers(-127, 128, (16, 16, 3, 3)).astype(np.int8)
+    cfg, sc = q.LayerConfig(m=4, base="legendre"), dict(s_w=0.01, s_w1=0.02, s_v=0.05, s_m=1.0, s_m1=1.0, s_y=1.0)
+    want = q.input_transform(xq, np.float32(0.02), cfg, q.StageMatrices(cfg), sc, {})
+    x, w = (torch.from_numpy(v).to("cuda:0") for v in (xq, wq))
+    assert np.array_equal(operands(x, w, wn.Scales.from_dict(dict(sc, s_x=0.02)), False), want)
+
+
 @pytest.mark.parametrize("frag,shape", [(False, (1025, 8, 8, 256)), (True, (1100, 8, 8, 192)), (False, (2101, 8, 8, 144))])
 def test_input_transform_work_groups_take_several_blocks(frag, shape):
     """More blocks than work groups; every image's tiles come out as in a batch of eight images."""

@@ -15,3 +15,8 @@ def test_single_kernel_cases_run_the_group_they_name(tmp_path):
 
 def test_dealing_of_block_pairs(tmp_path):
     assert run_host_program(tmp_path, "pair_dealing")[0] == "ok"
+
+
+def test_sixteen_bit_pixel_coordinates(tmp_path):
+    """Tiles reach past the image: 65532 rows are the most whose padding rows do not wrap round to row 0."""
+    assert run_host_program(tmp_path, "pixel_coordinates") == ["ok", "65532", "4095"]
