@@ -504,9 +504,25 @@ WINO_HOST_DEVICE bool inside_image(PixelPair pixel, PixelPair last) {
 // a tile has sixteen-bit coordinates and an image's offsets fit thirty bits.  Tiles reach row 4 TH and column
 // 4 TW, past the image's edge: those, not H and W, must stay below 2^16, or a row of padding would wrap round
 // to row 0.
-inline bool input_on_matrix_pipe(const Geometry& g, int brackets) {
+inline bool input_fits_matrix_pipe(const Geometry& g, int brackets) {
   return g.m == 4 && brackets == 1 && 4L * g.TH < 65536 && 4L * g.TW < 65536 && (long)g.W * g.C < 65536 &&
          (long)g.H * g.W * g.C < (1L << 30);
+}
+// And where it is the faster form.  Each wave reads 10 KB of matrix operands first and takes its 128 items
+// one half after the other, a longer chain than the vector form's, which only pays once there are enough
+// waves; beside filters in one launch, once the items are twice the filters.  us of the launch, vector -> matrix,
+// F(4,3) on 8x8 images, by (tile, channel) items:
+//   items                       32768         65536         98304        131072        262144        524288
+//   C = K = 64,  input     4.32 -> 4.84  4.72 -> 5.24  5.96 -> 5.72  6.40 -> 6.48  8.30 -> 8.60  12.6 -> 12.6
+//   C = K = 256, input     4.20 -> 4.72  4.48 -> 5.04  5.60 -> 5.42  5.76 -> 5.10  7.80 -> 6.76  11.8 -> 11.2
+//   C = K = 256, both      5.76 -> 6.16  6.24 -> 6.64  7.00 -> 7.04  7.36 -> 7.00  8.96 -> 7.98  13.6 -> 12.9
+//   C = K = 512, both      9.40 -> 10.5  9.72 -> 10.6  10.4 -> 11.1  10.5 -> 11.3  11.5 -> 12.2  16.2 -> 15.2
+//   C = K = 256, fragments 7.36 -> 8.18  6.48 -> 6.98  7.76 -> 7.40  7.36 -> 7.16  9.08 -> 7.96  13.8 -> 11.8
+// filters: how many the launch transforms as well (0: the input transform alone).
+constexpr long kMatrixInputItems = 3L << 15;
+inline bool input_on_matrix_pipe(const Geometry& g, int brackets, long filters) {
+  const long items = (long)g.T * g.C;
+  return input_fits_matrix_pipe(g, brackets) && items >= kMatrixInputItems && items >= 2 * filters;
 }
 // Few enough filters (and tiles) for every work group of the fused kernel to transform its own.
 inline bool fused_takes_raw_filters(const Geometry& g) {

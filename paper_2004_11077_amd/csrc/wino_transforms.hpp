@@ -1119,7 +1119,7 @@ hipError_t PerM<M>::input(const Geometry& g0, int br, const int8_t* x, int8_t* U
                           const StageMults& mu, hipStream_t st) {
   const bool leg = br != 0;
   const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
-  const bool mx = input_on_matrix_pipe(g0, br);
+  const bool mx = input_on_matrix_pipe(g0, br, 0);
   const int per = mx ? 2 : 1;                      // 256-item blocks per work group
   const unsigned pairs = (input_blocks(g0) + per - 1) / per;
   const unsigned nb = per == 2 ? min(pairs, kPairGroups) : pairs;
@@ -1137,8 +1137,8 @@ hipError_t PerM<M>::input(const Geometry& g0, int br, const int8_t* x, int8_t* U
     wino_launch((k_input_transform<M, true, false, 2>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (br == 3)
     wino_launch((k_input_transform<M, true, false, 3>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
-  else if (M != 4 && leg && whole)
-    wino_launch((k_input_transform<M, true, M != 4>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
+  else if (leg && whole)
+    wino_launch((k_input_transform<M, true, true>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (leg)
     wino_launch((k_input_transform<M, true, false>), dim3(nb), dim3(256), st, x, U, g, mu, pairs);
   else if (whole)
@@ -1153,7 +1153,7 @@ hipError_t PerM<M>::operands(const Geometry& g0, int br, const int8_t* x, int8_t
                              const int8_t* w, int8_t* V, const StageMults& mu_in,
                              const StageMults& mu_w, hipStream_t st) {
   const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
-  const bool mx = input_on_matrix_pipe(g0, br);
+  const bool mx = input_on_matrix_pipe(g0, br, (long)g0.K * g0.C);
   const int per = mx ? 2 : 1;                      // 256-item input blocks per work group
   const unsigned pairs = (input_blocks(g0) + per - 1) / per;
   const unsigned nb_in = per == 2 ? min(pairs, kPairGroups) : pairs, nb_w = weight_blocks(g0);
@@ -1173,8 +1173,8 @@ hipError_t PerM<M>::operands(const Geometry& g0, int br, const int8_t* x, int8_t
     wino_launch((k_operand_transforms<M, true, false, 2>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (br == 3)
     wino_launch((k_operand_transforms<M, true, false, 3>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
-  else if (M != 4 && leg && whole)
-    wino_launch((k_operand_transforms<M, true, M != 4>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
+  else if (leg && whole)
+    wino_launch((k_operand_transforms<M, true, true>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (leg)
     wino_launch((k_operand_transforms<M, true, false>), grid, bs, st, x, U, w, V, g, mu_in, mu_w, nb_in, pairs);
   else if (whole)

@@ -1,5 +1,5 @@
 // Host check of the sixteen-bit pixel coordinates of the input transform on the matrix pipe: for every image
-// edge that input_on_matrix_pipe admits, each row and column of each tile is inside the image exactly where
+// edge that input_fits_matrix_pipe admits, each row and column of each tile is inside the image exactly where
 // plain integers say so.  Prints the largest height and width admitted.
 #include <cstdio>
 
@@ -29,7 +29,7 @@ int main() {
       g.N = 2, g.m = 4, g.C = g.K = 16;
       g.H = side ? 4 : size, g.W = side ? size : 4;
       g.TH = (g.H + 3) / 4, g.TW = (g.W + 3) / 4, g.T = g.N * g.TH * g.TW;
-      if (!wino::input_on_matrix_pipe(g, 1)) continue;
+      if (!wino::input_fits_matrix_pipe(g, 1)) continue;
       (side ? widest : tallest) = size;
       if (!edge_ok(g.H, g.TH) || !edge_ok(g.W, g.TW)) return 1;
     }

@@ -44,7 +44,7 @@ def operands(x, w, sc, frag):
     return wn.defragment(u, d.n ** 2, d.tiles, C) if frag else u.reshape(d.n ** 2, d.tiles, C)
 
 
-# the last one: rows of 65536 bytes, which the general form transforms
+# the last one: rows of 65536 bytes; all of them few enough items for the general form
 @pytest.mark.parametrize("frag", [False, True])
 @pytest.mark.parametrize("shape", [(1, 4, 4, 16), (3, 5, 6, 48), (1, 9, 13, 80), (5, 4, 4, 256), (2, 7, 9, 272),
                                    (1, 4, 4096, 16)])
@@ -59,15 +59,27 @@ def test_input_transform(shape, frag):
     assert np.array_equal(operands(x, w, wn.Scales.from_dict(sc), frag), ora["U"])
 
 
+# enough items for the matrix pipe (test_matrix_rules.py): images of one tile, ragged edges, channels that do not fill 64,
+# whole tiles with an odd number of blocks, a partial last block, rows of nearly 65536 bytes
+MATRIX_INPUTS = [(6145, 4, 4, 16), (513, 9, 13, 16), (260, 5, 15, 48), (193, 7, 9, 128), (385, 4, 4, 256), (65, 7, 9, 272),
+                 (129, 6, 8, 512), (1, 27, 4095, 16)]
+
+
+@pytest.mark.parametrize("frag", [False, True])
+@pytest.mark.parametrize("shape", MATRIX_INPUTS)
+def test_input_transform_on_the_matrix_pipe(shape, frag):
+    test_input_transform(shape, frag)
+
+
 # the tallest image of the matrix pipe, and two whose last tiles reach row 65536: beyond sixteen bits it would count
-# as row 0, and the next image's rows would be read for padding
-@pytest.mark.parametrize("H", [65532, 65533, 65534])
-def test_input_transform_tall_images(H):
+# as row 0, and the next image's rows would be read for padding; rows of 65536 bytes, which the general form takes too
+@pytest.mark.parametrize("H,W", [(65532, 4), (65533, 4), (65534, 4), (27, 4096)])
+def test_input_transform_large_images(H, W):
     import torch
     import paper_2004_11077_amd as wn
     from oracle import quantised as q
     rng = np.random.default_rng(H)
-    xq = rng.integers(-127, 128, (2, H, 4, 16)).astype(np.int8)
+    xq = rng.integers(-127, 128, (2, H, W, 16)).astype(np.int8)
     wq = rng.integers(-127, 128, (16, 16, 3, 3)).astype(np.int8)
     cfg, sc = q.LayerConfig(m=4, base="legendre"), dict(s_w=0.01, s_w1=0.02, s_v=0.05, s_m=1.0, s_m1=1.0, s_y=1.0)
     want = q.input_transform(xq, np.float32(0.02), cfg, q.StageMatrices(cfg), sc, {})

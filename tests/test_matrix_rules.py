@@ -20,3 +20,23 @@ def test_dealing_of_block_pairs(tmp_path):
 def test_sixteen_bit_pixel_coordinates(tmp_path):
     """Tiles reach past the image: 65532 rows are the most whose padding rows do not wrap round to row 0."""
     assert run_host_program(tmp_path, "pixel_coordinates") == ["ok", "65532", "4095"]
+
+
+# N, H, W, C, K: routes of input alone, input beside filters
+INPUT_LINES = [((1535, 8, 8, 16, 16), "00"), ((1536, 8, 8, 16, 16), "11"),      # 3 * 2^15 items
+               ((511, 4, 4, 512, 512), "10"), ((1024, 4, 4, 512, 512), "11"),   # twice the filters
+               ((1023, 4, 4, 512, 512), "10")]
+
+
+def routes(tmp_path, layers):
+    return run_host_program(tmp_path, "matrix_routes", [str(v) for layer in layers for v in layer])
+
+
+def test_lines_between_vector_and_matrix_form(tmp_path):
+    lines = INPUT_LINES
+    assert routes(tmp_path, [layer for layer, _ in lines]) == [want for _, want in lines]
+
+
+def test_input_cases_run_on_the_matrix_pipe(tmp_path):
+    got = routes(tmp_path, [(*shape, 16) for shape in brackets.MATRIX_INPUTS])
+    assert all(r.startswith("11") for r in got)
