@@ -524,6 +524,29 @@ inline bool input_on_matrix_pipe(const Geometry& g, int brackets, long filters) 
   const long items = (long)g.T * g.C;
   return input_fits_matrix_pipe(g, brackets) && items >= kMatrixInputItems && items >= 2 * filters;
 }
+// Output transform of F(4,3) in the Legendre base from an int8 M: on the matrix pipe (k_output_pairs) where
+// offsets into M and into a few images of y fit 32 bits and it is the faster form, by the items of a point's
+// plane, T K.  us in a layer with one kernel per stage, vector -> matrix (8x8 images):
+//   items            2^16          2^18          2^19       3 * 2^18       2^20       3 * 2^19       2^21       3 * 2^20
+//   fp32 K = 64   5.5 ->  4.8   8.0 ->  6.0  12.2 -> 14.8  18.1 -> 18.4  24.9 -> 25.1  35.7 -> 32.9  45.4 -> 49.4
+//        K = 128                8.2 ->  6.3  12.4 -> 14.7                25.2 -> 23.8  35.5 -> 34.8  45.2 -> 49.0  67.3 -> 62.7
+//        K = 256  5.3 ->  4.7   7.8 ->  6.4  11.4 -> 14.6                22.6 -> 24.1                39.3 -> 49.7  56.8 -> 63.0
+//   int8 K = 64   5.4 ->  4.5   8.3 ->  5.7  12.9 -> 10.6  18.4 -> 13.6  24.3 -> 19.5  34.7 -> 22.5  43.7 -> 34.6
+//        K = 256  5.2 ->  4.6   8.1 ->  6.1  12.2 -> 11.2                18.8 -> 19.0                32.3 -> 36.1  45.6 -> 41.7
+// So: int8 y everywhere but on whole tiles (K a multiple of 256, which have a vector form of their own) whose planes are
+// a multiple of 2 MiB apart, which puts the nine planes a lane reads on the same channels; fp32 y up to 3 * 2^17 items
+// (layers of 6 * 2^16: -2 to -5 %, of 7 * 2^16: +1 to +2.6 % up to K = 64), and from 2^20 where neither holds (a store
+// of whole tiles is a KiB of a pixel there, 256 bytes here).  Beyond
+// 192 MB of M, more than the last-level cache keeps of it, never: loads of 64 bytes then cost more than the
+// arithmetic saves (2^24 items, K = 256: 285 / 240 us, fp32 / int8 y, against 348 at best).
+constexpr long kMatrixOutputBytes = 192L << 20;
+inline bool output_on_matrix_pipe(const Geometry& g, int out_type) {
+  const long items = (long)g.T * g.K;
+  if (36 * items > kMatrixOutputBytes || (long)g.H * g.W * g.K * 4 >= (1L << 30)) return false;
+  const bool whole = whole_tiles(g.K, g.H, g.W), same_channels = items % (1L << 21) == 0;
+  if (out_type == 2) return !(whole && same_channels);
+  return items <= 3L << 17 || (!whole && !same_channels && items >= 1L << 20);
+}
 // Few enough filters (and tiles) for every work group of the fused kernel to transform its own.
 inline bool fused_takes_raw_filters(const Geometry& g) {
   return (long)g.K * g.C <= 1024 && g.T <= 1024;

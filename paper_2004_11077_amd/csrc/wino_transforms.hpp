@@ -1012,12 +1012,9 @@ __global__ __launch_bounds__(256) void k_output_transform(const MT* __restrict__
 // gridDim.x, ... < pairs.  The codes of a half are fetched while the other half is computed.  Loads and
 // stores are unconditional: what is outside the image or the tensor is left to the buffer's bounds check, so
 // that a wait for the next codes never waits for stores.
-// us, vector ALU -> matrix pipe, fp32 / int8 y: 256 tiles, K = 512: 5.4 / 5.2 -> 4.8 / 4.4; 2048 tiles, K = 256: 9.9 /
-// 10.5 -> 9.1 / 7.8; 16384: 74.7 / 65.0 -> 67.5 / 44.9 (8x8 images).  Not where M is beyond what the last-level
-// cache holds (kMatrixOutputBytes): its loads of 64 bytes then cost more than the arithmetic saves, 32768
-// tiles 143 / 121 -> 187 / 121.  Not for a 9-bit M: 3.9 -> 4.4 us at 64 tiles, 25.4 -> 35.0 at 4096.
+// Where it is faster than the vector form: output_on_matrix_pipe.  Not for a 9-bit M: 3.9 -> 4.4 us at 64 tiles,
+// 25.4 -> 35.0 at 4096.
 // ---------------------------------------------------------------------------
-constexpr long kMatrixOutputBytes = 192L << 20;
 template <int OUT>
 __global__ __launch_bounds__(256, 3) void k_output_pairs(const int8_t* __restrict__ Mq, void* __restrict__ yv,
                                                          Geometry g, mb::PairMults mu, Divider by_k, int relu,
@@ -1083,12 +1080,6 @@ __global__ __launch_bounds__(256, 3) void k_output_pairs(const int8_t* __restric
     if (!more) break;
   }
 }
-// (offsets into M and into a few images of y then fit 32 bits, an item index 30)
-inline bool output_on_matrix_pipe(const Geometry& g, int out_type, const StageMults& mu) {
-  return 36L * g.T * g.K <= kMatrixOutputBytes && (long)g.H * g.W * g.K * 4 < (1L << 30) &&
-         (out_type == 2 || (out_type == 0 && mb::output_mults_fit(mu)));
-}
-
 // ---------------------------------------------------------------------------
 // Launchers of one M
 // ---------------------------------------------------------------------------
@@ -1215,7 +1206,7 @@ static hipError_t output_mt(const Geometry& g, const void* Mq, void* y, int out_
   }
   const ShiftTable none{};
   if constexpr (M == 4 && LEG && sizeof(MT) == 1)
-    if (output_on_matrix_pipe(g, out_type, mu)) {
+    if (output_on_matrix_pipe(g, out_type) && (out_type == 2 || (out_type == 0 && mb::output_mults_fit(mu)))) {
       const unsigned pairs = (blocks_for((long)g.T * g.K) + 1) / 2;
       const dim3 nb(min(pairs, kPairGroups)), bs(256);
       const Geometry gp = whole_tiles(g.K, g.H, g.W) ? with_output_groups(g, 2) : with_dealt_units(g, 0, 0);

@@ -128,18 +128,24 @@ def test_output_transform(shape, out_type, relu):
     assert_layer_parity(ora, gpu_layer(xq, wq, sc, **kw), out_type)
 
 
-@pytest.mark.parametrize("N,H,W,K", [(513, 16, 16, 208), (1030, 8, 8, 256)])
-def test_output_transform_work_groups_take_several_blocks(N, H, W, K):
+# The whole batch and eight of its images at a time: several blocks per work group (513 and 1030 images), and batches on
+# either side of the lines between the two forms (OUTPUT_LINES in test_matrix_rules.py).
+@pytest.mark.parametrize("N,H,W,K,out_type", [
+    (513, 16, 16, 208, "f32"), (1030, 8, 8, 256, "f32"), (1030, 8, 8, 256, "i8"),
+    (1536, 8, 8, 64, "f32"), (1537, 8, 8, 64, "f32"), (4095, 8, 8, 64, "f32"), (4096, 8, 8, 64, "f32"),
+    (8192, 8, 8, 64, "f32"), (8192, 8, 8, 64, "i8"), (2048, 8, 8, 256, "i8"), (2049, 8, 8, 256, "i8")])
+def test_output_transform_work_groups_take_several_blocks(N, H, W, K, out_type):
     import torch
     import paper_2004_11077_amd as wn
-    sc = wn.Scales.from_dict(dict(s_x=0.02, s_w=0.01, s_x1=0.03, s_w1=0.02, s_u=0.1, s_v=0.05, s_m=1.0, s_m1=1.5))
+    sc = wn.Scales.from_dict(dict(s_x=0.02, s_w=0.01, s_x1=0.03, s_w1=0.02, s_u=0.1, s_v=0.05, s_m=1.0, s_m1=1.5, s_y=20.0))
     gen = torch.Generator(device="cuda:0").manual_seed(2)
     per = (H // 4) * (W // 4)
     M = torch.randint(-127, 128, (36, N * per, K), generator=gen, dtype=torch.int8, device="cuda:0")
 
     def outputs(m, n):
-        d = wn.ConvDesc(n, H, W, 16, K, m=4, base=wn.BASE_LEGENDRE)
-        y = torch.full((n, H, W, K), 7.0, device="cuda:0")
+        d = wn.ConvDesc(n, H, W, 16, K, m=4, base=wn.BASE_LEGENDRE,
+                        out_type=wn.OUT_I8 if out_type == "i8" else wn.OUT_F32)
+        y = torch.full((n, H, W, K), 7, dtype=torch.int8 if out_type == "i8" else torch.float32, device="cuda:0")
         return wn.wino_output_transform(d, m, y, sc)
 
     y = outputs(M, N)

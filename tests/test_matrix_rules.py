@@ -22,10 +22,15 @@ def test_sixteen_bit_pixel_coordinates(tmp_path):
     assert run_host_program(tmp_path, "pixel_coordinates") == ["ok", "65532", "4095"]
 
 
-# N, H, W, C, K: routes of input alone, input beside filters
-INPUT_LINES = [((1535, 8, 8, 16, 16), "00"), ((1536, 8, 8, 16, 16), "11"),      # 3 * 2^15 items
-               ((511, 4, 4, 512, 512), "10"), ((1024, 4, 4, 512, 512), "11"),   # twice the filters
-               ((1023, 4, 4, 512, 512), "10")]
+# N, H, W, C, K: routes of input alone, input beside filters, output to fp32, output to int8 (int8 M)
+INPUT_LINES = [((1535, 8, 8, 16, 16), "0011"), ((1536, 8, 8, 16, 16), "1111"),      # 3 * 2^15 items
+               ((511, 4, 4, 512, 512), "1011"), ((1024, 4, 4, 512, 512), "1101"),   # twice the filters
+               ((1023, 4, 4, 512, 512), "1001")]
+OUTPUT_LINES = [((1536, 8, 8, 64, 64), "1111"), ((1537, 8, 8, 64, 64), "1101"),      # 3 * 2^17 items
+                ((4095, 8, 8, 64, 64), "1101"), ((4096, 8, 8, 64, 64), "1111"),      # 2^20
+                ((8192, 8, 8, 64, 64), "1101"), ((2048, 8, 8, 256, 256), "1100"),    # 2^21: planes 2 MiB apart
+                ((2049, 8, 8, 256, 256), "1101"),                                    # whole tiles
+                ((4096, 16, 16, 85 * 16, 16), "1111"), ((4096, 16, 16, 96, 96), "1100")]  # more than 192 MB of M
 
 
 def routes(tmp_path, layers):
@@ -33,7 +38,7 @@ def routes(tmp_path, layers):
 
 
 def test_lines_between_vector_and_matrix_form(tmp_path):
-    lines = INPUT_LINES
+    lines = INPUT_LINES + OUTPUT_LINES
     assert routes(tmp_path, [layer for layer, _ in lines]) == [want for _, want in lines]
 
 
