@@ -291,8 +291,11 @@ __global__ __launch_bounds__(NW * 64, WPE) void k_contract_out(const int8_t* __r
     // a wave: 16 columns of four output channels, i.e. the 32 channels of two tiles, per pass
     const int grp = lane >> 4;
     if constexpr (!FRAG) pair.load(mu, lane);
+    // A partial block's missing tiles are left out: one 8x8 image, C = 128, K = 16, kernel us with all TB tiles 7.1,
+    // without 6.5 (vector ALU 6.4).
+    const int tiles = min(TB, g.T - t0);
 #pragma unroll 1
-    for (int tl2 = wave; tl2 < TB / 2; tl2 += NW) {
+    for (int tl2 = wave; 2 * tl2 < tiles; tl2 += NW) {
       const int tl = 2 * tl2 + ((lane >> 3) & 1), kq = lane & 7;
       const int k = k0 + 4 * kq;
       const int at = (tl ^ (2 * grp)) * KB + ((kq ^ (tl & 7)) << 2);
