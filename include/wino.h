@@ -23,7 +23,12 @@
  * throws or aborts; wino_last_error() gives the text of the last failure on
  * the calling thread.  Functions taking a stream are asynchronous on it,
  * allocate nothing and never synchronise; all device buffers, the workspace
- * included, are owned by the caller.
+ * included, are owned by the caller.  The two calibration calls are the
+ * exception: they synchronise the stream (so they cannot be captured), and
+ * wino_flex_calibrate reads its scales back into page-locked host memory, at
+ * most eight buffers of 1 KiB that the library allocates (hipHostMalloc) when
+ * calls first need them, shares between threads and keeps until the process
+ * ends.
  */
 #ifndef WINO_H
 #define WINO_H
@@ -297,7 +302,8 @@ typedef struct {
  * wino_flex_calibrate is wino_calibrate for this variant (same workspace
  * size, same rule: scale = float(max |real| / qmax) stage after stage), cheap
  * enough for a training step: the scales are chosen on the device and the
- * stream is synchronised once, at the end.
+ * stream is synchronised once, at the end.  A process's first call, and the
+ * first ones that overlap in time, allocate page-locked host memory (see above).
  * Errors as for the static calls, plus EINVAL for a null, non-finite or
  * too large matrix entry. */
 int wino_flex_weight_transform(const wino_conv_desc_t* d, const wino_flex_matrices_t* f,

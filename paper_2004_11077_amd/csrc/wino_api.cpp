@@ -6,11 +6,11 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 
 #include "wino_kernels.hpp"
+#include "wino_readback.hpp"
 #include "wino_tables.hpp"
 
 using namespace wino;
@@ -1376,52 +1376,6 @@ int wino_flex_conv2d(const wino_conv_desc_t* d, const wino_flex_matrices_t* f, c
   return wino_flex_output_transform(&dd, f, M, y, s, hip_stream);
 }
 
-namespace {
-// A small page-locked buffer for one read-back: the copy then goes straight to it (7 us less than to
-// pageable memory, of the 265 of a training step).  At most kReadBacks exist, held by the calls under way on all
-// threads and kept for the next ones; without a free one, or if none can be had, `ptr` is null.
-class ReadBack {
- public:
-  static constexpr size_t kBytes = 1024;
-  ReadBack() {
-    std::lock_guard<std::mutex> lock(mutex());
-    Pool& p = pool();
-    if (p.free > 0) {
-      ptr = p.bufs[--p.free];
-    } else if (p.made < kReadBacks) {
-      if (hipHostMalloc(&ptr, kBytes, hipHostMallocPortable) == hipSuccess)
-        ++p.made;
-      else
-        ptr = nullptr, (void)hipGetLastError();
-    }
-  }
-  ~ReadBack() {
-    if (!ptr) return;
-    std::lock_guard<std::mutex> lock(mutex());
-    Pool& p = pool();
-    p.bufs[p.free++] = ptr;
-  }
-  ReadBack(const ReadBack&) = delete;
-  ReadBack& operator=(const ReadBack&) = delete;
-  void* ptr = nullptr;
-
- private:
-  static constexpr int kReadBacks = 8;
-  struct Pool {
-    void* bufs[kReadBacks];
-    int free = 0, made = 0;
-  };
-  static Pool& pool() {
-    static Pool p;
-    return p;
-  }
-  static std::mutex& mutex() {
-    static std::mutex m;
-    return m;
-  }
-};
-}  // namespace
-
 int wino_flex_calibrate(const wino_conv_desc_t* d, const wino_flex_matrices_t* f, const void* x,
                         const void* w, void* y, wino_scales_t* s, void* workspace,
                         size_t ws_bytes, void* hip_stream) {
@@ -1467,6 +1421,7 @@ int wino_flex_calibrate(const wino_conv_desc_t* d, const wino_flex_matrices_t* f
   if (e != hipSuccess) return fail_hip(e, "flex calibration read-back");
   std::memcpy(&got.y[0], back, sizeof got.y[0]);
   std::memcpy(got.scales, back + y_bytes, sizeof got.scales);
+  pinned.done();
   // A scale that underflowed to zero or overflowed is refused as the stage call that would take it
   // refuses it (U, V and M then hold nothing of use); s_m1 only where a stage call takes it, below.
   StageMults mu_unused;

@@ -81,3 +81,35 @@ def test_scales_that_no_stage_call_takes_are_refused(m, base, bh, s_x, s_w, size
     # the same call with ordinary scales goes through
     sc = wn.wino_flex_calibrate(desc, wn.FlexMatrices(fm.GP, fm.BPT, fm.APT), x, w, y, 0.1, 0.1, ws)
     assert 0 < sc.s_u < np.inf and 0 < sc.s_v < np.inf and 0 < sc.s_m < np.inf
+
+
+def test_calibrations_on_several_threads_and_streams():
+    """More threads than read-back buffers, each with a layer and a stream of its own: every one gets its scales."""
+    import threading
+    import torch
+    import paper_2004_11077_amd as wn
+    fm = noisy_matrices(4, "legendre", seed=9)
+    gfm = wn.FlexMatrices(fm.GP, fm.BPT, fm.APT)
+    desc = wn.ConvDesc(2, 9, 9, 16, 16, m=4, base=wn.BASE_LEGENDRE)
+    calls = []
+    for i in range(10):
+        xq, wq, s_x, s_w = small_layer(2, 9, 9, 16, 16, seed=60 + i)
+        x, w = torch.from_numpy(xq).cuda(), torch.from_numpy(wq).cuda()
+        ws = torch.empty(wn.wino_calibrate_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+        calls.append((desc, gfm, x, w, None, float(s_x) * (i + 1), float(s_w), ws, torch.cuda.Stream()))
+    torch.cuda.synchronize()
+
+    def scales(call):
+        sc = wn.wino_flex_calibrate(*call)
+        return [getattr(sc, k) for k in wn.Scales.SCALARS]
+
+    want = [scales(c) for c in calls]
+    got = [[] for _ in calls]
+    threads = [threading.Thread(target=lambda i=i: got[i].extend(scales(calls[i]) for _ in range(25)))
+               for i in range(len(calls))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len({tuple(v) for v in want}) == len(calls)
+    assert all(len(g) == 25 and all(v == w for v in g) for g, w in zip(got, want))

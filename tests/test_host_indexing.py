@@ -41,3 +41,8 @@ def test_index_dividers_are_exact(tmp_path):
 def test_work_groups_are_dealt_one_to_one_with_a_unit_on_one_xcd(tmp_path):
     word, shapes, dealt, aligned = run_host_program(tmp_path, "image_groups")
     assert word == "ok" and int(shapes) == 2 * 3 * 9 * 7 * 7 and int(dealt) > 300 and int(aligned) > 10
+
+
+@needs_hipcc
+def test_read_back_buffers_are_not_shared_and_not_reused_before_they_are_given_back(tmp_path):
+    assert run_host_program(tmp_path, "read_backs") == ["ok"]
