@@ -628,11 +628,13 @@ def main():
                     "int8 codes, exact to fp32 accumulation, on the bf16 matrix pipe (3 MFMAs per product)"}
         # the same for the flex layer (run-time matrices: here the static ones rounded to
         # fp32), which also returns the gradients of G_P, B_P, A_P; its launches but the last (which
-        # sums the partial matrix gradients) timed.  Images of 1, 2, 4, 8 or 16 tiles need no sum over
-        # tiles of its own.
+        # sums the partial matrix gradients) timed.  The sum over tiles is a launch of its own where
+        # the workspace has a region for per-tile dX besides dM, dU, dV and the partial sums.
         fnames = ("dY_M_to_dM_dAPT", "gemm_dV_and_dU") + extra_launch + ("input_and_filter_brackets",)
-        per_image = sdesc.tiles // sdesc.N
-        if per_image not in (1, 2, 4, 8, 16) or sdesc.C % (256 // per_image):
+        up = lambda v: -(-v // 256)
+        others = 256 * sum(up(4 * n2 * v) + up(v // p) for v, p in (
+            (T * wl.K, 1), (T * wl.C, 1), (parts * wl.K * wl.C, parts)))
+        if wn.wino_flex_backward_workspace_bytes(sdesc) > others:
             fnames += ("tile_dX_to_dx",)
         bfm = wn.FlexMatrices(*[np.array([[float(v) for v in row] for row in getattr(mats, nm)],
                                          dtype=np.float32) for nm in ("GP", "BPT", "APT")])

@@ -378,7 +378,8 @@ int wino_backward(const wino_conv_desc_t* d, const void* dy, const void* U, cons
  * Workspace (device, 256-byte aligned), wino_flex_backward_workspace_bytes():
  * fp32 dM [n*n][T][K], dU [n*n][T][C], dV [n*n][K][C] (plus its partial sums, as
  * in wino_backward), per-tile dX [n*n][T][C] (each region rounded up to 256
- * bytes), then the partial sums of the matrix gradients.
+ * bytes; none where an image is 1, 2, 4, 8 or 16 tiles and C a multiple of
+ * 256 / tiles), then the partial sums of the matrix gradients.
  * Errors: EINVAL, EUNSUPPORTED, EWORKSPACE, EHIP. */
 typedef struct {
   void* dGP;

@@ -1462,7 +1462,7 @@ FlexBwdLayout flex_bwd_layout(const Geometry& g) {
   l.dM = o;  o += round256(n2 * T * K * 4);
   l.dU = o;  o += round256(n2 * T * C * 4);
   l.dV = o;  o += round256((size_t)backward_dv_splits(g) * n2 * K * C * 4);
-  l.dXt = o; o += round256(n2 * T * C * 4);
+  l.dXt = o; o += flex_backward_takes_images(g) ? 0 : round256(n2 * T * C * 4);
   l.part_out = o; o += (size_t)l.out_blocks * 256;
   l.part_in = o;  o += (size_t)l.in_blocks * 256;
   l.part_w = o;   o += (size_t)l.w_blocks * 256;

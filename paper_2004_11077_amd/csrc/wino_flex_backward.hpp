@@ -9,7 +9,7 @@
 //   k_fbwd_output   dY, M  -> dM, per-block partial sums of dA_P^T
 //   fbwd_input_body   dU, x  -> per-tile dX, per-block partial sums of dB_P^T   \ one launch,
 //   fbwd_weight_body  dV, w  -> dw, per-block partial sums of dG_P              / k_fbwd_input_weight
-//                     (dx itself where a work group takes whole images, fbwd_takes_images)
+//                     (dx itself where a work group takes whole images, flex_backward_takes_images)
 //   k_bwd_tile_sum  per-tile dX -> dx elsewhere (fixed order over the <= 4 covering tiles)
 //   k_sum_partials  partial sums -> the three matrix gradients (fixed order)
 // The two contraction gradients between them are those of the static layer.
@@ -228,14 +228,6 @@ __global__ __launch_bounds__(256) void k_fbwd_output(const MT* __restrict__ Mq,
     }
   }
   store_sums<M>(s_sums, part + (long)blockIdx.x * kPartialStride);
-}
-
-// A work group of the input bracket can take all tiles of an image, 1, 2, 4, 8 or 16, for 256 / tiles channels: the
-// sum over the tiles that cover a pixel then needs no tensor of per-tile gradients (written and read, 38 MB
-// each for 128 images of 16x16, C = 128) and no launch of its own: 27.5 + 9.6 -> 32.4 us there, the step 9 us less.
-inline bool fbwd_takes_images(const Geometry& g) {
-  const int tiles = g.TH * g.TW;
-  return tiles <= 16 && (tiles & (tiles - 1)) == 0 && g.C % (256 / tiles) == 0 && (long)g.H * g.W * g.C < (1L << 29);
 }
 
 // dU, x -> per-tile dX [a*n+b][t][c] (IMAGES: dx) and the partial sums of dBPT (n x n).
@@ -467,7 +459,7 @@ hipError_t PerMFlexBwd<M>::input_weight(const Geometry& g, bool leg, const int8_
   const unsigned nb_w = (unsigned)(((long)g.K * g.C + 255) / 256);
   const dim3 grid(nb_in + nb_w), bs(256);
   const int parts = backward_dv_reader_parts(g);
-  const bool images = fbwd_takes_images(g);
+  const bool images = flex_backward_takes_images(g);
   const Geometry gi = images ? with_dealt_units(g, (long)g.C * g.TH * g.TW / 256, g.N) : g;
   float* out = images ? dx : dXt;
 #define WINO_FBWD_IN(LEGV, IMGV)                                                                              \
@@ -489,7 +481,7 @@ template <int M>
 hipError_t PerMFlexBwd<M>::tile_sum(const Geometry& g, const float* dXt, float* dx,
                                     hipStream_t st) {
   const long rows = (long)g.N * g.H, per_row = (long)g.W * (g.C / 4);
-  if (rows == 0 || per_row == 0 || fbwd_takes_images(g)) return hipSuccess;
+  if (rows == 0 || per_row == 0 || flex_backward_takes_images(g)) return hipSuccess;
   // grid: x over a row's (pixel, 4 channels) items, y and z over the image rows
   const long zs = (rows + 65534) / 65535;
   if (zs > 65535 || per_row >= (1L << 31)) return hipErrorInvalidValue;

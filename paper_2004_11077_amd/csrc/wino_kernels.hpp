@@ -547,6 +547,21 @@ inline bool output_on_matrix_pipe(const Geometry& g, int out_type) {
   if (out_type == 2) return !(whole && same_channels);
   return items <= 3L << 17 || (!whole && !same_channels && items >= 1L << 20);
 }
+// A work group of the input bracket of the flex backward pass can take all tiles of an image, 1, 2, 4, 8 or 16, for
+// 256 / tiles channels: the sum over the tiles that cover a pixel then needs no tensor of per-tile gradients (written
+// and read, 38 MB each for 128 images of 16x16, C = 128) and no launch of its own: 27.5 + 9.6 -> 32.4 us there, the
+// training step 9 us less.  Whole backward passes, us, per-tile gradients -> whole images, Legendre, C = K = 128 unless
+// said otherwise:
+//   tiles                        1 (64 images)      2 (64)         4 (256)          8 (64)         16 (128)
+//   F(2,3)  C = K = 512 at 1     41.8 ->  39.0   23.1 -> 20.6   37.6 ->  35.5   29.8 -> 26.2    47.3 ->  41.6
+//   F(4,3)  C = K = 512 at 1     54.3 ->  53.6   32.6 -> 29.8   57.3 ->  51.9   45.2 -> 43.9    88.5 ->  82.7
+//   F(6,3)  C = K = 512 at 1     93.4 ->  89.6   53.4 -> 51.8  107.6 ->  96.8   70.8 -> 65.9   187.6 -> 156.1
+// (one or two images of C = K = 64: 18.6 -> 16.1, 26.2 -> 24.1, 42.8 -> 43.0 for F(2,3), F(4,3), F(6,3).)
+inline bool flex_backward_takes_images(const Geometry& g) {
+  const int tiles = g.TH * g.TW;
+  return tiles >= 1 && tiles <= 16 && (tiles & (tiles - 1)) == 0 && g.C % (256 / tiles) == 0 &&
+         (long)g.H * g.W * g.C < (1L << 29);
+}
 // Few enough filters (and tiles) for every work group of the fused kernel to transform its own.
 inline bool fused_takes_raw_filters(const Geometry& g) {
   return (long)g.K * g.C <= 1024 && g.T <= 1024;

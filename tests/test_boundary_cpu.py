@@ -319,6 +319,11 @@ def test_flex_backward_argument_checks_before_any_launch():
     tensors = r256(36 * 8 * 48 * 4) + 2 * r256(36 * 8 * 32 * 4) + r256(36 * 48 * 32 * 4)
     blocks = -(-8 * 48 // 256) + -(-8 * 32 // 256) + -(-48 * 32 // 256)
     assert wn.wino_flex_backward_workspace_bytes(d) == tensors + blocks * 256
+    # images of four tiles, C a multiple of 64: no per-tile dX
+    d64 = wn.ConvDesc(2, 8, 8, 64, 48)
+    assert wn.wino_flex_backward_workspace_bytes(d64) == (
+        r256(36 * 8 * 48 * 4) + r256(36 * 8 * 64 * 4) + r256(36 * 48 * 64 * 4)
+        + 256 * (-(-8 * 48 // 256) + -(-8 * 64 // 256) + -(-48 * 64 // 256)))
     good = wn.FlexMatrices(np.ones((6, 3)), np.ones((6, 6)), np.ones((4, 6)))
     s = wn.Scales.from_dict({})
     grads = binding.FlexGrads(4096, 4096, 4096)
