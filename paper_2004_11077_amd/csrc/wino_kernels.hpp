@@ -472,28 +472,22 @@ inline int fused_tiles(const Geometry& g, int kb) {
   return best;
 }
 // The same for the single kernel with its brackets on the matrix pipe (F(4,3), Legendre base, one scale per
-// tensor): us per layer with transformed filters, C = K = 64, int8 output, against the kernel above ("vector").  The
-// rows of 16 tiles are from a build that spilled ten registers; at 8192 tiles the layer has since gained 2.9 us.
-//   tiles              256   1024   2048   3072   4096   6144   8192  10240  12288  16384  32768
-//   8-bit M  16       12.7   12.9   13.1   13.3   13.6   19.8   20.7   28.3   29.3   38.3   76.1
-//             8        8.6    8.6    8.7   12.3   12.4   18.3   23.4   28.6   34.0   44.9   89.8
-//             4        7.7    8.0   11.3   16.3   20.2   28.9   38.0   47.0   56.1   74.3  148.0
-//        vector        8.2    8.5   10.2   13.8   15.0   19.9   23.8   30.5   31.6   40.7   77.8
-//   9-bit M  16       10.9   11.5   12.1   16.9   17.6   24.5   31.2   38.5   44.9   59.6  121.1
-//             8        8.1    8.5   11.2   16.1   19.8   28.3   36.3   44.1   52.0   67.9  137.7
-//             4        6.6    9.0   15.5   22.0   28.4   41.3   54.3   67.1   79.9  105.6  212.9
-//        vector        7.3    8.8   12.2   15.9   19.3   26.1   33.8   40.8   47.3   62.1  124.1
+// tensor): the smallest groups of which there is at most one per compute unit, else the largest.  us per layer with
+// transformed filters, C = K = 64, int8 output, against the kernel above ("vector", in groups of its own rule):
+//   tiles              256   1024   1536   2048   3072   4096   6144   8192  10240  12288  16384  32768
+//   8-bit M   4        7.3    8.1   11.1   11.2   16.2   20.1   28.9   38.0   47.0   56.2   74.4  148.1
+//             8        8.7    8.7    8.8    8.7   12.3   12.4   18.3   23.3   28.6   34.0   44.9   90.0
+//            16       11.6   11.6   11.8   11.6   11.8   11.9   17.1   17.3   24.8   25.0   32.6   65.3
+//        vector        8.2    8.5          10.2   13.8   15.0   19.9   23.8   30.5   31.6   40.7   77.8
+//   9-bit M   4        6.6    9.2   12.7   15.5   21.9   28.4   41.5   54.4   67.2   80.2  105.9  214.0
+//             8        8.0    8.6   10.9   11.2   16.1   19.8   28.4   36.3   44.1   52.0   67.6  137.8
+//            16       10.0   10.4   10.4   10.6   14.8   15.0   20.8   26.7   32.8   39.1   50.8  101.3
+//        vector        7.3    8.8          12.2   15.9   19.3   26.1   33.8   40.8   47.3   62.1  124.1
+// (9 bits: two blocks of 32 channels.)  C = K = 32, C = 16 and K = 48, and fp32 output have the same order.
 inline int fused_matrix_tiles(const Geometry& g, int kb) {
-  struct Cost { int tiles; long first, each; };
-  constexpr Cost kCost8[3] = {{16, 50, 85}, {8, 36, 48}, {4, 30, 44}}, kCost9[3] = {{16, 50, 70}, {8, 35, 41}, {4, 28, 32}};
-  int best = 16;
-  long best_cost = 0;
-  for (const Cost& c : kb == 64 ? kCost8 : kCost9) {
-    const long groups = ((long)g.T + c.tiles - 1) / c.tiles * ((g.K + kb - 1) / kb);
-    const long cost = c.first + c.each * ((groups + 255) / 256);
-    if (best_cost == 0 || cost < best_cost) best = c.tiles, best_cost = cost;
-  }
-  return best;
+  for (int tiles : {4, 8})
+    if (((long)g.T + tiles - 1) / tiles * ((g.K + kb - 1) / kb) <= 256) return tiles;
+  return 16;
 }
 // Row and column of a pixel as input_pairs holds them, sixteen bits each (-1 is 65535).
 typedef unsigned short PixelPair __attribute__((ext_vector_type(2)));

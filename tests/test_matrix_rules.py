@@ -11,6 +11,11 @@ def test_single_kernel_cases_run_the_group_they_name(tmp_path):
     got = [int(v) for v in run_host_program(tmp_path, "matrix_rules", args)]
     want = [c[4] for c in brackets.FUSED_CASES]
     assert got == want and set(want) == {4, 8, 16}
+    # one group per compute unit, and one more (9 bits: two blocks of channels)
+    lines = [(1, 128, 128, 64, 8), (1, 128, 129, 64, 8), (2, 128, 128, 64, 8), (33, 4, 252, 64, 8),
+             (2, 64, 64, 64, 9), (2, 64, 65, 64, 9), (4, 64, 64, 64, 9), (4, 64, 65, 64, 9)]
+    got = run_host_program(tmp_path, "matrix_rules", [str(v) for line in lines for v in line])
+    assert [int(v) for v in got] == [4, 8, 8, 16, 4, 8, 8, 16]
 
 
 def test_dealing_of_block_pairs(tmp_path):
