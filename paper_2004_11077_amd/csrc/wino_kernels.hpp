@@ -165,6 +165,11 @@ inline Geometry with_dealt_units(Geometry g, long per_unit, long units) {
     g.img_blocks = (int)per_unit, g.img_blocks_end = (int)end;
   return g;
 }
+// Work for a group of four waves of 128 items each (input_pairs): two blocks, in fragment order eight tiles and a
+// 64-channel chunk.
+inline unsigned input_pair_count(const Geometry& g) {
+  return g.frag ? (unsigned)((((long)g.T + 7) >> 3) * ((g.C + 63) >> 6)) : (input_blocks(g) + 1) / 2;
+}
 // Geometry for the input transform's launch (whole: the block-uniform row-order kernel, one
 // work group per tile and 256 channels).
 // per: 256-item blocks per work group (1 or 2; an image of an odd number of blocks is then dealt

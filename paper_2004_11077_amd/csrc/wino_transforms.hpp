@@ -687,7 +687,9 @@ template <bool MX>
 using InputMults = std::conditional_t<MX, mb::PairMults, StageMults>;
 
 // F(4,3) in the Legendre base: a wave takes 128 (tile, channel) items, eight channels of a tile per lane,
-// a work group two of the 256-item blocks of input_items: pairs of blocks slot, slot + step, ... < pairs.
+// a work group two of the 256-item blocks of input_items (fragment order: eight tiles and a 64-channel chunk): pairs
+// slot, slot + step, ... < pairs (input_pair_count).  In fragment order a store of a wave is a whole line: 128 bytes, eight
+// tiles of 16 channels (with four tiles of two such slices WRITE_SIZE was 12333 KiB of 9216, C = 256, 1024 tiles).
 // The matrix operands are read once.  Lanes past the last item repeat it (and store the same codes to
 // the same place): with a condition around the stores the wait for the next pixels would wait for them too.
 template <bool WHOLE>
@@ -723,10 +725,10 @@ __device__ __forceinline__ void input_pairs(const int8_t* __restrict__ x, int8_t
     const unsigned block = 2 * pair + (wave >> 1);
     int t, c;
     if (!WHOLE && g.frag) {
-      const int quad = (int)fast_div(block, g.mul_ch, g.sh_ch);      // uniform
-      // lanes: eight bytes, four tiles, two 16-channel slices
-      t = quad * 4 + ((col >> 1) & 3);
-      c = ((int)block - quad * nch) * 64 + (wave & 1) * 32 + (col >> 3) * 16 + (col & 1) * 8;
+      const int oct = (int)fast_div(pair, g.mul_ch, g.sh_ch);        // uniform
+      // the wave: 16 channels; its lanes: eight bytes, eight tiles, together a whole line of a fragment
+      t = oct * 8 + (col >> 1);
+      c = ((int)pair - oct * nch) * 64 + wave * 16 + (col & 1) * 8;
       t = min(t, g.T - 1), c = min(c, g.C - 8);
       f.at = ((long)(t >> 4) * nch + (c >> 6)) * 1024 + ((c & 63) >> 4) * 256 + (t & 15) * 16 + (c & 15);
     } else if constexpr (WHOLE) {
@@ -1112,7 +1114,7 @@ hipError_t PerM<M>::input(const Geometry& g0, int br, const int8_t* x, int8_t* U
   const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
   const bool mx = input_on_matrix_pipe(g0, br, 0);
   const int per = mx ? 2 : 1;                      // 256-item blocks per work group
-  const unsigned pairs = (input_blocks(g0) + per - 1) / per;
+  const unsigned pairs = mx ? input_pair_count(g0) : input_blocks(g0);
   const unsigned nb = per == 2 ? min(pairs, kPairGroups) : pairs;
   const Geometry g = with_image_groups(g0, whole, per);
   if constexpr (M == 4)
@@ -1146,7 +1148,7 @@ hipError_t PerM<M>::operands(const Geometry& g0, int br, const int8_t* x, int8_t
   const bool whole = !g0.frag && whole_tiles(g0.C, g0.H, g0.W);
   const bool mx = input_on_matrix_pipe(g0, br, (long)g0.K * g0.C);
   const int per = mx ? 2 : 1;                      // 256-item input blocks per work group
-  const unsigned pairs = (input_blocks(g0) + per - 1) / per;
+  const unsigned pairs = mx ? input_pair_count(g0) : input_blocks(g0);
   const unsigned nb_in = per == 2 ? min(pairs, kPairGroups) : pairs, nb_w = weight_blocks(g0);
   const Geometry g = with_image_groups(g0, whole, per);
   const dim3 grid(nb_in + (nb_w + 7) / 8 * 8), bs(256);   // filter slots padded to whole sets of XCDs

@@ -14,7 +14,7 @@ int main() {
           g0.N = N, g0.H = HW, g0.W = HW, g0.C = C, g0.K = 64, g0.m = 4, g0.frag = frag;
           g0.TH = (HW + 3) / 4, g0.TW = g0.TH, g0.T = N * g0.TH * g0.TW;
           const wino::Geometry g = wino::with_image_groups(g0, !frag && wino::whole_tiles(C, HW, HW), 2);
-          const unsigned pairs = (wino::input_blocks(g0) + 1) / 2;
+          const unsigned pairs = wino::input_pair_count(g0);
           std::vector<int> slot_of(pairs, -1);
           for (unsigned s = 0; s < pairs; ++s) {
             const unsigned p = wino::image_on_one_xcd(g, s);
