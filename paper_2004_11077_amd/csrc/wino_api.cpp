@@ -355,41 +355,58 @@ bool fused_all_covers(const wino_conv_desc_t* d, const Plan& p) {
 
 // AUTO takes the two-kernel form where it was measured to be the faster one.  It saves the M
 // round trip and a launch; it pays with operands re-read through the L2 four times as often
-// (32 x 32 blocks against the 128 x 128 tiles of the stand-alone contraction) and with
-// operand transforms that are about 5 % slower into fragment order.  Its tile blocks run on the
+// (32 x 32 blocks against the 128 x 128 tiles of the stand-alone contraction).  Its tile blocks run on the
 // XCD whose input-transform work groups wrote their U (image_on_one_xcd), which is what makes it
-// the faster form on layers that fit the L2s.  Measured, whole layer, fp32 y, two-kernel form
-// against one kernel per stage (us):
-//  * C <= 128: it wins at every size tried, with raw or transformed filters, fp32 or int8
-//    output: 16x16 images, C = K = 128, N = 32 / 256 / 2048: 16.5 / 30.7 / 216 against
-//    17.6 / 37.0 / 227; C = 64, K = 128: 26 against 31; C = 128, K = 256: 52 against 54.
-//    (A block's operand bytes go with C, its output brackets do not, and the stand-alone
-//    kernels waste half of their 128-byte channel chunks and 128-wide k blocks on such
-//    layers.)
-//  * 128 < C <= 256, 8-bit M: it wins where the grid is about one work group per compute unit
-//    (8x8 images, C = K = 256, raw filters, N = 192 / 256: 22.0 / 24.2 against 23.2 / 25.6 --
-//    23.0 against 24.6 at N = 256 since the filter work groups lead the operand launch;
-//    filters transformed: 18.4 / 21.4 against 21.9 / 22.4), and loses on smaller and on larger
-//    grids (N = 64 / 128 / 320 / 512 / 1024 / 4096, raw filters: 19.9 / 21.0 / 32.8 / 42.6 / 75.8 /
-//    263 against 17.0 / 19.9 / 28.4 / 39.7 / 68.4 / 229).
-//  * 128 < C <= 256, 9-bit M (twice the bytes of M): it wins from 256 to 16384 tiles (N = 256 /
-//    1024 / 4096: 24.1 / 74.5 / 263 against 27.6 / 77.5 / 269; N = 16384: 1108 against 1077).
-//  * C > 256: a block's operand bytes go with C and it loses (C = K = 512, 4x4 images: 35 against
-//    25 at N = 256, 8-bit; C = K = 384, 8x8 images: 47 against 42).
-//  * F(6,3): 59 against 48 (its output bracket needs 64-bit arithmetic and runs better at the
+// the faster form on layers that fit the L2s.
+//  * C <= 128: from 64 blocks on (16x16 images, C = K = 128, 8-bit M, raw filters, us against one kernel per stage: 256
+//    blocks 0.88, 2048 blocks 0.95 of its time, 9-bit 0.78 and 0.83).  Below, a launch less does not pay for the
+//    fragment order.
+//  * Wider: a block's operand bytes go with C, its output brackets do not, so the wider the layer the fewer grids are left
+//    to it; a second round of blocks that fills few compute units costs a whole one.  Time of the two-kernel
+//    form over that of one kernel per stage, geometric means of 4000 layers (raw and transformed filters, both
+//    bases, fp32 and int8 y, images of 4x4 to 28x28, K = 32 to 512; a single layer lies within 7 % of its mean):
+//      blocks                 64-111  112-159  160-191  192-256  257-320  321-512  513-1024  1025-2200
+//      F(2,3) 8-bit C <= 192    0.98     0.89     0.85     0.86     0.96     0.88      0.86       0.86
+//             8-bit C <= 256    1.00     0.96     0.91     0.91     1.08     0.97      0.91       0.95
+//             8-bit C <= 320    1.00     0.97     0.92     0.96     0.96     0.94      0.96       1.00
+//             8-bit C <= 384    1.08     1.05     0.97     0.93     1.05     0.98      1.02       1.08
+//             9-bit C <= 192    0.95     0.82     0.77     0.82     0.81     0.80      0.78       0.78
+//             9-bit C <= 256    0.96     0.94     0.90     0.84     0.86     0.84      0.83       0.85
+//             9-bit C <= 320    0.99     0.89     0.85     0.89     0.95     0.85      0.85       0.92
+//             9-bit C <= 384    1.09     1.01     0.97     0.92     0.96     0.93      0.95       0.99
+//      F(4,3) 8-bit C <= 192    1.07     0.99     0.94     0.93     0.97     0.95      0.96       0.98
+//             8-bit C <= 256    1.16     1.04     1.01     1.01     1.09     1.06      1.05       1.09
+//             8-bit C <= 320    1.20     1.07     1.02     1.04     1.15     1.11      1.10       1.12
+//             9-bit C <= 192    1.01     0.92     0.85     0.80     0.87     0.86      0.86       0.86
+//             9-bit C <= 256    1.10     0.98     0.93     0.87     1.00     0.94      0.95       0.96
+//             9-bit C <= 320    1.13     1.02     0.95     0.93     1.05     0.97      1.00       1.00
+//             9-bit C <= 384    1.22     1.09     1.00     0.99     1.12     1.06      1.08       1.09
+//    (F(4,3), 8-bit, C = K = 256, 192 to 256 blocks: 0.88 to 0.92.)  With per-point scales F(2,3) 0.91, F(4,3) 0.96 over
+//    the layers that the table's lines take beyond C = 128.
+//  * Raw filters whose last 64-channel chunk is not full cost one more launch, the fill of V's padding: C = 160,
+//    F(4,3), 8-bit, K = 256, 128 / 256 / 512 / 1024 blocks 1.18 / 1.02 / 0.94 / 1.08.  They, and layers of less than a
+//    block of tiles (not measured: the padding of U counts there), keep the narrower rule.
+//  * F(6,3), never: 59 us against 48 (its output bracket needs 64-bit arithmetic and runs better at the
 //    stand-alone kernel's occupancy).
-constexpr int kConOutNarrowC = 128;            // up to here: whenever the grid has kConOutMinBlocksNarrow
-constexpr long kConOutMinBlocksNarrow = 64;
-constexpr int kConOutWideC = 256;              // up to here: between these block counts, with a 9-bit M,
-constexpr long kConOutMinBlocks = 192;         // or with an 8-bit M when the grid is about one work
-constexpr long kConOutMaxBlocks8 = 256;        // group per compute unit
-constexpr long kConOutMaxBlocks9 = 4096;
+struct ConOutGrids {
+  int channels;                    // up to this C
+  long from, to, again, end;       // blocks: from .. to, and again .. end where the last 64-channel chunk is full
+};
+constexpr ConOutGrids kConOutF2[2][3] = {{{192, 112, 4096}, {320, 160, 256, 321, 1024}, {384, 160, 256}},
+                                         {{192, 112, 4096}, {320, 112, 4096}, {384, 160, 256}}},
+                      kConOutF4[2][3] = {{{192, 160, 256, 321, 1024}, {256, 192, 256}, {0}},
+                                         {{192, 144, 4096}, {256, 160, 4096}, {320, 160, 256}}};
 
 bool auto_takes_conout(const wino_conv_desc_t* d, const Plan& p) {
   const long blocks = contract_output_blocks(p.g, p.m_bits);
-  if (d->C <= kConOutNarrowC) return blocks >= kConOutMinBlocksNarrow;
-  if (d->C > kConOutWideC || blocks < kConOutMinBlocks) return false;
-  return blocks <= (p.m_bits == 9 ? kConOutMaxBlocks9 : kConOutMaxBlocks8);
+  const int nine = p.m_bits == 9;
+  if (d->C <= 128) return blocks >= 64;
+  if ((!d->weights_pretransformed && d->C % 64 != 0) || p.g.T < 32)
+    return d->C <= 256 && blocks >= 192 && blocks <= (nine ? 4096 : 256);
+  for (const ConOutGrids& g : d->m == 2 ? kConOutF2[nine] : kConOutF4[nine])
+    if (d->C <= g.channels)
+      return (blocks >= g.from && blocks <= g.to) || (d->C % 64 == 0 && g.end && blocks >= g.again && blocks <= g.end);
+  return false;
 }
 
 // C <= 64, K > 64: the single kernel recomputes its input transform per block of output channels, which

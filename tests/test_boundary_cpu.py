@@ -205,7 +205,7 @@ def test_kernel_selection_and_workspace_of_the_whole_layer_call():
     assert wn.wino_preferred_operand_layout(big) == wn.LAYOUT_ROWS      # a larger grid: stage by stage
     # ... but a V that is handed over in fragment order is read by the form that can read it
     assert wn.wino_conv2d_launches(wn.ConvDesc(512, 8, 8, 256, 256, **pre))[-1] == "contraction_output"
-    # ... with a 9-bit M at any size, but not beyond 256 channels
+    # ... with a 9-bit M at any size, but not with 512 channels
     h9 = dict(m=4, fused=wn.FUSED_AUTO, bits_hadamard=9)
     assert wn.wino_conv2d_launches(wn.ConvDesc(4096, 8, 8, 256, 256, **h9))[-1] == "contraction_output"
     assert wn.wino_conv2d_launches(wn.ConvDesc(256, 8, 8, 512, 512, **h9))[-1] == "output_transform"
@@ -235,6 +235,49 @@ def test_kernel_selection_and_workspace_of_the_whole_layer_call():
         with pytest.raises(wn.WinoError) as e:
             wn.wino_set_option(opt, val)
         assert e.value.code == -1
+
+
+# blocks (32 tiles x 32 output channels) that AUTO gives to contraction + output in one kernel, [from, to] pairs
+CONOUT_GRIDS = [
+    (2, 8, 192, [(112, 4096)]), (2, 8, 256, [(160, 256), (321, 1024)]), (2, 8, 320, [(160, 256), (321, 1024)]),
+    (2, 8, 384, [(160, 256)]), (2, 8, 448, []), (2, 9, 192, [(112, 4096)]), (2, 9, 320, [(112, 4096)]),
+    (2, 9, 384, [(160, 256)]), (2, 9, 448, []),
+    (4, 8, 64 * 2, [(64, None)]), (4, 8, 192, [(160, 256), (321, 1024)]), (4, 8, 256, [(192, 256)]), (4, 8, 320, []),
+    (4, 9, 192, [(144, 4096)]), (4, 9, 256, [(160, 4096)]), (4, 9, 320, [(160, 256)]), (4, 9, 384, []),
+    (4, 8, 160, [(192, 256)]), (4, 9, 160, [(192, 4096)]), (4, 9, 272, [])]     # the last: V's padding to fill
+
+
+@pytest.mark.parametrize("m,bits,C,grids", CONOUT_GRIDS)
+def test_auto_takes_contraction_and_output_in_one_kernel(m, bits, C, grids):
+    def desc(blocks, K, fused, **kw):        # images of one tile, K / 32 blocks across
+        return wn.ConvDesc(blocks * 1024 // K, m, m, C, K, m=m, bits_hadamard=bits, fused=fused, **kw)
+
+    edges = {16, 48, 8192} | {e + i for lo, hi in grids for e, i in ((lo, -1), (lo, 0), (hi or lo, 0), (hi or lo, 1))}
+    for blocks in sorted(edges):
+        takes = any(lo <= blocks <= (hi or blocks) for lo, hi in grids)
+        auto = desc(blocks, 32, wn.FUSED_AUTO)
+        assert ("contraction_output" in wn.wino_conv2d_launches(auto)) == takes, blocks
+        # the layer needs no more workspace than one kernel per stage does
+        assert wn.wino_workspace_bytes(auto) <= wn.wino_workspace_bytes(desc(blocks, 32, wn.FUSED_OFF)) or C % 64
+    # few tiles beside many filters: one tile block, K / 32 blocks; a partial one keeps 192 to 256 (4096) blocks
+    for blocks in (112, 160, 256):
+        for T in (1, 31, 32, 33):
+            auto, off = (wn.ConvDesc(T, m, m, C, 32 * blocks // (2 if T == 33 else 1), m=m, bits_hadamard=bits, fused=f)
+                         for f in (wn.FUSED_AUTO, wn.FUSED_OFF))
+            takes = any(lo <= blocks <= (hi or blocks) for lo, hi in grids)
+            if T < 32 and C > 128:
+                takes = C <= 256 and blocks >= 192
+            assert ("contraction_output" in wn.wino_conv2d_launches(auto)) == takes, (blocks, T)
+            assert wn.wino_workspace_bytes(auto) <= wn.wino_workspace_bytes(off) or C % 64 or C <= 128
+    # transformed filters: the layout that goes with the choice, and either layout is taken
+    if C % 64 == 0:
+        for blocks in (48, 160, 256, 512):
+            takes = any(lo <= blocks <= (hi or blocks) for lo, hi in grids)
+            d = desc(blocks, 32, wn.FUSED_AUTO)
+            assert wn.wino_preferred_operand_layout(d) == (wn.LAYOUT_FRAGMENTS if takes else wn.LAYOUT_ROWS)
+            for layout, last in ((wn.LAYOUT_FRAGMENTS, "contraction_output"), (wn.LAYOUT_ROWS, "output_transform")):
+                given = desc(blocks, 32, wn.FUSED_AUTO, weights_pretransformed=1, operand_layout=layout)
+                assert wn.wino_conv2d_launches(given)[-1] == last
 
 
 def test_flex_calls_validate_matrices_and_options_before_any_launch():

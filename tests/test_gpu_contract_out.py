@@ -169,3 +169,42 @@ def test_many_tile_blocks_per_compute_unit():
     ora, sc = oracle_layer(xq, wq, s_x, s_w, **kw)
     got = whole_layer(xq, wq, sc, wn.FUSED_ON, **kw)
     assert_layer_parity(ora, got, "i8")
+
+
+# layers that AUTO gives to this kernel beyond 128 channels: partial blocks of tiles and channels, both tile sizes
+AUTO_CASES = [(2, "canonical", (9, 9, 9, 192, 512), 8), (2, "legendre", (50, 10, 7, 320, 176), 8),
+              (2, "canonical", (2, 19, 33, 384, 528), 9), (4, "legendre", (61, 10, 14, 192, 208), 8),
+              (4, "canonical", (21, 16, 15, 192, 432), 9), (4, "legendre", (19, 23, 9, 320, 560), 9),
+              (4, "legendre", (333, 4, 4, 192, 1024), 8)]
+
+
+@pytest.mark.parametrize("m,base,shape,bh", AUTO_CASES)
+@pytest.mark.parametrize("pp", [False, True])
+@pytest.mark.parametrize("pre", [False, True])
+def test_auto_gives_what_one_kernel_per_stage_gives(m, base, shape, bh, pp, pre):
+    import torch
+    import paper_2004_11077_amd as wn
+    N, H, W, C, K = shape
+    gen = torch.Generator(device="cuda:0").manual_seed(C + K)
+    x = torch.randint(0, 128, (N, H, W, C), generator=gen, dtype=torch.int8, device="cuda:0")
+    w = torch.randint(-127, 128, (K, C, 3, 3), generator=gen, dtype=torch.int8, device="cuda:0")
+    kw = dict(m=m, base=wn.BASE_LEGENDRE if base == "legendre" else wn.BASE_CANONICAL, bits_hadamard=bh)
+    plain = wn.ConvDesc(N, H, W, C, K, **kw)
+    cal = torch.empty(wn.wino_calibrate_workspace_bytes(plain), dtype=torch.uint8, device="cuda:0")
+    s = wn.wino_calibrate(plain, x, w, None, 0.02, 0.01, cal, per_point=pp)
+    for out_type, dtype in ((wn.OUT_F32, torch.float32), (wn.OUT_I8, torch.int8)):
+        got = []
+        for fused in (wn.FUSED_OFF, wn.FUSED_AUTO):
+            kk, wt = dict(kw, out_type=out_type, relu=1, fused=fused), w
+            if pre:
+                kk["operand_layout"] = (wn.LAYOUT_ROWS if fused == wn.FUSED_OFF else
+                                        wn.wino_preferred_operand_layout(wn.ConvDesc(N, H, W, C, K, **kk)))
+                d = wn.ConvDesc(N, H, W, C, K, **dict(kk, fused=wn.FUSED_OFF))
+                wt = wn.wino_weight_transform(d, w, torch.empty(wn.wino_operand_bytes(d)[0], dtype=torch.int8,
+                                                                device="cuda:0"), s)
+                kk["weights_pretransformed"] = 1
+            d = wn.ConvDesc(N, H, W, C, K, **kk)
+            assert wn.wino_conv2d_launches(d)[-1] == ("contraction_output" if fused == wn.FUSED_AUTO else "output_transform")
+            ws = torch.empty(wn.wino_workspace_bytes(d), dtype=torch.uint8, device="cuda:0")
+            got.append(wn.wino_conv2d(d, x, wt, torch.full((N, H, W, K), 7, dtype=dtype, device="cuda:0"), s, ws))
+        assert torch.equal(*got)
