@@ -358,13 +358,14 @@ bool fused_all_covers(const wino_conv_desc_t* d, const Plan& p) {
 // (32 x 32 blocks against the 128 x 128 tiles of the stand-alone contraction).  Its tile blocks run on the
 // XCD whose input-transform work groups wrote their U (image_on_one_xcd), which is what makes it
 // the faster form on layers that fit the L2s.
-//  * C <= 128: from 64 blocks on (16x16 images, C = K = 128, 8-bit M, raw filters, us against one kernel per stage: 256
-//    blocks 0.88, 2048 blocks 0.95 of its time, 9-bit 0.78 and 0.83).  Below, a launch less does not pay for the
-//    fragment order.
+//  * C <= 128: from 64 blocks on (8x8 images, C = K = 128, raw filters, time over that of one kernel per stage: 32 / 64 /
+//    128 / 512 / 2048 blocks 1.03 / 0.96 / 0.88 / 0.78 / 0.95, 9-bit 1.04 / 0.94 / 0.78 / 0.70 / 0.83).  Below, a launch less
+//    does not pay for the fragment order.  Raw filters with a partial chunk (below) lose up to about 128 blocks: C = 96,
+//    1.21 / 1.06 / 0.87 / 1.05 at 64 / 128 / 512 / 2048; they stay here, since one kernel per stage needs more workspace.
 //  * Wider: a block's operand bytes go with C, its output brackets do not, so the wider the layer the fewer grids are left
 //    to it; a second round of blocks that fills few compute units costs a whole one.  Time of the two-kernel
-//    form over that of one kernel per stage, geometric means of 4000 layers (raw and transformed filters, both
-//    bases, fp32 and int8 y, images of 4x4 to 28x28, K = 32 to 512; a single layer lies within 7 % of its mean):
+//    form over that of one kernel per stage, geometric means of 4700 layers (raw and transformed filters, both
+//    bases, fp32 and int8 y, images of 4x4 to 28x28, K = 32 to 512; most layers lie within 10 % of their mean):
 //      blocks                 64-111  112-159  160-191  192-256  257-320  321-512  513-1024  1025-2200
 //      F(2,3) 8-bit C <= 192    0.98     0.89     0.85     0.86     0.96     0.88      0.86       0.86
 //             8-bit C <= 256    1.00     0.96     0.91     0.91     1.08     0.97      0.91       0.95
